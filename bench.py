@@ -88,7 +88,7 @@ def main():
     ap.add_argument("--no-cpu", action="store_true", help="skip the CPU oracle leg")
     ap.add_argument("--also-dense", type=int, default=3, help="extra dense (prune off) steps reported beside a pruned run")
     ap.add_argument("--also-factorised", type=int, default=3,
-                    help="extra dense steps through the optional relation-factorised kernel (L2, d <= 282), reported beside")
+                    help="extra dense steps through the relation-factorised kernel (L2, d <= 282), reported beside")
     ap.add_argument("--general-form", type=int, default=0, metavar="STEPS",
                     help="also time kgc_join_ab (connector outputs supplied by the caller, pruned and dense) on the TransE connectors "
                          "A[r][h] = E[h] + Rv[r], B = E of the workload; needs R * N * d elements of extra memory")
@@ -154,10 +154,13 @@ def main():
     N, R, d, p = spec.N, spec.R, spec.d, spec.p
     E, Rv, cap, out = resident(wl)
 
-    def run(prune, steps, warmup, factorised=False, wl=wl, E=E, Rv=Rv, cap=cap, out=out):
+    def run(prune, steps, warmup, factorised=False, wl=wl, E=E, Rv=Rv, cap=cap, out=out, matrix=False):
         spec = wl.spec
         N, R, d, p = spec.N, spec.R, spec.d, spec.p
-        j = kgc.Join(dtype=spec.storage, prune=kgc.KGC_PRUNE_ON if prune else kgc.KGC_PRUNE_OFF, tile_cfg=args.tile,
+        # matrix: the kernel that contracts every pair of every relation on the matrix pipes, by its tile number (left
+        # alone, a dense L2 join of this size takes the relation-factorised kernel)
+        tile = args.tile or (18 if matrix and p == 2 and d <= 282 else 0)
+        j = kgc.Join(dtype=spec.storage, prune=kgc.KGC_PRUNE_ON if prune else kgc.KGC_PRUNE_OFF, tile_cfg=tile,
                      factorised=factorised)
         res = None
         for _ in range(warmup):
@@ -177,9 +180,10 @@ def main():
         ms_join = acc["ms_join"] / steps
         work = 2.0 * d * st["pairs_evaluated"]                 # flop (L2) or lane-ops (L1) of the join kernel per step
         if st["join_variant"] == 100:
-            # relation-factorised kernel: the matrix work is 1/R of the per-relation form and the time goes into
-            # vector arithmetic, 1.5 lane-ops per evaluated triple (one addition, half a three-way minimum)
-            work = 1.5 * st["pairs_evaluated"]
+            # relation-factorised kernel: the matrix work is 1/R of the per-relation form, and the vector arithmetic
+            # bounds 128 pairs of a column with about eight lane operations (four additions, two three-way minima, the
+            # threshold and the comparison)
+            work = 8.0 / 128.0 * st["pairs_evaluated"]
             roof = {"bound": "alu", "achieved": work / (ms_join * 1e-3) / 1e12 if ms_join > 0 else 0.0,
                     "peak": PEAK_VALU_TLANEOPS, "unit": "Tlane-op/s"}
         elif p == 2:
@@ -212,9 +216,9 @@ def main():
     # (a dense pass over the 1e15-triple workload would take minutes per step: the extra legs are only run when
     # their estimated cost is a few seconds)
     est_dense_s = 2.0 * d * N * N * R / (1.0e15 if p == 2 else 3.5e13)
-    est_fact_s = 1.5 * N * N * R / 3.0e13
+    est_fact_s = N * N * R / 2.0e13
     want_dense = args.also_dense > 0 and est_dense_s * (args.also_dense + 1) <= 20.0
-    dense = main_run if args.prune == "off" else (run(False, args.also_dense, 1) if want_dense else None)
+    dense = main_run if args.prune == "off" else (run(False, args.also_dense, 1, matrix=True) if want_dense else None)
     calib = calibrate(args.calibration_ms) if (p == 2 and args.calibration_ms > 0) else None
 
     def finish_roofline(r, wl_name, n_rows, n_rel, stats, mode):
@@ -277,7 +281,7 @@ def main():
         # the MFMA target (>= 50 % of the bf16 peak on dense tiles) is stated at N = 100,000, d = 200: a few dense steps there
         wl4 = workloads.generate("c4_large_l2")
         E4, Rv4, cap4, out4 = resident(wl4)
-        r4 = run(False, args.dense_c4, 1, wl=wl4, E=E4, Rv=Rv4, cap=cap4, out=out4)
+        r4 = run(False, args.dense_c4, 1, wl=wl4, E=E4, Rv=Rv4, cap=cap4, out=out4, matrix=True)
         s4 = wl4.spec
         roof4 = finish_roofline(r4["roofline"], s4.name, s4.N, s4.R, r4["stats"], "dense")
         line["dense_c4"] = {"workload": f"{s4.name}: N={s4.N} R={s4.R} d={s4.d} L2 {s4.storage} storage, delta={wl4.delta:.6g}, prune off",

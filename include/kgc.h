@@ -69,7 +69,9 @@ typedef struct {
     float   group_radius;     /* pruning only: radius of entity groups as a multiple of delta; 0 = 2.0 */
     int32_t range_kib;        /* dense L2 join: KiB of staged tail rows one block walks (L2 blocking); 0 = automatic */
     int32_t factorised;       /* 1: dense L2 joins with d <= 282 use the relation-factorised kernel (one MFMA tile
-                                 ||h - t||^2 per tile pair, then vector arithmetic per relation); same result set */
+                                 ||h - t||^2 per tile pair, then vector arithmetic per relation) whatever their size;
+                                 0: joins it is the faster form for (d <= 602, sizes: csrc/kgc.hip) use it when
+                                 tile_cfg is 0; same result set */
     int32_t reserved[3];      /* must be zero */
 } kgc_config;
 

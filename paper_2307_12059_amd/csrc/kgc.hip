@@ -43,6 +43,8 @@ static inline int64_t resident_range_bytes(int64_t tail_bytes) {
 }
 constexpr size_t kMaxLds = 160 * 1024;         // LDS per workgroup on gfx950
 constexpr int64_t kMaxTileList = 1ll << 30;    // entries of the surviving-tile list per relation batch (4 bytes each)
+constexpr unsigned int kFactListCap = 1u << 23;    // pairs the relation-factorised kernel may list per batch to start with (16 bytes each)
+constexpr unsigned long long kFactListMax = 1ull << 26;   // ... and at most (1 GiB)
 constexpr unsigned int kExactListCap = 1u << 20;   // accumulator blocks one batch may list for the exact stage (16 bytes each)
 
 struct DevBuf {
@@ -76,10 +78,13 @@ struct kgc_handle {
   DevBuf se_a, se_b;                           // connector rows of a relation batch (kgc_join_se)
   DevBuf xlist;                                // accumulator blocks listed for the exact stage (L2 joins)
   unsigned int xcap = kExactListCap;           // its length in entries: grows when a batch wanted to list more
+  DevBuf flist, umin;                          // relation-factorised join: listed pairs; minima of 2 r.h over 32 rows
+  unsigned int fcap = kFactListCap;            // entries of flist (tests set fewer)
   int list_seg_cap = 0;                        // > 0: the pruned barrier-free kernel keeps at most this many entries of a row's tile list in the LDS (tests)
   unsigned pairs_grid = 512;                   // workgroups of the tile-at-a-time kernel: two per compute unit (tests set fewer, so that a workgroup walks several batches of tiles)
   DevBuf zero_row, cent_a, rad_a;              // kgc_join_ab: the zero relation row; micro-tile summaries of A[r]
   DevBuf top1_a, top1_b, top1_pick, top_samples, topk_state;            // ... and the operands / entity samples of its sub-sampled dense pass
+  bool no_fact = false;                        // inside a call that the relation-factorised form did not suit
   int no_self = 0;                             // set by kgc_top1 around its inner joins: drop h == t
   bool static_mode = false;                    // inside kgc_join_static: the DevBufs point into the static array, nothing may allocate
   int64_t ws_override = 0;                     // ... and the staged operands of a relation batch get this many bytes
@@ -245,6 +250,16 @@ void launch_small_dot(hipStream_t st, const void* X, int dtype, int64_t n_rows, 
                      X, n_rows, Y, n_cols, d, out);
 }
 
+// r . e of a relation batch for every slot (k_fact_dot): rows read four elements at a time where they may be
+void launch_fact_dot(hipStream_t st, const void* Rv, const void* E, int dtype, const int32_t* slot_ent, int64_t Nslots, int r0, int RB,
+                     int RBp, int d, float* u, float* umin8, float* umin64, float* umax64) {
+  const bool bf = dtype == KGC_BF16;
+  const bool vec = d % 4 == 0 && (uintptr_t)E % (bf ? 8 : 16) == 0 && (uintptr_t)Rv % (bf ? 8 : 16) == 0;
+  auto kern = bf ? (vec ? k_fact_dot<true, true> : k_fact_dot<true, false>) : (vec ? k_fact_dot<false, true> : k_fact_dot<false, false>);
+  hipLaunchKernelGGL(kern, dim3((unsigned)(Nslots / 256), (unsigned)((RBp + 31) / 32), 1), dim3(256), 0, st,
+                     Rv, E, slot_ent, Nslots, r0, RB, RBp, d, u, umin8, umin64, umax64);
+}
+
 // Blocks for `items` work items, `per_block` each.  A launch may hold fewer than 2^32 threads per grid dimension, so
 // the count stops at 2^24 - 1 blocks (of at most 256 threads): enough for every per-row or per-slot kernel here
 // (N < 2^31); kernels that can be asked for more (k_fill_u32, the staging kernels) stride over their items.
@@ -258,6 +273,15 @@ hipError_t wait_event(hipEvent_t ev) {
   }
   return hipEventSynchronize(ev);
 }
+
+// rows of the relation-factorised join's per-relation tables: whole chunks of relations
+inline int64_t fact_rows(int64_t RB) { return (RB + kFactChunk - 1) / kFactChunk * kFactChunk; }
+// Dense L2 joins that the relation-factorised kernel takes by itself.  Its fixed part (products r.e, one contraction per
+// pair of entities, the list of pairs) is paid once, the other kernels contract every relation.  Measured, whole calls in
+// us, per-relation kernel / this one: N = 2,000, R = 8: 178 / 112 (d = 32), 164 / 118 (d = 100), 169 / 137 (d = 200);
+// N = 1,000, R = 8: 136 / 121, 130 / 128, 133 / 147; N = 1,000, R = 32: 319 / 213, 292 / 217, 278 / 235; N = 500, R = 32:
+// 255 / 306, 219 / 309, 208 / 325; R = 4: N = 4,000 151 / 114, 133 / 121, 142 / 145 and N = 16,000, d = 32: 202 / 239.
+inline bool fact_pays(int64_t N, int64_t R) { return R >= 8 && N >= 1000 && N * R >= 16000; }
 
 int grid_for(int64_t items, int per_block) {
   return (int)std::min<int64_t>((items + per_block - 1) / per_block, (1 << 24) - 1);
@@ -295,7 +319,7 @@ int kgc_create(const kgc_config* cfg, kgc_handle** out) {
   }
   h->err.reserve(256);          // later error messages fit without a host allocation
   // the first length of the exact stage's block list (it grows by itself; tests set it small to see it grow)
-  if (const char* e = std::getenv("KGC_EXACT_LIST_CAP")) h->xcap = (unsigned int)std::max(1L, std::atol(e));
+  if (const char* e = std::getenv("KGC_EXACT_LIST_CAP")) h->xcap = h->fcap = (unsigned int)std::max(1L, std::atol(e));
   if (const char* e = std::getenv("KGC_TILE_LIST_SEGMENT")) h->list_seg_cap = (int)std::max(1L, std::atol(e));
   if (const char* e = std::getenv("KGC_PAIRS_GRID")) h->pairs_grid = (unsigned)std::min(512L, std::max(1L, std::atol(e)));
   if (hipHostMalloc((void**)&h->host_counters, sizeof(DevCounters), hipHostMallocDefault) != hipSuccess) {
@@ -319,7 +343,8 @@ void kgc_destroy(kgc_handle* h) {
                     &h->cent, &h->rad, &h->bitmap, &h->row_start, &h->row_count, &h->cols, &h->active_rows, &h->cnorm,
                     &h->gram, &h->relu, &h->reln, &h->asg_a, &h->asg_b, &h->limr, &h->top1_buf, &h->top1_state,
                     &h->unit_first, &h->unit_n, &h->cent_u, &h->rad_u, &h->cnorm_u, &h->gram_u, &h->relu_u, &h->pair_list,
-                    &h->pair_count, &h->xlist, &h->tile_rows, &h->se_a, &h->se_b, &h->zero_row, &h->cent_a, &h->rad_a, &h->top1_a, &h->top1_b, &h->top1_pick, &h->top_samples, &h->topk_state})
+                    &h->pair_count, &h->xlist, &h->tile_rows, &h->se_a, &h->se_b, &h->zero_row, &h->cent_a, &h->rad_a, &h->top1_a, &h->top1_b, &h->top1_pick, &h->top_samples, &h->topk_state,
+                    &h->flist, &h->umin})
     release(*b);
   if (h->host_gstate) (void)hipHostFree(h->host_gstate);
   if (h->host_counters) (void)hipHostFree(h->host_counters);
@@ -1230,9 +1255,11 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
   // some room to spare (256 rows for KS <= 9, d <= 282; 128 rows for KS <= 19, d <= 602).  Pruned: the head-resident list-walking kernels
   // (KS <= 8, d <= 250; pruned_l2_tile).  Otherwise the streaming kernel.
   // the relation-factorised form (optional, dense L2 only, head tile in LDS) has one tile shape of its own
-  const bool fact = hd->cfg.factorised != 0 && p == 2 && !prune && KS <= kDirectMaxKS;
+  const bool fact = p == 2 && !prune && !win && !hd->static_mode && !hd->no_fact &&
+                    (hd->cfg.factorised != 0 ? KS <= kDirectMaxKS
+                                             : hd->cfg.tile_cfg == 0 && fact_pays(N, Rn) && KS <= kDirectHalfMaxKS && delta < 1e18f);
   int tile_id = kDefaultL2Tile;
-  if (fact) tile_id = kDirectL2Tile;
+  if (fact) tile_id = KS <= kDirectMaxKS ? kDirectL2Tile : kDirectHalfL2Tile;
   else if (hd->cfg.tile_cfg > 0) tile_id = hd->cfg.tile_cfg - 1;
   else if (!prune && KS <= kDirectMaxKS) tile_id = kDenseL2Tile;
   else if (!prune && KS <= kDirectHalfMaxKS) tile_id = kDirectHalfL2Tile;
@@ -1300,8 +1327,9 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
         (rc = ensure(hd, hd->opA, opA_per_rel * (size_t)(fact ? 1 : RBmax))) || (rc = ensure(hd, hd->normsB, Nslots * 4)) ||
         (rc = ensure(hd, hd->normsA, (size_t)(fact ? 1 : RBmax) * Nslots * 4)))
       return rc;
-    if (fact && ((rc = ensure(hd, hd->relu, (size_t)RBmax * Nslots * 4)) || (rc = ensure(hd, hd->reln, RBmax * 4)) ||
-                 (rc = ensure(hd, hd->limr, RBmax * 4))))
+    if (fact && ((rc = ensure(hd, hd->relu, (size_t)fact_rows(RBmax) * Nslots * 4)) ||
+                 (rc = ensure(hd, hd->limr, fact_rows(RBmax) * 4)) || (rc = ensure(hd, hd->umin, (size_t)fact_rows(RBmax) * (Nslots / 64) * 10 * 4)) ||
+                 (rc = ensure(hd, hd->flist, (size_t)hd->fcap * sizeof(ExactEntry)))))
       return rc;
   }
   if (prune) {
@@ -1531,33 +1559,30 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
     // pruned launches stride a fixed grid over the active rows (their number is only known on the device)
     const unsigned row_grid = (unsigned)std::min<int64_t>((int64_t)RB * nH, 4096);
     if (fact) {
-      // u[rl][slot] = r . e for the batch (tiled float32 product; padding slots stay 0), ||r||^2, thresholds
-      k_fill_u32<<<grid_for((int64_t)RB * Nslots, 256), 256, 0, st>>>((uint32_t*)hd->relu.p, (int64_t)RB * Nslots, 0u);
-      TileDistArgs td{};
-      td.X = (const char*)Rvecs + (size_t)r0 * d * (dtype == KGC_BF16 ? 2 : 4); td.dtypeX = dtype; td.n_rows = RB;
-      td.Y = E; td.dtypeY = dtype; td.col_ids = slot_ent; td.n_cols = Nslots; td.shift = nullptr; td.dtype_shift = dtype;
-      td.d = d; td.matrix = (float*)hd->relu.p;
-      k_tile_dist<0, kEpiMatrix><<<dim3((unsigned)((Nslots + 127) / 128), (unsigned)((RB + 127) / 128), 1), 256, 0, st>>>(td);
-      k_rel_centre_dot<<<grid_for((int64_t)RB * 64, 256), 256, 0, st>>>(Rvecs, dtype, d, (int)r0, RB, nullptr, 0,
-                                                                     (float*)hd->relu.p, (float*)hd->reln.p);
-      k_fact_params<<<grid_for(RB, 256), 256, 0, st>>>(cnt, (const float*)hd->reln.p, RB, delta, dtype, d, KS * kSliceK,
-                                                      (float*)hd->limr.p);
+      // u[rl][slot] = r . e with its extremes over 8 and 64 slots, then the thresholds
+      const int RBp = (int)fact_rows(RB);
+      float* umin8 = (float*)hd->umin.p;
+      float* umin64 = umin8 + (size_t)RBp * (Nslots / 64) * 8;
+      float* umax64 = umin64 + (size_t)RBp * (Nslots / 64);
+      launch_fact_dot(st, Rvecs, E, dtype, slot_ent, Nslots, (int)r0, RB, RBp, d, (float*)hd->relu.p, umin8, umin64, umax64);
+      k_fact_params<<<grid_for(RBp, 4), 256, 0, st>>>(cnt, Rvecs, (int)r0, RB, RBp, delta, dtype, d, KS * kSliceK, (float*)hd->limr.p);
       if (timed) KGC_HIP(hd, hipEventRecord(hd->join_ev[2 * b], st));
       JoinFactArgs fa{};
       fa.A = (const uint16_t*)hd->opA.p; fa.B = (const uint16_t*)hd->opB.p; fa.u = (const float*)hd->relu.p;
-      fa.limr = (const float*)hd->limr.p; fa.Nslots = Nslots; fa.KS = KS; fa.k16 = k16; fa.nH = nH; fa.nT = nT;
-      fa.r0 = (int)r0; fa.RB = RB; fa.cx = cx;
-      const size_t head_bytes = (size_t)KS * 256 * kSliceK * 2;
-      fa.rc = (int)std::max<size_t>(1, std::min<size_t>(64, (kMaxLds - head_bytes) / (256 * 4)));
-      const size_t dyn_lds = head_bytes + (size_t)fa.rc * 256 * 4;
-      // tail tiles in ranges of about 3 MiB of staged rows (they stay in L2 while the head tiles pass), cut
-      // further when there are too few head tiles to fill the chip
-      const int64_t tile_bytes = (int64_t)BN * KS * kSliceK * 2;
-      int64_t nsplit = (nT * tile_bytes + kL2RangeBytesResident - 1) / kL2RangeBytesResident;
-      nsplit = std::max<int64_t>(nsplit, (1024 + nH - 1) / nH);
-      nsplit = std::max<int64_t>(1, std::min<int64_t>(nsplit, std::min<int64_t>(nT, 65535)));
-      KGC_HIP(hd, hipFuncSetAttribute((const void*)k_join_l2_fact<2, 4>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn_lds));
-      hipLaunchKernelGGL((k_join_l2_fact<2, 4>), dim3((unsigned)nH, (unsigned)nsplit, 1), dim3(512), dyn_lds, st, fa);
+      fa.limr = (const float*)hd->limr.p; fa.umin8 = umin8; fa.umin64 = umin64; fa.umax64 = umax64; fa.Nslots = Nslots; fa.KS = KS; fa.k16 = k16;
+      fa.nT = nT; fa.r0 = (int)r0; fa.RBp = RBp;
+      fa.list = (ExactEntry*)hd->flist.p; fa.list_count = &cnt->n_fact; fa.list_cap = hd->fcap; fa.give_up = std::max<unsigned long long>(kFactListMax, hd->fcap);
+      void (*kern)(const JoinFactArgs) = BM == 256 ? k_join_l2_fact<4, 2, 4> : k_join_l2_fact<2, 2, 4>;
+      const size_t dyn_lds = (size_t)KS * BM * kSliceK * 2 + 8 * kFactWaveLds;
+      // a block takes a range of tail tiles of one head tile; with few tile pairs the relations are cut too
+      const int64_t pairs = (int64_t)nH * nT;
+      const int64_t nsplit = std::max<int64_t>(1, std::min<int64_t>({(4096 + nH - 1) / nH, (int64_t)nT, 65535}));
+      const int64_t nz = std::max<int64_t>(1, std::min<int64_t>((1024 + pairs - 1) / pairs, (RBp + 63) / 64));
+      fa.zrel = (int)((RBp + nz - 1) / nz + 7) / 8 * 8;
+      KGC_HIP(hd, hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn_lds));
+      hipLaunchKernelGGL(kern, dim3((unsigned)nH, (unsigned)nsplit, (unsigned)((RBp + fa.zrel - 1) / fa.zrel)), dim3(512), dyn_lds, st, fa);
+      k_exact_pairs<<<2048, 256, 0, st>>>(fa.list, fa.list_count, fa.list_cap, &cnt->exact_need, cx);
+      if (r0 + RBmax < r_end) k_fill_u32<<<1, 64, 0, st>>>((uint32_t*)&cnt->n_fact, 2, 0u);      // an empty list for the next batch
       if (timed) KGC_HIP(hd, hipEventRecord(hd->join_ev[2 * b + 1], st));
     } else if (p == 2) {
       int stage_grid = prune ? (int)std::min<int64_t>((int64_t)RB * nH * (BM / kStageRows), 4096)
@@ -1673,7 +1698,15 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
   pr.bitmap_valid = prune && nbatch == 1 && !empty_window; pr.bm_r0 = r_begin; pr.bm_r1 = r_end;
   // A batch that wanted to list more accumulator blocks than the list holds has dropped the rest (and counted
   // them): the list grows to what was asked for and the join runs again from the start.
-  if (hd->host_counters->exact_need > hd->xcap) {
+  if (fact && hd->host_counters->exact_need > hd->fcap) {      // (the same of the relation-factorised kernel's list of pairs)
+    const unsigned long long need = hd->host_counters->exact_need;
+    if (need <= kFactListMax) hd->fcap = (unsigned int)(need + need / 4 + 1024);
+    hd->no_fact = need > kFactListMax;                          // a threshold that passes so much: pair by pair, scored in place
+    const int rc2 = join_range_impl(hd, E, N, d, Rvecs, R, p, delta, r_begin, r_end, out_triples, cap, count, win, prep_mode);
+    hd->no_fact = false;
+    return rc2;
+  }
+  if (!fact && hd->host_counters->exact_need > hd->xcap) {
     const unsigned long long need = hd->host_counters->exact_need;
     hd->xcap = (unsigned int)std::min<unsigned long long>(need + need / 4 + 1024, 0xffffffffull);
     return join_range_impl(hd, E, N, d, Rvecs, R, p, delta, r_begin, r_end, out_triples, cap, count, win,

@@ -44,6 +44,7 @@ struct DevCounters {
   unsigned int max_b[1024];       // running maxima of ||bf16(t)||^2 (L2) or ||r||_1 (L1)
   unsigned int n_exact;           // accumulator blocks listed for the exact stage by the pruned L2 join kernels (per batch)
   unsigned int pair_mode;         // pruned L2 batch: 1 = its rows keep so few tiles that they are taken tile by tile
+  unsigned long long n_fact;      // pairs listed by the relation-factorised kernel (per batch)
 };
 
 __global__ void k_fill_u32(uint32_t* p, int64_t n, uint32_t v) {
@@ -1416,52 +1417,161 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1) void k_join_l2_direct(const JoinS
 }
 
 // ---------------------------------------------------------------------------------------------
-// Relation-factorised dense L2 join (optional mode).  For the TransE distance of Section 4.3,
+// Relation-factorised L2 join.  For the TransE distance of Section 4.3,
 //     ||h + r - t||^2 = ||h - t||^2 + 2 r.h - 2 r.t + ||r||^2,
 // and the only part that needs a d-long contraction per (h, t) pair, ||h - t||^2, does not depend on the
 // relation (the observation Section 5.2 makes for the tail side, taken one step further).  One block keeps
-// a 256-row head tile in LDS, forms the 256 x 256 tile G = ||h~ - t~||^2 ONCE with the matrix pipes (plain
-// entity rows on both sides, same augmented-K operands as the other forms), and then walks the relations of
-// the batch with vector arithmetic only: per relation and element one addition (G + 2 r.h) and half a
-// three-way minimum, the result compared against lim_r + 2 r.t per tail column.  The products r.e are a
-// float32 matrix u[r][slot] made beforehand by a tiled kernel.  Elements that pass go to the same exact
-// double-precision re-scoring as everywhere else, so the result set is unchanged.
-// Filter threshold: see k_fact_params.  LDS: the head tile (KS * 16 KiB) and 2 r.h of `rc` relations at a
-// time (rc KiB).
+// a head tile in LDS, forms the tile G = ||h~ - t~||^2 ONCE with the matrix pipes (plain entity rows on both
+// sides, same augmented-K operands as the other forms) and keeps it in registers while it walks the relations.
+// The filter asks of a pair whether G + 2 r.h <= lim_r + 2 r.t (lim_r: k_fact_params).  Asked pair by pair that is an
+// addition and half a minimum each, and the vector pipes bound the kernel (19.6 ms of the dense N = 15,000, R = 1,345
+// join at 88 % of the plain vector rate).  Rounding is monotonic, so a set of pairs of one relation is decided at once:
+//     min G + min 2 r.h  >  lim_r + max 2 r.t   over the set   =>   none of its pairs passes.
+// A wave asks this at three levels, each over what the level before left open:
+//   1. its whole TM * 32 x 64 pairs, one RELATION per lane (minima and maxima of r.e over 64 rows: k_fact_dot);
+//   2. eight head rows x one tail column, one COLUMN per lane: one coalesced load of r.t, TM * 4 additions and half as
+//      many minima per relation; the row minima of 2 r.h are wave-uniform and come through the scalar cache;
+//   3. the pairs themselves, with the accumulators in registers, for the (relation, eight rows) still open.
+// On embeddings in clusters level 1 leaves a relation open where its source cluster has a member among the head rows or
+// its target cluster among the tail columns, level 2 where eight rows hold both a member of the source cluster and a
+// neighbour of the tail.  The candidates are those of the pair-wise filter.
+// Measured (dense joins, kernel alone): N = 15,000, R = 1,345, d = 100: 19 -> 4.4 ms; N = 100,000, R = 200, d = 200:
+// 86 -> 9.2 ms, of which the contraction takes about half.  With one level of 32 rows in place of levels 1 and 2 they
+// took 7.3 and 19.4 ms: on 500 clusters half of all (relation, wave) pairs then went to level 3.
+// Candidates leave through a queue of 64 entries per wave (in LDS, no atomics) to a list in memory that
+// k_exact_pairs scores: a wave that scored its own would wait three memory round trips for one or two pairs.
+// A list that was too short is made longer by the host, which then runs the call again.
 struct JoinFactArgs {
   const uint16_t* A;         // staged head operands of the plain entity rows: [KS][Nslots][32]
   const uint16_t* B;         // staged tail operands: [KS][Nslots][32]
-  const float* u;            // [RB][Nslots] r . e (float32, from the caller's rows)
-  const float* limr;         // [RB] threshold on G + 2 r.h - 2 r.t, i.e. thr_r - ||r||^2
+  const float* u;            // [RBp][Nslots] r . e (float32, from the caller's rows), zero rows from RB on
+  const float* limr;         // [RBp] threshold on G + 2 r.h - 2 r.t, i.e. thr_r - ||r||^2
+  const float* umin8;        // [Nslots / 64][RBp][8] min of 2 r.e over 8 rows
+  const float* umin64;       // [Nslots / 64][RBp] min of 2 r.e over 64 rows ...
+  const float* umax64;       // ... and max
   int64_t Nslots;
   int KS, k16;
-  int nH, nT;
-  int r0, RB;
-  int rc;                    // relations per LDS chunk
-  RecheckCtx cx;
+  int nT;
+  int r0, RBp;               // RBp: relations of the batch, rounded up to kFactChunk
+  int zrel;                  // relations per block along grid z
+  ExactEntry* list;          // candidates for k_exact_pairs
+  unsigned long long* list_count;  // (may run past list_cap)
+  unsigned int list_cap;
+  unsigned long long give_up;      // with so many pairs listed the host takes another form: the waves end
 };
+constexpr int kFactChunk = 8;          // rows of the per-relation tables are rounded up to this
+constexpr int kFactQueue = 64;         // candidates a wave holds back
+constexpr int kFactIds = 128;          // relations a wave's level 1 has left open and level 2 has not taken yet
+constexpr int kFactBatch = 4;          // relations whose r.t and r.h a lane has in flight together
+constexpr size_t kFactWaveLds = 3 * kFactQueue * 4 + kFactIds * 2;
 
-template <int WGM, int WGN>
+// u[rl][slot] = r . e for the relations of a batch and the entity of every slot (0 for padding slots and for rows from RB
+// on), and the extremes of 2 r.e over 8 and over 64 consecutive slots (padding does not count), on the float32 matrix
+// pipes: a wave takes 32 relations x 64 slots, operands straight into registers in the permuted order of dimensions that
+// k_small_dot explains, every load of 64 dimensions issued before the first is used.  The 128 x 128 vector tile kernel
+// that did the products before left most of the chip idle on a thin product (R = 2, d = 200: 60 us of latency) and
+// needed a pass that cleared u and one that took the extremes: 204 us for the three, now 94 us (N = 15,000, R = 1,345,
+// d = 100, float32 rows; 4.0 GFLOP, 81 MB written), N = 100,000, R = 200, d = 200: 284 -> 162 us.
+template <bool BF16, bool VEC>
+__global__ __launch_bounds__(256) void k_fact_dot(const void* __restrict__ Rv, const void* __restrict__ E,
+                                                  const int32_t* __restrict__ slot_ent, int64_t Nslots, int r0, int RB, int RBp,
+                                                  int d, float* __restrict__ u, float* __restrict__ umin8,
+                                                  float* __restrict__ umin64, float* __restrict__ umax64) {
+  const int lane = threadIdx.x & 63, row = lane & 31, half = lane >> 5;
+  const int64_t g = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);         // this wave's 64 slots (Nslots is a multiple of 256)
+  const int rl0 = (int)blockIdx.y * 32;
+  const int64_t xo = (int64_t)(r0 + (rl0 + row < RB ? rl0 + row : RB - 1)) * d;      // (past the end: a valid row, dropped)
+  int ent[2];
+  int64_t yo[2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    ent[j] = slot_ent[g * 64 + 32 * j + row];
+    yo[j] = (int64_t)(ent[j] < 0 ? 0 : ent[j]) * d;
+  }
+  f32x16_t acc[2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) acc[j] = f32x16_t{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  constexpr int kG = 8;                                                   // groups of 8 dimensions per chunk
+  for (int k0 = 0; k0 < d; k0 += 8 * kG) {
+    f32x4_t xv[kG], yv[2][kG];
+#pragma unroll
+    for (int q = 0; q < kG; ++q) {
+      const int k = k0 + 8 * q + 4 * half;
+      xv[q] = exact_ld4<BF16, VEC>(Rv, xo, k, d);
+#pragma unroll
+      for (int j = 0; j < 2; ++j) yv[j][q] = exact_ld4<BF16, VEC>(E, yo[j], k, d);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int q = 0; q < kG; ++q) {
+      if (k0 + 8 * q >= d) break;                                         // the same for the whole wave
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(xv[q][e], yv[j][q][e], acc[j], 0, 0, 0);
+    }
+  }
+  // register v of lane l holds relation 8 (v / 4) + 4 (l / 32) + v % 4, slot l % 32
+#pragma unroll
+  for (int v = 0; v < 16; ++v) {
+    const int rl = rl0 + 8 * (v >> 2) + 4 * half + (v & 3);
+    float lo[2], hi[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const float x = ent[j] >= 0 && rl < RB ? acc[j][v] : 0.f;
+      if (rl < RBp) u[(int64_t)rl * Nslots + g * 64 + 32 * j + row] = x;
+      lo[j] = ent[j] >= 0 ? 2.f * x : 3e38f;
+      hi[j] = ent[j] >= 0 ? 2.f * x : -3e38f;
+#pragma unroll
+      for (int off = 1; off < 8; off <<= 1) {
+        lo[j] = fminf(lo[j], __shfl_xor(lo[j], off, 64));
+        hi[j] = fmaxf(hi[j], __shfl_xor(hi[j], off, 64));
+      }
+      if (rl < RBp && (lane & 7) == 0) umin8[(g * RBp + rl) * 8 + 4 * j + (row >> 3)] = lo[j];
+    }
+    float l = fminf(lo[0], lo[1]), h = fmaxf(hi[0], hi[1]);
+#pragma unroll
+    for (int off = 8; off < 32; off <<= 1) {
+      l = fminf(l, __shfl_xor(l, off, 64));
+      h = fmaxf(h, __shfl_xor(h, off, 64));
+    }
+    if (rl < RBp && row == 0) { umin64[g * RBp + rl] = l; umax64[g * RBp + rl] = h; }
+  }
+}
+
+// A wave-uniform read-only array of an earlier launch, read through the scalar cache whatever else the kernel stores.
+typedef const __attribute__((address_space(4))) float* scalar_f32_t;
+__device__ __forceinline__ scalar_f32_t scalar_f32(const float* p) { return (scalar_f32_t)(uintptr_t)p; }
+
+template <int TM, int WGM, int WGN>
 __global__ __launch_bounds__(WGM* WGN * 64, 1) void k_join_l2_fact(const JoinFactArgs a) {
-  constexpr int BM = 256, BN = 256;
+  constexpr int TN = 2;                                    // a wave holds 64 tail columns: one per lane in the bound
   constexpr int NT = WGM * WGN * 64;
-  constexpr int WTM = BM / WGM, WTN = BN / WGN;
-  constexpr int TM = WTM / 32, TN = WTN / 32;
+  constexpr int WTM = TM * 32, WTN = TN * 32;
+  constexpr int BM = WGM * WTM, BN = WGN * WTN;
   constexpr int LA = (BM * 4) / NT;
   constexpr int ASZ = BM * kSliceK;
   constexpr int ROWB = kSliceK * 2;
   static_assert(LA * NT == BM * 4, "tile rows must divide over the threads");
+  constexpr int NG = TM * 4;                               // groups of eight head rows
+  static_assert(TM == 2 || TM == 4, "a wave's rows are whole groups of 64 slots");
 
-  extern __shared__ __attribute__((aligned(16))) uint16_t lds[];   // [KS][BM][32] head slices, then float uh[rc][BM]
+  extern __shared__ __attribute__((aligned(16))) uint16_t lds[];   // [KS][BM][32] head slices, then the waves' queues
   const int KS = a.KS;
-  float* uh = (float*)(lds + (size_t)KS * ASZ);
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WGN, wn = wave % WGN;
+  char* wlds = (char*)(lds + (size_t)KS * ASZ) + wave * kFactWaveLds;
+  uint32_t* q = (uint32_t*)wlds;                           // candidates: relation, head slot, tail slot
+  uint16_t* ids = (uint16_t*)(wlds + 3 * kFactQueue * 4);  // relations of the batch (fewer than 65,536) that level 1 left open
+  int qn = 0;                                              // entries in the queue (the same in all lanes)
 
   const int tH = (int)blockIdx.x;
   const int t_begin = (int)(((int64_t)a.nT * blockIdx.y) / gridDim.y);
   const int t_end = (int)(((int64_t)a.nT * (blockIdx.y + 1)) / gridDim.y);
-  if (t_end <= t_begin) return;
+  const int rl_begin = (int)blockIdx.z * a.zrel;
+  const int rl_end = rl_begin + a.zrel < a.RBp ? rl_begin + a.zrel : a.RBp;
+  if (t_end <= t_begin || rl_end <= rl_begin) return;
   const int64_t slice_bytes = a.Nslots * ROWB;
 
   // ---- head tile: all K slices into LDS, once ----
@@ -1478,45 +1588,72 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1) void k_join_l2_fact(const JoinFac
       for (int i = 0; i < LA; ++i) *(uint4*)(&lds[ks * ASZ + st0 + i * st_step]) = t[i];
     }
   }
-  __syncthreads();
+  __syncthreads();                                         // the only barrier: from here on the waves run on their own
 
   const int rsw = lds_swizzle(lane & 31);
   const int rd_a = (wm * WTM + (lane & 31)) * kSliceK + (((lane >> 5) ^ rsw) * 8);
   const int rd_step = (((lane >> 5) ^ rsw) & 2) ? -16 : 16;
   const uint32_t boff = (uint32_t)((wn * WTN + (lane & 31)) * ROWB + (lane >> 5) * 16);
   const int last_two = (a.k16 - (KS - 1) * 2) >= 2;
-  // this lane's rows inside a 32-row block: 8 * (v / 4) + 4 * (lane / 32) + (v % 4); its column: lane % 32
-  const int urow = wm * WTM + 4 * (lane >> 5);
+  const int hrow0 = tH * BM + wm * WTM;                    // this wave's first head row
+  const scalar_f32_t um8 = scalar_f32(a.umin8 + (int64_t)(hrow0 >> 6) * a.RBp * 8);
+  const float* um64 = a.umin64 + (int64_t)(hrow0 >> 6) * a.RBp;
+  const scalar_f32_t limr = scalar_f32(a.limr);
+
+  // the queue's entries to the list, with one atomic; entries past its end are counted only
+#define KGC_FLUSH()                                                                               \
+  do {                                                                                            \
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");                                        \
+    __builtin_amdgcn_wave_barrier();                                                              \
+    const int fl = lane_id_here();                                                                \
+    unsigned long long base = 0ull;                                                               \
+    if (fl == 0) base = atomicAdd(a.list_count, (unsigned long long)qn);                          \
+    base = ((unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(base >> 32)) << 32) | \
+           (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)base);                         \
+    if (fl < qn && base + (unsigned)fl < a.list_cap) {                                            \
+      ExactEntry e;                                                                               \
+      e.r = (int32_t)q[fl]; e.hs0 = (int32_t)q[kFactQueue + fl]; e.ts0 = (int32_t)q[2 * kFactQueue + fl]; e.pad = 0; \
+      a.list[base + (unsigned)fl] = e;                                                            \
+    }                                                                                             \
+    if (base > a.give_up) return;                                                                 \
+    qn = 0;                                                                                       \
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");                                        \
+    __builtin_amdgcn_wave_barrier();                                                              \
+  } while (0)
 
   for (int tT = t_begin; tT < t_end; ++tT) {
-    // ---- G = ||h~ - t~||^2 for the 256 x 256 tile: tail fragments straight from the staged array ----
+    // ---- G = ||h~ - t~||^2: tail fragments straight from the staged array, the next slice's in flight ----
     f32x16_t acc[TM][TN];
     const char* pB = (const char*)a.B + (int64_t)tT * BN * ROWB + boff;
+    bf16x8_t nb0[TN], nb1[TN];
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      nb0[j] = *(const bf16x8_t*)(pB + j * 32 * ROWB);
+      nb1[j] = *(const bf16x8_t*)(pB + j * 32 * ROWB + 32);
+    }
+    const f32x16_t zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) acc[i][j] = zero16;
     for (int ks = 0; ks < KS; ++ks) {
       const uint16_t* Ac = lds + ks * ASZ + rd_a;
-      const bool two = ks < KS - 1 || last_two;
       bf16x8_t fb0[TN], fb1[TN], fa[TM];
 #pragma unroll
+      for (int j = 0; j < TN; ++j) { fb0[j] = nb0[j]; fb1[j] = nb1[j]; }
+      if (ks + 1 < KS) pB += slice_bytes;                  // (the last step asks for its own slice again)
+#pragma unroll
       for (int j = 0; j < TN; ++j) {
-        fb0[j] = *(const bf16x8_t*)(pB + j * 32 * ROWB);
-        fb1[j] = *(const bf16x8_t*)(pB + j * 32 * ROWB + 32);
+        nb0[j] = *(const bf16x8_t*)(pB + j * 32 * ROWB);
+        nb1[j] = *(const bf16x8_t*)(pB + j * 32 * ROWB + 32);
       }
-      pB += slice_bytes;
 #pragma unroll
       for (int i = 0; i < TM; ++i) fa[i] = *(const bf16x8_t*)(Ac + i * 32 * kSliceK);
-      if (ks == 0) {
-        const f32x16_t zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
+      for (int i = 0; i < TM; ++i)
 #pragma unroll
-          for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], fb0[j], zero16, 0, 0, 0);
-      } else {
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-          for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], fb0[j], acc[i][j], 0, 0, 0);
-      }
-      if (two) {
+        for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], fb0[j], acc[i][j], 0, 0, 0);
+      if (ks < KS - 1 || last_two) {
 #pragma unroll
         for (int i = 0; i < TM; ++i) fa[i] = *(const bf16x8_t*)(Ac + i * 32 * kSliceK + rd_step);
 #pragma unroll
@@ -1526,83 +1663,197 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1) void k_join_l2_fact(const JoinFac
       }
     }
 
-    // ---- the relations of the batch, rc at a time: 2 r.h of the head rows through LDS ----
-    const int64_t tcol0 = (int64_t)tT * BN + wn * WTN + (lane & 31);     // this lane's column of block j: + 32 j
-    for (int rl0 = 0; rl0 < a.RB; rl0 += a.rc) {
-      const int nr = a.RB - rl0 < a.rc ? a.RB - rl0 : a.rc;
-      __syncthreads();                                                    // the previous chunk has been read
-      for (int e = tid; e < nr * BM; e += NT) {
-        const int q = e / BM, row = e - q * BM;
-        uh[q * BM + row] = 2.f * a.u[(int64_t)(rl0 + q) * a.Nslots + (int64_t)tH * BM + row];
+    // ---- column minima of eight rows: lane l ends up with column l of the wave's 64.  MFMA 32x32 accumulator layout:
+    // register v of lane l holds row 8*(v/4) + 4*(l/32) + (v%4), column l%32. ----
+    float gm[NG];
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+      const int i = g >> 2, v = (g & 3) * 4;
+      float m[TN];
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        m[j] = fminf(fminf(acc[i][j][v], acc[i][j][v + 1]), fminf(acc[i][j][v + 2], acc[i][j][v + 3]));
+        m[j] = fminf(m[j], __shfl_xor(m[j], 32, 64));
       }
-      __syncthreads();
-      // the per-column part of the threshold (lim_r + 2 r.t) is fetched one relation ahead of its use
-      float nlimr = a.limr[rl0], nut[TN];
+      gm[g] = lane < 32 ? m[0] : m[1];
+    }
+    float gt = gm[0];
 #pragma unroll
-      for (int j = 0; j < TN; ++j) nut[j] = a.u[(int64_t)rl0 * a.Nslots + tcol0 + 32 * j];
-      for (int q = 0; q < nr; ++q) {
-        const int rl = rl0 + q;
-        float lim[TN], mn[TN];
+    for (int g = 1; g < NG; ++g) gt = fminf(gt, gm[g]);
 #pragma unroll
-        for (int j = 0; j < TN; ++j) {
-          lim[j] = nlimr + 2.f * nut[j];
-          mn[j] = 3e38f;
+    for (int off = 1; off < 64; off <<= 1) gt = fminf(gt, __shfl_xor(gt, off, 64));
+
+    const int tcol = tT * BN + wn * WTN;                                  // this wave's first tail column
+    const float* ux64 = a.umax64 + (int64_t)(tcol >> 6) * a.RBp;
+    const float* ut0 = a.u + tcol + lane;
+    const float* uh0 = a.u + hrow0 + lane;
+    int cnt = 0, rb = rl_begin;
+    for (;;) {
+      // ---- level 1: one relation per lane ----
+      while (rb < rl_end && cnt <= kFactIds - 64) {
+        const int rl = rb + lane < rl_end ? rb + lane : rl_end - 1;
+        float um = um64[rl];
+#pragma unroll
+        for (int h = 1; h < TM / 2; ++h) um = fminf(um, um64[(int64_t)h * a.RBp + rl]);
+        const bool open = rb + lane < rl_end && !(gt + um > a.limr[rl] + ux64[rl]);
+        const unsigned long long b = __builtin_amdgcn_ballot_w64(open);
+        if (open) ids[cnt + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u))] = (uint16_t)rl;
+        cnt += __builtin_popcountll(b);
+        rb += 64;
+      }
+      const bool last = rb >= rl_end;
+      const int take = last ? cnt : cnt / kFactBatch * kFactBatch;        // (not the last: more than half full)
+      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+      __builtin_amdgcn_wave_barrier();
+      // ---- level 2: the open relations, kFactBatch at a time, the next batch's r.t and r.h in flight ----
+      int nr[kFactBatch];
+      float nt[kFactBatch], nh[kFactBatch][TM / 2];
+#define KGC_FACT_LOAD(e0)                                                                         \
+  _Pragma("unroll") for (int k = 0; k < kFactBatch; ++k) {                                        \
+    const int e = (e0) + k < take ? (e0) + k : take - 1;                                          \
+    nr[k] = __builtin_amdgcn_readfirstlane((int)ids[e]);                                          \
+    const int64_t uo = (int64_t)nr[k] * a.Nslots;                                                 \
+    nt[k] = ut0[uo];                                                                              \
+    _Pragma("unroll") for (int h = 0; h < TM / 2; ++h) nh[k][h] = uh0[uo + 64 * h];               \
+  }
+      if (take > 0) KGC_FACT_LOAD(0);
+      for (int e0 = 0; e0 < take; e0 += kFactBatch) {
+        int rk[kFactBatch];
+        float ut[kFactBatch], uh[kFactBatch][TM / 2];
+#pragma unroll
+        for (int k = 0; k < kFactBatch; ++k) {
+          rk[k] = nr[k]; ut[k] = nt[k];
+#pragma unroll
+          for (int h = 0; h < TM / 2; ++h) uh[k][h] = nh[k][h];
         }
-        {
-          const int rn = q + 1 < nr ? rl + 1 : rl;              // the last one re-reads itself
-          nlimr = a.limr[rn];
+        if (e0 + kFactBatch < take) KGC_FACT_LOAD(e0 + kFactBatch);
+        unsigned int todo = 0u;                            // relations of the batch that level 2 leaves open
 #pragma unroll
-          for (int j = 0; j < TN; ++j) nut[j] = a.u[(int64_t)rn * a.Nslots + tcol0 + 32 * j];
+        for (int k = 0; k < kFactBatch; ++k) {
+          const scalar_f32_t ug = um8 + (int64_t)rk[k] * 8;
+          float m = gm[0] + ug[0];
+#pragma unroll
+          for (int g = 1; g < NG; ++g) m = fminf(m, gm[g] + ug[(int64_t)(g >> 3) * a.RBp * 8 + (g & 7)]);
+          if (__builtin_amdgcn_ballot_w64(!(m > limr[rk[k]] + 2.f * ut[k])) != 0ull && e0 + k < take) todo |= 1u << k;
         }
-        const float* uq = uh + q * BM + urow;
-        // per element one addition and half a three-way minimum; the 2 r.h values of this lane's rows come
-        // from LDS, four rows per read (two addresses per wave), two reads ahead of their use
-        constexpr int NH4 = TM * 4;
-        float4 hq0 = *(const float4*)(uq), hq1 = *(const float4*)(uq + 8);
+        while (todo) {                                     // one body for the batch's relations: it is long
+          const int k = __builtin_ctz(todo);
+          todo &= todo - 1u;
+          int rel = rk[0];
+          float utk = ut[0], uhk[TM / 2];
 #pragma unroll
-        for (int k = 0; k < NH4; ++k) {
-          const int i = k >> 2, vg = k & 3;                          // rows v = 4 vg .. 4 vg + 3 of block i
-          const float4 hh = hq0;
-          hq0 = hq1;
-          if (k + 2 < NH4) hq1 = *(const float4*)(uq + ((k + 2) >> 2) * 32 + 8 * ((k + 2) & 3));
+          for (int h = 0; h < TM / 2; ++h) uhk[h] = uh[0][h];
 #pragma unroll
-          for (int j = 0; j < TN; ++j) {
-            mn[j] = fminf(fminf(mn[j], acc[i][j][4 * vg + 0] + hh.x), acc[i][j][4 * vg + 1] + hh.y);
-            mn[j] = fminf(fminf(mn[j], acc[i][j][4 * vg + 2] + hh.z), acc[i][j][4 * vg + 3] + hh.w);
-          }
-        }
-        bool any = false;
+          for (int kk = 1; kk < kFactBatch; ++kk)
+            if (k == kk) {
+              rel = rk[kk]; utk = ut[kk];
 #pragma unroll
-        for (int j = 0; j < TN; ++j) any |= mn[j] <= lim[j];
-        if (__builtin_amdgcn_ballot_w64(any) == 0ull) continue;
-        // rare: the elements of this relation that pass, then the exact path.  MFMA 32x32 accumulator layout:
-        // register v of lane l holds row 8*(v/4) + 4*(l/32) + (v%4), column l%32.
-        const int64_t hbase = (int64_t)tH * BM + wm * WTM;
-        const int64_t tbase = (int64_t)tT * BN + wn * WTN;
-        constexpr int NW = (TM * TN + 3) / 4;
+              for (int h = 0; h < TM / 2; ++h) uhk[h] = uh[kk][h];
+            }
+          const float lim = limr[rel] + 2.f * utk;
+          float ug[NG];
 #pragma unroll
-        for (int w = 0; w < NW; ++w) {
-          unsigned long long cm = 0ull;
+          for (int g = 0; g < NG; ++g) ug[g] = um8[((int64_t)(g >> 3) * a.RBp + rel) * 8 + (g & 7)];
+          // ---- level 3: the pairs of the open eights ----
+          const int lq = lane_id_here();
+          float limj[TN];
 #pragma unroll
-          for (int qq = 0; qq < 4; ++qq) {
-            const int tile = w * 4 + qq;
-            if (tile < TM * TN) {
-              const int i = tile / TN, j = tile % TN;
+          for (int j = 0; j < TN; ++j) limj[j] = __shfl(lim, 32 * j + (lq & 31), 64);
 #pragma unroll
-              for (int v = 0; v < 16; ++v)
-                if (acc[i][j][v] + uq[i * 32 + 8 * (v >> 2) + (v & 3)] <= lim[j]) cm |= 1ull << (qq * 16 + v);
+          for (int g = 0; g < NG; ++g) {
+            if (__builtin_amdgcn_ballot_w64(!(gm[g] + ug[g] > lim)) == 0ull) continue;
+            uint32_t cm = 0u;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {                  // rows 8 g + 4 (lane / 32) + v of the wave
+              const float x = 2.f * __shfl(uhk[g >> 3], 8 * (g & 7) + 4 * (lq >> 5) + v, 64);
+#pragma unroll
+              for (int j = 0; j < TN; ++j)
+                if (!(acc[g >> 2][j][4 * (g & 3) + v] + x > limj[j])) cm |= 1u << (j * 4 + v);
+            }
+            for (;;) {                                     // one pair per lane and round into the queue
+              const unsigned long long b = __builtin_amdgcn_ballot_w64(cm != 0u);
+              if (b == 0ull) break;
+              const int n = __builtin_popcountll(b);
+              if (qn + n > kFactQueue) KGC_FLUSH();
+              if (cm != 0u) {
+                const int e = __builtin_ctz(cm);
+                const int pos = qn + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u));
+                q[pos] = (uint32_t)(a.r0 + rel);
+                q[kFactQueue + pos] = (uint32_t)(hrow0 + 8 * g + 4 * (lq >> 5) + (e & 3));
+                q[2 * kFactQueue + pos] = (uint32_t)(tcol + (e >> 2) * 32 + (lq & 31));
+                cm &= cm - 1u;
+              }
+              qn += n;
             }
           }
-          if (__builtin_amdgcn_ballot_w64(cm != 0ull) == 0ull) continue;
-          recheck_and_emit(cm, a.r0 + rl, a.cx, [=](int e, int src, int64_t& hslot, int64_t& tslot) {
-            const int tile = w * 4 + (e >> 4), v = e & 15;
-            const int i = tile / TN, j = tile % TN;
-            hslot = hbase + i * 32 + 8 * (v >> 2) + 4 * (src >> 5) + (v & 3);
-            tslot = tbase + j * 32 + (src & 31);
-          });
         }
       }
+#undef KGC_FACT_LOAD
+      // what did not fill a batch goes to the front
+      const uint16_t rest = ids[take + lane < cnt ? take + lane : 0];
+      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+      __builtin_amdgcn_wave_barrier();
+      if (take + lane < cnt) ids[lane] = rest;
+      cnt -= take;
+      if (last) break;
     }
+  }
+  if (qn > 0) KGC_FLUSH();
+#undef KGC_FLUSH
+}
+
+// Exact scores of the pairs listed by k_join_l2_fact.  A wave takes 64 consecutive entries, four at a time (one per
+// 16-lane group: the loads of a row are coalesced), gathers the results so that lane l speaks for entry l, and the
+// workgroup's waves reserve their output records with one atomic between them per round.
+__global__ __launch_bounds__(256) void k_exact_pairs(const ExactEntry* __restrict__ list, const unsigned long long* __restrict__ count,
+                                                     unsigned int cap, unsigned int* __restrict__ need, const RecheckCtx cx) {
+  __shared__ unsigned int wave_hits[4];
+  __shared__ unsigned long long base_s;
+  const unsigned int n = *count < cap ? (unsigned int)*count : cap;
+  const int lane = lane_id(), wave = (int)(threadIdx.x >> 6), grp = lane >> 4, sub = lane & 15;
+  for (unsigned int e0 = blockIdx.x * 256u; e0 < n; e0 += gridDim.x * 256u) {       // the same for the whole block
+    const unsigned int first = e0 + (unsigned)wave * 64u;
+    int32_t r = 0, h = -1, t = -1;
+    if (first + (unsigned)lane < n) {
+      const ExactEntry en = list[first + (unsigned)lane];
+      r = en.r; h = cx.slot_ent[en.hs0]; t = cx.slot_ent_t[en.ts0];
+      if (h < 0 || t < 0 || (cx.no_self && h == t)) h = -1;
+    }
+    bool hit = false;
+    float distf = 0.f;
+    for (int s = 0; s < 16; ++s) {
+      if (first + (unsigned)s * 4u >= n) break;            // the same for the whole wave
+      const int src = 4 * s + grp;
+      const int32_t hs = __shfl(h, src, 64), rs = __shfl(r, src, 64), ts = __shfl(t, src, 64);
+      const double dist = hs >= 0 ? group16_exact_dist(cx, hs, rs, ts, sub) : 0.0;
+      const int ok = (hs >= 0 && dist <= cx.delta) ? 1 : 0;
+      const float df = (float)dist;
+      const int from = 16 * (lane & 3);
+      const int okl = __shfl(ok, from, 64);
+      const float dl = __shfl(df, from, 64);
+      if ((lane >> 2) == s) { hit = okl != 0; distf = dl; }
+    }
+    const unsigned long long m = __builtin_amdgcn_ballot_w64(hit);
+    if (lane == 0) wave_hits[wave] = (unsigned int)__builtin_popcountll(m);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      const unsigned int total = wave_hits[0] + wave_hits[1] + wave_hits[2] + wave_hits[3];
+      base_s = total ? atomicAdd(cx.hit_counter, (unsigned long long)total) : 0ull;
+    }
+    __syncthreads();
+    unsigned long long pos = base_s;
+    for (int w = 0; w < wave; ++w) pos += wave_hits[w];
+    pos += __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+    if (hit && pos < cx.cap) {
+      kgc_triple rec;
+      rec.h = h; rec.r = r; rec.t = t; rec.dist = distf;
+      cx.out[pos] = rec;
+    }
+    __syncthreads();
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0 && n) {
+    atomicAdd(cx.cand_counter, (unsigned long long)n);
+    atomicMax(need, *count < 0xffffffffull ? (unsigned int)*count : 0xffffffffu);
   }
 }
 
@@ -1612,33 +1863,36 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1) void k_join_l2_fact(const JoinFac
 // (m = 0 for bf16 storage, where rounding changes nothing), and ||h - t|| <= delta + ||r|| for a hit, hence the
 // first term; e_acc bounds the float32 accumulation of G as in k_join_params; e_u bounds the float32 error of
 // the two products (d + 8) 2^-24 ||r|| ||e|| each, doubled, and of the final sums.
-__global__ __launch_bounds__(256) void k_fact_params(const DevCounters* cnt, const float* __restrict__ rn, int RB, float delta,
-                                                     int dtype, int d, int kp, float* __restrict__ limr) {
-  __shared__ float sm[2];
-  if (threadIdx.x < 64) {
-    float ma = 0.f, mb = 0.f;
-    for (int i = threadIdx.x; i < 1024; i += 64) {
-      ma = fmaxf(ma, __uint_as_float(cnt->max_a[i]));
-      mb = fmaxf(mb, __uint_as_float(cnt->max_b[i]));
-    }
-    for (int off = 32; off > 0; off >>= 1) {
-      ma = fmaxf(ma, __shfl_xor(ma, off, 64));
-      mb = fmaxf(mb, __shfl_xor(mb, off, 64));
-    }
-    if (threadIdx.x == 0) { sm[0] = ma; sm[1] = mb; }
+// One wave per relation: the maxima of the staged norms, ||r||^2 in float32, the threshold.
+__global__ __launch_bounds__(256) void k_fact_params(const DevCounters* cnt, const void* __restrict__ Rv, int r0, int RB, int RBp,
+                                                     float delta, int dtype, int d, int kp, float* __restrict__ limr) {
+  const int lane = threadIdx.x & 63;
+  const int rl = (int)blockIdx.x * 4 + (int)(threadIdx.x >> 6);
+  if (rl >= RBp) return;
+  if (rl >= RB || delta < 0.f) {                                       // nothing passes
+    if (lane == 0) limr[rl] = -__builtin_inff();
+    return;
   }
-  __syncthreads();
-  const float ma = sm[0], mb = sm[1];
-  const int rl = (int)(blockIdx.x * blockDim.x + threadIdx.x);
-  if (rl >= RB) return;
-  if (delta < 0.f) { limr[rl] = -3e38f; return; }
+  float ma = 0.f, mb = 0.f, rn = 0.f;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    ma = fmaxf(ma, __uint_as_float(cnt->max_a[i * 64 + lane]));
+    mb = fmaxf(mb, __uint_as_float(cnt->max_b[i * 64 + lane]));
+  }
+  for (int k = lane; k < d; k += 64) { const float x = ld_elem(Rv, (int64_t)(r0 + rl) * d + k, dtype); rn += x * x; }
+  for (int off = 32; off > 0; off >>= 1) {
+    ma = fmaxf(ma, __shfl_xor(ma, off, 64));
+    mb = fmaxf(mb, __shfl_xor(mb, off, 64));
+    rn += __shfl_xor(rn, off, 64);
+  }
   const float na = sqrtf(ma) * 1.01f, nb = sqrtf(mb) * 1.01f;
   const float m = dtype == KGC_BF16 ? 0.f : (1.01f / 256.f) * (na + nb);
-  const float rnorm = sqrtf(rn[rl]) * 1.0001f;
+  const float rnorm = sqrtf(rn) * 1.0001f;
   const float eacc = (float)(kp + 16) * 1.2e-7f * 2.f * (ma + mb);
-  const float eu = 4.f * (float)(d + 12) * 6e-8f * rnorm * (na + nb) + 1e-6f * (rn[rl] + ma + mb);
+  const float eu = 4.f * (float)(d + 12) * 6e-8f * rnorm * (na + nb) + 1e-6f * (rn + ma + mb);
   const float thr = (delta * delta + m * (2.f * (delta + rnorm) + m) + eacc + eu) * (1.f + 1e-6f);
-  limr[rl] = thr - rn[rl];
+  // norms that leave float32's range decide nothing: every pair of the relation goes to the exact stage
+  if (lane == 0) limr[rl] = thr < 1e37f && rn < 1e37f ? thr - rn : __builtin_inff();
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -1,0 +1,98 @@
+"""GPU tests of the relation-factorised L2 join where joins take it by themselves: the same records, bit for bit, as the
+kernels that contract every relation on its own (the exact stage decides both in double from the caller's rows)."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+PRUNE_OFF, PRUNE_ON = 1, 2
+
+
+def _case(seed, N, R, d, k, sigma, dtype):
+    import torch
+    g = np.random.default_rng(seed)
+    cent = g.standard_normal((k, d))
+    lab = g.integers(0, k, N)
+    E = cent[lab] + sigma * g.standard_normal((N, d))
+    src = g.integers(0, k, R)
+    Rv = cent[(src + 1 + g.integers(0, k - 1, R)) % k] - cent[src] + 0.02 * g.standard_normal((R, d))
+    tt = torch.float32 if dtype == "f32" else torch.bfloat16
+    return (torch.from_numpy(E.astype(np.float32)).cuda().to(tt).contiguous(),
+            torch.from_numpy(Rv.astype(np.float32)).cuda().to(tt).contiguous())
+
+
+def _records(j, E, Rv, delta, cap):
+    got = j.join(E, Rv, 2, delta, cap)
+    assert got["code"] == 0, got["code"]
+    o = np.lexsort((got["t"], got["h"], got["r"]))
+    return np.stack([got["r"][o], got["h"][o], got["t"][o], got["dist"][o].view(np.int32)], 1), got["stats"]
+
+
+# d at the edges of the K slices and of the two tile shapes (256 head rows up to d = 282, 128 up to 602), N that fills
+# its last tile with one row, or all but one, relations in one, several and not-whole groups of 64
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("N,R,d", [(1025, 385, 10), (1537, 200, 26), (2047, 97, 58), (769, 700, 122), (4097, 25, 282),
+                                   (1281, 260, 283), (2049, 129, 314), (3000, 64, 602), (15000, 8, 100)])
+def test_matches_the_per_relation_kernels(N, R, d, dtype):
+    import paper_2307_12059_amd as kgc
+    sigma = 0.1
+    E, Rv = _case(N + R + d, N, R, d, 9, sigma, dtype)
+    delta = float(np.float32(sigma * np.sqrt(2.0 * d) * 0.97))
+    cap = 1 << 23
+    a = kgc.Join(dtype=dtype, prune=PRUNE_OFF)
+    b = kgc.Join(dtype=dtype, prune=PRUNE_OFF, tile_cfg=18 if d <= 282 else 17)
+    try:
+        got, st = _records(a, E, Rv, delta, cap)
+        want, st2 = _records(b, E, Rv, delta, cap)
+    finally:
+        a.close()
+        b.close()
+    assert st["join_variant"] == 100 and st2["join_variant"] == (18 if d <= 282 else 17)
+    assert want.shape[0] > 1000
+    assert got.shape == want.shape
+    np.testing.assert_array_equal(got[:, :3], want[:, :3])
+    # one distance, summed in double in the same order by both: the same float
+    np.testing.assert_array_equal(got[:, 3], want[:, 3])
+
+
+def test_list_of_pairs_grows(monkeypatch):
+    import paper_2307_12059_amd as kgc
+    E, Rv = _case(7, 1025, 400, 40, 9, 0.1, "f32")
+    delta = float(np.float32(0.1 * np.sqrt(80.0)))
+    a = kgc.Join(prune=PRUNE_OFF)
+    monkeypatch.setenv("KGC_EXACT_LIST_CAP", "3")
+    b = kgc.Join(prune=PRUNE_OFF)
+    try:
+        want, _ = _records(a, E, Rv, delta, 1 << 23)
+        for _ in range(2):
+            got, st = _records(b, E, Rv, delta, 1 << 23)
+            assert st["join_variant"] == 100
+            np.testing.assert_array_equal(got, want)
+    finally:
+        a.close()
+        b.close()
+
+
+def test_every_pair_passes_and_far_translations():
+    """Thresholds that decide nothing (all pairs are hits: more than the list may hold), and relations far longer than
+    the embeddings, whose products lose the small distances in float32: both are left to the exact stage."""
+    import paper_2307_12059_amd as kgc
+    E, Rv = _case(8, 1100, 400, 24, 5, 0.1, "f32")
+    j = kgc.Join(prune=PRUNE_OFF)
+    k = kgc.Join(prune=PRUNE_OFF, tile_cfg=18)
+    try:
+        got = j.join(E, Rv, 2, 1e3, 16)
+        assert got["count"] == 1100 * 1100 * 400
+        far, _ = _records(j, E, Rv * 300.0, 2.0, 1 << 20)
+        want, _ = _records(k, E, Rv * 300.0, 2.0, 1 << 20)
+        np.testing.assert_array_equal(far, want)
+        E2 = E.clone()
+        E2[:550] -= 1000.0
+        R2 = Rv + 1000.0
+        far, st = _records(j, E2, R2, 0.4, 1 << 22)
+        want, _ = _records(k, E2, R2, 0.4, 1 << 22)
+        assert want.shape[0] > 100
+        np.testing.assert_array_equal(far, want)
+    finally:
+        j.close()
+        k.close()
