@@ -195,7 +195,7 @@ def main():
         roof["frac"] = roof["achieved"] / roof["peak"]
         roof["traffic"] = None      # filled below for configurations with a committed counter measurement
         v = st["join_variant"]
-        roof["kernel"] = ("k_join_l1" if p == 1 else "k_join_l2_fact" if v == 100 else "k_join_l2_dense" if v == 18
+        roof["kernel"] = ("k_join_l2_fact" if v == 100 else "k_join_l1" if p == 1 else "k_join_l2_dense" if v == 18
                           else "k_join_l2_direct" if v >= 15 else "k_join_l2_ares" if v >= 11
                           else "k_join_l2_stream" if v >= 6 else "k_join_l2")
         if prune and p == 2 and 6 <= v <= 14:

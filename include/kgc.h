@@ -94,8 +94,9 @@ typedef struct {
     int32_t  tile_m, tile_n;    /* tile shape used (heads x tails) */
     int32_t  k_padded;          /* contraction length after appending the norm columns and padding (L2) */
     int32_t  relation_batches;
-    int32_t  join_variant;      /* which join kernel ran: 0 = L1 (VALU); for L2 the tile_cfg number that was used,
-                                   100 = the relation-factorised kernel */
+    int32_t  join_variant;      /* which join kernel ran: 0 = L1 (VALU); for L2 the tile_cfg number that was used;
+                                   100 = the relation-factorised kernel (dense joins of either norm, and pruned L2
+                                   joins whose rows form one group) */
     int32_t  exact_blocks;      /* 32 x 32 blocks of pairs that the pruned L2 joins re-scored as whole blocks in double
                                    precision (their candidates come in patches); 0 for the other paths */
 } kgc_stats;

@@ -2,6 +2,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cstddef>
 #include <cstdlib>
 #include <cmath>
 #include <cstdio>
@@ -78,12 +79,14 @@ struct kgc_handle {
   DevBuf se_a, se_b;                           // connector rows of a relation batch (kgc_join_se)
   DevBuf xlist;                                // accumulator blocks listed for the exact stage (L2 joins)
   unsigned int xcap = kExactListCap;           // its length in entries: grows when a batch wanted to list more
+  DevBuf fop_a, fop_b, fu;                     // ... its operands and products r.e where it takes a part of a pruned join
   DevBuf flist, umin;                          // relation-factorised join: listed pairs; minima of 2 r.h over 32 rows
   unsigned int fcap = kFactListCap;            // entries of flist (tests set fewer)
   int list_seg_cap = 0;                        // > 0: the pruned barrier-free kernel keeps at most this many entries of a row's tile list in the LDS (tests)
   unsigned pairs_grid = 512;                   // workgroups of the tile-at-a-time kernel: two per compute unit (tests set fewer, so that a workgroup walks several batches of tiles)
   DevBuf zero_row, cent_a, rad_a;              // kgc_join_ab: the zero relation row; micro-tile summaries of A[r]
   DevBuf top1_a, top1_b, top1_pick, top_samples, topk_state;            // ... and the operands / entity samples of its sub-sampled dense pass
+  bool as_dense = false;                       // inside a pruned call whose rows form one group: the join without pruning
   bool no_fact = false;                        // inside a call that the relation-factorised form did not suit
   int no_self = 0;                             // set by kgc_top1 around its inner joins: drop h == t
   bool static_mode = false;                    // inside kgc_join_static: the DevBufs point into the static array, nothing may allocate
@@ -239,6 +242,13 @@ void launch_exact_blocks(hipStream_t st, const ExactEntry* list, const unsigned 
   hipLaunchKernelGGL(kern, dim3(256), dim3(kExactWaves * 64), 0, st, list, count, cap, total, need, cx);      // one workgroup per compute unit
 }
 
+// the L1 join kernel for the storage type and row alignment
+using JoinL1Kernel = void (*)(const JoinL1Args);
+JoinL1Kernel l1_kernel_for(const RecheckCtx& cx) {
+  const bool bf = cx.dtype == KGC_BF16, vec = cx.vec_ok != 0;
+  return bf ? (vec ? k_join_l1<true, true> : k_join_l1<true, false>) : (vec ? k_join_l1<false, true> : k_join_l1<false, false>);
+}
+
 // out[i][j] = x_i . y_j, one wave per 32 x 32 results on the float32 matrix pipes (k_small_dot): X rows of the storage
 // type, Y rows float32
 void launch_small_dot(hipStream_t st, const void* X, int dtype, int64_t n_rows, const float* Y, int64_t n_cols, int d, float* out) {
@@ -259,6 +269,15 @@ void launch_fact_dot(hipStream_t st, const void* Rv, const void* E, int dtype, c
   hipLaunchKernelGGL(kern, dim3((unsigned)(Nslots / 256), (unsigned)((RBp + 31) / 32), 1), dim3(256), 0, st,
                      Rv, E, slot_ent, Nslots, r0, RB, RBp, d, u, umin8, umin64, umax64);
 }
+
+// One relation batch of the relation-factorised join over a run of slots.
+struct FactJob {
+  const void* E; const void* Rv; int dtype, d, r0, RB; float delta;
+  const int32_t* slot_ent; int64_t Nslots;            // the run: a multiple of kSlotAlign slots
+  const uint16_t* A; const uint16_t* B;               // its staged operands (plain rows, plain norms)
+  float* u; float* umin; float* limr;                 // fact_rows(RB) x Nslots, x (Nslots / 64) x 10, x 1
+  ExactEntry* list; unsigned int list_cap; unsigned long long give_up;
+};
 
 // Blocks for `items` work items, `per_block` each.  A launch may hold fewer than 2^32 threads per grid dimension, so
 // the count stops at 2^24 - 1 blocks (of at most 256 threads): enough for every per-row or per-slot kernel here
@@ -283,8 +302,67 @@ inline int64_t fact_rows(int64_t RB) { return (RB + kFactChunk - 1) / kFactChunk
 // 255 / 306, 219 / 309, 208 / 325; R = 4: N = 4,000 151 / 114, 133 / 121, 142 / 145 and N = 16,000, d = 32: 202 / 239.
 inline bool fact_pays(int64_t N, int64_t R) { return R >= 8 && N >= 1000 && N * R >= 16000; }
 
+// Dense L1 joins that the relation-factorised kernel takes first: ||x||_2 <= ||x||_1, so every hit is among the pairs
+// within delta in L2, which its list then scores in L1.  Where the list grows past fact_list_max the L1 kernel does the
+// call instead.
+// Measured, whole calls in us, L1 kernel / this one, clusters of narrow spread: N = 1,000, R = 40, d = 100: 131 / 185;
+// 3,000, 5, 100: 137 / 111; 4,000, 8, 32: 220 / 121; 8,000, 4, 32: 355 / 201; 700, 400, 32: 311 / 263; 20,000, 18, 100:
+// 8,434 / 831.  Where the spread is so wide that the list overflows the try is lost: 4,000, 18, 100: 929 / 1,115;
+// 20,000, 18, 100: 20,318 / 24,882; 10,000, 18, 512: 8,638 / 9,856.
+inline bool fact_pays_l1(int64_t N, int64_t R, int d) { return (double)N * (double)N * (double)R * d >= 6e9; }
+// Longest list of pairs worth scoring one by one.  L1: a listed pair costs about as much as 250 pairs of the L1 kernel.
+inline unsigned long long fact_list_max(int64_t N, int64_t R, int p) {
+  if (p == 2) return kFactListMax;
+  return std::min<unsigned long long>(kFactListMax, (unsigned long long)((double)N * (double)N * (double)R / 512.0));
+}
+
+// Units of the bound test (groups, micro-tiles without one) up to which a pruned L2 join is taken as a dense one: with
+// three units the bound could rule out at most eight of nine pairs, and the factorised kernel decides a pair and relation
+// in a sixteenth to a sixtieth of a contraction's time.
+constexpr int kFewUnits = 3;
+// Rows without a group from which their pairs are worth the factorised kernel's fixed part.  Measured, whole calls in us, without
+// it / with it (n rows, R, d, as many rows again in groups): 1,100, 900, 64: 1,459 / 641; 1,500, 450, 64: 1,995 / 1,438;
+// 3,000, 120, 64: 2,140 / 1,373; 6,000, 30, 64: 3,241 / 1,184; 20,000, 100, 100: 20,042 / 2,483.  Below, the pairs are few.
+inline bool part_pays(int64_t n, int64_t R) { return n >= 1024 && R >= 8 && (double)n * (double)n * (double)R >= 1e9; }
+
 int grid_for(int64_t items, int per_block) {
   return (int)std::min<int64_t>((items + per_block - 1) / per_block, (1 << 24) - 1);
+}
+// workgroups of k_row_l1_max: eight half-waves each, up to eight workgroups per compute unit
+int grid_l1_max(int64_t rows) { return (int)std::min<int64_t>((rows + 7) / 8, 2048); }
+
+// u[rl][slot] = r . e with its extremes over 8 and 64 slots, then the thresholds
+void launch_fact_products(hipStream_t st, const FactJob& j, DevCounters* cnt) {
+  const int RBp = (int)fact_rows(j.RB), KS = (j.d + kNormCols + kSliceK - 1) / kSliceK;
+  float* umin64 = j.umin + (size_t)RBp * (j.Nslots / 64) * 8;
+  launch_fact_dot(st, j.Rv, j.E, j.dtype, j.slot_ent, j.Nslots, j.r0, j.RB, RBp, j.d, j.u, j.umin, umin64,
+                  umin64 + (size_t)RBp * (j.Nslots / 64));
+  k_fact_params<<<grid_for(RBp, 4), 256, 0, st>>>(cnt, j.Rv, j.r0, j.RB, RBp, j.delta, j.dtype, j.d, KS * kSliceK, j.limr);
+}
+
+// the kernel and the scores of the pairs it lists (cx counts its slots from the job's first)
+int launch_fact_join(kgc_handle* hd, hipStream_t st, const FactJob& j, DevCounters* cnt, const RecheckCtx& cx) {
+  const int RBp = (int)fact_rows(j.RB), KS = (j.d + kNormCols + kSliceK - 1) / kSliceK;
+  const TileCfg tc = kL2Tiles[KS <= kDirectMaxKS ? kDirectL2Tile : kDirectHalfL2Tile];
+  const int nH = (int)(j.Nslots / tc.bm), nT = (int)(j.Nslots / tc.bn);
+  JoinFactArgs fa{};
+  fa.A = j.A; fa.B = j.B; fa.u = j.u; fa.limr = j.limr; fa.umin8 = j.umin;
+  fa.umin64 = j.umin + (size_t)RBp * (j.Nslots / 64) * 8;
+  fa.umax64 = fa.umin64 + (size_t)RBp * (j.Nslots / 64);
+  fa.Nslots = j.Nslots; fa.KS = KS; fa.k16 = (j.d + kNormCols + 15) / 16;
+  fa.nT = nT; fa.r0 = j.r0; fa.RBp = RBp;
+  fa.list = j.list; fa.list_count = &cnt->n_fact; fa.list_cap = j.list_cap; fa.give_up = j.give_up;
+  void (*kern)(const JoinFactArgs) = tc.bm == 256 ? k_join_l2_fact<4, 2, 4> : k_join_l2_fact<2, 2, 4>;
+  const size_t dyn_lds = (size_t)KS * tc.bm * kSliceK * 2 + 8 * kFactWaveLds;
+  // a block takes a range of tail tiles of one head tile; with few tile pairs the relations are cut too
+  const int64_t pairs = (int64_t)nH * nT;
+  const int64_t nsplit = std::max<int64_t>(1, std::min<int64_t>({(4096 + nH - 1) / nH, (int64_t)nT, 65535}));
+  const int64_t nz = std::max<int64_t>(1, std::min<int64_t>((1024 + pairs - 1) / pairs, (RBp + 63) / 64));
+  fa.zrel = (int)((RBp + nz - 1) / nz + 7) / 8 * 8;
+  KGC_HIP(hd, hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn_lds));
+  hipLaunchKernelGGL(kern, dim3((unsigned)nH, (unsigned)nsplit, (unsigned)((RBp + fa.zrel - 1) / fa.zrel)), dim3(512), dyn_lds, st, fa);
+  k_exact_pairs<<<2048, 256, 0, st>>>(fa.list, fa.list_count, fa.list_cap, &cnt->fact_need, cx);
+  return KGC_OK;
 }
 
 }  // namespace
@@ -344,7 +422,7 @@ void kgc_destroy(kgc_handle* h) {
                     &h->gram, &h->relu, &h->reln, &h->asg_a, &h->asg_b, &h->limr, &h->top1_buf, &h->top1_state,
                     &h->unit_first, &h->unit_n, &h->cent_u, &h->rad_u, &h->cnorm_u, &h->gram_u, &h->relu_u, &h->pair_list,
                     &h->pair_count, &h->xlist, &h->tile_rows, &h->se_a, &h->se_b, &h->zero_row, &h->cent_a, &h->rad_a, &h->top1_a, &h->top1_b, &h->top1_pick, &h->top_samples, &h->topk_state,
-                    &h->flist, &h->umin})
+                    &h->flist, &h->umin, &h->fop_a, &h->fop_b, &h->fu})
     release(*b);
   if (h->host_gstate) (void)hipHostFree(h->host_gstate);
   if (h->host_counters) (void)hipHostFree(h->host_counters);
@@ -489,7 +567,7 @@ int kgc_join_ab(kgc_handle* hd, const void* A, const void* B, int64_t N, int32_t
       if (p == 2) k_tile_dist<2, kEpiBound><<<g, 256, 0, st>>>(ta);
       else k_tile_dist<1, kEpiBound><<<g, 256, 0, st>>>(ta);
       k_fill_u32<<<1, 64, 0, st>>>((uint32_t*)&cnt->tile_cursor, 3, 0u);      // cursor and n_active
-      k_rows_from_bitmap<<<(unsigned)(((int64_t)RB * nH + 256 * bitmap_rows_per_lane(words_per_row) - 1) / (256 * bitmap_rows_per_lane(words_per_row))), 256, 0, st>>>(
+      k_rows_from_bitmap<<<(unsigned)(((int64_t)RB * nH + 256 * bitmap_rows_per_lane(words_per_row, (int64_t)RB * nH) - 1) / (256 * bitmap_rows_per_lane(words_per_row, (int64_t)RB * nH))), 256, 0, st>>>(
           (const uint32_t*)hd->bitmap.p, words_per_row, (int64_t)RB * nH, (uint32_t*)hd->row_start.p,
           (uint32_t*)hd->row_count.p, (uint32_t*)hd->cols.p, &cnt->tile_cursor, (uint32_t*)hd->active_rows.p, &cnt->n_active,
           pairs_ok ? (uint32_t*)hd->tile_rows.p : nullptr);
@@ -566,10 +644,10 @@ int kgc_join_ab(kgc_handle* hd, const void* A, const void* B, int64_t N, int32_t
         k_fill_u32<<<1, 64, 0, st>>>(&cnt->n_exact, 1, 0u);
       }
     } else {
-      k_row_l1_max<<<grid_for((int64_t)RB * N * 32, 256), 256, 0, st>>>((const char*)A + (size_t)r0 * N * d * esz, (int64_t)RB * N, d,
+      k_row_l1_max<<<grid_l1_max((int64_t)RB * N), 256, 0, st>>>((const char*)A + (size_t)r0 * N * d * esz, (int64_t)RB * N, d,
                                                                     dtype, cnt->max_a);
       if (b_per_relation || r0 == 0)
-        k_row_l1_max<<<grid_for((int64_t)(b_per_relation ? RB : 1) * N * 32, 256), 256, 0, st>>>(
+        k_row_l1_max<<<grid_l1_max((int64_t)(b_per_relation ? RB : 1) * N), 256, 0, st>>>(
             (const char*)B + (b_per_relation ? (size_t)r0 * N * d * esz : 0), (int64_t)(b_per_relation ? RB : 1) * N, d, dtype,
             cnt->max_b);
       k_join_params<<<1, 64, 0, st>>>(cnt, prm, delta, p, dtype, d, 0);
@@ -578,16 +656,16 @@ int kgc_join_ab(kgc_handle* hd, const void* A, const void* B, int64_t N, int32_t
       if (prune) {
         la.row_start = (const uint32_t*)hd->row_start.p; la.row_count = (const uint32_t*)hd->row_count.p;
         la.cols = (const uint32_t*)hd->cols.p; la.active_rows = active_rows; la.n_active = n_active;
-        hipLaunchKernelGGL(k_join_l1, dim3(row_grid, 1, 1), dim3(256), 0, st, la);
+        hipLaunchKernelGGL(l1_kernel_for(la.cx), dim3(row_grid, 1, 1), dim3(256), 0, st, la);
       } else {
-        hipLaunchKernelGGL(k_join_l1, dim3((unsigned)nT, (unsigned)nH, (unsigned)RB), dim3(256), 0, st, la);
+        hipLaunchKernelGGL(l1_kernel_for(la.cx), dim3((unsigned)nT, (unsigned)nH, (unsigned)RB), dim3(256), 0, st, la);
       }
     }
     hd->stats.join_launches++;
   }
   KGC_HIP(hd, hipEventRecord(hd->join_ev[1], st));
   KGC_HIP(hd, hipGetLastError());
-  KGC_HIP(hd, hipMemcpyAsync(hd->host_counters, cnt, 48, hipMemcpyDeviceToHost, st));
+  KGC_HIP(hd, hipMemcpyAsync(hd->host_counters, cnt, offsetof(DevCounters, max_a), hipMemcpyDeviceToHost, st));
   KGC_HIP(hd, hipEventRecord(hd->ev[2], st));
   KGC_HIP(hd, wait_event(hd->ev[2]));
 
@@ -650,12 +728,20 @@ int kgc_join_se(kgc_handle* hd, const void* E, int64_t N, int32_t d, const void*
   for (int64_t r0 = 0; r0 < R; r0 += RB_max, ++batches) {
     const int RB = (int)std::min<int64_t>(RB_max, R - r0);
     for (int side = 0; side < 2; ++side) {
-      TileDistArgs td{};
-      td.X = E; td.dtypeX = dtype; td.n_rows = N;
-      td.Y = (const char*)(side ? W_rhs : W_lhs) + (size_t)r0 * d * d * esz; td.dtypeY = dtype; td.n_cols = d;
-      td.y_rel_rows = d; td.shift = nullptr; td.dtype_shift = dtype; td.d = d;
-      td.matrix = (float*)(side ? hd->se_b.p : hd->se_a.p); td.matrix_rel_stride = (int64_t)N * d;
-      k_tile_dist<0, kEpiMatrix><<<dim3((unsigned)((d + 127) / 128), (unsigned)((N + 127) / 128), (unsigned)RB), 256, 0, st>>>(td);
+      const void* W = (const char*)(side ? W_rhs : W_lhs) + (size_t)r0 * d * d * esz;
+      const bool bf = dtype == KGC_BF16;
+      const bool vec = d % 4 == 0 && (uintptr_t)E % (bf ? 8 : 16) == 0 && (uintptr_t)W % (bf ? 8 : 16) == 0;
+      float* out = (float*)(side ? hd->se_b.p : hd->se_a.p);
+      if (vec) {
+        hipLaunchKernelGGL(bf ? k_connect<true> : k_connect<false>, dim3((unsigned)((N + 127) / 128), (unsigned)((d + 127) / 128), (unsigned)RB),
+                           dim3(256), 0, st, E, N, W, d, out);
+      } else {
+        TileDistArgs td{};
+        td.X = E; td.dtypeX = dtype; td.n_rows = N; td.Y = W; td.dtypeY = dtype; td.n_cols = d;
+        td.y_rel_rows = d; td.shift = nullptr; td.dtype_shift = dtype; td.d = d;
+        td.matrix = out; td.matrix_rel_stride = (int64_t)N * d;
+        k_tile_dist<0, kEpiMatrix><<<dim3((unsigned)((d + 127) / 128), (unsigned)((N + 127) / 128), (unsigned)RB), 256, 0, st>>>(td);
+      }
     }
     KGC_HIP(hd, hipGetLastError());
     // the batch through the general form, on float32 rows whatever the handle's storage type
@@ -700,7 +786,7 @@ int group_rows(kgc_handle* hd, const void* E, int64_t N, int32_t d, int32_t p, f
   UnitTable ut{};
   // worst case: every group of kSmallGroup rows is padded to a micro-tile
   const int64_t max_padded_groups = std::min<int64_t>(kMaxGroups, N / kSmallGroup + 1);
-  const int64_t slots_cap = ((N + (kMicro - 1) * max_padded_groups) + kSlotAlign - 1) / kSlotAlign * kSlotAlign;
+  const int64_t slots_cap = ((N + (kMicro - 1) * max_padded_groups) + 2 * kSlotAlign - 1) / kSlotAlign * kSlotAlign;
   if ((rc = ensure(hd, hd->slot_ent, slots_cap * 4)) || (rc = ensure(hd, hd->gstate, sizeof(GroupState))) ||
       (rc = ensure(hd, hd->unc_a, N * 4)) || (rc = ensure(hd, hd->unc_b, N * 4)) ||
       (rc = ensure(hd, hd->group_of, N * 4)) || (rc = ensure(hd, hd->piv_ent, kPivotsPerRound * 4)) ||
@@ -830,10 +916,9 @@ constexpr int kTopSamples = 1 << 16;
 
 // Upper bounds of the smallest eligible distance for kgc_top1 / kgc_topk.  *sample_bound: the smallest of
 // kTopSamples sampled triples, scored exactly (its triple is known to qualify); *bound: that, or the tighter bound
-// of the sub-sampled dense pass when it applies.  samples (optional, host, kTopSamples doubles) receives every
-// sampled distance.
+// of the sub-sampled dense pass when it applies.  keep_samples: every sampled distance stays in hd->top_samples.
 int top_bounds(kgc_handle* hd, const void* E, int64_t N, int32_t d, const void* Rvecs, int32_t r_begin, int32_t R, int32_t p,
-               int32_t exclude_self, const RecheckCtx& cx, double* sample_bound_out, double* bound_out, double* samples) {
+               int32_t exclude_self, const RecheckCtx& cx, double* sample_bound_out, double* bound_out, bool keep_samples) {
   // R counts the relations of the search, r_begin .. r_begin + R - 1
   int rc;
   hipStream_t st = hd->stream;
@@ -841,29 +926,22 @@ int top_bounds(kgc_handle* hd, const void* E, int64_t N, int32_t d, const void* 
   Top1State* ts = (Top1State*)hd->top1_state.p;
   Top1State host{};
   double* dev_samples = nullptr;
-  if (samples) {
+  if (keep_samples) {
     if ((rc = ensure(hd, hd->top_samples, (size_t)kTopSamples * 8))) return rc;
     dev_samples = (double*)hd->top_samples.p;
   }
   // 1. an upper bound of the answer: the smallest of 65,536 sampled eligible triples
   const int n_sample = kTopSamples;
   k_fill_u32<<<1, 64, 0, st>>>((uint32_t*)ts, sizeof(Top1State) / 4, 0xffffffffu);
-  k_top1_sample<<<grid_for((int64_t)n_sample * 16, 256), 256, 0, st>>>(cx, N, r_begin, R, n_sample, exclude_self ? 1 : 0, ts, dev_samples);
-  if (samples) KGC_HIP(hd, hipMemcpyAsync(samples, dev_samples, (size_t)kTopSamples * 8, hipMemcpyDeviceToHost, st));
-  KGC_HIP(hd, hipMemcpyAsync(&host, ts, sizeof(Top1State), hipMemcpyDeviceToHost, st));
-  KGC_HIP(hd, hipStreamSynchronize(st));
-  double bound;
-  std::memcpy(&bound, &host.sample_min, sizeof(double));
-  if (!(bound >= 0.0) || std::isinf(bound)) return fail(hd, KGC_E_INVALID, "non-finite distances: E or Rvecs hold non-finite values");
-  const double sample_bound = bound;
-
+  k_top1_sample<<<1024, 256, 0, st>>>(cx, N, r_begin, R, n_sample, exclude_self ? 1 : 0, ts, dev_samples);
   // 1b. (L2, head tile fits in LDS, enough entities)  A random triple is almost never a close one, so the
   //     sampled bound is usually far above the answer, where a join prunes nothing.  A dense pass over a
   //     sub-sample -- up to 8,192 heads x 8,192 other tails x the first 32 relations, the barrier-free kernel
   //     with an epilogue that keeps only the smallest squared distance -- costs about a millisecond and
   //     usually lands within a few tens of percent of the answer.
   const int KS = (d + kNormCols + kSliceK - 1) / kSliceK;
-  if (KS <= kDirectMaxKS && N >= 1024) {     // (the pass measures in L2; for an L1 search its bound is scaled below)
+  const bool sub_pass = KS <= kDirectMaxKS && N >= 1024;
+  if (sub_pass) {     // (the pass measures in L2; for an L1 search its bound is scaled below)
     const int m = (int)std::min<int64_t>(8192, (N / 2) / 256 * 256);
     const int Rs = (int)std::min<int32_t>(R, 32);
     const int k16 = (d + kNormCols + 15) / 16;
@@ -893,8 +971,15 @@ int top_bounds(kgc_handle* hd, const void* E, int64_t N, int32_t d, const void* 
     hipLaunchKernelGGL((k_join_l2_direct<256, 2, 4, kEpiMinDist>), dim3((unsigned)(m / 256), (unsigned)Rs, 1), dim3(512), dyn_lds,
                        st, sa);
     k_top1_bound<<<1, 64, 0, st>>>(cnt, hd->cfg.dtype, KS * kSliceK, ts);
-    KGC_HIP(hd, hipMemcpyAsync(&host, ts, sizeof(Top1State), hipMemcpyDeviceToHost, st));
-    KGC_HIP(hd, hipStreamSynchronize(st));
+  }
+  // one read-back for both
+  KGC_HIP(hd, hipMemcpyAsync(&host, ts, sizeof(Top1State), hipMemcpyDeviceToHost, st));
+  KGC_HIP(hd, hipStreamSynchronize(st));
+  double bound;
+  std::memcpy(&bound, &host.sample_min, sizeof(double));
+  if (!(bound >= 0.0) || std::isinf(bound)) return fail(hd, KGC_E_INVALID, "non-finite distances: E or Rvecs hold non-finite values");
+  const double sample_bound = bound;
+  if (sub_pass) {
     // ||x||_1 <= sqrt(d) ||x||_2: the pair that attains the L2 bound is at most that far apart in L1
     const double sub = p == 2 ? host.sub_bound : host.sub_bound * std::sqrt((double)d) * (1.0 + 1e-6);
     if (host.sub_bound >= 0.0 && sub < bound) bound = sub;
@@ -929,7 +1014,7 @@ int kgc_top1(kgc_handle* hd, const void* E, int64_t N, int32_t d, const void* Rv
   set_alignment(cx);
 
   double sample_bound = 0.0, bound = 0.0;
-  if ((rc = top_bounds(hd, E, N, d, Rvecs, 0, R, p, exclude_self, cx, &sample_bound, &bound, nullptr)) != KGC_OK) return rc;
+  if ((rc = top_bounds(hd, E, N, d, Rvecs, 0, R, p, exclude_self, cx, &sample_bound, &bound, false)) != KGC_OK) return rc;
 
   // 2. Joins with a shrinking threshold: every triple at or below the bound comes back; if there are more
   //    than the buffer holds, the smallest distance among those that did come back is the next bound.  The
@@ -1000,11 +1085,10 @@ int kgc_topk_range(kgc_handle* hd, const void* E, int64_t N, int32_t d, const vo
   // thresholds to try: from just above the smallest distance upwards.  The k-th smallest of the sampled
   // distances bounds the k-th smallest of all from above (the sample is drawn with replacement, so on small
   // problems it can hold a triple twice: the loop below then simply goes on growing the threshold).
-  std::vector<double> samples(kTopSamples);
   double sample_bound = 0.0, thr = 0.0;
-  if ((rc = top_bounds(hd, E, N, d, Rvecs, r_begin, Rn, p, exclude_self, cx, &sample_bound, &thr, samples.data())) != KGC_OK) return rc;
-  std::nth_element(samples.begin(), samples.begin() + (size_t)(k - 1), samples.end());
-  const double kth_sample = samples[(size_t)(k - 1)];
+  if ((rc = top_bounds(hd, E, N, d, Rvecs, r_begin, Rn, p, exclude_self, cx, &sample_bound, &thr, true)) != KGC_OK) return rc;
+  double kth_sample = 0.0;                                     // looked up when a join has returned too few (the 65,536
+  bool have_kth = false;                                       // doubles and the selection cost half a millisecond)
   const bool take_all = eligible <= (double)kTopCap / 4;       // a small problem: every triple fits the buffer
   double lo = 0.0;                                             // a threshold known to return fewer than k
   bool have_lo = false;
@@ -1019,6 +1103,14 @@ int kgc_topk_range(kgc_handle* hd, const void* E, int64_t N, int32_t d, const vo
     const uint64_t want = (double)k < eligible ? k : (uint64_t)eligible;
     if (count < want) {                                        // too few: grow (towards the sampled bound first)
       lo = thr; have_lo = true;
+      if (!have_kth) {
+        std::vector<double> samples(kTopSamples);
+        KGC_HIP(hd, hipMemcpyAsync(samples.data(), hd->top_samples.p, (size_t)kTopSamples * 8, hipMemcpyDeviceToHost, st));
+        KGC_HIP(hd, hipStreamSynchronize(st));
+        std::nth_element(samples.begin(), samples.begin() + (size_t)(k - 1), samples.end());
+        kth_sample = samples[(size_t)(k - 1)];
+        have_kth = true;
+      }
       // 8 % steps near the smallest distance (the counts rise steeply there), larger ones if that drags on
       const double grown = thr > 0.0 ? thr * (rounds < 24 ? 1.08 : 1.5) : (kth_sample > 0.0 ? kth_sample * 0x1p-20 : 1e-30);
       thr = (thr < kth_sample && grown > kth_sample) ? kth_sample : grown;
@@ -1038,7 +1130,7 @@ int kgc_topk_range(kgc_handle* hd, const void* E, int64_t N, int32_t d, const vo
   k_topk_init<<<1, 256, 0, st>>>(tk, k);
   for (int shift = 24; shift >= 0; shift -= 8) {
     k_topk_hist<<<256, 256, 0, st>>>((const kgc_triple*)hd->top1_buf.p, &cnt->hits, kTopCap, shift, tk);
-    k_topk_digit<<<1, 64, 0, st>>>(shift, tk);
+    k_topk_digit<<<1, 256, 0, st>>>(shift, tk);
   }
   k_topk_emit<<<256, 256, 0, st>>>((const kgc_triple*)hd->top1_buf.p, &cnt->hits, kTopCap, k, tk, out_triples);
   KGC_HIP(hd, hipGetLastError());
@@ -1246,7 +1338,7 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
 
   hipStream_t st = hd->stream;
   const int dtype = hd->cfg.dtype;
-  const bool prune = hd->cfg.prune != KGC_PRUNE_OFF;
+  const bool prune = hd->cfg.prune != KGC_PRUNE_OFF && !hd->as_dense;
 
   // tile shape
   const int KS = (d + kNormCols + kSliceK - 1) / kSliceK;
@@ -1254,10 +1346,17 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
   // automatic choice.  Dense: the barrier-free head-resident kernel while the head tile fits in LDS with
   // some room to spare (256 rows for KS <= 9, d <= 282; 128 rows for KS <= 19, d <= 602).  Pruned: the head-resident list-walking kernels
   // (KS <= 8, d <= 250; pruned_l2_tile).  Otherwise the streaming kernel.
-  // the relation-factorised form (optional, dense L2 only, head tile in LDS) has one tile shape of its own
-  const bool fact = p == 2 && !prune && !win && !hd->static_mode && !hd->no_fact &&
-                    (hd->cfg.factorised != 0 ? KS <= kDirectMaxKS
-                                             : hd->cfg.tile_cfg == 0 && fact_pays(N, Rn) && KS <= kDirectHalfMaxKS && delta < 1e18f);
+  // the relation-factorised form (dense, head tile in LDS) has one tile shape of its own; a tile_cfg asks for another kernel
+  const bool fact = !prune && !win && !hd->static_mode && !hd->no_fact &&
+                    (p == 2 && hd->cfg.factorised != 0 ? KS <= kDirectMaxKS
+                     : p == 2 ? hd->cfg.tile_cfg == 0 && fact_pays(N, Rn) && KS <= kDirectHalfMaxKS && delta < 1e18f
+                              : hd->cfg.tile_cfg == 0 && fact_pays_l1(N, Rn, d) && KS <= kDirectHalfMaxKS && delta >= 0.f && delta < 1e18f);
+  // ... and the part of a pruned L2 join that the bound test can do nothing for
+  const bool part_ok = p == 2 && prune && !win && !hd->static_mode && !hd->no_fact && hd->cfg.tile_cfg == 0 && hd->cfg.factorised == 0 &&
+                       KS <= kDirectHalfMaxKS && delta >= 0.f && delta < 1e18f;
+  const bool l2_ops = p == 2 || fact;          // staged operands of the matrix pipes
+  const unsigned long long fact_most = fact_list_max(N, Rn, p);
+  const unsigned int fact_cap = p == 2 ? hd->fcap : (unsigned int)std::min<unsigned long long>(hd->fcap, fact_most);
   int tile_id = kDefaultL2Tile;
   if (fact) tile_id = KS <= kDirectMaxKS ? kDirectL2Tile : kDirectHalfL2Tile;
   else if (hd->cfg.tile_cfg > 0) tile_id = hd->cfg.tile_cfg - 1;
@@ -1269,7 +1368,7 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
   const bool pairs_ok = prune && p == 2 && tile_id == kResidentL2Tile;
   if (p == 2 && prune && !tc.listed_kernel)
     return fail(hd, KGC_E_INVALID, "this tile variant has no pruned mode; choose a streaming variant");
-  const int BM = (p == 2) ? tc.bm : kL1Tile, BN = (p == 2) ? tc.bn : kL1Tile;
+  const int BM = l2_ops ? tc.bm : kL1Tile, BN = l2_ops ? tc.bn : kL1Tile;
 
   if ((rc = ensure(hd, hd->counters, sizeof(DevCounters))) || (rc = ensure(hd, hd->params, sizeof(JoinParams))))
     return rc;
@@ -1285,8 +1384,8 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
   if (!reuse) {
     k_fill_u32<<<grid_for(sizeof(DevCounters) / 4, 256), 256, 0, st>>>((uint32_t*)cnt, sizeof(DevCounters) / 4, 0u);
   } else {    // (the running maxima of the staged tail rows stay)
-    k_fill_u32<<<1, 64, 0, st>>>((uint32_t*)cnt, 12, 0u);
-    k_fill_u32<<<1, 64, 0, st>>>(&cnt->n_exact, 2, 0u);
+    k_fill_u32<<<1, 64, 0, st>>>((uint32_t*)cnt, offsetof(DevCounters, max_a) / 4, 0u);
+    k_fill_u32<<<1, 64, 0, st>>>(&cnt->n_exact, (sizeof(DevCounters) - offsetof(DevCounters, n_exact)) / 4, 0u);
   }
   pr.valid = false;
 
@@ -1300,6 +1399,19 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
     Nslots = pr.Nslots; n_groups = pr.n_groups; ut = pr.ut;
   } else if (prune) {
     if ((rc = group_rows(hd, E, N, d, p, delta, KS, k16, &Nslots, &n_groups, &ut)) != KGC_OK) return rc;
+    const int64_t units = (int64_t)ut.n_big + (hd->host_gstate->tail_fill + kMicro - 1) / kMicro;      // (without those that are all padding)
+    if (part_ok && units <= kFewUnits && fact_pays(N, Rn)) {
+      // (almost) all rows in one group: there is nothing to prune by, and the factorised kernel takes the join as a
+      // dense one.  Broad embeddings, N = 20,000, R = 37, d = 512: 71 -> 1.4 ms.
+      float ms = 0.f;
+      (void)hipEventElapsedTime(&ms, hd->ev[0], hd->ev[3]);
+      hd->as_dense = true;
+      rc = join_range_impl(hd, E, N, d, Rvecs, R, p, delta, r_begin, r_end, out_triples, cap, count, nullptr, kPrepFresh);
+      hd->as_dense = false;
+      pr.valid = false;
+      hd->stats.groups = n_groups; hd->stats.ms_prune += ms; hd->stats.ms_total += ms;
+      return rc;
+    }
   } else {
     if ((rc = ensure(hd, hd->slot_ent, Nslots * 4))) return rc;
     k_identity_slots<<<grid_for(Nslots, 256), 256, 0, st>>>((int32_t*)hd->slot_ent.p, N, Nslots);
@@ -1309,12 +1421,21 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
   const int64_t n_micro = Nslots / kMicro;
   const int words_per_row = (nT + 31) / 32;
   const int64_t tiles_per_rel = (int64_t)nH * nT;
+  // Rows without a group lie in the packed region behind the groups, in micro-tiles of strangers whose radius lets no
+  // bound rule anything out.  The pairs inside that region go to the factorised kernel, which contracts each once for
+  // all relations; the tile lists leave them out.
+  int64_t part0 = Nslots;                                // first slot of the part (whole tiles of every shape)
+  if (part_ok) {
+    const int64_t f = ((int64_t)ut.tail_first * kMicro + kSlotAlign - 1) / kSlotAlign * kSlotAlign;
+    if (part_pays(Nslots - f, Rn)) part0 = f;
+  }
+  const int64_t part_n = Nslots - part0;
   if (nH > 65535) return fail(hd, KGC_E_INVALID, "N too large for one launch grid");
 
   // ---- relation batches: staged A operands (L2) and the tile lists (pruning) must fit the workspace ----
   const int64_t ws = hd->ws_override > 0 ? hd->ws_override
                                            : hd->cfg.workspace_bytes > 0 ? hd->cfg.workspace_bytes : kDefaultWorkspace;
-  const size_t opA_per_rel = (p == 2) ? (size_t)KS * Nslots * kSliceK * 2 : 0;
+  const size_t opA_per_rel = l2_ops ? (size_t)KS * Nslots * kSliceK * 2 : 0;
   int64_t RBmax = Rn;
   if (p == 2 && !fact) RBmax = std::max<int64_t>(1, std::min<int64_t>(Rn, ws / (int64_t)(opA_per_rel + Nslots * 4)));
   if (fact) RBmax = std::max<int64_t>(1, std::min<int64_t>(Rn, ws / (int64_t)(Nslots * 4)));      // u[r][slot]
@@ -1322,7 +1443,7 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
   RBmax = std::max<int64_t>(1, std::min<int64_t>(RBmax, 65535));
   if (prune && tiles_per_rel > kMaxTileList) return fail(hd, KGC_E_INVALID, "N too large for the pruned tile list");
 
-  if (p == 2) {
+  if (l2_ops) {
     if ((rc = ensure(hd, hd->opB, (size_t)KS * Nslots * kSliceK * 2)) ||
         (rc = ensure(hd, hd->opA, opA_per_rel * (size_t)(fact ? 1 : RBmax))) || (rc = ensure(hd, hd->normsB, Nslots * 4)) ||
         (rc = ensure(hd, hd->normsA, (size_t)(fact ? 1 : RBmax) * Nslots * 4)))
@@ -1352,7 +1473,7 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
       return rc;
     // with few micro-tiles the M x M matrix of centre distances and the R x M products cost more than the handful of
     // micro-tile pairs that are looked up in them
-    fine_direct = use_units && p == 2 && n_micro <= 8192;
+    fine_direct = use_units && p == 2 && n_micro <= 8192 && (int64_t)ut.n_units * 16 > n_micro;
     if (use_units && p == 2 && ((rc = ensure(hd, hd->gram_u, (size_t)ut.n_units * ut.n_units * 4)) ||
                                 (rc = ensure(hd, hd->relu_u, (size_t)RBmax * ut.n_units * 4))))
       return rc;
@@ -1390,7 +1511,7 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
           k_tile_dist<2, kEpiMatrix><<<g, 256, 0, st>>>(ta);
       }
       if (use_units) {
-        k_unit_summary<2><<<(unsigned)ut.n_units, 64, 0, st>>>((const float*)hd->cent.p, (const float*)hd->rad.p, d, ut,
+        k_unit_summary<2><<<(unsigned)ut.n_units, kUnitWaves * 64, 0, st>>>((const float*)hd->cent.p, (const float*)hd->rad.p, d, ut,
                                                             (float*)hd->cent_u.p, (float*)hd->rad_u.p, (float*)hd->cnorm_u.p);
         TileDistArgs tu{};
         tu.X = hd->cent_u.p; tu.dtypeX = KGC_F32; tu.n_rows = ut.n_units; tu.Y = hd->cent_u.p; tu.dtypeY = KGC_F32;
@@ -1402,14 +1523,14 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
       k_micro_summary<1><<<(unsigned)n_micro, 64, 0, st>>>(E, dtype, d, slot_ent, n_micro, (float*)hd->cent.p,
                                                             (float*)hd->rad.p, (float*)hd->cnorm.p);
       if (use_units)
-        k_unit_summary<1><<<(unsigned)ut.n_units, 64, 0, st>>>((const float*)hd->cent.p, (const float*)hd->rad.p, d, ut,
+        k_unit_summary<1><<<(unsigned)ut.n_units, kUnitWaves * 64, 0, st>>>((const float*)hd->cent.p, (const float*)hd->rad.p, d, ut,
                                                                (float*)hd->cent_u.p, (float*)hd->rad_u.p, (float*)hd->cnorm_u.p);
     }
   }
   const size_t stage_lds = (size_t)kStageRows * (KS * kSliceK + 8) * 2;
   if (reuse) {
     // tail operands, summaries and (L1) the join parameters are in place
-  } else if (p == 2) {
+  } else if (l2_ops) {
     k_stage_operands<false><<<grid_for(Nslots / kStageRows, 1), 256, stage_lds, st>>>(
         E, Rvecs, dtype, d, 0, 1, slot_ent, Nslots, KS, (uint16_t*)hd->opB.p, (float*)hd->normsB.p, cnt->max_b, nullptr, nullptr, 0, kStageRows,
         0, nullptr, fact ? -1.f : delta);      // (the factorised filter has an error analysis of its own: plain norms)
@@ -1418,12 +1539,39 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
           E, nullptr, dtype, d, 0, 1, slot_ent, Nslots, KS, (uint16_t*)hd->opA.p, (float*)hd->normsA.p, cnt->max_a, nullptr,
           nullptr, 0, kStageRows);
   } else {
-    k_row_l1_max<<<grid_for(N * 32, 256), 256, 0, st>>>(E, N, d, dtype, cnt->max_a);
-    k_row_l1_max<<<grid_for((int64_t)R * 32, 256), 256, 0, st>>>(Rvecs, R, d, dtype, cnt->max_b);
+    k_row_l1_max<<<grid_l1_max(N), 256, 0, st>>>(E, N, d, dtype, cnt->max_a);
+    k_row_l1_max<<<grid_l1_max(R), 256, 0, st>>>(Rvecs, R, d, dtype, cnt->max_b);
     k_join_params<<<1, 64, 0, st>>>(cnt, prm, delta, p, dtype, d, 0);
   }
   KGC_HIP(hd, hipEventRecord(hd->ev[1], st));
-  const bool bitmap_ready = reuse && pr.bitmap_valid && pr.bm_r0 == r_begin && pr.bm_r1 == r_end && nbatch == 1;
+  if (part_n) {
+    const size_t op = (size_t)KS * part_n * kSliceK * 2;
+    const int64_t RBf = std::max<int64_t>(1, std::min<int64_t>({Rn, ws / (part_n * 4), 65535}));
+    if ((rc = ensure(hd, hd->fop_a, op)) || (rc = ensure(hd, hd->fop_b, op)) || (rc = ensure(hd, hd->fu, (size_t)fact_rows(RBf) * part_n * 4)) ||
+        (rc = ensure(hd, hd->limr, fact_rows(RBf) * 4)) || (rc = ensure(hd, hd->umin, (size_t)fact_rows(RBf) * (part_n / 64) * 10 * 4)) ||
+        (rc = ensure(hd, hd->flist, (size_t)hd->fcap * sizeof(ExactEntry))))
+      return rc;
+    FactJob fj{};
+    fj.E = E; fj.Rv = Rvecs; fj.dtype = dtype; fj.d = d; fj.delta = delta; fj.slot_ent = slot_ent + part0; fj.Nslots = part_n;
+    fj.A = (const uint16_t*)hd->fop_a.p; fj.B = (const uint16_t*)hd->fop_b.p;
+    fj.u = (float*)hd->fu.p; fj.umin = (float*)hd->umin.p; fj.limr = (float*)hd->limr.p;
+    fj.list = (ExactEntry*)hd->flist.p; fj.list_cap = hd->fcap; fj.give_up = std::max<unsigned long long>(fact_most, hd->fcap);
+    // (the running maxima of the norms, shared with the other kernels' operands, only widen the thresholds)
+    k_stage_operands<false><<<grid_for(part_n / kStageRows, 1), 256, stage_lds, st>>>(
+        E, nullptr, dtype, d, 0, 1, fj.slot_ent, part_n, KS, (uint16_t*)hd->fop_b.p, nullptr, cnt->max_b, nullptr, nullptr, 0, kStageRows,
+        0, nullptr, -1.f);
+    k_stage_operands<true><<<grid_for(part_n / kStageRows, 1), 256, stage_lds, st>>>(
+        E, nullptr, dtype, d, 0, 1, fj.slot_ent, part_n, KS, (uint16_t*)hd->fop_a.p, nullptr, cnt->max_a, nullptr, nullptr, 0, kStageRows);
+    RecheckCtx cxf = cx;
+    cxf.slot_ent = cxf.slot_ent_t = fj.slot_ent;
+    for (int64_t r0 = r_begin; r0 < r_end; r0 += RBf) {
+      fj.r0 = (int)r0; fj.RB = (int)std::min<int64_t>(RBf, r_end - r0);
+      launch_fact_products(st, fj, cnt);
+      if ((rc = launch_fact_join(hd, st, fj, cnt, cxf)) != KGC_OK) return rc;
+      if (r0 + RBf < r_end) k_fill_u32<<<1, 64, 0, st>>>((uint32_t*)&cnt->n_fact, 2, 0u);      // an empty list for the next batch
+    }
+  }
+  const bool bitmap_ready = reuse && part_n == 0 && pr.bitmap_valid && pr.bm_r0 == r_begin && pr.bm_r1 == r_end && nbatch == 1;
   pr.E = E; pr.Rv = Rvecs; pr.N = N; pr.d = d; pr.p = p; pr.dtype = dtype; pr.prune = (int)prune; pr.tile_id = tile_id;
   pr.delta = delta; pr.group_radius = hd->cfg.group_radius; pr.Nslots = Nslots; pr.n_groups = n_groups; pr.ut = ut;
   pr.bitmap_valid = false;
@@ -1454,7 +1602,7 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
       // The bound test (flat, or the micro-tile level of the two-level one) can list the surviving tiles itself; when they are few, that list serves the tile-at-a-time
       // join kernel and the pass over the bitmap is skipped (the device decides, k_batch_tiles).  Not with a window:
       // the list would hold the tiles outside it too.
-      const bool direct_lists = pairs_ok && !win && !bitmap_ready && delta >= 0.f && p == 2;
+      const bool direct_lists = pairs_ok && !win && !bitmap_ready && delta >= 0.f && p == 2 && part_n == 0;
       if (b > 0) k_fill_u32<<<1, 64, 0, st>>>((uint32_t*)&cnt->tile_cursor, 3, 0u);      // cursor and n_active (zero at the start of a call)
       if (bitmap_ready) {
         // the bound test of these relations is still in the bitmap (the previous window of the same relation range)
@@ -1478,6 +1626,7 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
         ba.rad = (const float*)hd->rad.p; ba.cnorm = (const float*)hd->cnorm.p; ba.n_micro = n_micro; ba.RB = RB;
         ba.d = d; ba.delta = delta; ba.bitmap = (uint32_t*)hd->bitmap.p; ba.nH = nH; ba.words_per_row = words_per_row;
         ba.micro_per_bm = BM / kMicro; ba.micro_per_bn = BN / kMicro;
+        ba.both_from = part0 / kMicro;
         if (direct_lists) {
           ba.list_cols = (uint32_t*)hd->cols.p; ba.list_rows = (uint32_t*)hd->tile_rows.p; ba.list_active = (uint32_t*)hd->active_rows.p;
           ba.list_count = &cnt->tile_cursor;
@@ -1497,9 +1646,10 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
           BoundL2Args bu = ba;
           bu.D = (const float*)hd->gram_u.p; bu.u = (const float*)hd->relu_u.p; bu.rad = (const float*)hd->rad_u.p;
           bu.cnorm = (const float*)hd->cnorm_u.p; bu.n_micro = ut.n_units;
+          bu.both_from = ut.n_big + part0 / kMicro - ut.tail_first;
           BoundPairs bp{(unsigned long long*)hd->pair_list.p, (unsigned long long*)hd->pair_count.p, kBoundPairCap};
-          if (ut.n_units <= 8192 && (int64_t)ut.n_units * 4 > n_micro) {
-            // units of a micro-tile or two (few unit pairs survive): the flat kernel's form -- table, first comparison per
+          if (ut.n_units <= 8192 && ((int64_t)ut.n_units * 4 > n_micro || part_n)) {
+            // units of a micro-tile or two, or pairs of rows without a group left out (few unit pairs survive): the flat kernel's form -- table, first comparison per
             // chunk, loads in groups -- 137 -> 59 us on the N = 100,000 workload
             const dim3 gu((unsigned)((ut.n_units + 255) / 256), (unsigned)((ut.n_units + kHeadsFlat - 1) / kHeadsFlat),
                           (unsigned)((RB + kRelChunk - 1) / kRelChunk));
@@ -1544,11 +1694,12 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
       if (direct_lists)
         k_batch_tiles<<<1, 64, 0, st>>>(cnt, 1, 1, (unsigned long long)RB * nH,
                                         (unsigned long long)std::min<int64_t>((int64_t)RB * nH, (int64_t)RB * tiles_per_rel));
-      k_rows_from_bitmap<<<(unsigned)(((int64_t)RB * nH + 256 * bitmap_rows_per_lane(words_per_row) - 1) / (256 * bitmap_rows_per_lane(words_per_row))), 256, 0, st>>>(
+      k_rows_from_bitmap<<<(unsigned)(((int64_t)RB * nH + 256 * bitmap_rows_per_lane(words_per_row, (int64_t)RB * nH) - 1) / (256 * bitmap_rows_per_lane(words_per_row, (int64_t)RB * nH))), 256, 0, st>>>(
           (const uint32_t*)hd->bitmap.p, words_per_row, (int64_t)RB * nH, (uint32_t*)hd->row_start.p,
           (uint32_t*)hd->row_count.p, (uint32_t*)hd->cols.p, &cnt->tile_cursor, (uint32_t*)hd->active_rows.p,
           &cnt->n_active, pairs_ok ? (uint32_t*)hd->tile_rows.p : nullptr, nH, wH0, wH1, wT0, wT1,
-          direct_lists ? &cnt->pair_mode : nullptr, direct_lists ? &cnt->tiles : nullptr);
+          direct_lists ? &cnt->pair_mode : nullptr, direct_lists ? &cnt->tiles : nullptr,
+          part_n ? (int)(part0 / BM) : 0x7fffffff, part_n ? (int)(part0 / BN) : 0x7fffffff);
       if (!direct_lists) k_batch_tiles<<<1, 64, 0, st>>>(cnt, pairs_ok ? 1 : 0, 0, 0ull, 0ull);
       row_start = (const uint32_t*)hd->row_start.p;
       row_count = (const uint32_t*)hd->row_count.p;
@@ -1559,29 +1710,14 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
     // pruned launches stride a fixed grid over the active rows (their number is only known on the device)
     const unsigned row_grid = (unsigned)std::min<int64_t>((int64_t)RB * nH, 4096);
     if (fact) {
-      // u[rl][slot] = r . e with its extremes over 8 and 64 slots, then the thresholds
-      const int RBp = (int)fact_rows(RB);
-      float* umin8 = (float*)hd->umin.p;
-      float* umin64 = umin8 + (size_t)RBp * (Nslots / 64) * 8;
-      float* umax64 = umin64 + (size_t)RBp * (Nslots / 64);
-      launch_fact_dot(st, Rvecs, E, dtype, slot_ent, Nslots, (int)r0, RB, RBp, d, (float*)hd->relu.p, umin8, umin64, umax64);
-      k_fact_params<<<grid_for(RBp, 4), 256, 0, st>>>(cnt, Rvecs, (int)r0, RB, RBp, delta, dtype, d, KS * kSliceK, (float*)hd->limr.p);
+      FactJob fj{};
+      fj.E = E; fj.Rv = Rvecs; fj.dtype = dtype; fj.d = d; fj.r0 = (int)r0; fj.RB = RB; fj.delta = delta;
+      fj.slot_ent = slot_ent; fj.Nslots = Nslots; fj.A = (const uint16_t*)hd->opA.p; fj.B = (const uint16_t*)hd->opB.p;
+      fj.u = (float*)hd->relu.p; fj.umin = (float*)hd->umin.p; fj.limr = (float*)hd->limr.p;
+      fj.list = (ExactEntry*)hd->flist.p; fj.list_cap = fact_cap; fj.give_up = std::max<unsigned long long>(fact_most, fact_cap);
+      launch_fact_products(st, fj, cnt);
       if (timed) KGC_HIP(hd, hipEventRecord(hd->join_ev[2 * b], st));
-      JoinFactArgs fa{};
-      fa.A = (const uint16_t*)hd->opA.p; fa.B = (const uint16_t*)hd->opB.p; fa.u = (const float*)hd->relu.p;
-      fa.limr = (const float*)hd->limr.p; fa.umin8 = umin8; fa.umin64 = umin64; fa.umax64 = umax64; fa.Nslots = Nslots; fa.KS = KS; fa.k16 = k16;
-      fa.nT = nT; fa.r0 = (int)r0; fa.RBp = RBp;
-      fa.list = (ExactEntry*)hd->flist.p; fa.list_count = &cnt->n_fact; fa.list_cap = hd->fcap; fa.give_up = std::max<unsigned long long>(kFactListMax, hd->fcap);
-      void (*kern)(const JoinFactArgs) = BM == 256 ? k_join_l2_fact<4, 2, 4> : k_join_l2_fact<2, 2, 4>;
-      const size_t dyn_lds = (size_t)KS * BM * kSliceK * 2 + 8 * kFactWaveLds;
-      // a block takes a range of tail tiles of one head tile; with few tile pairs the relations are cut too
-      const int64_t pairs = (int64_t)nH * nT;
-      const int64_t nsplit = std::max<int64_t>(1, std::min<int64_t>({(4096 + nH - 1) / nH, (int64_t)nT, 65535}));
-      const int64_t nz = std::max<int64_t>(1, std::min<int64_t>((1024 + pairs - 1) / pairs, (RBp + 63) / 64));
-      fa.zrel = (int)((RBp + nz - 1) / nz + 7) / 8 * 8;
-      KGC_HIP(hd, hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn_lds));
-      hipLaunchKernelGGL(kern, dim3((unsigned)nH, (unsigned)nsplit, (unsigned)((RBp + fa.zrel - 1) / fa.zrel)), dim3(512), dyn_lds, st, fa);
-      k_exact_pairs<<<2048, 256, 0, st>>>(fa.list, fa.list_count, fa.list_cap, &cnt->exact_need, cx);
+      if ((rc = launch_fact_join(hd, st, fj, cnt, cx)) != KGC_OK) return rc;
       if (r0 + RBmax < r_end) k_fill_u32<<<1, 64, 0, st>>>((uint32_t*)&cnt->n_fact, 2, 0u);      // an empty list for the next batch
       if (timed) KGC_HIP(hd, hipEventRecord(hd->join_ev[2 * b + 1], st));
     } else if (p == 2) {
@@ -1683,30 +1819,30 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
       la.n_active = n_active; la.cx = cx;
       if (!prune) { la.nH = nHw; la.nT = nTw; la.cx = cxw; }
       if (timed) KGC_HIP(hd, hipEventRecord(hd->join_ev[2 * b], st));
-      hipLaunchKernelGGL(k_join_l1, prune ? dim3(row_grid, 1, 1) : dim3((unsigned)nTw, (unsigned)nHw, (unsigned)RB), dim3(256), 0,
+      hipLaunchKernelGGL(l1_kernel_for(la.cx), prune ? dim3(row_grid, 1, 1) : dim3((unsigned)nTw, (unsigned)nHw, (unsigned)RB), dim3(256), 0,
                          st, la);
       if (timed) KGC_HIP(hd, hipEventRecord(hd->join_ev[2 * b + 1], st));
     }
     hd->stats.join_launches++;
   }
   KGC_HIP(hd, hipGetLastError());
-  KGC_HIP(hd, hipMemcpyAsync(hd->host_counters, cnt, 48, hipMemcpyDeviceToHost, st));
+  KGC_HIP(hd, hipMemcpyAsync(hd->host_counters, cnt, offsetof(DevCounters, max_a), hipMemcpyDeviceToHost, st));
   KGC_HIP(hd, hipEventRecord(hd->ev[2], st));
   KGC_HIP(hd, wait_event(hd->ev[2]));
 
   pr.valid = !fact;                  // what the handle now holds describes this join
-  pr.bitmap_valid = prune && nbatch == 1 && !empty_window; pr.bm_r0 = r_begin; pr.bm_r1 = r_end;
+  pr.bitmap_valid = prune && nbatch == 1 && !empty_window && part_n == 0; pr.bm_r0 = r_begin; pr.bm_r1 = r_end;
   // A batch that wanted to list more accumulator blocks than the list holds has dropped the rest (and counted
   // them): the list grows to what was asked for and the join runs again from the start.
-  if (fact && hd->host_counters->exact_need > hd->fcap) {      // (the same of the relation-factorised kernel's list of pairs)
-    const unsigned long long need = hd->host_counters->exact_need;
-    if (need <= kFactListMax) hd->fcap = (unsigned int)(need + need / 4 + 1024);
-    hd->no_fact = need > kFactListMax;                          // a threshold that passes so much: pair by pair, scored in place
+  if (hd->host_counters->fact_need > fact_cap) {      // (the same of the relation-factorised kernel's list of pairs)
+    const unsigned long long need = hd->host_counters->fact_need;
+    if (need <= fact_most) hd->fcap = (unsigned int)(need + need / 4 + 1024);
+    hd->no_fact = need > fact_most;                          // a threshold that passes so much: pair by pair, scored in place
     const int rc2 = join_range_impl(hd, E, N, d, Rvecs, R, p, delta, r_begin, r_end, out_triples, cap, count, win, prep_mode);
     hd->no_fact = false;
     return rc2;
   }
-  if (!fact && hd->host_counters->exact_need > hd->xcap) {
+  if (hd->host_counters->exact_need > hd->xcap) {
     const unsigned long long need = hd->host_counters->exact_need;
     hd->xcap = (unsigned int)std::min<unsigned long long>(need + need / 4 + 1024, 0xffffffffull);
     return join_range_impl(hd, E, N, d, Rvecs, R, p, delta, r_begin, r_end, out_triples, cap, count, win,
@@ -1717,14 +1853,14 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
   s.emitted = hd->host_counters->hits;
   s.candidates = hd->host_counters->candidates;
   s.tiles_total = (uint64_t)tiles_per_rel * (uint64_t)Rn;
-  s.tiles_evaluated = prune ? hd->host_counters->tiles : s.tiles_total;
+  s.tiles_evaluated = prune ? hd->host_counters->tiles + (uint64_t)(part_n / BM) * (uint64_t)(part_n / BN) * (uint64_t)Rn : s.tiles_total;
   s.tiles_pruned = s.tiles_total - s.tiles_evaluated;
   s.pairs_evaluated = prune ? s.tiles_evaluated * (uint64_t)BM * (uint64_t)BN : s.triples_total;
   s.groups = n_groups;
   s.tile_m = BM; s.tile_n = BN;
-  s.k_padded = (p == 2) ? k16 * 16 : d;
+  s.k_padded = l2_ops ? k16 * 16 : d;
   s.relation_batches = nbatch;
-  s.join_variant = (p == 2) ? (fact ? 100 : tile_id + 1) : 0;
+  s.join_variant = fact ? 100 : p == 2 ? tile_id + 1 : 0;
   s.exact_blocks = (int32_t)std::min<unsigned long long>(hd->host_counters->exact_total, 2147483647ull);
   // phase times from the events: [ev0 grouping ev3 | summaries + B staging ev1 | per batch: bound test + A staging | join]
   float ms = 0.f, ms_group = 0.f, ms_between = 0.f;

@@ -40,6 +40,7 @@ struct DevCounters {
   unsigned int exact_need;        // most accumulator blocks any one batch wanted to list (see list_block)
   unsigned long long tiles;       // surviving tiles over all batches
   unsigned long long exact_total; // accumulator blocks scored by the block form of the exact stage, over all batches
+  unsigned int fact_need, pad;    // most pairs any one batch of the relation-factorised kernel wanted to list
   unsigned int max_a[1024];       // running maxima of ||bf16(h + r)||^2 (L2) or ||e||_1 (L1), float bits, spread over slots
   unsigned int max_b[1024];       // running maxima of ||bf16(t)||^2 (L2) or ||r||_1 (L1)
   unsigned int n_exact;           // accumulator blocks listed for the exact stage by the pruned L2 join kernels (per batch)
@@ -297,22 +298,34 @@ __global__ void k_scatter_norms(const float* __restrict__ norms, const int32_t* 
   if (ent >= 0) outp[(int64_t)rl * N + ent] = norms[i];
 }
 
-// max over rows of the L1 norm (used for the float32 error bound of the L1 filter)
+// max over rows of the L1 norm (used for the float32 error bound of the L1 filter); a half-wave takes four rows at a
+// time, their loads in flight together
 __global__ __launch_bounds__(256) void k_row_l1_max(const void* __restrict__ X, int64_t rows, int d, int dtype,
                                                     unsigned int* __restrict__ max_bits) {
   const int j = threadIdx.x & 31;
   const int64_t hw = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 5;
   const int64_t nhw = ((int64_t)gridDim.x * blockDim.x) >> 5;
   float vmax = 0.f;
-  for (int64_t row = hw; row < rows; row += nhw) {
-    float s = 0.f;
-    for (int c = j; c < d; c += 32) s += fabsf(ld_elem(X, row * d + c, dtype));
-    s += __shfl_xor(s, 16, 32);
-    s += __shfl_xor(s, 8, 32);
-    s += __shfl_xor(s, 4, 32);
-    s += __shfl_xor(s, 2, 32);
-    s += __shfl_xor(s, 1, 32);
-    vmax = fmaxf(vmax, s);
+  for (int64_t row = hw; row < rows; row += 4 * nhw) {
+    float s[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) s[q] = 0.f;
+    for (int c = j; c < d; c += 32) {
+      float v[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) v[q] = ld_elem(X, (row + q * nhw < rows ? row + q * nhw : row) * d + c, dtype);      // (past the end: this row again)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) s[q] += fabsf(v[q]);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      s[q] += __shfl_xor(s[q], 16, 32);
+      s[q] += __shfl_xor(s[q], 8, 32);
+      s[q] += __shfl_xor(s[q], 4, 32);
+      s[q] += __shfl_xor(s[q], 2, 32);
+      s[q] += __shfl_xor(s[q], 1, 32);
+      vmax = fmaxf(vmax, s[q]);
+    }
   }
   if (j == 0) atomicMax(&max_bits[blockIdx.x % kMaxSlots], __float_as_uint(vmax));
 }
@@ -1373,15 +1386,35 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1) void k_join_l2_direct(const JoinS
           if (EPI == kEpiJoin) {                                                                  \
             recheck_and_emit(cm, a.r0 + rl, a.cx, map);                                           \
           } else {                                                                                \
-            /* every lane files its own elements; the lowest pivot position within reach wins (only the */ \
-            /* position matters to the round: the low word, a distance in the float32 form, stays 0)   */ \
-            while (cm) {                                                                          \
-              const int e = (int)__builtin_ctzll(cm);                                             \
-              cm &= cm - 1ull;                                                                    \
-              int64_t hslot, tslot;                                                               \
-              map(e, lane, hslot, tslot);                                                         \
-              if (hslot < a.n_heads && a.group_of[hslot] < 0)                                     \
-                atomicMin(&a.best[hslot], (unsigned long long)(uint32_t)tslot << 32);             \
+            /* only the lowest pivot position within reach matters to the round (the low word, a distance in the */ \
+            /* float32 form, stays 0).  At most a quarter of the pairs within reach: every lane files its own     */ \
+            if (__builtin_amdgcn_ballot_w64(__builtin_popcountll(cm) > 16) == 0ull) {              \
+              while (cm) {                                                                        \
+                const int e = (int)__builtin_ctzll(cm);                                           \
+                cm &= cm - 1ull;                                                                  \
+                int64_t hslot, tslot;                                                             \
+                map(e, lane, hslot, tslot);                                                       \
+                if (hslot < a.n_heads && a.group_of[hslot] < 0)                                   \
+                  atomicMin(&a.best[hslot], (unsigned long long)(uint32_t)tslot << 32);           \
+              }                                                                                   \
+              continue;                                                                           \
+            }                                                                                     \
+            /* many (a radius that spans the rows): per element one lane of each half, whose 32 lanes hold one  */ \
+            /* head row and pivots in ascending order, files it, and only if nothing lower is there yet (N =    */ \
+            /* 20,000, d = 512, one group: 5.9 -> 0.36 ms for the rounds, which atomics on one row bounded)     */ \
+            _Pragma("unroll 1") for (int e = 0; e < 64; ++e) {                                    \
+              const bool in = (cm >> e) & 1ull;                                                   \
+              const unsigned long long b = __builtin_amdgcn_ballot_w64(in);                       \
+              if (b == 0ull) continue;                                                            \
+              const uint32_t half = (uint32_t)(lane < 32 ? b : b >> 32);                          \
+              if (in && (lane & 31) == __builtin_ctz(half)) {                                     \
+                int64_t hslot, tslot;                                                             \
+                map(e, lane, hslot, tslot);                                                       \
+                const unsigned long long v64 = (unsigned long long)(uint32_t)tslot << 32;         \
+                if (hslot < a.n_heads && a.group_of[hslot] < 0 &&                                 \
+                    __hip_atomic_load(&a.best[hslot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > v64) \
+                  atomicMin(&a.best[hslot], v64);                                                 \
+              }                                                                                   \
             }                                                                                     \
           }                                                                                       \
         }                                                                                         \
@@ -1809,7 +1842,7 @@ __global__ __launch_bounds__(256) void k_exact_pairs(const ExactEntry* __restric
                                                      unsigned int cap, unsigned int* __restrict__ need, const RecheckCtx cx) {
   __shared__ unsigned int wave_hits[4];
   __shared__ unsigned long long base_s;
-  const unsigned int n = *count < cap ? (unsigned int)*count : cap;
+  const unsigned int n = *count <= cap ? (unsigned int)*count : 0u;      // (a list that did not fit: the host runs the call again)
   const int lane = lane_id(), wave = (int)(threadIdx.x >> 6), grp = lane >> 4, sub = lane & 15;
   for (unsigned int e0 = blockIdx.x * 256u; e0 < n; e0 += gridDim.x * 256u) {       // the same for the whole block
     const unsigned int first = e0 + (unsigned)wave * 64u;
@@ -1851,7 +1884,7 @@ __global__ __launch_bounds__(256) void k_exact_pairs(const ExactEntry* __restric
     }
     __syncthreads();
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0 && n) {
+  if (blockIdx.x == 0 && threadIdx.x == 0 && *count) {
     atomicAdd(cx.cand_counter, (unsigned long long)n);
     atomicMax(need, *count < 0xffffffffull ? (unsigned int)*count : 0xffffffffu);
   }
@@ -1916,21 +1949,27 @@ __device__ __forceinline__ uint32_t top1_hash(uint32_t x) {
   return x;
 }
 
+// The minimum is taken per wave first: with one atomic per sample the 65,536 on one word were the kernel's time (190 us).
 __global__ __launch_bounds__(256) void k_top1_sample(RecheckCtx cx, int64_t N, int r_begin, int R, int n, int no_self,
                                                      Top1State* st, double* all = nullptr) {
-  const int64_t g = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 4;
   const int sub = threadIdx.x & 15;
-  if (g >= n) return;                                   // whole 16-lane groups leave together
-  const uint32_t a = top1_hash((uint32_t)g * 3u + 1u), b = top1_hash((uint32_t)g * 3u + 2u), c = top1_hash((uint32_t)g * 3u + 3u);
-  const int32_t h = (int32_t)(((uint64_t)a * (uint64_t)N) >> 32);
-  int32_t t = (int32_t)(((uint64_t)b * (uint64_t)N) >> 32);
-  const int32_t r = r_begin + (int32_t)(((uint64_t)c * (uint64_t)R) >> 32);      // R relations from r_begin on
-  if (no_self && t == h) t = (t + 1 == N) ? 0 : t + 1;  // N >= 2 is checked on the host
-  const double dist = group16_exact_dist(cx, h, r, t, sub);
-  if (sub == 0) {
-    atomicMin(&st->sample_min, (unsigned long long)__double_as_longlong(dist));
-    if (all) all[g] = dist;                               // top-k: the whole sample goes to the host
+  unsigned long long best = ~0ull;                        // bits of non-negative doubles order like the numbers
+  for (int64_t g = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 4; g < n; g += ((int64_t)gridDim.x * blockDim.x) >> 4) {
+    const uint32_t a = top1_hash((uint32_t)g * 3u + 1u), b = top1_hash((uint32_t)g * 3u + 2u), c = top1_hash((uint32_t)g * 3u + 3u);
+    const int32_t h = (int32_t)(((uint64_t)a * (uint64_t)N) >> 32);
+    int32_t t = (int32_t)(((uint64_t)b * (uint64_t)N) >> 32);
+    const int32_t r = r_begin + (int32_t)(((uint64_t)c * (uint64_t)R) >> 32);      // R relations from r_begin on
+    if (no_self && t == h) t = (t + 1 == N) ? 0 : t + 1;  // N >= 2 is checked on the host
+    const double dist = group16_exact_dist(cx, h, r, t, sub);      // (all 16 lanes of a group run the same rounds)
+    const unsigned long long bits = (unsigned long long)__double_as_longlong(dist);
+    best = bits < best ? bits : best;
+    if (all && sub == 0) all[g] = dist;                   // top-k: the sample stays on the device until it is asked for
   }
+  for (int off = 16; off < 64; off <<= 1) {
+    const unsigned long long o = (unsigned long long)__shfl_xor((long long)best, off, 64);
+    best = o < best ? o : best;
+  }
+  if ((threadIdx.x & 63) == 0 && best != ~0ull) atomicMin(&st->sample_min, best);
 }
 
 __global__ __launch_bounds__(256) void k_top1_min(const kgc_triple* __restrict__ rec, const unsigned long long* __restrict__ count,
@@ -2020,20 +2059,29 @@ __global__ __launch_bounds__(256) void k_topk_hist(const kgc_triple* __restrict_
   if (h[threadIdx.x]) atomicAdd(&ts->hist[threadIdx.x], h[threadIdx.x]);
 }
 
-// one thread: which digit holds the need-th record among the matching keys; fix it and clear the histogram
-__global__ void k_topk_digit(int shift, TopkState* ts) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  unsigned long long need = ts->need, acc = 0ull;
-  int dsel = 255;
-  for (int b = 0; b < 256; ++b) {
-    const unsigned long long c = ts->hist[b];
-    if (acc + c >= need) { dsel = b; break; }
-    acc += c;
+// which digit holds the need-th record among the matching keys (one workgroup, one digit per thread: a prefix sum);
+// fix it and clear the histogram
+__global__ __launch_bounds__(256) void k_topk_digit(int shift, TopkState* ts) {
+  __shared__ unsigned int incl[256];
+  const int b = threadIdx.x;
+  const unsigned int c = ts->hist[b];
+  const unsigned long long need = ts->need;
+  incl[b] = c;
+  __syncthreads();
+  for (int off = 1; off < 256; off <<= 1) {
+    const unsigned int v = b >= off ? incl[b - off] : 0u;
+    __syncthreads();
+    incl[b] += v;
+    __syncthreads();
   }
-  ts->need = need - acc;            // still wanted inside the chosen digit
-  ts->prefix |= (unsigned int)dsel << shift;
-  ts->mask |= 255u << shift;
-  for (int b = 0; b < 256; ++b) ts->hist[b] = 0u;
+  const unsigned long long hi = incl[b], lo = hi - c;
+  const bool none = b == 255 && hi < need;                // fewer records than asked for: the last digit, all of them counted
+  if ((lo < need && hi >= need) || none) {                // one thread (need > 0)
+    ts->need = need - (none ? hi : lo);                   // still wanted inside the chosen digit
+    ts->prefix |= (unsigned int)b << shift;
+    ts->mask |= 255u << shift;
+  }
+  ts->hist[b] = 0u;
 }
 
 // after four passes prefix is the k-th smallest key T and need the number of records with key == T to take:
@@ -2085,14 +2133,25 @@ struct JoinL1Args {
 // staged through LDS in 16-dimension slices, dimension-major, a = h + r formed while staging; each
 // thread keeps an 8 x 8 block of sums in registers (two 4-row groups x two 4-column groups).  In pruned
 // mode the block walks the surviving tail tiles of its (relation, head tile) row.
+// The kernel is bound by the vector units (two operations per pair and dimension), so dimensions are left out where they
+// decide nothing (padding rows stand far from all others: as copies of row 0 they were 23 of 24 M candidates of a
+// structured-embedding join, all of them re-scored for nothing): terms are >= 0 and rounding is monotonic, a sum that has passed the threshold stays above it.  After
+// every slice a wave takes the minimum of each lane's 64 sums (32 operations against the slice's 2,048); once at most
+// kL1Early pairs of its 4,096 are still at or below the threshold, they are its candidates -- a superset of those that
+// the full sum would leave, decided in double -- and the wave only helps to stage.  A tile ends with its last wave.
+// N = 20,000, R = 18, d = 100, every pair: 8.4 ms (clusters of spread 0.1) and 20 ms (0.7), where all sums to the end are
+// 37 ms at the plain vector rate; structured embedding, N = 15,000, R = 64, pruned: 4.35 -> 1.95 ms (mostly the padding).
 constexpr int kL1Tile = 128;
 constexpr int kL1K = 16;
+constexpr int kL1Early = 8;        // open pairs of a wave that go to the exact stage before the last dimension
+template <bool BF16, bool VEC>
 __global__ __launch_bounds__(256, 3) void k_join_l1(const JoinL1Args a) {
   constexpr int BM = kL1Tile, BN = kL1Tile, BK = kL1K;
   __shared__ __attribute__((aligned(16))) float As[BK][BM];
   __shared__ __attribute__((aligned(16))) float Bs[BK][BN];
   __shared__ int32_t hent[BM], tent[BN];
   __shared__ BlockQueue queue;
+  __shared__ uint32_t decided[2][4];      // per slice (alternating) and wave: the wave's candidates are known
 
   const int tid = threadIdx.x, wave = tid >> 6;
   if (tid == 0) { queue.count = 0u; queue.pending = 0u; queue.flag = 0u; queue.nhits = 0u; }   // published by the first barrier
@@ -2111,7 +2170,7 @@ __global__ __launch_bounds__(256, 3) void k_join_l1(const JoinL1Args a) {
   }
   if (t_end <= t_begin) break;
   const int r = a.r0 + rl;
-  const int d = a.cx.d, dtype = a.cx.dtype;
+  const int d = a.cx.d;
   const float thr = a.prm->thr;
   const int tx = tid & 15, ty = tid >> 4;
   // staging assignment: thread -> (row = tid / 2, eight dimensions starting at (tid % 2) * 8)
@@ -2134,44 +2193,71 @@ __global__ __launch_bounds__(256, 3) void k_join_l1(const JoinL1Args a) {
     const int64_t ho = (int64_t)r * a.cx.hstride + (int64_t)(he < 0 ? 0 : he) * d,
                   to = (int64_t)r * a.cx.tstride + (int64_t)(te < 0 ? 0 : te) * d;
 
+    unsigned long long cm[1] = {0ull};
+    bool done = false;                      // the same for the whole wave
+    int par = 0;
+    f32x4_t xh[2], xr[2], xt[2];            // a slice's elements of this thread: head, relation, tail
+#define KGC_L1_LOAD(k0)                                                     \
+  _Pragma("unroll") for (int q = 0; q < 2; ++q) {                           \
+    const int k = (k0) + sk0 + 4 * q;                                       \
+    xh[q] = exact_ld4<BF16, VEC>(a.cx.E, ho, k, d);                         \
+    xr[q] = exact_ld4<BF16, VEC>(a.cx.Rv, ro, k, d);                        \
+    xt[q] = exact_ld4<BF16, VEC>(a.cx.Et, to, k, d);                        \
+  }
+    KGC_L1_LOAD(0);
 #pragma unroll 1
-    for (int k0 = 0; k0 < d; k0 += BK) {
-      float va[8], vb[8];
-#pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        const int k = k0 + sk0 + q;
-        const bool in = k < d;
-        va[q] = in ? ld_elem(a.cx.E, ho + k, dtype) + ld_elem(a.cx.Rv, ro + k, dtype) : 0.f;
-        vb[q] = in ? ld_elem(a.cx.Et, to + k, dtype) : 0.f;
-      }
+    for (int k0 = 0; k0 < d; k0 += BK, par ^= 1) {
       __syncthreads();                      // previous slice fully consumed
+      if (k0 > 0 && (decided[par ^ 1][0] & decided[par ^ 1][1] & decided[par ^ 1][2] & decided[par ^ 1][3])) break;   // (the same for the whole block)
 #pragma unroll
       for (int q = 0; q < 8; ++q) {
-        As[sk0 + q][srow] = va[q];
-        Bs[sk0 + q][srow] = vb[q];
+        As[sk0 + q][srow] = he < 0 ? 1e38f : xh[q >> 2][q & 3] + xr[q >> 2][q & 3];
+        Bs[sk0 + q][srow] = te < 0 ? -1e38f : xt[q >> 2][q & 3];
       }
       __syncthreads();
+      if (k0 + BK < d) { KGC_L1_LOAD(k0 + BK); }      // the next slice, in flight while this one is summed
+      if (!done) {
 #pragma unroll
-      for (int k = 0; k < BK; ++k) {
-        const float4 a0 = *(const float4*)(&As[k][ty * 4]);
-        const float4 a1 = *(const float4*)(&As[k][64 + ty * 4]);
-        const float4 b0 = *(const float4*)(&Bs[k][tx * 4]);
-        const float4 b1 = *(const float4*)(&Bs[k][64 + tx * 4]);
-        const float av[8] = {a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w};
-        const float bv[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
+        for (int k = 0; k < BK; ++k) {
+          const float4 a0 = *(const float4*)(&As[k][ty * 4]);
+          const float4 a1 = *(const float4*)(&As[k][64 + ty * 4]);
+          const float4 b0 = *(const float4*)(&Bs[k][tx * 4]);
+          const float4 b1 = *(const float4*)(&Bs[k][64 + tx * 4]);
+          const float av[8] = {a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w};
+          const float bv[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
+#pragma unroll
+          for (int i = 0; i < 8; ++i)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) acc[i][j] += fabsf(av[i] - bv[j]);
+        }
+        // (the minimum passes over a NaN, whose pair is no candidate either)
+        float m = acc[0][0];
 #pragma unroll
         for (int i = 0; i < 8; ++i)
 #pragma unroll
-          for (int j = 0; j < 8; ++j) acc[i][j] += fabsf(av[i] - bv[j]);
+          for (int j = 0; j < 8; ++j) m = fminf(m, acc[i][j]);
+        const unsigned long long open = __builtin_amdgcn_ballot_w64(m <= thr);
+        const bool last = k0 + BK >= d;
+        done = open == 0ull || last;
+        if (open != 0ull && (last || __builtin_popcountll(open) <= kL1Early)) {
+#pragma unroll
+          for (int i = 0; i < 8; ++i)
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+              if (acc[i][j] <= thr) cm[0] |= 1ull << (i * 8 + j);
+          if (!last) {                      // several pairs of one lane count one by one
+            int n = __builtin_popcountll(cm[0]);
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1) n += __shfl_xor(n, off, 64);
+            done = n <= kL1Early;
+            if (!done) cm[0] = 0ull;
+          }
+        }
       }
+      if ((tid & 63) == 0) decided[par][wave] = done ? 1u : 0u;
     }
+#undef KGC_L1_LOAD
 
-    unsigned long long cm[1] = {0ull};
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-#pragma unroll
-      for (int j = 0; j < 8; ++j)
-        if (acc[i][j] <= thr) cm[0] |= 1ull << (i * 8 + j);
     // the exact path is entered by the whole block or not at all
     if (__builtin_amdgcn_ballot_w64(cm[0] != 0ull) != 0ull && (tid & 63) == 0) queue.flag = 1u;
     __syncthreads();

@@ -1,0 +1,86 @@
+"""GPU tests of pruned L2 joins that hand rows to the relation-factorised kernel: the rows without a group (the packed
+region behind the groups) and joins whose rows form one group.  The records are those of the dense per-relation kernels,
+bit for bit where the distance is summed in the same order and to a rounding of float32 elsewhere."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+PRUNE_OFF, PRUNE_ON = 1, 2
+
+
+def _torch(x, dtype):
+    import torch
+    return torch.from_numpy(x.astype(np.float32)).cuda().to(torch.float32 if dtype == "f32" else torch.bfloat16).contiguous()
+
+
+def _records(E, Rv, delta, cap, dtype, **cfg):
+    import paper_2307_12059_amd as kgc
+    j = kgc.Join(dtype=dtype, **cfg)
+    try:
+        out = []
+        for _ in range(2):                     # the second call finds the handle's buffers in place
+            got = j.join(E, Rv, 2, delta, cap)
+            assert got["code"] == 0
+            o = np.lexsort((got["t"], got["h"], got["r"]))
+            out.append((np.stack([got["r"][o], got["h"][o], got["t"][o]], 1), got["dist"][o]))
+        np.testing.assert_array_equal(out[0][0], out[1][0])
+        return out[0][0], out[0][1], got["stats"]
+    finally:
+        j.close()
+
+
+def _same(a, b):
+    assert a[0].shape == b[0].shape
+    np.testing.assert_array_equal(a[0], b[0])
+    np.testing.assert_allclose(a[1], b[1], rtol=2.0 ** -22, atol=1e-30)
+
+
+# clusters of 40 rows and rows far from everything, in random order; the latter fill, with the padding, a region whose
+# first slot is no whole tile.  Relations lead from cluster to cluster, from a lone row to a lone row, and between the two
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("n_lone,n_big,R,d", [(1400, 37, 560, 20), (1281, 40, 650, 100), (1500, 41, 480, 250), (1300, 38, 600, 283),
+                                              (1537, 130, 430, 64), (1290, 36, 610, 602)])
+def test_rows_without_a_group(n_lone, n_big, R, d, dtype):
+    g = np.random.default_rng(n_lone + d)
+    cent = g.standard_normal((n_big, d))
+    E = np.concatenate([np.repeat(cent, 40, 0) + 0.1 * g.standard_normal((40 * n_big, d)), g.standard_normal((n_lone, d))])
+    N = E.shape[0]
+    E = E[g.permutation(N)]
+    h, t = g.integers(0, N, R), g.integers(0, N, R)
+    Rv = E[t] - E[h] + 0.03 * g.standard_normal((R, d))
+    Et, Rt = _torch(E, dtype), _torch(Rv, dtype)
+    delta = float(np.float32(0.1 * np.sqrt(2.0 * d)))
+    got = _records(Et, Rt, delta, 1 << 20, dtype, prune=PRUNE_ON)
+    want = _records(Et, Rt, delta, 1 << 20, dtype, prune=PRUNE_OFF, tile_cfg=18 if d <= 282 else 17)
+    assert want[0].shape[0] > R and got[2]["groups"] >= n_big and got[2]["tiles_pruned"] > 0
+    _same(got, want)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("N,R,d", [(1000, 16, 33), (2311, 37, 130), (1100, 20, 512)])
+def test_one_group(N, R, d, dtype):
+    g = np.random.default_rng(N)
+    E = g.standard_normal((N, d))
+    Rv = 0.5 * g.standard_normal((R, d))
+    Et, Rt = _torch(E, dtype), _torch(Rv, dtype)
+    delta = float(np.float32(np.sqrt(2.25 * d) - 2.2))
+    got = _records(Et, Rt, delta, 1 << 22, dtype, prune=PRUNE_ON)
+    want = _records(Et, Rt, delta, 1 << 22, dtype, prune=PRUNE_OFF, tile_cfg=18 if d <= 282 else 17)
+    assert got[2]["join_variant"] == 100 and got[2]["groups"] >= 1 and want[0].shape[0] > 100
+    _same(got, want)
+
+
+def test_list_of_pairs_grows(monkeypatch):
+    """The list of the region's pairs, and the list of the other tiles' blocks, are both too short at first."""
+    g = np.random.default_rng(5)
+    cent = g.standard_normal((30, 40))
+    lone = g.standard_normal((1300, 40))
+    E = np.concatenate([np.repeat(cent, 50, 0) + 0.1 * g.standard_normal((1500, 40)), lone])
+    Rv = np.concatenate([lone[1:601] - lone[:600], cent[1:] - cent[:-1]])
+    Et, Rt = _torch(E, "f32"), _torch(Rv, "f32")
+    want = _records(Et, Rt, 1.0, 1 << 20, "f32", prune=PRUNE_OFF, tile_cfg=18)
+    monkeypatch.setenv("KGC_EXACT_LIST_CAP", "3")
+    got = _records(Et, Rt, 1.0, 1 << 20, "f32", prune=PRUNE_ON)
+    assert want[0].shape[0] > 10000
+    _same(got, want)
