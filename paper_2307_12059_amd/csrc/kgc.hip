@@ -328,6 +328,8 @@ inline bool part_pays(int64_t n, int64_t R) { return n >= 1024 && R >= 8 && (dou
 int grid_for(int64_t items, int per_block) {
   return (int)std::min<int64_t>((items + per_block - 1) / per_block, (1 << 24) - 1);
 }
+// grid of the barrier-free kernel over tile lists: rows in sets of 256 workgroups, long rows in parts along y
+dim3 listed_direct_grid(unsigned row_grid) { return dim3((std::min(row_grid, 512u) + 255u) & ~255u, kListParts, 1); }
 // workgroups of k_row_l1_max: eight half-waves each, up to eight workgroups per compute unit
 int grid_l1_max(int64_t rows) { return (int)std::min<int64_t>((rows + 7) / 8, 2048); }
 
@@ -625,7 +627,7 @@ int kgc_join_ab(kgc_handle* hd, const void* A, const void* B, int64_t N, int32_t
         sa.row_start = (const uint32_t*)hd->row_start.p; sa.row_count = (const uint32_t*)hd->row_count.p;
         sa.cols = (const uint32_t*)hd->cols.p; sa.active_rows = active_rows; sa.n_active = n_active;
         if (pairs_ok) { sa.tile_rows = (const uint32_t*)hd->tile_rows.p; sa.tile_total = &cnt->tile_cursor; sa.pair_mode = &cnt->pair_mode; }
-        hipLaunchKernelGGL(kern, dim3(tile_id == kDirectL2Tile ? (row_grid + 255u) & ~255u : row_grid, 1, 1), dim3(tc.threads), dyn_lds, st, sa);
+        hipLaunchKernelGGL(kern, tile_id == kDirectL2Tile ? listed_direct_grid(row_grid) : dim3(row_grid, 1, 1), dim3(tc.threads), dyn_lds, st, sa);
         if (pairs_ok) {
           const size_t pair_lds = (size_t)2 * KS * 128 * kSliceK * 2;
           KGC_HIP(hd, hipFuncSetAttribute((const void*)k_join_l2_pairs, hipFuncAttributeMaxDynamicSharedMemorySize, (int)pair_lds));
@@ -1784,7 +1786,7 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
           KGC_HIP(hd, hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn_lds));
         }
         // (the barrier-free kernel deals rows to workgroups in sets of 256: its grid is a whole number of sets)
-        const dim3 grid = prune ? dim3(tile_id == kDirectL2Tile ? (row_grid + 255u) & ~255u : row_grid, 1, 1)
+        const dim3 grid = prune ? (tile_id == kDirectL2Tile ? listed_direct_grid(row_grid) : dim3(row_grid, 1, 1))
                                 : dim3((unsigned)nHw, (unsigned)RB, (unsigned)nsplit);
         // the head-resident and streaming kernels list the accumulator blocks that hold candidates; a kernel of its own
         // then scores the list (the barrier-free dense kernels re-score in place: their candidates are few per tile)

@@ -1206,6 +1206,7 @@ __global__ __launch_bounds__(256, 2) void k_join_l2_pairs(const JoinStreamArgs a
 // LISTED (pruned joins over many entities, kEpiJoin): the grid strides over the active rows, and a row's tile list
 // sits in the LDS behind the head slices (a.cols_lds entries), so that the tile loop holds no load of the list among
 // its prefetches.
+constexpr int kListPart = 16, kListParts = 8;      // LISTED: tiles of a part of a row, and parts of a row, at least and at most
 template <int BM, int WGM, int WGN, int EPI, bool LISTED = false>
 __global__ __launch_bounds__(WGM* WGN * 64, 1) void k_join_l2_direct(const JoinStreamArgs a) {
   constexpr int BN = 256;
@@ -1238,6 +1239,14 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1) void k_join_l2_direct(const JoinS
     const int64_t row = (int64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)a.active_rows[row_i]);
     rl = (int)(row / a.nH); tH = (int)(row - (int64_t)rl * a.nH);
     t_begin = __builtin_amdgcn_readfirstlane((int)a.row_start[row]); ntiles = __builtin_amdgcn_readfirstlane((int)a.row_count[row]);
+    // A long row is cut into as many parts as have kListPart tiles, at most gridDim.y: where a few rows hold most of a
+    // batch's tiles (a group against all rows without one), one workgroup each would leave the chip idle.
+    const int parts = ntiles / kListPart < (int)gridDim.y ? (ntiles / kListPart > 1 ? ntiles / kListPart : 1) : (int)gridDim.y;
+    const int part = (int)blockIdx.y;
+    if (part >= parts) continue;                           // (the same for the whole block)
+    const int p0 = (int)((int64_t)ntiles * part / parts), p1 = (int)((int64_t)ntiles * (part + 1) / parts);
+    t_begin += p0;
+    ntiles = p1 - p0;
     __syncthreads();                                       // the previous row is done with the LDS
   } else {
     tH = (int)blockIdx.x; rl = (int)blockIdx.y;
