@@ -1797,7 +1797,15 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
           sa.xlist = (ExactEntry*)hd->xlist.p; sa.xcount = &cnt->n_exact; sa.xcap = hd->xcap;
         }
         if (pairs_ok) { sa.tile_rows = (const uint32_t*)hd->tile_rows.p; sa.tile_total = &cnt->tile_cursor; sa.pair_mode = &cnt->pair_mode; }
+        // the barrier-free kernel over tile lists hands its candidates on (not in a call whose list has overflowed for good)
+        const bool lists_pairs = prune && tile_id == kDirectL2Tile && !hd->no_fact;
+        if (lists_pairs) {
+          if ((rc = ensure(hd, hd->flist, (size_t)hd->fcap * sizeof(ExactEntry)))) return rc;
+          sa.plist = (ExactEntry*)hd->flist.p; sa.pcount = &cnt->n_fact; sa.pcap = fact_cap;
+          if (b > 0 || part_n) k_fill_u32<<<1, 64, 0, st>>>((uint32_t*)&cnt->n_fact, 2, 0u);      // an empty list (zero at the start of a call)
+        }
         hipLaunchKernelGGL(kern, grid, dim3(tc.threads), dyn_lds, st, sa);
+        if (lists_pairs) k_exact_pairs<<<2048, 256, 0, st>>>(sa.plist, sa.pcount, sa.pcap, &cnt->fact_need, sa.cx);
         if (pairs_ok) {          // the same batch tile by tile, when the device chose that (the other kernel then returned at once)
           const size_t pair_lds = (size_t)2 * KS * 128 * kSliceK * 2;
           KGC_HIP(hd, hipFuncSetAttribute((const void*)k_join_l2_pairs, hipFuncAttributeMaxDynamicSharedMemorySize, (int)pair_lds));

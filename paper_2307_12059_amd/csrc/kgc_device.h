@@ -463,6 +463,37 @@ __device__ __forceinline__ void recheck_and_emit(unsigned long long cm, int32_t 
   if (lane == 0 && ncand) atomicAdd(cx.cand_counter, ncand);
 }
 
+// The candidates of a wave onto a list of pairs, with one atomic; entries past its end are counted only.  Where a relation
+// aligns two large groups, a wave of a tile holds hundreds of candidates: scored in place, four per memory round trip,
+// they held up the whole batch (N = 1,000,000, whole call: 108 -> 81 ms).  All 64 lanes call this together.
+template <typename MapFn>
+__device__ __forceinline__ void list_pairs(unsigned long long cm, int32_t r, ExactEntry* list, unsigned long long* count,
+                                           unsigned int cap, MapFn map) {
+  const int lane = lane_id_here();
+  int incl = __builtin_popcountll(cm);
+  const int own = incl;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const int o = __shfl_up(incl, off, 64);
+    if (lane >= off) incl += o;
+  }
+  unsigned long long base = 0ull;
+  if (lane == 63) base = atomicAdd(count, (unsigned long long)incl);
+  base = (unsigned long long)__shfl((long long)base, 63, 64) + (unsigned long long)(incl - own);
+  while (cm) {
+    const int e = (int)__builtin_ctzll(cm);
+    cm &= cm - 1ull;
+    int64_t hslot, tslot;
+    map(e, lane, hslot, tslot);
+    if (base < cap) {
+      ExactEntry x;
+      x.r = r; x.hs0 = (int32_t)hslot; x.ts0 = (int32_t)tslot; x.pad = 0;
+      list[base] = x;
+    }
+    ++base;
+  }
+}
+
 // ---- block-cooperative form of the second stage ----
 // Candidates of a tile cluster in one or two waves (an aligned pair of entity groups is a 32 x 32 patch),
 // so re-scoring them inside the owning wave leaves the other waves idle.  Here every wave pushes its

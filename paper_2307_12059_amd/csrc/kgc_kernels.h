@@ -537,6 +537,8 @@ struct JoinStreamArgs {
                                       // kEpiMinDist: one word, min over all scored pairs of the float bits of the squared distance
   const int32_t* group_of;            // entities that already belong to a group (>= 0) are left alone
   int64_t n_heads;                    // entities (head slots past it are padding)
+  // k_join_l2_direct over tile lists, optional: candidates leave to a list that k_exact_pairs scores (NULL: the owning wave scores them)
+  ExactEntry* plist; unsigned long long* pcount; unsigned int pcap;
 };
 enum { kEpiJoin = 0, kEpiAssignMin = 1, kEpiMinDist = 2 };
 
@@ -1393,7 +1395,8 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1) void k_join_l2_direct(const JoinS
             tslot = tbase + j * 32 + (src & 31);                                                  \
           };                                                                                      \
           if (EPI == kEpiJoin) {                                                                  \
-            recheck_and_emit(cm, a.r0 + rl, a.cx, map);                                           \
+            if (LISTED && a.plist) list_pairs(cm, a.r0 + rl, a.plist, a.pcount, a.pcap, map);     \
+            else recheck_and_emit(cm, a.r0 + rl, a.cx, map);                                      \
           } else {                                                                                \
             /* only the lowest pivot position within reach matters to the round (the low word, a distance in the */ \
             /* float32 form, stays 0).  At most a quarter of the pairs within reach: every lane files its own     */ \

@@ -84,3 +84,24 @@ def test_list_of_pairs_grows(monkeypatch):
     got = _records(Et, Rt, 1.0, 1 << 20, "f32", prune=PRUNE_ON)
     assert want[0].shape[0] > 10000
     _same(got, want)
+
+
+# the barrier-free kernel over tile lists (taken by itself from 262,144 entities on, here by its number): its candidates go
+# through a list that is long enough, or that has to grow; few rows with long tile lists are walked in parts
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("cap", [None, "3"])
+@pytest.mark.parametrize("N,R,d,k", [(1500, 6, 40, 9), (9000, 3, 100, 2), (5000, 4, 250, 40)])
+def test_barrier_free_kernel_lists_its_candidates(N, R, d, k, cap, dtype, monkeypatch):
+    g = np.random.default_rng(N + k)
+    cent = g.standard_normal((k, d))
+    E = cent[g.integers(0, k, N)] + 0.1 * g.standard_normal((N, d))
+    src = g.integers(0, k, R)
+    Rv = cent[(src + 1) % k] - cent[src] + 0.02 * g.standard_normal((R, d))
+    Et, Rt = _torch(E, dtype), _torch(Rv, dtype)
+    delta = float(np.float32(0.1 * np.sqrt(2.0 * d) * 0.9))
+    want = _records(Et, Rt, delta, 1 << 23, dtype, prune=PRUNE_OFF, tile_cfg=18)
+    if cap:
+        monkeypatch.setenv("KGC_EXACT_LIST_CAP", cap)
+    got = _records(Et, Rt, delta, 1 << 23, dtype, prune=PRUNE_ON, tile_cfg=15)
+    assert got[2]["join_variant"] == 15 and want[0].shape[0] > 50
+    _same(got, want)
