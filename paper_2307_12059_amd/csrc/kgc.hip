@@ -352,17 +352,17 @@ int launch_fact_join(kgc_handle* hd, hipStream_t st, const FactJob& j, DevCounte
   fa.umin64 = j.umin + (size_t)RBp * (j.Nslots / 64) * 8;
   fa.umax64 = fa.umin64 + (size_t)RBp * (j.Nslots / 64);
   fa.Nslots = j.Nslots; fa.KS = KS; fa.k16 = (j.d + kNormCols + 15) / 16;
-  fa.nT = nT; fa.r0 = j.r0; fa.RBp = RBp;
+  fa.nT = nT; fa.r0 = j.r0; fa.RB = j.RB; fa.RBp = RBp;
   fa.list = j.list; fa.list_count = &cnt->n_fact; fa.list_cap = j.list_cap; fa.give_up = j.give_up;
   void (*kern)(const JoinFactArgs) = tc.bm == 256 ? k_join_l2_fact<4, 2, 4> : k_join_l2_fact<2, 2, 4>;
   const size_t dyn_lds = (size_t)KS * tc.bm * kSliceK * 2 + 8 * kFactWaveLds;
   // a block takes a range of tail tiles of one head tile; with few tile pairs the relations are cut too
   const int64_t pairs = (int64_t)nH * nT;
   const int64_t nsplit = std::max<int64_t>(1, std::min<int64_t>({(4096 + nH - 1) / nH, (int64_t)nT, 65535}));
-  const int64_t nz = std::max<int64_t>(1, std::min<int64_t>((1024 + pairs - 1) / pairs, (RBp + 63) / 64));
-  fa.zrel = (int)((RBp + nz - 1) / nz + 7) / 8 * 8;
+  const int64_t nz = std::max<int64_t>(1, std::min<int64_t>((1024 + pairs - 1) / pairs, (j.RB + 63) / 64));
+  fa.zrel = (int)((j.RB + nz - 1) / nz + 7) / 8 * 8;
   KGC_HIP(hd, hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn_lds));
-  hipLaunchKernelGGL(kern, dim3((unsigned)nH, (unsigned)nsplit, (unsigned)((RBp + fa.zrel - 1) / fa.zrel)), dim3(512), dyn_lds, st, fa);
+  hipLaunchKernelGGL(kern, dim3((unsigned)nH, (unsigned)nsplit, (unsigned)((j.RB + fa.zrel - 1) / fa.zrel)), dim3(512), dyn_lds, st, fa);
   k_exact_pairs<<<2048, 256, 0, st>>>(fa.list, fa.list_count, fa.list_cap, &cnt->fact_need, cx);
   return KGC_OK;
 }

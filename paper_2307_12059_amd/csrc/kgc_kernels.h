@@ -1497,7 +1497,7 @@ struct JoinFactArgs {
   int64_t Nslots;
   int KS, k16;
   int nT;
-  int r0, RBp;               // RBp: relations of the batch, rounded up to kFactChunk
+  int r0, RB, RBp;           // RBp: rows of the per-relation tables (RB rounded up to kFactChunk)
   int zrel;                  // relations per block along grid z
   ExactEntry* list;          // candidates for k_exact_pairs
   unsigned long long* list_count;  // (may run past list_cap)
@@ -1615,7 +1615,9 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1) void k_join_l2_fact(const JoinFac
   const int t_begin = (int)(((int64_t)a.nT * blockIdx.y) / gridDim.y);
   const int t_end = (int)(((int64_t)a.nT * (blockIdx.y + 1)) / gridDim.y);
   const int rl_begin = (int)blockIdx.z * a.zrel;
-  const int rl_end = rl_begin + a.zrel < a.RBp ? rl_begin + a.zrel : a.RBp;
+  // The tables' padding rows are not walked: a NaN keeps a pair open whatever the threshold (rows whose norms leave
+  // float32's range), and the exact stage would read past the last relation.
+  const int rl_end = rl_begin + a.zrel < a.RB ? rl_begin + a.zrel : a.RB;
   if (t_end <= t_begin || rl_end <= rl_begin) return;
   const int64_t slice_bytes = a.Nslots * ROWB;
 
@@ -1914,7 +1916,7 @@ __global__ __launch_bounds__(256) void k_fact_params(const DevCounters* cnt, con
   const int lane = threadIdx.x & 63;
   const int rl = (int)blockIdx.x * 4 + (int)(threadIdx.x >> 6);
   if (rl >= RBp) return;
-  if (rl >= RB || delta < 0.f) {                                       // nothing passes
+  if (rl >= RB || delta < 0.f) {                                       // nothing passes (rows from RB on are not walked)
     if (lane == 0) limr[rl] = -__builtin_inff();
     return;
   }

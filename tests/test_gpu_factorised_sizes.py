@@ -96,3 +96,34 @@ def test_every_pair_passes_and_far_translations():
     finally:
         j.close()
         k.close()
+
+
+# relations that do not fill the last eight rows of the per-relation tables, entities whose squared norms leave float32's
+# range: every filter value is a NaN or an infinity, all pairs go to the exact stage, and none of a relation that is not there
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("r_range", [None, (3, 20)])
+def test_norms_past_float32_stay_with_the_relations_of_the_call(r_range, dtype):
+    import torch
+    import paper_2307_12059_amd as kgc
+    g = np.random.default_rng(3)
+    N, R, d, k = 1000, 17 if r_range is None else 25, 32, 20
+    lab = g.integers(0, k, N)
+    E = 1e19 * g.standard_normal((k, d))[lab]
+    Rv = 1e19 * g.standard_normal((R, d))
+    Rv[::2] = 0.0
+    tt = torch.float32 if dtype == "f32" else torch.bfloat16
+    Et, Rt = (torch.from_numpy(x.astype(np.float32)).cuda().to(tt).contiguous() for x in (E, Rv))
+    lo, hi = r_range or (0, R)
+    assert (hi - lo) % 8 != 0
+    j = kgc.Join(dtype=dtype, prune=PRUNE_OFF)
+    try:
+        got = j.join(Et, Rt, 2, 1.0, 1 << 20, r_range=r_range)
+    finally:
+        j.close()
+    assert got["code"] == 0 and got["stats"]["join_variant"] == 100
+    assert got["r"].min() >= lo and got["r"].max() < hi
+    h, t = np.nonzero(lab[:, None] == lab[None, :])                # two rows are the same or some 1e19 apart
+    r = np.arange(lo + lo % 2, hi, 2)
+    want = ((r[:, None] * N + h) * N + t).ravel()
+    np.testing.assert_array_equal(np.sort((got["r"].astype(np.int64) * N + got["h"]) * N + got["t"]), np.sort(want))
+    assert not got["dist"].any()
