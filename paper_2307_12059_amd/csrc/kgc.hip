@@ -260,7 +260,7 @@ void launch_small_dot(hipStream_t st, const void* X, int dtype, int64_t n_rows, 
                      X, n_rows, Y, n_cols, d, out);
 }
 
-// r . e of a relation batch for every slot (k_fact_dot): rows read four elements at a time where they may be
+// r . e~ of a relation batch for every slot (k_fact_dot): rows read four elements at a time where they may be
 void launch_fact_dot(hipStream_t st, const void* Rv, const void* E, int dtype, const int32_t* slot_ent, int64_t Nslots, int r0, int RB,
                      int RBp, int d, float* u, float* umin8, float* umin64, float* umax64) {
   const bool bf = dtype == KGC_BF16;
@@ -274,7 +274,7 @@ void launch_fact_dot(hipStream_t st, const void* Rv, const void* E, int dtype, c
 struct FactJob {
   const void* E; const void* Rv; int dtype, d, r0, RB; float delta;
   const int32_t* slot_ent; int64_t Nslots;            // the run: a multiple of kSlotAlign slots
-  const uint16_t* A; const uint16_t* B;               // its staged operands (plain rows, plain norms)
+  const uint16_t* A; const uint16_t* B;               // its staged operands (plain rows, norms less their slacks)
   float* u; float* umin; float* limr;                 // fact_rows(RB) x Nslots, x (Nslots / 64) x 10, x 1
   ExactEntry* list; unsigned int list_cap; unsigned long long give_up;
 };
@@ -333,7 +333,7 @@ dim3 listed_direct_grid(unsigned row_grid) { return dim3((std::min(row_grid, 512
 // workgroups of k_row_l1_max: eight half-waves each, up to eight workgroups per compute unit
 int grid_l1_max(int64_t rows) { return (int)std::min<int64_t>((rows + 7) / 8, 2048); }
 
-// u[rl][slot] = r . e with its extremes over 8 and 64 slots, then the thresholds
+// u[rl][slot] = r . e~ with its extremes over 8 and 64 slots, then the thresholds
 void launch_fact_products(hipStream_t st, const FactJob& j, DevCounters* cnt) {
   const int RBp = (int)fact_rows(j.RB), KS = (j.d + kNormCols + kSliceK - 1) / kSliceK;
   float* umin64 = j.umin + (size_t)RBp * (j.Nslots / 64) * 8;
@@ -1535,11 +1535,11 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
   } else if (l2_ops) {
     k_stage_operands<false><<<grid_for(Nslots / kStageRows, 1), 256, stage_lds, st>>>(
         E, Rvecs, dtype, d, 0, 1, slot_ent, Nslots, KS, (uint16_t*)hd->opB.p, (float*)hd->normsB.p, cnt->max_b, nullptr, nullptr, 0, kStageRows,
-        0, nullptr, fact ? -1.f : delta);      // (the factorised filter has an error analysis of its own: plain norms)
+        0, nullptr, delta);
     if (fact)     // the head side of the factorised form carries no relation: the plain rows, once
       k_stage_operands<true><<<grid_for(Nslots / kStageRows, 1), 256, stage_lds, st>>>(
           E, nullptr, dtype, d, 0, 1, slot_ent, Nslots, KS, (uint16_t*)hd->opA.p, (float*)hd->normsA.p, cnt->max_a, nullptr,
-          nullptr, 0, kStageRows);
+          nullptr, 0, kStageRows, 0, nullptr, delta);
   } else {
     k_row_l1_max<<<grid_l1_max(N), 256, 0, st>>>(E, N, d, dtype, cnt->max_a);
     k_row_l1_max<<<grid_l1_max(R), 256, 0, st>>>(Rvecs, R, d, dtype, cnt->max_b);
@@ -1561,9 +1561,10 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
     // (the running maxima of the norms, shared with the other kernels' operands, only widen the thresholds)
     k_stage_operands<false><<<grid_for(part_n / kStageRows, 1), 256, stage_lds, st>>>(
         E, nullptr, dtype, d, 0, 1, fj.slot_ent, part_n, KS, (uint16_t*)hd->fop_b.p, nullptr, cnt->max_b, nullptr, nullptr, 0, kStageRows,
-        0, nullptr, -1.f);
+        0, nullptr, delta);
     k_stage_operands<true><<<grid_for(part_n / kStageRows, 1), 256, stage_lds, st>>>(
-        E, nullptr, dtype, d, 0, 1, fj.slot_ent, part_n, KS, (uint16_t*)hd->fop_a.p, nullptr, cnt->max_a, nullptr, nullptr, 0, kStageRows);
+        E, nullptr, dtype, d, 0, 1, fj.slot_ent, part_n, KS, (uint16_t*)hd->fop_a.p, nullptr, cnt->max_a, nullptr, nullptr, 0, kStageRows,
+        0, nullptr, delta);
     RecheckCtx cxf = cx;
     cxf.slot_ent = cxf.slot_ent_t = fj.slot_ent;
     for (int64_t r0 = r_begin; r0 < r_end; r0 += RBf) {

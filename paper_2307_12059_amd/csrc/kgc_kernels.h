@@ -1472,6 +1472,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1) void k_join_l2_direct(const JoinS
 // addition and half a minimum each, and the vector pipes bound the kernel (19.6 ms of the dense N = 15,000, R = 1,345
 // join at 88 % of the plain vector rate).  Rounding is monotonic, so a set of pairs of one relation is decided at once:
 //     min G + min 2 r.h  >  lim_r + max 2 r.t   over the set   =>   none of its pairs passes.
+// (r.h and r.t are those of the bf16-rounded rows, and G is less the rows' rounding slacks.)
 // A wave asks this at three levels, each over what the level before left open:
 //   1. its whole TM * 32 x 64 pairs, one RELATION per lane (minima and maxima of r.e over 64 rows: k_fact_dot);
 //   2. eight head rows x one tail column, one COLUMN per lane: one coalesced load of r.t, TM * 4 additions and half as
@@ -1489,7 +1490,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1) void k_join_l2_direct(const JoinS
 struct JoinFactArgs {
   const uint16_t* A;         // staged head operands of the plain entity rows: [KS][Nslots][32]
   const uint16_t* B;         // staged tail operands: [KS][Nslots][32]
-  const float* u;            // [RBp][Nslots] r . e (float32, from the caller's rows), zero rows from RB on
+  const float* u;            // [RBp][Nslots] r . e~ (float32, e~: the bf16-rounded row), zero rows from RB on
   const float* limr;         // [RBp] threshold on G + 2 r.h - 2 r.t, i.e. thr_r - ||r||^2
   const float* umin8;        // [Nslots / 64][RBp][8] min of 2 r.e over 8 rows
   const float* umin64;       // [Nslots / 64][RBp] min of 2 r.e over 64 rows ...
@@ -1510,8 +1511,8 @@ constexpr int kFactIds = 128;          // relations a wave's level 1 has left op
 constexpr int kFactBatch = 4;          // relations whose r.t and r.h a lane has in flight together
 constexpr size_t kFactWaveLds = 3 * kFactQueue * 4 + kFactIds * 2;
 
-// u[rl][slot] = r . e for the relations of a batch and the entity of every slot (0 for padding slots and for rows from RB
-// on), and the extremes of 2 r.e over 8 and over 64 consecutive slots (padding does not count), on the float32 matrix
+// u[rl][slot] = r . e~ for the relations of a batch and the bf16-rounded row of every slot's entity (why rounded:
+// k_fact_params; 0 for padding slots and for rows from RB on), and the extremes of 2 r.e over 8 and over 64 consecutive slots (padding does not count), on the float32 matrix
 // pipes: a wave takes 32 relations x 64 slots, operands straight into registers in the permuted order of dimensions that
 // k_small_dot explains, every load of 64 dimensions issued before the first is used.  The 128 x 128 vector tile kernel
 // that did the products before left most of the chip idle on a thin product (R = 2, d = 200: 60 us of latency) and
@@ -1550,6 +1551,12 @@ __global__ __launch_bounds__(256) void k_fact_dot(const void* __restrict__ Rv, c
 #pragma unroll
     for (int q = 0; q < kG; ++q) {
       if (k0 + 8 * q >= d) break;                                         // the same for the whole wave
+      if (!BF16) {                                                        // (as k_stage_operands rounds them)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) yv[j][q][e] = bf16_to_f32(f32_to_bf16_rne(yv[j][q][e]));
+      }
 #pragma unroll
       for (int e = 0; e < 4; ++e)
 #pragma unroll
@@ -1904,12 +1911,16 @@ __global__ __launch_bounds__(256) void k_exact_pairs(const ExactEntry* __restric
   }
 }
 
-// Per-relation filter thresholds of the factorised join: limr[rl] = thr_r - ||r||^2, where a true hit has
-//     G + 2 r.h - 2 r.t + ||r||^2 <= thr_r = delta^2 + m (2 (delta + ||r||) + m) + e_acc + e_u:
-// G is taken on bf16-rounded rows, which moves ||h - t|| by at most m = 2^-8 1.01 (max||h~|| + max||t~||)
-// (m = 0 for bf16 storage, where rounding changes nothing), and ||h - t|| <= delta + ||r|| for a hit, hence the
-// first term; e_acc bounds the float32 accumulation of G as in k_join_params; e_u bounds the float32 error of
-// the two products (d + 8) 2^-24 ||r|| ||e|| each, doubled, and of the final sums.
+// Per-relation filter thresholds of the factorised join: limr[rl] = thr_r - ||r||^2.  A hit x = h + r - t, ||x|| <= delta,
+// has on the bf16-rounded rows x~ = h~ + r - t~ with ||x~|| <= delta + e_h + e_t (e = the distance that the rounding moves a
+// row), and with products of the ROUNDED rows the expansion of ||x~||^2 is exact, so that, as in k_stage_operands,
+//     (||h~ - t~||^2 - slack_h - slack_t) + 2 r.h~ - 2 r.t~ + ||r||^2 <= delta^2.
+// The staged norms carry the slacks: every row pays for its own rounding, and the length of r does not enter.  (Products of
+// the caller's rows left a term 2 (delta + ||r||) m, m from the largest norms: N = 1,000, R = 16, d = 32, relations 16 times
+// as long as delta: 37,789 candidates where the per-relation kernel has 76, 190 us a call against 100.)
+// thr_r = delta^2 + e_acc + e_u: e_acc bounds the float32 accumulation of the contraction as in k_join_params; e_u bounds the
+// float32 errors of the two products, (d + 12) 2^-24 ||r|| ||e~|| each and doubled (taken twice), of ||r||^2 and of the
+// final sums.
 // One wave per relation: the maxima of the staged norms, ||r||^2 in float32, the threshold.
 __global__ __launch_bounds__(256) void k_fact_params(const DevCounters* cnt, const void* __restrict__ Rv, int r0, int RB, int RBp,
                                                      float delta, int dtype, int d, int kp, float* __restrict__ limr) {
@@ -1933,11 +1944,10 @@ __global__ __launch_bounds__(256) void k_fact_params(const DevCounters* cnt, con
     rn += __shfl_xor(rn, off, 64);
   }
   const float na = sqrtf(ma) * 1.01f, nb = sqrtf(mb) * 1.01f;
-  const float m = dtype == KGC_BF16 ? 0.f : (1.01f / 256.f) * (na + nb);
   const float rnorm = sqrtf(rn) * 1.0001f;
   const float eacc = (float)(kp + 16) * 1.2e-7f * 2.f * (ma + mb);
-  const float eu = 4.f * (float)(d + 12) * 6e-8f * rnorm * (na + nb) + 1e-6f * (rn + ma + mb);
-  const float thr = (delta * delta + m * (2.f * (delta + rnorm) + m) + eacc + eu) * (1.f + 1e-6f);
+  const float eu = 4.f * (float)(d + 12) * 6e-8f * rnorm * (na + nb) + 2e-6f * (rn + ma + mb);
+  const float thr = (delta * delta + eacc + eu) * (1.f + 1e-6f);
   // norms that leave float32's range decide nothing: every pair of the relation goes to the exact stage
   if (lane == 0) limr[rl] = thr < 1e37f && rn < 1e37f ? thr - rn : __builtin_inff();
 }
