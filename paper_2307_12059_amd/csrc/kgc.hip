@@ -260,16 +260,6 @@ void launch_small_dot(hipStream_t st, const void* X, int dtype, int64_t n_rows, 
                      X, n_rows, Y, n_cols, d, out);
 }
 
-// r . e~ of a relation batch for every slot (k_fact_dot): rows read four elements at a time where they may be
-void launch_fact_dot(hipStream_t st, const void* Rv, const void* E, int dtype, const int32_t* slot_ent, int64_t Nslots, int r0, int RB,
-                     int RBp, int d, float* u, float* umin8, float* umin64, float* umax64) {
-  const bool bf = dtype == KGC_BF16;
-  const bool vec = d % 4 == 0 && (uintptr_t)E % (bf ? 8 : 16) == 0 && (uintptr_t)Rv % (bf ? 8 : 16) == 0;
-  auto kern = bf ? (vec ? k_fact_dot<true, true> : k_fact_dot<true, false>) : (vec ? k_fact_dot<false, true> : k_fact_dot<false, false>);
-  hipLaunchKernelGGL(kern, dim3((unsigned)(Nslots / 256), (unsigned)((RBp + 31) / 32), 1), dim3(256), 0, st,
-                     Rv, E, slot_ent, Nslots, r0, RB, RBp, d, u, umin8, umin64, umax64);
-}
-
 // One relation batch of the relation-factorised join over a run of slots.
 struct FactJob {
   const void* E; const void* Rv; int dtype, d, r0, RB; float delta;
@@ -296,10 +286,13 @@ hipError_t wait_event(hipEvent_t ev) {
 // rows of the relation-factorised join's per-relation tables: whole chunks of relations
 inline int64_t fact_rows(int64_t RB) { return (RB + kFactChunk - 1) / kFactChunk * kFactChunk; }
 // Dense L2 joins that the relation-factorised kernel takes by itself.  Its fixed part (products r.e, one contraction per
-// pair of entities, the list of pairs) is paid once, the other kernels contract every relation.  Measured, whole calls in
-// us, per-relation kernel / this one: N = 2,000, R = 8: 178 / 112 (d = 32), 164 / 118 (d = 100), 169 / 137 (d = 200);
-// N = 1,000, R = 8: 136 / 121, 130 / 128, 133 / 147; N = 1,000, R = 32: 319 / 213, 292 / 217, 278 / 235; N = 500, R = 32:
-// 255 / 306, 219 / 309, 208 / 325; R = 4: N = 4,000 151 / 114, 133 / 121, 142 / 145 and N = 16,000, d = 32: 202 / 239.
+// pair of entities, the list of pairs) is paid once, the other kernels contract every relation and score their candidates in
+// place.  Measured, whole calls in us, per-relation kernel / this one, float32, clusters of 60 rows in random order.  A few to
+// a thousand hits: N = 1,000, R = 16: 113 / 127 (d = 32), 129 / 127 (100), 151 / 165 (282), 223 / 197 (600); N = 2,000, R = 8:
+// 109 / 113 (32), 123 / 123 (100), 139 / 140 (200), 240 / 214 (600); N = 16,000, R = 8: 290 / 316 (32), 2,588 / 680 (600);
+// N = 1,000, R = 64, d = 32: 121 / 120; N = 1,000, R = 256, d = 100: 523 / 212; N = 3,000, R = 100, d = 64: 279 / 230.  With
+// 31,000 hits N = 1,000, R = 16, d = 32: 310 / 138, with 15,000 N = 16,000, R = 8, d = 32: 483 / 336.  The line lies where the
+// two are level without hits; below it (N = 1,000, R = 8; R = 4) the fixed part is not earned back.
 inline bool fact_pays(int64_t N, int64_t R) { return R >= 8 && N >= 1000 && N * R >= 16000; }
 
 // Dense L1 joins that the relation-factorised kernel takes first: ||x||_2 <= ||x||_1, so every hit is among the pairs
@@ -333,13 +326,24 @@ dim3 listed_direct_grid(unsigned row_grid) { return dim3((std::min(row_grid, 512
 // workgroups of k_row_l1_max: eight half-waves each, up to eight workgroups per compute unit
 int grid_l1_max(int64_t rows) { return (int)std::min<int64_t>((rows + 7) / 8, 2048); }
 
-// u[rl][slot] = r . e~ with its extremes over 8 and 64 slots, then the thresholds
-void launch_fact_products(hipStream_t st, const FactJob& j, DevCounters* cnt) {
+// the two sides' operands (the same plain rows, blockIdx.y picks the form)
+void launch_fact_stage(hipStream_t st, const FactJob& j, uint16_t* A, uint16_t* B, DevCounters* cnt) {
+  const int KS = (j.d + kNormCols + kSliceK - 1) / kSliceK;
+  const size_t stage_lds = (size_t)kStageRows * (KS * kSliceK + 8) * 2;
+  k_stage_pair<<<dim3((unsigned)grid_for(j.Nslots / kStageRows, 1), 2, 1), 256, stage_lds, st>>>(j.E, j.dtype, j.d, j.slot_ent, j.Nslots, KS, A, B,
+                                                                                             cnt->max_a, cnt->max_b, j.delta);
+}
+
+// u[rl][slot] = r . e~ with its extremes over 8 and 64 slots, and the thresholds: rows read four elements at a time where
+// they may be
+void launch_fact_products(hipStream_t st, const FactJob& j, const DevCounters* cnt) {
   const int RBp = (int)fact_rows(j.RB), KS = (j.d + kNormCols + kSliceK - 1) / kSliceK;
   float* umin64 = j.umin + (size_t)RBp * (j.Nslots / 64) * 8;
-  launch_fact_dot(st, j.Rv, j.E, j.dtype, j.slot_ent, j.Nslots, j.r0, j.RB, RBp, j.d, j.u, j.umin, umin64,
-                  umin64 + (size_t)RBp * (j.Nslots / 64));
-  k_fact_params<<<grid_for(RBp, 4), 256, 0, st>>>(cnt, j.Rv, j.r0, j.RB, RBp, j.delta, j.dtype, j.d, KS * kSliceK, j.limr);
+  const bool bf = j.dtype == KGC_BF16;
+  const bool vec = j.d % 4 == 0 && (uintptr_t)j.E % (bf ? 8 : 16) == 0 && (uintptr_t)j.Rv % (bf ? 8 : 16) == 0;
+  auto kern = bf ? (vec ? k_fact_dot<true, true> : k_fact_dot<true, false>) : (vec ? k_fact_dot<false, true> : k_fact_dot<false, false>);
+  hipLaunchKernelGGL(kern, dim3((unsigned)(j.Nslots / 256) + 1u, (unsigned)((RBp + 31) / 32), 1), dim3(256), 0, st, j.Rv, j.E, j.slot_ent, j.Nslots,
+                     j.r0, j.RB, RBp, j.d, j.u, j.umin, umin64, umin64 + (size_t)RBp * (j.Nslots / 64), cnt, j.delta, KS * kSliceK, j.limr);
 }
 
 // the kernel and the scores of the pairs it lists (cx counts its slots from the job's first)
@@ -356,11 +360,14 @@ int launch_fact_join(kgc_handle* hd, hipStream_t st, const FactJob& j, DevCounte
   fa.list = j.list; fa.list_count = &cnt->n_fact; fa.list_cap = j.list_cap; fa.give_up = j.give_up;
   void (*kern)(const JoinFactArgs) = tc.bm == 256 ? k_join_l2_fact<4, 2, 4> : k_join_l2_fact<2, 2, 4>;
   const size_t dyn_lds = (size_t)KS * tc.bm * kSliceK * 2 + 8 * kFactWaveLds;
-  // a block takes a range of tail tiles of one head tile; with few tile pairs the relations are cut too
+  // A block takes a range of tail tiles of one head tile.  With few tile pairs the relations are cut too, down to one level-2
+  // batch: a wave walks its relations one after the other, about 3 us each where its rows hold members of all clusters, and
+  // a second contraction of the tile beside it costs an idle compute unit nothing.  (Cuts of 64: N = 1,000, R = 64, d = 32: 16
+  // blocks, 198 us.)
   const int64_t pairs = (int64_t)nH * nT;
   const int64_t nsplit = std::max<int64_t>(1, std::min<int64_t>({(4096 + nH - 1) / nH, (int64_t)nT, 65535}));
-  const int64_t nz = std::max<int64_t>(1, std::min<int64_t>((1024 + pairs - 1) / pairs, (j.RB + 63) / 64));
-  fa.zrel = (int)((j.RB + nz - 1) / nz + 7) / 8 * 8;
+  const int64_t nz = std::max<int64_t>(1, std::min<int64_t>((512 + pairs - 1) / pairs, (j.RB + kFactBatch - 1) / kFactBatch));
+  fa.zrel = (int)(((j.RB + nz - 1) / nz + kFactBatch - 1) / kFactBatch * kFactBatch);
   KGC_HIP(hd, hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn_lds));
   hipLaunchKernelGGL(kern, dim3((unsigned)nH, (unsigned)nsplit, (unsigned)((j.RB + fa.zrel - 1) / fa.zrel)), dim3(512), dyn_lds, st, fa);
   k_exact_pairs<<<2048, 256, 0, st>>>(fa.list, fa.list_count, fa.list_cap, &cnt->fact_need, cx);
@@ -1529,17 +1536,17 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
                                                                (float*)hd->cent_u.p, (float*)hd->rad_u.p, (float*)hd->cnorm_u.p);
     }
   }
+  FactJob fj{};      // of the factorised form: the whole join, or its part
+  fj.E = E; fj.Rv = Rvecs; fj.dtype = dtype; fj.d = d; fj.delta = delta; fj.slot_ent = slot_ent; fj.Nslots = Nslots;
   const size_t stage_lds = (size_t)kStageRows * (KS * kSliceK + 8) * 2;
   if (reuse) {
     // tail operands, summaries and (L1) the join parameters are in place
-  } else if (l2_ops) {
+  } else if (fact) {      // the head side of the factorised form carries no relation: the plain rows, once
+    launch_fact_stage(st, fj, (uint16_t*)hd->opA.p, (uint16_t*)hd->opB.p, cnt);
+  } else if (p == 2) {
     k_stage_operands<false><<<grid_for(Nslots / kStageRows, 1), 256, stage_lds, st>>>(
         E, Rvecs, dtype, d, 0, 1, slot_ent, Nslots, KS, (uint16_t*)hd->opB.p, (float*)hd->normsB.p, cnt->max_b, nullptr, nullptr, 0, kStageRows,
         0, nullptr, delta);
-    if (fact)     // the head side of the factorised form carries no relation: the plain rows, once
-      k_stage_operands<true><<<grid_for(Nslots / kStageRows, 1), 256, stage_lds, st>>>(
-          E, nullptr, dtype, d, 0, 1, slot_ent, Nslots, KS, (uint16_t*)hd->opA.p, (float*)hd->normsA.p, cnt->max_a, nullptr,
-          nullptr, 0, kStageRows, 0, nullptr, delta);
   } else {
     k_row_l1_max<<<grid_l1_max(N), 256, 0, st>>>(E, N, d, dtype, cnt->max_a);
     k_row_l1_max<<<grid_l1_max(R), 256, 0, st>>>(Rvecs, R, d, dtype, cnt->max_b);
@@ -1553,18 +1560,12 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
         (rc = ensure(hd, hd->limr, fact_rows(RBf) * 4)) || (rc = ensure(hd, hd->umin, (size_t)fact_rows(RBf) * (part_n / 64) * 10 * 4)) ||
         (rc = ensure(hd, hd->flist, (size_t)hd->fcap * sizeof(ExactEntry))))
       return rc;
-    FactJob fj{};
-    fj.E = E; fj.Rv = Rvecs; fj.dtype = dtype; fj.d = d; fj.delta = delta; fj.slot_ent = slot_ent + part0; fj.Nslots = part_n;
+    fj.slot_ent = slot_ent + part0; fj.Nslots = part_n;
     fj.A = (const uint16_t*)hd->fop_a.p; fj.B = (const uint16_t*)hd->fop_b.p;
     fj.u = (float*)hd->fu.p; fj.umin = (float*)hd->umin.p; fj.limr = (float*)hd->limr.p;
     fj.list = (ExactEntry*)hd->flist.p; fj.list_cap = hd->fcap; fj.give_up = std::max<unsigned long long>(fact_most, hd->fcap);
     // (the running maxima of the norms, shared with the other kernels' operands, only widen the thresholds)
-    k_stage_operands<false><<<grid_for(part_n / kStageRows, 1), 256, stage_lds, st>>>(
-        E, nullptr, dtype, d, 0, 1, fj.slot_ent, part_n, KS, (uint16_t*)hd->fop_b.p, nullptr, cnt->max_b, nullptr, nullptr, 0, kStageRows,
-        0, nullptr, delta);
-    k_stage_operands<true><<<grid_for(part_n / kStageRows, 1), 256, stage_lds, st>>>(
-        E, nullptr, dtype, d, 0, 1, fj.slot_ent, part_n, KS, (uint16_t*)hd->fop_a.p, nullptr, cnt->max_a, nullptr, nullptr, 0, kStageRows,
-        0, nullptr, delta);
+    launch_fact_stage(st, fj, (uint16_t*)hd->fop_a.p, (uint16_t*)hd->fop_b.p, cnt);
     RecheckCtx cxf = cx;
     cxf.slot_ent = cxf.slot_ent_t = fj.slot_ent;
     for (int64_t r0 = r_begin; r0 < r_end; r0 += RBf) {
@@ -1713,9 +1714,8 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
     // pruned launches stride a fixed grid over the active rows (their number is only known on the device)
     const unsigned row_grid = (unsigned)std::min<int64_t>((int64_t)RB * nH, 4096);
     if (fact) {
-      FactJob fj{};
-      fj.E = E; fj.Rv = Rvecs; fj.dtype = dtype; fj.d = d; fj.r0 = (int)r0; fj.RB = RB; fj.delta = delta;
-      fj.slot_ent = slot_ent; fj.Nslots = Nslots; fj.A = (const uint16_t*)hd->opA.p; fj.B = (const uint16_t*)hd->opB.p;
+      fj.r0 = (int)r0; fj.RB = RB;
+      fj.A = (const uint16_t*)hd->opA.p; fj.B = (const uint16_t*)hd->opB.p;
       fj.u = (float*)hd->relu.p; fj.umin = (float*)hd->umin.p; fj.limr = (float*)hd->limr.p;
       fj.list = (ExactEntry*)hd->flist.p; fj.list_cap = fact_cap; fj.give_up = std::max<unsigned long long>(fact_most, fact_cap);
       launch_fact_products(st, fj, cnt);

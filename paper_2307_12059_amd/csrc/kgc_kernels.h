@@ -169,16 +169,15 @@ __device__ __forceinline__ float stage_reduce8(const float v[8], int lane) {
 }
 
 template <bool IS_A>
-__global__ __launch_bounds__(256, 4) void k_stage_operands(const void* __restrict__ E, const void* __restrict__ Rv,
-                                                        int dtype, int d, int r0, int RB,
-                                                        const int32_t* __restrict__ slot_ent, int64_t Nslots, int KS,
-                                                        uint16_t* __restrict__ out, float* __restrict__ norms,
-                                                        unsigned int* __restrict__ max_slots,
-                                                        const uint32_t* __restrict__ active_rows,
-                                                        const unsigned int* __restrict__ n_active, int nH, int bm,
-                                                        int64_t rel_stride = 0, const int32_t* __restrict__ n_rows_dev = nullptr,
-                                                        float slack_delta = -1.f,
-                                                        int64_t n_identity = 0) {      // slot_ent == NULL: slot s holds entity s, s < n_identity
+__device__ __forceinline__ void stage_operands(const void* __restrict__ E, const void* __restrict__ Rv,
+                                               int dtype, int d, int r0, int RB,
+                                               const int32_t* __restrict__ slot_ent, int64_t Nslots, int KS,
+                                               uint16_t* __restrict__ out, float* __restrict__ norms,
+                                               unsigned int* __restrict__ max_slots,
+                                               const uint32_t* __restrict__ active_rows,
+                                               const unsigned int* __restrict__ n_active, int nH, int bm,
+                                               int64_t rel_stride, const int32_t* __restrict__ n_rows_dev,
+                                               float slack_delta, int64_t n_identity) {
   extern __shared__ __attribute__((aligned(16))) uint16_t tile_all[];   // [4 waves][16 rows][KS * 32 + 8]
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int half = lane >> 5, l32 = lane & 31;
@@ -286,6 +285,33 @@ __global__ __launch_bounds__(256, 4) void k_stage_operands(const void* __restric
     for (int off = 32; off > 0; off >>= 1) vmax = fmaxf(vmax, __shfl_xor(vmax, off, 64));
     if (lane == 0) atomicMax(&max_slots[(blockIdx.x * 4 + wave) % kMaxSlots], __float_as_uint(vmax));   // non-negative floats order like their bits
   }
+}
+
+template <bool IS_A>
+__global__ __launch_bounds__(256, 4) void k_stage_operands(const void* __restrict__ E, const void* __restrict__ Rv,
+                                                        int dtype, int d, int r0, int RB,
+                                                        const int32_t* __restrict__ slot_ent, int64_t Nslots, int KS,
+                                                        uint16_t* __restrict__ out, float* __restrict__ norms,
+                                                        unsigned int* __restrict__ max_slots,
+                                                        const uint32_t* __restrict__ active_rows,
+                                                        const unsigned int* __restrict__ n_active, int nH, int bm,
+                                                        int64_t rel_stride = 0, const int32_t* __restrict__ n_rows_dev = nullptr,
+                                                        float slack_delta = -1.f,
+                                                        int64_t n_identity = 0) {      // slot_ent == NULL: slot s holds entity s, s < n_identity
+  stage_operands<IS_A>(E, Rv, dtype, d, r0, RB, slot_ent, Nslots, KS, out, norms, max_slots, active_rows, n_active, nH, bm, rel_stride,
+                       n_rows_dev, slack_delta, n_identity);
+}
+// Both sides of the relation-factorised join, which are the same plain rows in the two operand forms, in one launch:
+// blockIdx.y = 0 stages the head side, 1 the tail side.
+__global__ __launch_bounds__(256, 4) void k_stage_pair(const void* __restrict__ E, int dtype, int d, const int32_t* __restrict__ slot_ent,
+                                                       int64_t Nslots, int KS, uint16_t* __restrict__ out_a, uint16_t* __restrict__ out_b,
+                                                       unsigned int* __restrict__ max_a, unsigned int* __restrict__ max_b, float delta) {
+  if (blockIdx.y == 0)
+    stage_operands<true>(E, nullptr, dtype, d, 0, 1, slot_ent, Nslots, KS, out_a, nullptr, max_a, nullptr, nullptr, 0, kStageRows, 0,
+                         nullptr, delta, 0);
+  else
+    stage_operands<false>(E, nullptr, dtype, d, 0, 1, slot_ent, Nslots, KS, out_b, nullptr, max_b, nullptr, nullptr, 0, kStageRows, 0,
+                          nullptr, delta, 0);
 }
 
 // squared norms scattered back to entity order (kgc_norms)
@@ -1468,7 +1494,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1) void k_join_l2_direct(const JoinS
 // relation (the observation Section 5.2 makes for the tail side, taken one step further).  One block keeps
 // a head tile in LDS, forms the tile G = ||h~ - t~||^2 ONCE with the matrix pipes (plain entity rows on both
 // sides, same augmented-K operands as the other forms) and keeps it in registers while it walks the relations.
-// The filter asks of a pair whether G + 2 r.h <= lim_r + 2 r.t (lim_r: k_fact_params).  Asked pair by pair that is an
+// The filter asks of a pair whether G + 2 r.h <= lim_r + 2 r.t (lim_r: fact_params).  Asked pair by pair that is an
 // addition and half a minimum each, and the vector pipes bound the kernel (19.6 ms of the dense N = 15,000, R = 1,345
 // join at 88 % of the plain vector rate).  Rounding is monotonic, so a set of pairs of one relation is decided at once:
 //     min G + min 2 r.h  >  lim_r + max 2 r.t   over the set   =>   none of its pairs passes.
@@ -1505,24 +1531,80 @@ struct JoinFactArgs {
   unsigned int list_cap;
   unsigned long long give_up;      // with so many pairs listed the host takes another form: the waves end
 };
-constexpr int kFactChunk = 8;          // rows of the per-relation tables are rounded up to this
 constexpr int kFactQueue = 64;         // candidates a wave holds back
 constexpr int kFactIds = 128;          // relations a wave's level 1 has left open and level 2 has not taken yet
 constexpr int kFactBatch = 4;          // relations whose r.t and r.h a lane has in flight together
 constexpr size_t kFactWaveLds = 3 * kFactQueue * 4 + kFactIds * 2;
 
+// Per-relation filter thresholds of the factorised join: limr[rl] = thr_r - ||r||^2.  A hit x = h + r - t, ||x|| <= delta,
+// has on the bf16-rounded rows x~ = h~ + r - t~ with ||x~|| <= delta + e_h + e_t (e = the distance that the rounding moves a
+// row), and with products of the ROUNDED rows the expansion of ||x~||^2 is exact, so that, as in k_stage_operands,
+//     (||h~ - t~||^2 - slack_h - slack_t) + 2 r.h~ - 2 r.t~ + ||r||^2 <= delta^2.
+// The staged norms carry the slacks: every row pays for its own rounding, and the length of r does not enter.  (Products of
+// the caller's rows left a term 2 (delta + ||r||) m, m from the largest norms: N = 1,000, R = 16, d = 32, relations 16 times
+// as long as delta: 37,789 candidates where the per-relation kernel has 76, 190 us a call against 100.)
+// thr_r = delta^2 + e_acc + e_u: e_acc bounds the float32 accumulation of the contraction as in k_join_params; e_u bounds the
+// float32 errors of the two products, (d + 12) 2^-24 ||r|| ||e~|| each and doubled (taken twice), of ||r||^2 and of the
+// final sums.
+// One wave, kFactChunk relations from rl0 on: the maxima of the staged norms, ||r||^2 in float32, the thresholds.
+constexpr int kFactChunk = 8;          // rows of the per-relation tables are rounded up to this
+__device__ __forceinline__ void fact_params(const DevCounters* __restrict__ cnt, const void* __restrict__ Rv, int dtype, int r0, int rl0, int RB,
+                                            int RBp, float delta, int d, int kp, float* __restrict__ limr) {
+  if (rl0 >= RBp) return;                                              // (RBp is a multiple of kFactChunk)
+  const int lane = threadIdx.x & 63;
+  float ma = 0.f, mb = 0.f, rn[kFactChunk];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    ma = fmaxf(ma, __uint_as_float(cnt->max_a[i * 64 + lane]));
+    mb = fmaxf(mb, __uint_as_float(cnt->max_b[i * 64 + lane]));
+  }
+#pragma unroll
+  for (int i = 0; i < kFactChunk; ++i) rn[i] = 0.f;
+  for (int k = lane; k < d; k += 64)
+#pragma unroll
+    for (int i = 0; i < kFactChunk; ++i) {
+      const float x = ld_elem(Rv, (int64_t)(r0 + (rl0 + i < RB ? rl0 + i : RB - 1)) * d + k, dtype);
+      rn[i] += x * x;
+    }
+  for (int off = 32; off > 0; off >>= 1) {
+    ma = fmaxf(ma, __shfl_xor(ma, off, 64));
+    mb = fmaxf(mb, __shfl_xor(mb, off, 64));
+#pragma unroll
+    for (int i = 0; i < kFactChunk; ++i) rn[i] += __shfl_xor(rn[i], off, 64);
+  }
+  const float na = sqrtf(ma) * 1.01f, nb = sqrtf(mb) * 1.01f;
+  const float eacc = (float)(kp + 16) * 1.2e-7f * 2.f * (ma + mb);
+#pragma unroll
+  for (int i = 0; i < kFactChunk; ++i) {
+    const float rnorm = sqrtf(rn[i]) * 1.0001f;
+    const float eu = 4.f * (float)(d + 12) * 6e-8f * rnorm * (na + nb) + 2e-6f * (rn[i] + ma + mb);
+    const float thr = (delta * delta + eacc + eu) * (1.f + 1e-6f);
+    // nothing passes a negative threshold (nor a relation that is not there: those are not walked either); norms that leave
+    // float32's range decide nothing, every pair of the relation goes to the exact stage
+    float lim = thr < 1e37f && rn[i] < 1e37f ? thr - rn[i] : __builtin_inff();
+    if (rl0 + i >= RB || delta < 0.f) lim = -__builtin_inff();
+    if (lane == 0) limr[rl0 + i] = lim;
+  }
+}
+
 // u[rl][slot] = r . e~ for the relations of a batch and the bf16-rounded row of every slot's entity (why rounded:
-// k_fact_params; 0 for padding slots and for rows from RB on), and the extremes of 2 r.e over 8 and over 64 consecutive slots (padding does not count), on the float32 matrix
-// pipes: a wave takes 32 relations x 64 slots, operands straight into registers in the permuted order of dimensions that
-// k_small_dot explains, every load of 64 dimensions issued before the first is used.  The 128 x 128 vector tile kernel
-// that did the products before left most of the chip idle on a thin product (R = 2, d = 200: 60 us of latency) and
-// needed a pass that cleared u and one that took the extremes: 204 us for the three, now 94 us (N = 15,000, R = 1,345,
-// d = 100, float32 rows; 4.0 GFLOP, 81 MB written), N = 100,000, R = 200, d = 200: 284 -> 162 us.
+// fact_params; 0 for padding slots and for rows from RB on), and the extremes of 2 r.e~ over 8 and over 64 consecutive
+// slots (padding does not count), on the float32 matrix pipes: a wave takes 32 relations x 64 slots, operands straight into
+// registers in the permuted order of dimensions that k_small_dot explains, every load of 64 dimensions issued before the
+// first is used.  The 128 x 128 vector tile kernel that did the products before left most of the chip idle on a thin product
+// (R = 2, d = 200: 60 us of latency) and needed a pass that cleared u and one that took the extremes: 204 us for the three,
+// now 94 us (N = 15,000, R = 1,345, d = 100, float32 rows; 4.0 GFLOP, 81 MB written), N = 100,000, R = 200, d = 200:
+// 284 -> 162 us.  One more workgroup per 32 relations makes their thresholds.
 template <bool BF16, bool VEC>
 __global__ __launch_bounds__(256) void k_fact_dot(const void* __restrict__ Rv, const void* __restrict__ E,
                                                   const int32_t* __restrict__ slot_ent, int64_t Nslots, int r0, int RB, int RBp,
                                                   int d, float* __restrict__ u, float* __restrict__ umin8,
-                                                  float* __restrict__ umin64, float* __restrict__ umax64) {
+                                                  float* __restrict__ umin64, float* __restrict__ umax64,
+                                                  const DevCounters* __restrict__ cnt, float delta, int kp, float* __restrict__ limr) {
+  if (blockIdx.x == gridDim.x - 1) {
+    fact_params(cnt, Rv, BF16 ? KGC_BF16 : KGC_F32, r0, (int)blockIdx.y * 32 + (int)(threadIdx.x >> 6) * kFactChunk, RB, RBp, delta, d, kp, limr);
+    return;
+  }
   const int lane = threadIdx.x & 63, row = lane & 31, half = lane >> 5;
   const int64_t g = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);         // this wave's 64 slots (Nslots is a multiple of 256)
   const int rl0 = (int)blockIdx.y * 32;
@@ -1856,26 +1938,32 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1) void k_join_l2_fact(const JoinFac
 #undef KGC_FLUSH
 }
 
-// Exact scores of the pairs listed by k_join_l2_fact.  A wave takes 64 consecutive entries, four at a time (one per
+// Exact scores of the pairs listed by k_join_l2_fact.  A wave takes up to 64 consecutive entries, four at a time (one per
 // 16-lane group: the loads of a row are coalesced), gathers the results so that lane l speaks for entry l, and the
-// workgroup's waves reserve their output records with one atomic between them per round.
+// workgroup's waves reserve their output records with one atomic between them per round.  Four entries are a chain of
+// memory round trips, so a short list is spread over waves (64 each: N = 1,000, R = 16, 115 pairs 13 us, and
+// 82 us for 1,034 pairs of 282 dimensions); more than 256 workgroups would wait on the atomics instead.
+constexpr unsigned int kExactPairWaves = 1024;
 __global__ __launch_bounds__(256) void k_exact_pairs(const ExactEntry* __restrict__ list, const unsigned long long* __restrict__ count,
                                                      unsigned int cap, unsigned int* __restrict__ need, const RecheckCtx cx) {
   __shared__ unsigned int wave_hits[4];
   __shared__ unsigned long long base_s;
   const unsigned int n = *count <= cap ? (unsigned int)*count : 0u;      // (a list that did not fit: the host runs the call again)
   const int lane = lane_id(), wave = (int)(threadIdx.x >> 6), grp = lane >> 4, sub = lane & 15;
-  for (unsigned int e0 = blockIdx.x * 256u; e0 < n; e0 += gridDim.x * 256u) {       // the same for the whole block
-    const unsigned int first = e0 + (unsigned)wave * 64u;
+  // entries a wave takes at a time: a short list is dealt to 1,024 waves, four to 64 each
+  const unsigned int share = (n + kExactPairWaves * 4u - 1u) / (kExactPairWaves * 4u) * 4u;
+  const unsigned int per = share < 4u ? 4u : share < 64u ? share : 64u;
+  for (unsigned int e0 = blockIdx.x * 4u * per; e0 < n; e0 += gridDim.x * 4u * per) {       // the same for the whole block
+    const unsigned int first = e0 + (unsigned)wave * per;
     int32_t r = 0, h = -1, t = -1;
-    if (first + (unsigned)lane < n) {
+    if ((unsigned)lane < per && first + (unsigned)lane < n) {
       const ExactEntry en = list[first + (unsigned)lane];
       r = en.r; h = cx.slot_ent[en.hs0]; t = cx.slot_ent_t[en.ts0];
       if (h < 0 || t < 0 || (cx.no_self && h == t)) h = -1;
     }
     bool hit = false;
     float distf = 0.f;
-    for (int s = 0; s < 16; ++s) {
+    for (int s = 0; s < (int)(per >> 2); ++s) {
       if (first + (unsigned)s * 4u >= n) break;            // the same for the whole wave
       const int src = 4 * s + grp;
       const int32_t hs = __shfl(h, src, 64), rs = __shfl(r, src, 64), ts = __shfl(t, src, 64);
@@ -1909,47 +1997,6 @@ __global__ __launch_bounds__(256) void k_exact_pairs(const ExactEntry* __restric
     atomicAdd(cx.cand_counter, (unsigned long long)n);
     atomicMax(need, *count < 0xffffffffull ? (unsigned int)*count : 0xffffffffu);
   }
-}
-
-// Per-relation filter thresholds of the factorised join: limr[rl] = thr_r - ||r||^2.  A hit x = h + r - t, ||x|| <= delta,
-// has on the bf16-rounded rows x~ = h~ + r - t~ with ||x~|| <= delta + e_h + e_t (e = the distance that the rounding moves a
-// row), and with products of the ROUNDED rows the expansion of ||x~||^2 is exact, so that, as in k_stage_operands,
-//     (||h~ - t~||^2 - slack_h - slack_t) + 2 r.h~ - 2 r.t~ + ||r||^2 <= delta^2.
-// The staged norms carry the slacks: every row pays for its own rounding, and the length of r does not enter.  (Products of
-// the caller's rows left a term 2 (delta + ||r||) m, m from the largest norms: N = 1,000, R = 16, d = 32, relations 16 times
-// as long as delta: 37,789 candidates where the per-relation kernel has 76, 190 us a call against 100.)
-// thr_r = delta^2 + e_acc + e_u: e_acc bounds the float32 accumulation of the contraction as in k_join_params; e_u bounds the
-// float32 errors of the two products, (d + 12) 2^-24 ||r|| ||e~|| each and doubled (taken twice), of ||r||^2 and of the
-// final sums.
-// One wave per relation: the maxima of the staged norms, ||r||^2 in float32, the threshold.
-__global__ __launch_bounds__(256) void k_fact_params(const DevCounters* cnt, const void* __restrict__ Rv, int r0, int RB, int RBp,
-                                                     float delta, int dtype, int d, int kp, float* __restrict__ limr) {
-  const int lane = threadIdx.x & 63;
-  const int rl = (int)blockIdx.x * 4 + (int)(threadIdx.x >> 6);
-  if (rl >= RBp) return;
-  if (rl >= RB || delta < 0.f) {                                       // nothing passes (rows from RB on are not walked)
-    if (lane == 0) limr[rl] = -__builtin_inff();
-    return;
-  }
-  float ma = 0.f, mb = 0.f, rn = 0.f;
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    ma = fmaxf(ma, __uint_as_float(cnt->max_a[i * 64 + lane]));
-    mb = fmaxf(mb, __uint_as_float(cnt->max_b[i * 64 + lane]));
-  }
-  for (int k = lane; k < d; k += 64) { const float x = ld_elem(Rv, (int64_t)(r0 + rl) * d + k, dtype); rn += x * x; }
-  for (int off = 32; off > 0; off >>= 1) {
-    ma = fmaxf(ma, __shfl_xor(ma, off, 64));
-    mb = fmaxf(mb, __shfl_xor(mb, off, 64));
-    rn += __shfl_xor(rn, off, 64);
-  }
-  const float na = sqrtf(ma) * 1.01f, nb = sqrtf(mb) * 1.01f;
-  const float rnorm = sqrtf(rn) * 1.0001f;
-  const float eacc = (float)(kp + 16) * 1.2e-7f * 2.f * (ma + mb);
-  const float eu = 4.f * (float)(d + 12) * 6e-8f * rnorm * (na + nb) + 2e-6f * (rn + ma + mb);
-  const float thr = (delta * delta + eacc + eu) * (1.f + 1e-6f);
-  // norms that leave float32's range decide nothing: every pair of the relation goes to the exact stage
-  if (lane == 0) limr[rl] = thr < 1e37f && rn < 1e37f ? thr - rn : __builtin_inff();
 }
 
 // ---------------------------------------------------------------------------------------------
