@@ -44,8 +44,7 @@ static inline int64_t resident_range_bytes(int64_t tail_bytes) {
 }
 constexpr size_t kMaxLds = 160 * 1024;         // LDS per workgroup on gfx950
 constexpr int64_t kMaxTileList = 1ll << 30;    // entries of the surviving-tile list per relation batch (4 bytes each)
-constexpr unsigned int kFactListCap = 1u << 23;    // pairs the relation-factorised kernel may list per batch to start with (16 bytes each)
-constexpr unsigned long long kFactListMax = 1ull << 26;   // ... and at most (1 GiB)
+constexpr unsigned long long kFactListMax = 1ull << 26;   // pairs one batch may list for the exact stage, 16 bytes each (1 GiB)
 constexpr unsigned int kExactListCap = 1u << 20;   // accumulator blocks one batch may list for the exact stage (16 bytes each)
 
 struct DevBuf {
@@ -81,7 +80,9 @@ struct kgc_handle {
   unsigned int xcap = kExactListCap;           // its length in entries: grows when a batch wanted to list more
   DevBuf fop_a, fop_b, fu;                     // ... its operands and products r.e where it takes a part of a pruned join
   DevBuf flist, umin;                          // relation-factorised join: listed pairs; minima of 2 r.h over 32 rows
-  unsigned int fcap = kFactListCap;            // entries of flist (tests set fewer)
+  unsigned int fcap = 0;                       // entries of flist that an earlier call needed (see fact_list_start)
+  unsigned int fcap_start = 0;                 // > 0: ... and to start with (tests)
+  size_t flist_limit = 0;                      // > 0: bytes past which flist counts as not to be had (tests)
   int list_seg_cap = 0;                        // > 0: the pruned barrier-free kernel keeps at most this many entries of a row's tile list in the LDS (tests)
   unsigned pairs_grid = 512;                   // workgroups of the tile-at-a-time kernel: two per compute unit (tests set fewer, so that a workgroup walks several batches of tiles)
   DevBuf zero_row, cent_a, rad_a;              // kgc_join_ab: the zero relation row; micro-tile summaries of A[r]
@@ -303,10 +304,19 @@ inline bool fact_pays(int64_t N, int64_t R) { return R >= 8 && N >= 1000 && N * 
 // 8,434 / 831.  Where the spread is so wide that the list overflows the try is lost: 4,000, 18, 100: 929 / 1,115;
 // 20,000, 18, 100: 20,318 / 24,882; 10,000, 18, 512: 8,638 / 9,856.
 inline bool fact_pays_l1(int64_t N, int64_t R, int d) { return (double)N * (double)N * (double)R * d >= 6e9; }
-// Longest list of pairs worth scoring one by one.  L1: a listed pair costs about as much as 250 pairs of the L1 kernel.
-inline unsigned long long fact_list_max(int64_t N, int64_t R, int p) {
-  if (p == 2) return kFactListMax;
-  return std::min<unsigned long long>(kFactListMax, (unsigned long long)((double)N * (double)N * (double)R / 512.0));
+// Longest list of pairs a call may use: what the workspace leaves for it (an eighth, never less than the 16 MiB that the list
+// of accumulator blocks starts with), and no more than is worth scoring one by one.  L1: a listed pair costs about as much as
+// 250 pairs of the L1 kernel.
+inline unsigned long long fact_list_max(int64_t N, int64_t R, int p, int64_t ws) {
+  const unsigned long long room = std::max<unsigned long long>(1ull << 20, (unsigned long long)(ws / 8) / sizeof(ExactEntry));
+  // (L2: every pair there is, padding slots too: where norms leave float32's range they all go to the exact stage)
+  const double n = (double)(N + kSlotAlign), worth = p == 2 ? n * n * (double)R : (double)N * (double)N * (double)R / 512.0;
+  return std::max<unsigned long long>(1ull, (unsigned long long)std::min((double)std::min(kFactListMax, room), worth));
+}
+// ... and the length it starts with: one pair in 64 (4 MiB for the smallest joins, 128 MiB from 5 * 10^8 triples on).  A batch
+// that wanted to list more makes it longer and runs again.
+inline unsigned int fact_list_start(int64_t N, int64_t R) {
+  return (unsigned int)std::min((double)(1u << 23), std::max((double)(1u << 18), (double)N * (double)N * (double)R / 64.0));
 }
 
 // Units of the bound test (groups, micro-tiles without one) up to which a pruned L2 join is taken as a dense one: with
@@ -317,6 +327,21 @@ constexpr int kFewUnits = 3;
 // it / with it (n rows, R, d, as many rows again in groups): 1,100, 900, 64: 1,459 / 641; 1,500, 450, 64: 1,995 / 1,438;
 // 3,000, 120, 64: 2,140 / 1,373; 6,000, 30, 64: 3,241 / 1,184; 20,000, 100, 100: 20,042 / 2,483.  Below, the pairs are few.
 inline bool part_pays(int64_t n, int64_t R) { return n >= 1024 && R >= 8 && (double)n * (double)n * (double)R >= 1e9; }
+
+// the list of pairs with room for `entries`; false: it is not to be had, and the call does without it
+bool have_list(kgc_handle* hd, unsigned int entries) {
+  const size_t bytes = (size_t)entries * sizeof(ExactEntry);
+  if (hd->flist.p && hd->flist.bytes >= bytes) return true;
+  release(hd->flist);
+  if ((hd->flist_limit > 0 && bytes > hd->flist_limit) || hipMalloc(&hd->flist.p, bytes) != hipSuccess) {
+    (void)hipGetLastError();                               // (the failure is dealt with)
+    hd->flist.p = nullptr;
+    hd->fcap = 0;                                          // the next call asks for what it would start with
+    return false;
+  }
+  hd->flist.bytes = bytes;
+  return true;
+}
 
 int grid_for(int64_t items, int per_block) {
   return (int)std::min<int64_t>((items + per_block - 1) / per_block, (1 << 24) - 1);
@@ -406,7 +431,8 @@ int kgc_create(const kgc_config* cfg, kgc_handle** out) {
   }
   h->err.reserve(256);          // later error messages fit without a host allocation
   // the first length of the exact stage's block list (it grows by itself; tests set it small to see it grow)
-  if (const char* e = std::getenv("KGC_EXACT_LIST_CAP")) h->xcap = h->fcap = (unsigned int)std::max(1L, std::atol(e));
+  if (const char* e = std::getenv("KGC_EXACT_LIST_CAP")) h->xcap = h->fcap_start = (unsigned int)std::max(1L, std::atol(e));
+  if (const char* e = std::getenv("KGC_PAIR_LIST_LIMIT")) h->flist_limit = (size_t)std::max(1L, std::atol(e));
   if (const char* e = std::getenv("KGC_TILE_LIST_SEGMENT")) h->list_seg_cap = (int)std::max(1L, std::atol(e));
   if (const char* e = std::getenv("KGC_PAIRS_GRID")) h->pairs_grid = (unsigned)std::min(512L, std::max(1L, std::atol(e)));
   if (hipHostMalloc((void**)&h->host_counters, sizeof(DevCounters), hipHostMallocDefault) != hipSuccess) {
@@ -1364,8 +1390,19 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
   const bool part_ok = p == 2 && prune && !win && !hd->static_mode && !hd->no_fact && hd->cfg.tile_cfg == 0 && hd->cfg.factorised == 0 &&
                        KS <= kDirectHalfMaxKS && delta >= 0.f && delta < 1e18f;
   const bool l2_ops = p == 2 || fact;          // staged operands of the matrix pipes
-  const unsigned long long fact_most = fact_list_max(N, Rn, p);
-  const unsigned int fact_cap = p == 2 ? hd->fcap : (unsigned int)std::min<unsigned long long>(hd->fcap, fact_most);
+  const int64_t ws = hd->ws_override > 0 ? hd->ws_override
+                                           : hd->cfg.workspace_bytes > 0 ? hd->cfg.workspace_bytes : kDefaultWorkspace;
+  const unsigned long long fact_most = fact_list_max(N, Rn, p, ws);
+  const unsigned int fact_cap = (unsigned int)std::min<unsigned long long>(
+      std::max(hd->fcap, hd->fcap_start > 0 ? hd->fcap_start : fact_list_start(N, Rn)), fact_most);
+  // the same call again without the list of pairs (dense: the kernels that contract every relation or sum in L1)
+  auto without_list = [&]() {
+    hd->no_fact = true;
+    const int rc2 = join_range_impl(hd, E, N, d, Rvecs, R, p, delta, r_begin, r_end, out_triples, cap, count, win,
+                                    prep_mode == kPrepFresh && hd->prep.valid ? kPrepReuse : prep_mode);
+    hd->no_fact = false;
+    return rc2;
+  };
   int tile_id = kDefaultL2Tile;
   if (fact) tile_id = KS <= kDirectMaxKS ? kDirectL2Tile : kDirectHalfL2Tile;
   else if (hd->cfg.tile_cfg > 0) tile_id = hd->cfg.tile_cfg - 1;
@@ -1439,11 +1476,15 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
     if (part_pays(Nslots - f, Rn)) part0 = f;
   }
   const int64_t part_n = Nslots - part0;
+  // the barrier-free kernel over tile lists hands its candidates on (not in a call that does without the list)
+  const bool lists_pairs = prune && p == 2 && tile_id == kDirectL2Tile && !hd->no_fact;
+  if ((fact || part_n || lists_pairs) && !have_list(hd, fact_cap)) {
+    pr.valid = reuse;                                      // (what the handle held is still there)
+    return without_list();
+  }
   if (nH > 65535) return fail(hd, KGC_E_INVALID, "N too large for one launch grid");
 
   // ---- relation batches: staged A operands (L2) and the tile lists (pruning) must fit the workspace ----
-  const int64_t ws = hd->ws_override > 0 ? hd->ws_override
-                                           : hd->cfg.workspace_bytes > 0 ? hd->cfg.workspace_bytes : kDefaultWorkspace;
   const size_t opA_per_rel = l2_ops ? (size_t)KS * Nslots * kSliceK * 2 : 0;
   int64_t RBmax = Rn;
   if (p == 2 && !fact) RBmax = std::max<int64_t>(1, std::min<int64_t>(Rn, ws / (int64_t)(opA_per_rel + Nslots * 4)));
@@ -1458,8 +1499,7 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
         (rc = ensure(hd, hd->normsA, (size_t)(fact ? 1 : RBmax) * Nslots * 4)))
       return rc;
     if (fact && ((rc = ensure(hd, hd->relu, (size_t)fact_rows(RBmax) * Nslots * 4)) ||
-                 (rc = ensure(hd, hd->limr, fact_rows(RBmax) * 4)) || (rc = ensure(hd, hd->umin, (size_t)fact_rows(RBmax) * (Nslots / 64) * 10 * 4)) ||
-                 (rc = ensure(hd, hd->flist, (size_t)hd->fcap * sizeof(ExactEntry)))))
+                 (rc = ensure(hd, hd->limr, fact_rows(RBmax) * 4)) || (rc = ensure(hd, hd->umin, (size_t)fact_rows(RBmax) * (Nslots / 64) * 10 * 4))))
       return rc;
   }
   if (prune) {
@@ -1557,13 +1597,12 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
     const size_t op = (size_t)KS * part_n * kSliceK * 2;
     const int64_t RBf = std::max<int64_t>(1, std::min<int64_t>({Rn, ws / (part_n * 4), 65535}));
     if ((rc = ensure(hd, hd->fop_a, op)) || (rc = ensure(hd, hd->fop_b, op)) || (rc = ensure(hd, hd->fu, (size_t)fact_rows(RBf) * part_n * 4)) ||
-        (rc = ensure(hd, hd->limr, fact_rows(RBf) * 4)) || (rc = ensure(hd, hd->umin, (size_t)fact_rows(RBf) * (part_n / 64) * 10 * 4)) ||
-        (rc = ensure(hd, hd->flist, (size_t)hd->fcap * sizeof(ExactEntry))))
+        (rc = ensure(hd, hd->limr, fact_rows(RBf) * 4)) || (rc = ensure(hd, hd->umin, (size_t)fact_rows(RBf) * (part_n / 64) * 10 * 4)))
       return rc;
     fj.slot_ent = slot_ent + part0; fj.Nslots = part_n;
     fj.A = (const uint16_t*)hd->fop_a.p; fj.B = (const uint16_t*)hd->fop_b.p;
     fj.u = (float*)hd->fu.p; fj.umin = (float*)hd->umin.p; fj.limr = (float*)hd->limr.p;
-    fj.list = (ExactEntry*)hd->flist.p; fj.list_cap = hd->fcap; fj.give_up = std::max<unsigned long long>(fact_most, hd->fcap);
+    fj.list = (ExactEntry*)hd->flist.p; fj.list_cap = fact_cap; fj.give_up = fact_most;
     // (the running maxima of the norms, shared with the other kernels' operands, only widen the thresholds)
     launch_fact_stage(st, fj, (uint16_t*)hd->fop_a.p, (uint16_t*)hd->fop_b.p, cnt);
     RecheckCtx cxf = cx;
@@ -1717,7 +1756,7 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
       fj.r0 = (int)r0; fj.RB = RB;
       fj.A = (const uint16_t*)hd->opA.p; fj.B = (const uint16_t*)hd->opB.p;
       fj.u = (float*)hd->relu.p; fj.umin = (float*)hd->umin.p; fj.limr = (float*)hd->limr.p;
-      fj.list = (ExactEntry*)hd->flist.p; fj.list_cap = fact_cap; fj.give_up = std::max<unsigned long long>(fact_most, fact_cap);
+      fj.list = (ExactEntry*)hd->flist.p; fj.list_cap = fact_cap; fj.give_up = fact_most;
       launch_fact_products(st, fj, cnt);
       if (timed) KGC_HIP(hd, hipEventRecord(hd->join_ev[2 * b], st));
       if ((rc = launch_fact_join(hd, st, fj, cnt, cx)) != KGC_OK) return rc;
@@ -1798,10 +1837,7 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
           sa.xlist = (ExactEntry*)hd->xlist.p; sa.xcount = &cnt->n_exact; sa.xcap = hd->xcap;
         }
         if (pairs_ok) { sa.tile_rows = (const uint32_t*)hd->tile_rows.p; sa.tile_total = &cnt->tile_cursor; sa.pair_mode = &cnt->pair_mode; }
-        // the barrier-free kernel over tile lists hands its candidates on (not in a call whose list has overflowed for good)
-        const bool lists_pairs = prune && tile_id == kDirectL2Tile && !hd->no_fact;
         if (lists_pairs) {
-          if ((rc = ensure(hd, hd->flist, (size_t)hd->fcap * sizeof(ExactEntry)))) return rc;
           sa.plist = (ExactEntry*)hd->flist.p; sa.pcount = &cnt->n_fact; sa.pcap = fact_cap;
           if (b > 0 || part_n) k_fill_u32<<<1, 64, 0, st>>>((uint32_t*)&cnt->n_fact, 2, 0u);      // an empty list (zero at the start of a call)
         }
@@ -1845,13 +1881,12 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
   pr.bitmap_valid = prune && nbatch == 1 && !empty_window && part_n == 0; pr.bm_r0 = r_begin; pr.bm_r1 = r_end;
   // A batch that wanted to list more accumulator blocks than the list holds has dropped the rest (and counted
   // them): the list grows to what was asked for and the join runs again from the start.
-  if (hd->host_counters->fact_need > fact_cap) {      // (the same of the relation-factorised kernel's list of pairs)
+  if (hd->host_counters->fact_need > fact_cap) {      // (the same of the list of pairs)
     const unsigned long long need = hd->host_counters->fact_need;
-    if (need <= fact_most) hd->fcap = (unsigned int)(need + need / 4 + 1024);
-    hd->no_fact = need > fact_most;                          // a threshold that passes so much: pair by pair, scored in place
-    const int rc2 = join_range_impl(hd, E, N, d, Rvecs, R, p, delta, r_begin, r_end, out_triples, cap, count, win, prep_mode);
-    hd->no_fact = false;
-    return rc2;
+    if (need > fact_most) return without_list();      // a threshold that passes so much: pair by pair, scored in place
+    hd->fcap = (unsigned int)std::min<unsigned long long>(need + need / 4 + 1024, kFactListMax);
+    return join_range_impl(hd, E, N, d, Rvecs, R, p, delta, r_begin, r_end, out_triples, cap, count, win,
+                           prep_mode == kPrepFresh && pr.valid ? kPrepReuse : prep_mode);      // (what was just prepared is still good)
   }
   if (hd->host_counters->exact_need > hd->xcap) {
     const unsigned long long need = hd->host_counters->exact_need;
