@@ -1395,12 +1395,16 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
   const unsigned long long fact_most = fact_list_max(N, Rn, p, ws);
   const unsigned int fact_cap = (unsigned int)std::min<unsigned long long>(
       std::max(hd->fcap, hd->fcap_start > 0 ? hd->fcap_start : fact_list_start(N, Rn)), fact_most);
-  // the same call again without the list of pairs (dense: the kernels that contract every relation or sum in L1)
+  // The same call again without the list of pairs (dense: the kernels that contract every relation or sum in L1; a pruned join
+  // whose rows form one group goes back to the pruned kernels, which score whole blocks of candidates).
   auto without_list = [&]() {
     hd->no_fact = true;
+    const bool as_dense = hd->as_dense;
+    hd->as_dense = false;
     const int rc2 = join_range_impl(hd, E, N, d, Rvecs, R, p, delta, r_begin, r_end, out_triples, cap, count, win,
                                     prep_mode == kPrepFresh && hd->prep.valid ? kPrepReuse : prep_mode);
     hd->no_fact = false;
+    hd->as_dense = as_dense;
     return rc2;
   };
   int tile_id = kDefaultL2Tile;

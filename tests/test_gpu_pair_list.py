@@ -55,8 +55,7 @@ def test_list_that_cannot_be_had(name, limit, monkeypatch):
             got = _call(j, E, Rv, p, delta)
             np.testing.assert_array_equal(got[0], want[0])
             np.testing.assert_allclose(got[1], want[1], rtol=2.0 ** -22, atol=1e-30)
-            if name != "one_group":            # (what follows there is the subject of a test of its own)
-                assert got[2] == variant
+            assert got[2] == variant
     finally:
         for j in (a, grows, b):
             j.close()
