@@ -64,7 +64,11 @@ typedef struct {
                                        instantiation per number of K steps, the dense default).  Dense mode, and 15
                                        also pruned, walking tile lists: the pruned default from 262,144 entities on
                                  A variant that cannot run the request (pruned mode, d) fails with KGC_E_INVALID. */
-    int64_t workspace_bytes;  /* cap on scratch held for staged operands; 0 = 16 GiB.  Larger joins run in relation batches */
+    int64_t workspace_bytes;  /* cap on the scratch that a batch of relations needs: staged operands (or, in the
+                                 relation-factorised form, the tables of its products) of one relation at least;
+                                 0 = 16 GiB.  Larger joins run in relation batches.  Beside it the handle holds what
+                                 does not grow with the relations, the tile lists, and the list of candidate pairs
+                                 (up to an eighth of this and 1 GiB, 16 MiB at least) */
     void*   stream;           /* hipStream_t to enqueue on; NULL = the default stream */
     float   group_radius;     /* pruning only: radius of entity groups as a multiple of delta; 0 = 2.0 */
     int32_t range_kib;        /* dense L2 join: KiB of staged tail rows one block walks (L2 blocking); 0 = automatic */

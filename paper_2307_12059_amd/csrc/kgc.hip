@@ -78,8 +78,7 @@ struct kgc_handle {
   DevBuf se_a, se_b;                           // connector rows of a relation batch (kgc_join_se)
   DevBuf xlist;                                // accumulator blocks listed for the exact stage (L2 joins)
   unsigned int xcap = kExactListCap;           // its length in entries: grows when a batch wanted to list more
-  DevBuf fop_a, fop_b, fu;                     // ... its operands and products r.e where it takes a part of a pruned join
-  DevBuf flist, umin;                          // relation-factorised join: listed pairs; minima of 2 r.h over 32 rows
+  DevBuf flist, umin;                          // listed pairs; relation-factorised join: extremes of 2 r.e over 8 and 64 rows
   unsigned int fcap = 0;                       // entries of flist that an earlier call needed (see fact_list_start)
   unsigned int fcap_start = 0;                 // > 0: ... and to start with (tests)
   size_t flist_limit = 0;                      // > 0: bytes past which flist counts as not to be had (tests)
@@ -286,6 +285,13 @@ hipError_t wait_event(hipEvent_t ev) {
 
 // rows of the relation-factorised join's per-relation tables: whole chunks of relations
 inline int64_t fact_rows(int64_t RB) { return (RB + kFactChunk - 1) / kFactChunk * kFactChunk; }
+// bytes per row of those of `slots` slots: u and the extremes over 8 and 64 slots
+inline int64_t fact_row_bytes(int64_t slots) { return slots * 4 + slots / 64 * 40; }
+// relations whose tables fit `bytes` (one at least), in whole chunks where that many fit
+inline int64_t fact_batch(int64_t bytes, int64_t slots, int64_t R) {
+  const int64_t rows = std::max<int64_t>(1, std::max<int64_t>(bytes, 0) / fact_row_bytes(slots));
+  return std::min<int64_t>({R, rows >= kFactChunk ? rows / kFactChunk * kFactChunk : rows, 65528});
+}
 // Dense L2 joins that the relation-factorised kernel takes by itself.  Its fixed part (products r.e, one contraction per
 // pair of entities, the list of pairs) is paid once, the other kernels contract every relation and score their candidates in
 // place.  Measured, whole calls in us, per-relation kernel / this one, float32, clusters of 60 rows in random order.  A few to
@@ -457,7 +463,7 @@ void kgc_destroy(kgc_handle* h) {
                     &h->gram, &h->relu, &h->reln, &h->asg_a, &h->asg_b, &h->limr, &h->top1_buf, &h->top1_state,
                     &h->unit_first, &h->unit_n, &h->cent_u, &h->rad_u, &h->cnorm_u, &h->gram_u, &h->relu_u, &h->pair_list,
                     &h->pair_count, &h->xlist, &h->tile_rows, &h->se_a, &h->se_b, &h->zero_row, &h->cent_a, &h->rad_a, &h->top1_a, &h->top1_b, &h->top1_pick, &h->top_samples, &h->topk_state,
-                    &h->flist, &h->umin, &h->fop_a, &h->fop_b, &h->fu})
+                    &h->flist, &h->umin})
     release(*b);
   if (h->host_gstate) (void)hipHostFree(h->host_gstate);
   if (h->host_counters) (void)hipHostFree(h->host_counters);
@@ -1492,14 +1498,18 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
   const size_t opA_per_rel = l2_ops ? (size_t)KS * Nslots * kSliceK * 2 : 0;
   int64_t RBmax = Rn;
   if (p == 2 && !fact) RBmax = std::max<int64_t>(1, std::min<int64_t>(Rn, ws / (int64_t)(opA_per_rel + Nslots * 4)));
-  if (fact) RBmax = std::max<int64_t>(1, std::min<int64_t>(Rn, ws / (int64_t)(Nslots * 4)));      // u[r][slot]
+  if (fact) RBmax = fact_batch(ws, Nslots, Rn);
   if (prune) RBmax = std::max<int64_t>(1, std::min<int64_t>(RBmax, kMaxTileList / tiles_per_rel));
   RBmax = std::max<int64_t>(1, std::min<int64_t>(RBmax, 65535));
   if (prune && tiles_per_rel > kMaxTileList) return fail(hd, KGC_E_INVALID, "N too large for the pruned tile list");
+  // the part's two operands and its tables lie where the batches stage their head rows afterwards
+  const size_t part_op = (size_t)KS * part_n * kSliceK * 2, opA_bytes = opA_per_rel * (size_t)(fact ? 1 : RBmax);
+  const int64_t RBf = part_n ? fact_batch(std::max<int64_t>(ws, (int64_t)opA_bytes) - 2 * (int64_t)part_op, part_n, Rn) : 0;
+  const size_t part_bytes = 2 * part_op + (size_t)fact_rows(RBf) * fact_row_bytes(part_n);
 
   if (l2_ops) {
     if ((rc = ensure(hd, hd->opB, (size_t)KS * Nslots * kSliceK * 2)) ||
-        (rc = ensure(hd, hd->opA, opA_per_rel * (size_t)(fact ? 1 : RBmax))) || (rc = ensure(hd, hd->normsB, Nslots * 4)) ||
+        (rc = ensure(hd, hd->opA, std::max(opA_bytes, part_bytes))) || (rc = ensure(hd, hd->normsB, Nslots * 4)) ||
         (rc = ensure(hd, hd->normsA, (size_t)(fact ? 1 : RBmax) * Nslots * 4)))
       return rc;
     if (fact && ((rc = ensure(hd, hd->relu, (size_t)fact_rows(RBmax) * Nslots * 4)) ||
@@ -1598,17 +1608,14 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
   }
   KGC_HIP(hd, hipEventRecord(hd->ev[1], st));
   if (part_n) {
-    const size_t op = (size_t)KS * part_n * kSliceK * 2;
-    const int64_t RBf = std::max<int64_t>(1, std::min<int64_t>({Rn, ws / (part_n * 4), 65535}));
-    if ((rc = ensure(hd, hd->fop_a, op)) || (rc = ensure(hd, hd->fop_b, op)) || (rc = ensure(hd, hd->fu, (size_t)fact_rows(RBf) * part_n * 4)) ||
-        (rc = ensure(hd, hd->limr, fact_rows(RBf) * 4)) || (rc = ensure(hd, hd->umin, (size_t)fact_rows(RBf) * (part_n / 64) * 10 * 4)))
-      return rc;
+    if ((rc = ensure(hd, hd->limr, fact_rows(RBf) * 4))) return rc;
+    char* const at = (char*)hd->opA.p;
     fj.slot_ent = slot_ent + part0; fj.Nslots = part_n;
-    fj.A = (const uint16_t*)hd->fop_a.p; fj.B = (const uint16_t*)hd->fop_b.p;
-    fj.u = (float*)hd->fu.p; fj.umin = (float*)hd->umin.p; fj.limr = (float*)hd->limr.p;
+    fj.A = (const uint16_t*)at; fj.B = (const uint16_t*)(at + part_op);
+    fj.u = (float*)(at + 2 * part_op); fj.umin = fj.u + fact_rows(RBf) * part_n; fj.limr = (float*)hd->limr.p;
     fj.list = (ExactEntry*)hd->flist.p; fj.list_cap = fact_cap; fj.give_up = fact_most;
     // (the running maxima of the norms, shared with the other kernels' operands, only widen the thresholds)
-    launch_fact_stage(st, fj, (uint16_t*)hd->fop_a.p, (uint16_t*)hd->fop_b.p, cnt);
+    launch_fact_stage(st, fj, (uint16_t*)at, (uint16_t*)(at + part_op), cnt);
     RecheckCtx cxf = cx;
     cxf.slot_ent = cxf.slot_ent_t = fj.slot_ent;
     for (int64_t r0 = r_begin; r0 < r_end; r0 += RBf) {

@@ -105,3 +105,67 @@ def test_barrier_free_kernel_lists_its_candidates(N, R, d, k, cap, dtype, monkey
     got = _records(Et, Rt, delta, 1 << 23, dtype, prune=PRUNE_ON, tile_cfg=15)
     assert got[2]["join_variant"] == 15 and want[0].shape[0] > 50
     _same(got, want)
+
+
+def _lone_rows(seed, n_lone, n_big, R, d, dtype):
+    g = np.random.default_rng(seed)
+    cent = g.standard_normal((n_big, d))
+    E = np.concatenate([np.repeat(cent, 40, 0) + 0.1 * g.standard_normal((40 * n_big, d)), g.standard_normal((n_lone, d))])
+    N = E.shape[0]
+    E = E[g.permutation(N)]
+    h, t = g.integers(0, N, R), g.integers(0, N, R)
+    return _torch(E, dtype), _torch(E[t] - E[h] + 0.03 * g.standard_normal((R, d)), dtype)
+
+
+# a workspace of one relation's operands: the part runs in batches of a few relations (R is no multiple of eight), the other
+# tiles one relation at a time, and the list is emptied in between
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("extra", [0, 40, 400])
+def test_rows_without_a_group_in_relation_batches(extra, dtype):
+    n_lone, n_big, R, d = 1400, 37, 557, 20
+    Et, Rt = _lone_rows(41, n_lone, n_big, R, d, dtype)
+    delta = float(np.float32(0.1 * np.sqrt(2.0 * d)))
+    # two operands of 1,400 to 1,536 slots in one K slice of 64 bytes a slot, and the tables of `extra` relations
+    ws = 2 * 64 * 1536 + extra * (4 * 1536 + 40 * 24)
+    want = _records(Et, Rt, delta, 1 << 20, dtype, prune=PRUNE_ON)
+    got = _records(Et, Rt, delta, 1 << 20, dtype, prune=PRUNE_ON, workspace_bytes=ws)
+    assert want[2]["relation_batches"] == 1 and got[2]["relation_batches"] > 40 and want[0].shape[0] > R
+    _same(got, want)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("cap", [None, "3"])
+def test_barrier_free_kernel_in_relation_batches(cap, dtype, monkeypatch):
+    g = np.random.default_rng(17)
+    N, R, d, k = 2500, 7, 40, 9
+    cent = g.standard_normal((k, d))
+    E = cent[g.integers(0, k, N)] + 0.1 * g.standard_normal((N, d))
+    Rv = np.roll(cent, -1, 0)[:R] - cent[:R] + 0.02 * g.standard_normal((R, d))
+    Et, Rt = _torch(E, dtype), _torch(Rv, dtype)
+    delta = float(np.float32(0.1 * np.sqrt(2.0 * d) * 0.9))
+    want = _records(Et, Rt, delta, 1 << 23, dtype, prune=PRUNE_ON, tile_cfg=15)
+    if cap:
+        monkeypatch.setenv("KGC_EXACT_LIST_CAP", cap)
+    got = _records(Et, Rt, delta, 1 << 23, dtype, prune=PRUNE_ON, tile_cfg=15, workspace_bytes=1)
+    assert want[2]["relation_batches"] == 1 and got[2]["relation_batches"] == R and want[0].shape[0] > 50
+    _same(got, want)
+
+
+def test_the_part_keeps_to_the_workspace():
+    """What a join with a part holds more than the same join without one (its kernel asked for by number) is the list of
+    pairs: operands and tables share the memory of the batches."""
+    import torch
+    import paper_2307_12059_amd as kgc
+    Et, Rt = _lone_rows(43, 12000, 40, 1000, 64, "f32")
+    out = torch.empty((1 << 20, 4), dtype=torch.int32, device="cuda")
+    held = {}
+    for tile in (14, 0):
+        torch.cuda.synchronize()
+        before = torch.cuda.mem_get_info()[0]
+        j = kgc.Join(prune=PRUNE_ON, tile_cfg=tile, workspace_bytes=32 << 20)
+        got = j.join(Et, Rt, 2, 1.0, 1 << 20, out=out, fetch=False)
+        held[tile] = (before - torch.cuda.mem_get_info()[0], got["count"])
+        j.close()
+    assert held[0][1] == held[14][1] > 1000
+    # the tables alone would be 1,000 x 12,000 x 4.6 bytes
+    assert held[0][0] <= held[14][0] + (16 << 20) + (8 << 20), held
