@@ -334,6 +334,15 @@ constexpr int kFewUnits = 3;
 // 3,000, 120, 64: 2,140 / 1,373; 6,000, 30, 64: 3,241 / 1,184; 20,000, 100, 100: 20,042 / 2,483.  Below, the pairs are few.
 inline bool part_pays(int64_t n, int64_t R) { return n >= 1024 && R >= 8 && (double)n * (double)n * (double)R >= 1e9; }
 
+// summaries of the bound test's units (P: the join's metric)
+template <int P>
+void launch_unit_summary(kgc_handle* hd, int d, const UnitTable& ut) {
+  const bool small = hd->host_gstate->max_unit <= kSmallUnit;
+  auto kern = small ? k_unit_summary_small<P> : k_unit_summary<P>;
+  hipLaunchKernelGGL(kern, dim3((unsigned)ut.n_units), dim3(small ? 64 : kUnitWaves * 64), 0, hd->stream, (const float*)hd->cent.p,
+                     (const float*)hd->rad.p, d, ut, (float*)hd->cent_u.p, (float*)hd->rad_u.p, (float*)hd->cnorm_u.p);
+}
+
 // the list of pairs with room for `entries`; false: it is not to be had, and the call does without it
 bool have_list(kgc_handle* hd, unsigned int entries) {
   const size_t bytes = (size_t)entries * sizeof(ExactEntry);
@@ -1574,8 +1583,7 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
           k_tile_dist<2, kEpiMatrix><<<g, 256, 0, st>>>(ta);
       }
       if (use_units) {
-        k_unit_summary<2><<<(unsigned)ut.n_units, kUnitWaves * 64, 0, st>>>((const float*)hd->cent.p, (const float*)hd->rad.p, d, ut,
-                                                            (float*)hd->cent_u.p, (float*)hd->rad_u.p, (float*)hd->cnorm_u.p);
+        launch_unit_summary<2>(hd, d, ut);
         TileDistArgs tu{};
         tu.X = hd->cent_u.p; tu.dtypeX = KGC_F32; tu.n_rows = ut.n_units; tu.Y = hd->cent_u.p; tu.dtypeY = KGC_F32;
         tu.n_cols = ut.n_units; tu.shift = nullptr; tu.dtype_shift = KGC_F32; tu.d = d; tu.matrix = (float*)hd->gram_u.p; tu.symmetric = 1;
@@ -1585,9 +1593,7 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
     } else {
       k_micro_summary<1><<<(unsigned)n_micro, 64, 0, st>>>(E, dtype, d, slot_ent, n_micro, (float*)hd->cent.p,
                                                             (float*)hd->rad.p, (float*)hd->cnorm.p);
-      if (use_units)
-        k_unit_summary<1><<<(unsigned)ut.n_units, kUnitWaves * 64, 0, st>>>((const float*)hd->cent.p, (const float*)hd->rad.p, d, ut,
-                                                               (float*)hd->cent_u.p, (float*)hd->rad_u.p, (float*)hd->cnorm_u.p);
+      if (use_units) launch_unit_summary<1>(hd, d, ut);
     }
   }
   FactJob fj{};      // of the factorised form: the whole join, or its part

@@ -32,6 +32,7 @@ struct GroupState {
   int32_t tail_base;    // first slot of the unpadded tail region
   int32_t tail_fill;    // running count of rows placed in the tail region
   int32_t n_big;        // groups of at least kSmallGroup rows: each is one unit of the two-level bound test
+  int32_t max_unit;     // micro-tiles of the largest of them
 };
 
 // Start of a round: pivots are an even-stride sample (one in 2^shift, at most kPivotsPerRound) of the
@@ -135,15 +136,18 @@ __global__ __launch_bounds__(1024) void k_group_layout(GroupState* gs, const int
   const int G = gs->n_groups;
   const int per = (G + 1023) / 1024;
   const int g0 = tid * per, g1 = (g0 + per < G) ? g0 + per : G;
-  int sum = 0, placed = 0, nbig = 0;
+  __shared__ int largest;
+  if (tid == 0) largest = 0;
+  int sum = 0, placed = 0, nbig = 0, most = 0;
   for (int g = g0; g < g1; ++g) {
     const int sz = gsize[g];
-    if (sz >= kSmallGroup) { sum += (sz + kMicro - 1) / kMicro * kMicro; placed += sz; ++nbig; }
+    if (sz >= kSmallGroup) { sum += (sz + kMicro - 1) / kMicro * kMicro; placed += sz; ++nbig; most = sz > most ? sz : most; }
   }
   part[tid] = sum;
   placed_part[tid] = placed;
   big_part[tid] = nbig;
   __syncthreads();
+  if (most > 0) atomicMax(&largest, most);      // (read after the scan's barriers)
   for (int off = 1; off < 1024; off <<= 1) {          // inclusive scan, Hillis-Steele
     const int v = tid >= off ? part[tid - off] : 0;
     const int w = tid >= off ? placed_part[tid - off] : 0;
@@ -175,6 +179,7 @@ __global__ __launch_bounds__(1024) void k_group_layout(GroupState* gs, const int
     int total_padded = part[1023];
     if (N - placed_part[1023] >= kTailAligned) total_padded = (total_padded + slot_align - 1) / slot_align * slot_align;
     gs->n_big = big_part[1023];
+    gs->max_unit = (largest + kMicro - 1) / kMicro;
     gs->tail_base = total_padded;
     gs->tail_fill = 0;
     const int64_t total = (int64_t)total_padded + (N - placed_part[1023]);
@@ -1011,6 +1016,58 @@ __global__ __launch_bounds__(kUnitWaves * 64) void k_unit_summary(const float* _
       radU[u] = cntm > 0 ? rmax * (1.f + kBoundSlack) + 1e-30f : -1.f;
       cnormU[u] = cntm > 0 ? sqrtf(c2) * (1.f + kBoundSlack) : 0.f;
     }
+  }
+}
+
+// The same where no unit has more than kSmallUnit micro-tiles: a wave per unit, whose micro-tiles' centres are read once, side
+// by side (the chunk's centre comes from their sum, and each one's distance grows by its part of the chunk).  N = 100,000,
+// d = 200, units of one to three: 5.3 us, where the workgroups of sixteen waves take 24 for the launch of 1,024 threads and
+// two barriers per 64 dimensions.
+constexpr int kSmallUnit = 4;
+template <int P>
+__global__ __launch_bounds__(64) void k_unit_summary_small(const float* __restrict__ cent, const float* __restrict__ rad, int d,
+                                                           UnitTable ut, float* __restrict__ centU, float* __restrict__ radU,
+                                                           float* __restrict__ cnormU) {
+  const int u = (int)blockIdx.x;
+  if (u >= ut.n_units) return;
+  const int lane = threadIdx.x;
+  int first, n;
+  unit_range(ut, u, first, n);
+  float rm[kSmallUnit], dist[kSmallUnit];
+  int cntm = 0;
+#pragma unroll
+  for (int i = 0; i < kSmallUnit; ++i) {
+    rm[i] = i < n ? rad[first + i] : -1.f;                // (-1: an empty micro-tile, or none; the same for the whole wave)
+    cntm += !(rm[i] < 0.f);
+    dist[i] = 0.f;
+  }
+  const float inv = cntm > 0 ? 1.f / (float)cntm : 0.f;
+  float c2 = 0.f;
+  for (int k = lane; k < d; k += 64) {
+    float v[kSmallUnit], s = 0.f;
+#pragma unroll
+    for (int i = 0; i < kSmallUnit; ++i) v[i] = cent[(int64_t)(first + (i < n ? i : 0)) * d + k];
+#pragma unroll
+    for (int i = 0; i < kSmallUnit; ++i)
+      if (!(rm[i] < 0.f)) s += v[i];
+    const float ck = s * inv;
+    centU[(int64_t)u * d + k] = ck;
+    c2 += ck * ck;
+#pragma unroll
+    for (int i = 0; i < kSmallUnit; ++i) { const float x = v[i] - ck; dist[i] += (P == 2) ? x * x : fabsf(x); }
+  }
+  for (int off = 32; off > 0; off >>= 1) {
+    c2 += __shfl_xor(c2, off, 64);
+#pragma unroll
+    for (int i = 0; i < kSmallUnit; ++i) dist[i] += __shfl_xor(dist[i], off, 64);
+  }
+  float rmax = 0.f;
+#pragma unroll
+  for (int i = 0; i < kSmallUnit; ++i)
+    if (!(rm[i] < 0.f)) rmax = fmaxf(rmax, ((P == 2) ? sqrtf(dist[i]) : dist[i]) * (1.f + kBoundSlack) + rm[i]);
+  if (lane == 0) {
+    radU[u] = cntm > 0 ? rmax * (1.f + kBoundSlack) + 1e-30f : -1.f;
+    cnormU[u] = cntm > 0 ? sqrtf(c2) * (1.f + kBoundSlack) : 0.f;
   }
 }
 

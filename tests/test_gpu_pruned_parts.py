@@ -169,3 +169,33 @@ def test_the_part_keeps_to_the_workspace():
     assert held[0][1] == held[14][1] > 1000
     # the tables alone would be 1,000 x 12,000 x 4.6 bytes
     assert held[0][0] <= held[14][0] + (16 << 20) + (8 << 20), held
+
+
+# the largest unit of the two-level bound test on both sides of the size up to which one wave summarises a unit, beside
+# units of one micro-tile; both norms
+@pytest.mark.parametrize("p", [1, 2])
+@pytest.mark.parametrize("rows", [32, 4 * 32, 4 * 32 + 1, 33 * 32 + 1])
+def test_summaries_of_large_units(rows, p):
+    import paper_2307_12059_amd as kgc
+    g = np.random.default_rng(rows)
+    d, k = 70, 40
+    cent = g.standard_normal((k, d))
+    lab = np.concatenate([np.zeros(rows, int), np.repeat(np.arange(1, k), 30), np.arange(1, k)])
+    E = (cent[lab] + 0.1 * g.standard_normal((lab.size, d)))[g.permutation(lab.size)]
+    Rv = np.roll(cent, -1, 0)[[0, 5, k - 1]] - cent[[0, 5, k - 1]] + 0.02 * g.standard_normal((3, d))
+    Et, Rt = _torch(E, "f32"), _torch(Rv, "f32")
+    delta = float(np.float32(0.1 * np.sqrt(2.0 * d) * 0.95 if p == 2 else 0.1 * np.sqrt(2.0) * d * 0.75))
+    out = []
+    for prune in (PRUNE_ON, PRUNE_OFF):
+        j = kgc.Join(prune=prune)
+        try:
+            got = j.join(Et, Rt, p, delta, 1 << 20)
+        finally:
+            j.close()
+        assert got["code"] == 0
+        o = np.lexsort((got["t"], got["h"], got["r"]))
+        out.append((np.stack([got["r"][o], got["h"][o], got["t"][o]], 1), got["dist"][o]))
+        if prune == PRUNE_ON:
+            assert got["stats"]["tiles_pruned"] > 0
+    assert out[0][0].shape[0] > 200
+    _same(out[0], out[1])
