@@ -269,11 +269,15 @@ def main():
         line["roofline_pruned"] = finish_roofline(main_run["roofline"], spec.name, N, R, main_run["stats"], "pruned")
     if dense is not None and dense is not main_run:
         line["dense"] = {"ms_per_step": dense["ms_per_step"], "value": N * N * R / (dense["ms_per_step"] * 1e-3),
-                         "hits": dense["count"], "phase_ms": dense["phase_ms"],
-                         "speedup_prune_on_vs_off": dense["ms_per_step"] / main_run["ms_per_step"]}
+                         "hits": dense["count"], "phase_ms": dense["phase_ms"], "kernel": dense["roofline"]["kernel"],
+                         "speedup_prune_on_vs_this_kernel": dense["ms_per_step"] / main_run["ms_per_step"]}
         assert dense["count"] == main_run["count"], "pruned and dense runs disagree on the number of hits"
     if p == 2 and d <= 282 and args.also_factorised > 0 and est_fact_s * (args.also_factorised + 1) <= 20.0:
-        fr = run(False, args.also_factorised, 1, factorised=True)
+        fr = run(False, args.also_factorised, 1)                   # what a caller gets who turns pruning off
+        if args.prune == "on":
+            line["speedup_prune_on_vs_off"] = fr["ms_per_step"] / main_run["ms_per_step"]
+        if fr["stats"]["join_variant"] != 100:
+            fr = run(False, args.also_factorised, 1, factorised=True)
         assert fr["count"] == main_run["count"], "factorised and main runs disagree on the number of hits"
         line["dense_factorised"] = {"ms_per_step": fr["ms_per_step"], "value": N * N * R / (fr["ms_per_step"] * 1e-3),
                                     "hits": fr["count"], "phase_ms": fr["phase_ms"], "roofline": fr["roofline"]}
