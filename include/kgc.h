@@ -61,7 +61,8 @@ typedef struct {
                                        blocks per CU, is the pruned default below 262,144 entities)
                                  15-18 head tile resident, tail fragments straight to registers, no barrier in the
                                        loop (15-16: d <= 282; 17: d <= 602; 18: d <= 282, one straight-line
-                                       instantiation per number of K steps, the dense default).  Dense mode, and 15
+                                       instantiation per number of K steps: 18 and 17 are the dense defaults where the
+                                       relation-factorised form is not taken, see factorised).  Dense mode, and 15
                                        also pruned, walking tile lists: the pruned default from 262,144 entities on
                                  A variant that cannot run the request (pruned mode, d) fails with KGC_E_INVALID. */
     int64_t workspace_bytes;  /* cap on the scratch that a batch of relations needs: staged operands (or, in the
@@ -71,11 +72,13 @@ typedef struct {
                                  (up to an eighth of this and 1 GiB, 16 MiB at least) */
     void*   stream;           /* hipStream_t to enqueue on; NULL = the default stream */
     float   group_radius;     /* pruning only: radius of entity groups as a multiple of delta; 0 = 2.0 */
-    int32_t range_kib;        /* dense L2 join: KiB of staged tail rows one block walks (L2 blocking); 0 = automatic */
+    int32_t range_kib;        /* dense L2 join, kernels 6-18: KiB of staged tail rows one block walks (L2 blocking);
+                                 0 = automatic */
     int32_t factorised;       /* 1: dense L2 joins with d <= 282 use the relation-factorised kernel (one MFMA tile
                                  ||h - t||^2 per tile pair, then vector arithmetic per relation) whatever their size;
                                  0: joins it is the faster form for (d <= 602, sizes: csrc/kgc.hip) use it when
-                                 tile_cfg is 0; same result set */
+                                 tile_cfg is 0: dense ones of either norm, and of pruned L2 joins the pairs among rows
+                                 without a group and joins whose rows form one group; same result set */
     int32_t reserved[3];      /* must be zero */
 } kgc_config;
 
@@ -123,7 +126,8 @@ int kgc_create(const kgc_config* cfg, kgc_handle** out);
  * a NULL pointer where data is required.  The call synchronises the stream once, to read the count.
  *
  * How the set is found: the L2 join scores tile pairs with a bf16 MFMA contraction whose result is a
- * conservative filter; the L1 join uses float32 vector arithmetic as the filter.  Every triple that
+ * conservative filter; the L1 join uses float32 vector arithmetic as the filter, or, where it is dense and large,
+ * first the L2 filter (a triple within delta in L1 is within delta in L2).  Every triple that
  * passes the filter is re-scored from the caller's E / Rv in double precision in the order
  * (E[h] + Rv[r]) - E[t], dimensions summed by a wave-level tree, and the <= delta decision is taken
  * on that double value. */

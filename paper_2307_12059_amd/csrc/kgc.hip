@@ -305,11 +305,13 @@ inline bool fact_pays(int64_t N, int64_t R) { return R >= 8 && N >= 1000 && N * 
 // Dense L1 joins that the relation-factorised kernel takes first: ||x||_2 <= ||x||_1, so every hit is among the pairs
 // within delta in L2, which its list then scores in L1.  Where the list grows past fact_list_max the L1 kernel does the
 // call instead.
-// Measured, whole calls in us, L1 kernel / this one, clusters of narrow spread: N = 1,000, R = 40, d = 100: 131 / 185;
-// 3,000, 5, 100: 137 / 111; 4,000, 8, 32: 220 / 121; 8,000, 4, 32: 355 / 201; 700, 400, 32: 311 / 263; 20,000, 18, 100:
-// 8,434 / 831.  Where the spread is so wide that the list overflows the try is lost: 4,000, 18, 100: 929 / 1,115;
-// 20,000, 18, 100: 20,318 / 24,882; 10,000, 18, 512: 8,638 / 9,856.
-inline bool fact_pays_l1(int64_t N, int64_t R, int d) { return (double)N * (double)N * (double)R * d >= 6e9; }
+// Measured, whole calls in us, L1 kernel / this one, clusters of 60 rows: N = 8,000, R = 4, d = 32: 358 / 199; 20,000, 18, 100:
+// 8,108 / 925.  The outcome depends on delta against the spread, which no size tells: where the list overflows the try is
+// lost, 998 / 1,195 (4,000, 18, 100, broad clusters), 20,469 / 25,169 (20,000, 18, 100), 19,996 / 21,705 (10,000, 18, 512).
+// Few rows under many relations lose as much as they gain (N = 700, R = 400, d = 32: 311 / 263 with many clusters, 880 /
+// 1,067 with eleven) and stay with the L1 kernel, as do joins too small to earn the fixed part back (N = 1,000, R = 40, d =
+// 100: 131 / 185).
+inline bool fact_pays_l1(int64_t N, int64_t R, int d) { return N >= 1000 && (double)N * (double)N * (double)R * d >= 6e9; }
 // Longest list of pairs a call may use: what the workspace leaves for it (an eighth, never less than the 16 MiB that the list
 // of accumulator blocks starts with), and no more than is worth scoring one by one.  L1: a listed pair costs about as much as
 // 250 pairs of the L1 kernel.
@@ -330,8 +332,9 @@ inline unsigned int fact_list_start(int64_t N, int64_t R) {
 // in a sixteenth to a sixtieth of a contraction's time.
 constexpr int kFewUnits = 3;
 // Rows without a group from which their pairs are worth the factorised kernel's fixed part.  Measured, whole calls in us, without
-// it / with it (n rows, R, d, as many rows again in groups): 1,100, 900, 64: 1,459 / 641; 1,500, 450, 64: 1,995 / 1,438;
-// 3,000, 120, 64: 2,140 / 1,373; 6,000, 30, 64: 3,241 / 1,184; 20,000, 100, 100: 20,042 / 2,483.  Below, the pairs are few.
+// it / with it (n rows, R, d, as many rows again in groups of 40, relations between any two rows): 1,100, 900, 64: 2,656 /
+// 2,670; 1,500, 450, 64: 3,012 / 2,996; 3,000, 120, 64: 1,858 / 1,407; 6,000, 30, 64: 2,623 / 1,078; 20,000, 100, 100: 19,664 /
+// 3,361; where the other tiles keep little, 1,100, 900, 64: 1,459 / 641.  Below, the pairs are few.
 inline bool part_pays(int64_t n, int64_t R) { return n >= 1024 && R >= 8 && (double)n * (double)n * (double)R >= 1e9; }
 
 // summaries of the bound test's units (P: the join's metric)

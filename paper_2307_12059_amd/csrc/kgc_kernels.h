@@ -1507,7 +1507,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1) void k_join_l2_direct(const JoinS
 // On embeddings in clusters level 1 leaves a relation open where its source cluster has a member among the head rows or
 // its target cluster among the tail columns, level 2 where eight rows hold both a member of the source cluster and a
 // neighbour of the tail.  The candidates are those of the pair-wise filter.
-// Measured (dense joins, kernel alone): N = 15,000, R = 1,345, d = 100: 19 -> 4.4 ms; N = 100,000, R = 200, d = 200:
+// Measured (dense joins, kernel alone): N = 15,000, R = 1,345, d = 100: 19 -> 4.7 ms; N = 100,000, R = 200, d = 200:
 // 86 -> 9.2 ms, of which the contraction takes about half.  With one level of 32 rows in place of levels 1 and 2 they
 // took 7.3 and 19.4 ms: on 500 clusters half of all (relation, wave) pairs then went to level 3.
 // Candidates leave through a queue of 64 entries per wave (in LDS, no atomics) to a list in memory that
@@ -1593,8 +1593,8 @@ __device__ __forceinline__ void fact_params(const DevCounters* __restrict__ cnt,
 // registers in the permuted order of dimensions that k_small_dot explains, every load of 64 dimensions issued before the
 // first is used.  The 128 x 128 vector tile kernel that did the products before left most of the chip idle on a thin product
 // (R = 2, d = 200: 60 us of latency) and needed a pass that cleared u and one that took the extremes: 204 us for the three,
-// now 94 us (N = 15,000, R = 1,345, d = 100, float32 rows; 4.0 GFLOP, 81 MB written), N = 100,000, R = 200, d = 200:
-// 284 -> 162 us.  One more workgroup per 32 relations makes their thresholds.
+// now 87 us (N = 15,000, R = 1,345, d = 100, float32 rows; 4.0 GFLOP, 81 MB written), N = 100,000, R = 200, d = 200:
+// 284 -> 136 us.  One more workgroup per 32 relations makes their thresholds.
 template <bool BF16, bool VEC>
 __global__ __launch_bounds__(256) void k_fact_dot(const void* __restrict__ Rv, const void* __restrict__ E,
                                                   const int32_t* __restrict__ slot_ent, int64_t Nslots, int r0, int RB, int RBp,

@@ -79,3 +79,15 @@ def test_dense_takes_the_factorised_kernel_first(N, R, d, sigma, variant, dtype)
     r, h, t = want[picks, 0], want[picks, 1], want[picks, 2]
     ref = np.abs((E[h].astype(np.float64) + Rv[r]) - E[t]).sum(1)
     np.testing.assert_allclose(want[picks, 3].view(np.float32), ref, rtol=2.0 ** -23)      # a rounding to float32
+
+
+# the line below which few rows under many relations stay with the L1 kernel
+@pytest.mark.parametrize("N,variant", [(999, 0), (1000, 100)])
+def test_few_rows_stay_with_the_l1_kernel(N, variant):
+    E, Rv = _case(N, N, 400, 32, 120, 0.05, "f32")
+    delta = float(np.float32(0.05 * np.sqrt(2.0) * 0.798 * 32))
+    got = _join(E, Rv, delta, 1 << 22, "f32", prune=PRUNE_OFF)
+    want = _join(E, Rv, delta, 1 << 22, "f32", prune=PRUNE_OFF, tile_cfg=17)
+    assert got["stats"]["join_variant"] == variant and want["stats"]["join_variant"] == 0
+    assert want["count"] > 1000
+    np.testing.assert_array_equal(_records(got), _records(want))
