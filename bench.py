@@ -154,12 +154,12 @@ def main():
     N, R, d, p = spec.N, spec.R, spec.d, spec.p
     E, Rv, cap, out = resident(wl)
 
-    def run(prune, steps, warmup, factorised=False, wl=wl, E=E, Rv=Rv, cap=cap, out=out, matrix=False):
+    def run(prune, steps, warmup, factorised=False, wl=wl, E=E, Rv=Rv, cap=cap, out=out, matrix=False, by_number=0):
         spec = wl.spec
         N, R, d, p = spec.N, spec.R, spec.d, spec.p
         # matrix: the kernel that contracts every pair of every relation on the matrix pipes, by its tile number (left
         # alone, a dense L2 join of this size takes the relation-factorised kernel)
-        tile = args.tile or (18 if matrix and p == 2 and d <= 282 else 0)
+        tile = args.tile or by_number or (18 if matrix and p == 2 and d <= 282 else 0)
         j = kgc.Join(dtype=spec.storage, prune=kgc.KGC_PRUNE_ON if prune else kgc.KGC_PRUNE_OFF, tile_cfg=tile,
                      factorised=factorised)
         res = None
@@ -191,7 +191,8 @@ def main():
                     "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s"}
         else:
             roof = {"bound": "alu", "achieved": work / (ms_join * 1e-3) / 1e12 if ms_join > 0 else 0.0,
-                    "peak": PEAK_VALU_TLANEOPS, "unit": "Tlane-op/s"}
+                    "peak": PEAK_VALU_TLANEOPS, "unit": "Tlane-op/s",
+                    "note": "counted as if every dimension of every pair were summed; tiles end earlier"}
         roof["frac"] = roof["achieved"] / roof["peak"]
         roof["traffic"] = None      # filled below for configurations with a committed counter measurement
         v = st["join_variant"]
@@ -219,6 +220,12 @@ def main():
     est_fact_s = N * N * R / 2.0e13
     want_dense = args.also_dense > 0 and est_dense_s * (args.also_dense + 1) <= 20.0
     dense = main_run if args.prune == "off" else (run(False, args.also_dense, 1, matrix=True) if want_dense else None)
+    # Part of a pruned L2 join may go to the relation-factorised kernel, which does not contract each relation: the rate of
+    # the kernel over tile lists is taken in steps that ask for it by its number and leave it every tile.
+    rated = main_run
+    if args.prune == "on" and p == 2 and main_run["stats"]["join_variant"] != 100:
+        rated = run(True, 2, 1, by_number=main_run["stats"]["join_variant"])
+        assert rated["count"] == main_run["count"], "the kernel by its number and the main run disagree on the number of hits"
     calib = calibrate(args.calibration_ms) if (p == 2 and args.calibration_ms > 0) else None
 
     def finish_roofline(r, wl_name, n_rows, n_rel, stats, mode):
@@ -235,9 +242,10 @@ def main():
                 r["frac_calibrated"] = r["achieved"] / calib["mfma_only"]
         return r
 
-    roof = finish_roofline((dense or main_run)["roofline"], spec.name, N, R, (dense or main_run)["stats"],
+    roof = finish_roofline((dense or rated)["roofline"], spec.name, N, R, (dense or rated)["stats"],
                            "dense" if dense is not None else "pruned")
-    roof["measured_in"] = "dense (prune off) steps of this invocation" if dense is not None else "the timed (pruned) steps"
+    in_pruned = "the timed (pruned) steps" if rated is main_run else "pruned steps that ask for this kernel by number"
+    roof["measured_in"] = "dense (prune off) steps of this invocation" if dense is not None else in_pruned
     line = {
         "metric": "triple-scores/sec (effective N\u00b2R) + MFMA util %",
         "value": N * N * R / (main_run["ms_per_step"] * 1e-3),
@@ -265,8 +273,9 @@ def main():
     if calib is not None:
         line["calibration"] = calib
     if args.prune == "on":
-        # the timed (pruned) steps' own join kernel: same accounting, on the pairs of the surviving tiles
-        line["roofline_pruned"] = finish_roofline(main_run["roofline"], spec.name, N, R, main_run["stats"], "pruned")
+        # the pruned steps' join kernel: same accounting, on the pairs of the surviving tiles
+        line["roofline_pruned"] = finish_roofline(rated["roofline"], spec.name, N, R, rated["stats"], "pruned")
+        line["roofline_pruned"]["measured_in"] = in_pruned
     if dense is not None and dense is not main_run:
         line["dense"] = {"ms_per_step": dense["ms_per_step"], "value": N * N * R / (dense["ms_per_step"] * 1e-3),
                          "hits": dense["count"], "phase_ms": dense["phase_ms"], "kernel": dense["roofline"]["kernel"],

@@ -1555,7 +1555,8 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
   }
   const int nbatch = (int)((Rn + RBmax - 1) / RBmax);
   const bool timed = !hd->static_mode;          // per-batch event pairs (creating events allocates)
-  while (timed && (int)hd->join_ev.size() < 2 * nbatch) {
+  const int part_ev = 2 * nbatch;               // ... and one around the part
+  while (timed && (int)hd->join_ev.size() < part_ev + (part_n ? 2 : 0)) {
     hipEvent_t e;
     KGC_HIP(hd, hipEventCreate(&e));
     hd->join_ev.push_back(e);
@@ -1624,6 +1625,7 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
     fj.u = (float*)(at + 2 * part_op); fj.umin = fj.u + fact_rows(RBf) * part_n; fj.limr = (float*)hd->limr.p;
     fj.list = (ExactEntry*)hd->flist.p; fj.list_cap = fact_cap; fj.give_up = fact_most;
     // (the running maxima of the norms, shared with the other kernels' operands, only widen the thresholds)
+    if (timed) KGC_HIP(hd, hipEventRecord(hd->join_ev[part_ev], st));
     launch_fact_stage(st, fj, (uint16_t*)at, (uint16_t*)(at + part_op), cnt);
     RecheckCtx cxf = cx;
     cxf.slot_ent = cxf.slot_ent_t = fj.slot_ent;
@@ -1633,6 +1635,7 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
       if ((rc = launch_fact_join(hd, st, fj, cnt, cxf)) != KGC_OK) return rc;
       if (r0 + RBf < r_end) k_fill_u32<<<1, 64, 0, st>>>((uint32_t*)&cnt->n_fact, 2, 0u);      // an empty list for the next batch
     }
+    if (timed) KGC_HIP(hd, hipEventRecord(hd->join_ev[part_ev + 1], st));
   }
   const bool bitmap_ready = reuse && part_n == 0 && pr.bitmap_valid && pr.bm_r0 == r_begin && pr.bm_r1 == r_end && nbatch == 1;
   pr.E = E; pr.Rv = Rvecs; pr.N = N; pr.d = d; pr.p = p; pr.dtype = dtype; pr.prune = (int)prune; pr.tile_id = tile_id;
@@ -1928,15 +1931,16 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
   s.relation_batches = nbatch;
   s.join_variant = fact ? 100 : p == 2 ? tile_id + 1 : 0;
   s.exact_blocks = (int32_t)std::min<unsigned long long>(hd->host_counters->exact_total, 2147483647ull);
-  // phase times from the events: [ev0 grouping ev3 | summaries + B staging ev1 | per batch: bound test + A staging | join]
+  // phase times from the events: [ev0 grouping ev3 | summaries + B staging ev1 | the part, a join | per batch: bound test + A staging | join]
   float ms = 0.f, ms_group = 0.f, ms_between = 0.f;
   (void)hipEventElapsedTime(&s.ms_total, hd->ev[0], hd->ev[2]);
   (void)hipEventElapsedTime(&ms_group, hd->ev[0], hd->ev[3]);
   (void)hipEventElapsedTime(&s.ms_precompute, hd->ev[3], hd->ev[1]);
   if (!timed && hipEventElapsedTime(&ms, hd->ev[1], hd->ev[2]) == hipSuccess) s.ms_join = ms;   // staging of the batches included
+  if (timed && part_n && hipEventElapsedTime(&ms, hd->join_ev[part_ev], hd->join_ev[part_ev + 1]) == hipSuccess) s.ms_join += ms;
   for (int i = 0; timed && i < nbatch; ++i) {
     if (hipEventElapsedTime(&ms, hd->join_ev[2 * i], hd->join_ev[2 * i + 1]) == hipSuccess) s.ms_join += ms;
-    hipEvent_t prev = i == 0 ? hd->ev[1] : hd->join_ev[2 * i - 1];
+    hipEvent_t prev = i > 0 ? hd->join_ev[2 * i - 1] : part_n ? hd->join_ev[part_ev + 1] : hd->ev[1];
     if (hipEventElapsedTime(&ms, prev, hd->join_ev[2 * i]) == hipSuccess) ms_between += ms;
   }
   // the per-batch gap holds the bound test (pruning) and the A staging (precompute); it is booked under pruning
