@@ -148,7 +148,8 @@ __global__ __launch_bounds__(1024) void k_group_layout(GroupState* gs, const int
   placed_part[tid] = placed;
   big_part[tid] = nbig;
   __syncthreads();
-  if (most > 0) atomicMax(&largest, most);      // (read after the scan's barriers)
+  for (int off = 32; off > 0; off >>= 1) most = max(most, __shfl_xor(most, off, 64));
+  if ((tid & 63) == 0) atomicMax(&largest, most);      // (one per wave: 1,024 on one word took 3 us; read after the scan's barriers)
   for (int off = 1; off < 1024; off <<= 1) {          // inclusive scan, Hillis-Steele
     const int v = tid >= off ? part[tid - off] : 0;
     const int w = tid >= off ? placed_part[tid - off] : 0;
