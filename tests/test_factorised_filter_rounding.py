@@ -1,4 +1,4 @@
-"""The float32 arithmetic of the relation-factorised filter (k_stage_operands, k_fact_dot, k_fact_params and level 3 of
+"""The float32 arithmetic of the relation-factorised filter (k_stage_operands, k_fact_dot with fact_params, and level 3 of
 k_join_l2_fact in csrc/kgc_kernels.h) against the definition in double.
 
 The filter keeps (h, r, t) when G + 2 r.h~ <= limr + 2 r.t~, with rows rounded to bfloat16, G = ||h~ - t~||^2 less the rows'
