@@ -82,6 +82,7 @@ struct kgc_handle {
   unsigned int fcap = 0;                       // entries of flist that an earlier call needed (see fact_list_start)
   unsigned int fcap_start = 0;                 // > 0: ... and to start with (tests)
   size_t flist_limit = 0;                      // > 0: bytes past which flist counts as not to be had (tests)
+  int order_rows = 0;                          // > 0, < 0: dense factorised joins put their rows in order always, never (tests)
   int list_seg_cap = 0;                        // > 0: the pruned barrier-free kernel keeps at most this many entries of a row's tile list in the LDS (tests)
   unsigned pairs_grid = 512;                   // workgroups of the tile-at-a-time kernel: two per compute unit (tests set fewer, so that a workgroup walks several batches of tiles)
   DevBuf zero_row, cent_a, rad_a;              // kgc_join_ab: the zero relation row; micro-tile summaries of A[r]
@@ -259,6 +260,17 @@ void launch_small_dot(hipStream_t st, const void* X, int dtype, int64_t n_rows, 
   hipLaunchKernelGGL(kern, dim3((unsigned)((n_cols + 31) / 32), (unsigned)((n_rows + 31) / 32), 1), dim3(64), 0, st,
                      X, n_rows, Y, n_cols, d, out);
 }
+
+// Dense factorised joins whose rows are put in order first (order_rows): what the order saves is bounds that sets of
+// strangers leave open, which grow with N^2 R, and what it costs is four launches and a contraction with an eighth of the rows
+// (4,096 at most), about d N min(N, 32,768).  Measured, whole calls in us, caller's order (random) / put in order, float32
+// unless noted: N = 2,000, R = 8, d = 32: 97 / 100; 3,000, 16, 100: 113 / 118; 2,000, 30, 100: 113 / 116; 1,000, 64, 32: 106 /
+// 107; 6,000, 16, 100: 144 / 128; 3,000, 100, 64: 212 / 145; 8,000, 400, 256: 586 / 239; 15,000, 1,345, 100: 4,843 / 589; 50,000,
+// 200, 64: 2,854 / 961; 100,000, 200, 200 (bf16): 9,175 / 4,675; L1 40,000, 18, 100: 2,849 / 825.  Where d is long against the
+// relations the contraction decides: 20,000, 8, 512: 723 / 783; 50,000, 8, 512 (bf16): 3,058 / 3,333; 20,000, 32, 512: 796 /
+// 780; 10,000, 16, 512: 326 / 324; 10,000, 8, 256: 207 / 200.  With a quarter, an eighth and a sixteenth of
+// the rows as pivots 15,000, 1,345, 100 takes 688 / 589 / 658 us, L1 12,000, 100, 32 in groups of a dozen 321 / 310 / 386.
+inline bool order_pays(int64_t N, int64_t R, int d) { return N >= 1000 && N * R >= 60000 && R * 32 >= d; }
 
 // One relation batch of the relation-factorised join over a run of slots.
 struct FactJob {
@@ -451,6 +463,7 @@ int kgc_create(const kgc_config* cfg, kgc_handle** out) {
   // the first length of the exact stage's block list (it grows by itself; tests set it small to see it grow)
   if (const char* e = std::getenv("KGC_EXACT_LIST_CAP")) h->xcap = h->fcap_start = (unsigned int)std::max(1L, std::atol(e));
   if (const char* e = std::getenv("KGC_PAIR_LIST_LIMIT")) h->flist_limit = (size_t)std::max(1L, std::atol(e));
+  if (const char* e = std::getenv("KGC_ROW_ORDER")) h->order_rows = std::atol(e) > 0 ? 1 : -1;
   if (const char* e = std::getenv("KGC_TILE_LIST_SEGMENT")) h->list_seg_cap = (int)std::max(1L, std::atol(e));
   if (const char* e = std::getenv("KGC_PAIRS_GRID")) h->pairs_grid = (unsigned)std::min(512L, std::max(1L, std::atol(e)));
   if (hipHostMalloc((void**)&h->host_counters, sizeof(DevCounters), hipHostMallocDefault) != hipSuccess) {
@@ -958,6 +971,35 @@ int group_rows(kgc_handle* hd, const void* E, int64_t N, int32_t d, int32_t p, f
   return KGC_OK;
 }
 
+// Row order of a dense relation-factorised join (kgc_prune.h): the rows' and the pivots' operands lie where those of the
+// join are staged afterwards (`rows`, `pivots`: KS slices of Nslots and of at most kOrderPivots rows).
+int order_rows(kgc_handle* hd, const void* E, int64_t N, int32_t d, int KS, int k16, int64_t Nslots, uint16_t* rows, uint16_t* pivots) {
+  int rc;
+  hipStream_t st = hd->stream;
+  const int P = (int)std::min<int64_t>(kOrderPivots, std::max<int64_t>(256, N / 8 / 256 * 256));
+  if ((rc = ensure(hd, hd->piv_ent, kPivotsPerRound * 4)) || (rc = ensure(hd, hd->best, N * 8))) return rc;
+  int32_t* piv = (int32_t*)hd->piv_ent.p;
+  int32_t* near_all = (int32_t*)hd->best.p;
+  int32_t* near_first = near_all + N;
+  k_order_begin<<<grid_for(N, 256), 256, 0, st>>>(N, P, piv, near_all, near_first);
+  const size_t stage_lds = (size_t)kStageRows * (KS * kSliceK + 8) * 2;
+  k_order_stage<<<dim3((unsigned)grid_for(Nslots / kStageRows, 1), 2, 1), 256, stage_lds, st>>>(E, hd->cfg.dtype, d, N, Nslots, KS, piv, P,
+                                                                                             rows, pivots);
+  const int bm = KS <= kDirectMaxKS ? 256 : 128;
+  void (*kern)(const JoinStreamArgs) = bm == 256 ? k_join_l2_direct<256, 2, 4, kEpiNear> : k_join_l2_direct<128, 1, 8, kEpiNear>;
+  const size_t dyn_lds = (size_t)KS * bm * kSliceK * 2;
+  KGC_HIP(hd, hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn_lds));
+  JoinStreamArgs sa{};
+  sa.A = rows; sa.B = pivots; sa.Nslots = Nslots; sa.KS = KS; sa.k16 = k16; sa.nH = (int)(Nslots / bm); sa.nT = P / 256; sa.RB = 1;
+  sa.tail_slots = P; sa.near_all = near_all; sa.near_first = near_first; sa.n_heads = N;
+  // the pivot tiles are dealt to so many blocks per head tile as fill the chip
+  const int64_t z = std::max<int64_t>(1, std::min<int64_t>(sa.nT, (512 + sa.nH - 1) / sa.nH));
+  hipLaunchKernelGGL(kern, dim3((unsigned)sa.nH, 1, (unsigned)z), dim3(512), dyn_lds, st, sa);
+  k_order_sort<<<1, 1024, 0, st>>>(near_all, near_first, piv, N, Nslots, P, (int32_t*)hd->slot_ent.p);
+  KGC_HIP(hd, hipGetLastError());
+  return KGC_OK;
+}
+
 // kgc_top1 / kgc_topk switch the handle to "no self pairs" around their inner joins; this puts it back on every way out
 struct NoSelfScope {
   kgc_handle* h;
@@ -1407,6 +1449,7 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
   // ... and the part of a pruned L2 join that the bound test can do nothing for
   const bool part_ok = p == 2 && prune && !win && !hd->static_mode && !hd->no_fact && hd->cfg.tile_cfg == 0 && hd->cfg.factorised == 0 &&
                        KS <= kDirectHalfMaxKS && delta >= 0.f && delta < 1e18f;
+  const bool ordered = fact && (hd->order_rows > 0 || (hd->order_rows == 0 && order_pays(N, Rn, d))) && N >= 256;
   const bool l2_ops = p == 2 || fact;          // staged operands of the matrix pipes
   const int64_t ws = hd->ws_override > 0 ? hd->ws_override
                                            : hd->cfg.workspace_bytes > 0 ? hd->cfg.workspace_bytes : kDefaultWorkspace;
@@ -1482,7 +1525,7 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
     }
   } else {
     if ((rc = ensure(hd, hd->slot_ent, Nslots * 4))) return rc;
-    k_identity_slots<<<grid_for(Nslots, 256), 256, 0, st>>>((int32_t*)hd->slot_ent.p, N, Nslots);
+    if (!ordered) k_identity_slots<<<grid_for(Nslots, 256), 256, 0, st>>>((int32_t*)hd->slot_ent.p, N, Nslots);
   }
   const int32_t* slot_ent = (const int32_t*)hd->slot_ent.p;
   const int nH = (int)(Nslots / BM), nT = (int)(Nslots / BN);
@@ -1568,6 +1611,11 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
   cx.hit_counter = &cnt->hits; cx.cand_counter = &cnt->candidates;
   set_alignment(cx);
 
+  if (ordered) {
+    if ((rc = ensure(hd, hd->asg_b, (size_t)KS * kPivotsPerRound * kSliceK * 2)) ||
+        (rc = order_rows(hd, E, N, d, KS, k16, Nslots, (uint16_t*)hd->opA.p, (uint16_t*)hd->asg_b.p)) != KGC_OK)
+      return rc;
+  }
   KGC_HIP(hd, hipEventRecord(hd->ev[3], st));     // end of grouping
   if (prune && !reuse) {
     if (p == 2) {

@@ -562,11 +562,13 @@ struct JoinStreamArgs {
   unsigned long long* best;           // kEpiAssignMin: per entity, min over the pivots within reach of (pivot position << 32);
                                       // kEpiMinDist: one word, min over all scored pairs of the float bits of the squared distance
   const int32_t* group_of;            // entities that already belong to a group (>= 0) are left alone
+  int32_t* near_all; int32_t* near_first;   // kEpiNear: per entity, min over all pivots / those of the first tile of (distance bits, position)
   int64_t n_heads;                    // entities (head slots past it are padding)
   // k_join_l2_direct over tile lists, optional: candidates leave to a list that k_exact_pairs scores (NULL: the owning wave scores them)
   ExactEntry* plist; unsigned long long* pcount; unsigned int pcap;
 };
-enum { kEpiJoin = 0, kEpiAssignMin = 1, kEpiMinDist = 2 };
+enum { kEpiJoin = 0, kEpiAssignMin = 1, kEpiMinDist = 2, kEpiNear = 3 };
+constexpr int kNearBits = 12;              // kEpiNear: low bits of a key that hold the pivot's position (kOrderPivots of them at most)
 
 // A 32 x 32 accumulator block with candidates, at the end of a tile: listed for k_exact_blocks.  A full list drops
 // the entry but still counts it: the host then sees how long the list has to be and runs the join again.
@@ -1354,8 +1356,16 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1) void k_join_l2_direct(const JoinS
   __builtin_bit_cast(bf16x8_t, u32x4_t{Q[8 * (J) + 4 * (STEP)], Q[8 * (J) + 4 * (STEP) + 1],      \
                                        Q[8 * (J) + 4 * (STEP) + 2], Q[8 * (J) + 4 * (STEP) + 3]})
 
+  // kEpiNear takes the transpose: a lane then holds one head row (column of the accumulator) and many pivots, whose
+  // minimum needs no exchange between lanes
+#define KGC_MFMA(FA, FB, C)                                                                       \
+  (EPI == kEpiNear ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(FB, FA, C, 0, 0, 0) : __builtin_amdgcn_mfma_f32_32x32x16_bf16(FA, FB, C, 0, 0, 0))
   const float thr = a.prm ? a.prm->thr : a.thr_value;
   float run_min = 3e38f;                                   // kEpiMinDist
+  int near[EPI == kEpiNear ? TM : 1];                      // kEpiNear: smallest key of this lane's head row in each block of 32
+  if constexpr (EPI == kEpiNear)
+#pragma unroll
+    for (int i = 0; i < TM; ++i) near[i] = 0x7fffffff;
   const int last_two = (a.k16 - (KS - 1) * 2) >= 2;
   int ck = 0, ct = 0;
   f32x16_t acc[TM][TN];
@@ -1366,6 +1376,15 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1) void k_join_l2_direct(const JoinS
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 
+  // kEpiNear: the keys so far to memory (the two halves of the wave hold pivots of the same head rows)
+#define KGC_NEAR_OUT(OUT)                                                                         \
+  do {                                                                                            \
+    _Pragma("unroll") for (int i = 0; i < TM; ++i) {                                              \
+      const int key = min(near[i], __shfl_xor(near[i], 32, 64));                                  \
+      const int64_t e = (int64_t)tH * BM + wm * WTM + i * 32 + (lane & 31);                       \
+      if (lane < 32 && e < a.n_heads) atomicMin(&(OUT)[e], key);                                  \
+    }                                                                                             \
+  } while (0)
   // One slice: head fragments from LDS, tail fragments from register set Q; at the end of a tile the filter
   // on the squared distance and the rare exact path.  MFMA 32x32 accumulator layout: register v of lane l
   // holds row 8*(v/4) + 4*(l/32) + (v%4), column l%32.
@@ -1380,24 +1399,36 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1) void k_join_l2_direct(const JoinS
       const f32x16_t zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}; \
       _Pragma("unroll") for (int i = 0; i < TM; ++i)                                              \
         _Pragma("unroll") for (int j = 0; j < TN; ++j)                                            \
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], KGC_FRAG(Q, j, 0), zero16, 0, 0, 0); \
+          acc[i][j] = KGC_MFMA(fa[i], KGC_FRAG(Q, j, 0), zero16); \
     } else {                                                                                      \
       _Pragma("unroll") for (int i = 0; i < TM; ++i)                                              \
         _Pragma("unroll") for (int j = 0; j < TN; ++j)                                            \
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], KGC_FRAG(Q, j, 0), acc[i][j], 0, 0, 0); \
+          acc[i][j] = KGC_MFMA(fa[i], KGC_FRAG(Q, j, 0), acc[i][j]); \
     }                                                                                             \
     if (two) {                                                                                    \
       _Pragma("unroll") for (int i = 0; i < TM; ++i) fa[i] = *(const bf16x8_t*)(Ac + i * 32 * kSliceK + rd_step); \
       _Pragma("unroll") for (int i = 0; i < TM; ++i)                                              \
         _Pragma("unroll") for (int j = 0; j < TN; ++j)                                            \
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], KGC_FRAG(Q, j, 1), acc[i][j], 0, 0, 0); \
+          acc[i][j] = KGC_MFMA(fa[i], KGC_FRAG(Q, j, 1), acc[i][j]); \
     }                                                                                             \
     if (last_slice) {                                                                             \
+      if constexpr (EPI == kEpiNear) {                                                            \
+        const int where = (t_begin + ct) * BN + wn * WTN + 4 * (lane >> 5);                       \
+        _Pragma("unroll") for (int i = 0; i < TM; ++i) {                                          \
+          int key = 0x7fffffff;                                                                   \
+          _Pragma("unroll") for (int j = 0; j < TN; ++j)                                          \
+            _Pragma("unroll") for (int v = 0; v < 16; ++v)                                        \
+              key = min(key, (__float_as_int(acc[i][j][v]) & ~((1 << kNearBits) - 1)) | (j * 32 + 8 * (v >> 2) + (v & 3))); \
+          near[i] = min(near[i], key | where);                                                    \
+        }                                                                                         \
+        if (t_begin + ct == 0) KGC_NEAR_OUT(a.near_first);                                        \
+      }                                                                                           \
       float mn = acc[0][0][0];                                                                    \
       _Pragma("unroll") for (int i = 0; i < TM; ++i)                                              \
         _Pragma("unroll") for (int j = 0; j < TN; ++j)                                            \
           _Pragma("unroll") for (int v = 0; v < 16; ++v) mn = fminf(mn, acc[i][j][v]);            \
-      if (EPI == kEpiMinDist) {                                                                   \
+      if (EPI == kEpiNear) {                                                                      \
+      } else if (EPI == kEpiMinDist) {                                                            \
         run_min = fminf(run_min, mn);        /* only the smallest squared distance is wanted */    \
       } else if (__builtin_amdgcn_ballot_w64(mn <= thr) != 0ull) {                                \
         const int64_t hbase = (int64_t)tH * BM + wm * WTM;                                        \
@@ -1475,8 +1506,11 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1) void k_join_l2_direct(const JoinS
     KGC_GLOAD(q1);
     if (i + 2 < total) KGC_COMPUTE(q2);
   }
+  if constexpr (EPI == kEpiNear) KGC_NEAR_OUT(a.near_all);
 #undef KGC_GLOAD
 #undef KGC_FRAG
+#undef KGC_MFMA
+#undef KGC_NEAR_OUT
 #undef KGC_COMPUTE
   if (!LISTED && EPI == kEpiMinDist) {                     // (not listed: a single pass)
     for (int off = 32; off > 0; off >>= 1) run_min = fminf(run_min, __shfl_xor(run_min, off, 64));

@@ -199,6 +199,101 @@ __global__ void k_scatter_slots(GroupState* gs, const int32_t* group_of, const i
   if (i < N) slot_ent[off >= 0 ? off + in_group : gs->tail_base + in_tail] = (int32_t)i;
 }
 
+// ---------------------------------------------------------------------------------------------
+// Row order of the relation-factorised join: rows that lie close together become neighbours, so that the sets of pairs its
+// bounds are taken over (a wave's 128 x 64 pairs, eight rows x a column) hold few clusters.  Every row goes to the nearest of
+// P evenly spread rows ("pivots", an eighth of the rows, 256 to 4,096), and the pivots' runs lie side by side where the
+// pivots share the nearest of the first 256 pivots, which are evenly spread too: a cluster that several pivots cut into
+// runs stays together.  One contraction of all rows with the pivots (k_join_l2_direct<.., kEpiNear>) finds both; nothing is
+// read back and no slot is padding, so the order costs four launches.  Any order is a valid one: which pivot a row ends
+// up with does not touch the result.  Measured at N = 15,000, d = 100 (1,792 pivots): begin 3, operands 6, contraction 16, sort 17 us,
+// and the join kernel 4,670 -> 358 us with R = 1,345 (two thirds of its relations had been open to level 2); N = 100,000, d = 200:
+// 318 us in all, join kernel 9,010 -> 4,240 us.
+constexpr int kOrderPivots = 4096;
+static_assert(kOrderPivots <= 1 << kNearBits, "a pivot's position must fit the low bits of a key");
+// Position i of the pivot list: tile i / 256 takes every m-th of the P evenly spread rows (m tiles).
+__global__ void k_order_begin(int64_t N, int P, int32_t* __restrict__ piv_ent, int32_t* __restrict__ near_all, int32_t* __restrict__ near_first) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < P) {
+    const int m = P / 256;
+    piv_ent[i] = (int32_t)((int64_t)((i % 256) * m + i / 256) * N / P);
+  }
+  if (i < N) near_all[i] = near_first[i] = 0x7fffffff;
+}
+// the operands of that contraction in one launch: blockIdx.y = 0 all rows in the caller's order, 1 the pivots
+__global__ __launch_bounds__(256, 4) void k_order_stage(const void* __restrict__ E, int dtype, int d, int64_t N, int64_t Npad, int KS,
+                                                        const int32_t* __restrict__ piv_ent, int P, uint16_t* __restrict__ rows,
+                                                        uint16_t* __restrict__ pivots) {
+  if (blockIdx.y == 0)
+    stage_operands<true>(E, nullptr, dtype, d, 0, 1, nullptr, Npad, KS, rows, nullptr, nullptr, nullptr, nullptr, 0, kStageRows, 0, nullptr,
+                         -1.f, N);
+  else
+    stage_operands<false>(E, nullptr, dtype, d, 0, 1, piv_ent, P, KS, pivots, nullptr, nullptr, nullptr, nullptr, 0, kStageRows, 0, nullptr,
+                          -1.f, 0);
+}
+// Counting sort of the rows by pivot, one workgroup: sizes of the runs, offsets (the pivots of one of the first 256 side by
+// side), places.
+__global__ __launch_bounds__(1024) void k_order_sort(const int32_t* __restrict__ near_all, const int32_t* __restrict__ near_first,
+                                                     const int32_t* __restrict__ piv_ent, int64_t N, int64_t Nslots, int P,
+                                                     int32_t* __restrict__ slot_ent) {
+  __shared__ int run[kOrderPivots];
+  __shared__ int area[256], wave_sum[4];
+  const int tid = threadIdx.x;
+  for (int p = tid; p < P; p += 1024) run[p] = 0;
+  if (tid < 256) area[tid] = 0;
+  __syncthreads();
+  constexpr int kU = 8;                                    // rows a thread has in flight
+  for (int64_t e0 = tid; e0 < N; e0 += 1024 * kU) {
+    int p[kU];
+#pragma unroll
+    for (int q = 0; q < kU; ++q) p[q] = e0 + 1024 * q < N ? near_all[e0 + 1024 * q] & ((1 << kNearBits) - 1) : -1;
+#pragma unroll
+    for (int q = 0; q < kU; ++q)
+      if (p[q] >= 0) atomicAdd(&run[p[q]], 1);
+  }
+  __syncthreads();
+  int of[kOrderPivots / 1024], size[kOrderPivots / 1024], before[kOrderPivots / 1024];
+#pragma unroll
+  for (int q = 0; q < kOrderPivots / 1024; ++q) {
+    const int p = tid + 1024 * q;
+    of[q] = p < P ? near_first[piv_ent[p]] & 255 : 0;
+    size[q] = p < P ? run[p] : 0;
+  }
+#pragma unroll
+  for (int q = 0; q < kOrderPivots / 1024; ++q) before[q] = size[q] ? atomicAdd(&area[of[q]], size[q]) : 0;
+  __syncthreads();
+  // exclusive scan of the 256 areas by the first four waves
+  int mine = 0, sum = 0;
+  if (tid < 256) {
+    mine = sum = area[tid];
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const int v = __shfl_up(sum, off, 64);
+      if ((tid & 63) >= off) sum += v;
+    }
+    if ((tid & 63) == 63) wave_sum[tid >> 6] = sum;
+  }
+  __syncthreads();
+  if (tid < 256) {
+    for (int w = 0; w < (tid >> 6); ++w) sum += wave_sum[w];
+    area[tid] = sum - mine;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < kOrderPivots / 1024; ++q)
+    if (tid + 1024 * q < P) run[tid + 1024 * q] = area[of[q]] + before[q];
+  __syncthreads();
+  for (int64_t e0 = tid; e0 < N; e0 += 1024 * kU) {
+    int p[kU];
+#pragma unroll
+    for (int q = 0; q < kU; ++q) p[q] = e0 + 1024 * q < N ? near_all[e0 + 1024 * q] & ((1 << kNearBits) - 1) : -1;
+#pragma unroll
+    for (int q = 0; q < kU; ++q)
+      if (p[q] >= 0) slot_ent[atomicAdd(&run[p[q]], 1)] = (int32_t)(e0 + 1024 * q);
+  }
+  for (int64_t s = N + tid; s < Nslots; s += 1024) slot_ent[s] = -1;
+}
+
 // One wave per micro-tile: centre = mean of its rows, radius = max distance of a row to the centre (in
 // the join's metric), widened for float32 rounding.  An empty micro-tile gets radius -1.
 // The rows are read once, 64 dimensions at a time with the lanes on consecutive dimensions: the 32 loads of a chunk

@@ -147,3 +147,30 @@ def test_candidates_do_not_grow_with_the_longest_row_or_relation(N, R, d, delta,
     assert st["join_variant"] == 100 and st2["join_variant"] == 18
     np.testing.assert_array_equal(got, want)
     assert st["candidates"] <= 2 * st2["candidates"] + N // 4, (st["candidates"], st2["candidates"])
+
+
+# Row order: one tile of pivots and one row more than it, two tiles, the most (sixteen); both tile shapes and norms; rows
+# that the caller has in order already, or backwards; one relation
+@pytest.mark.parametrize("N,R,d,p,dtype,rows", [(256, 9, 20, 2, "f32", "random"), (257, 3, 100, 2, "bf16", "random"),
+                                                (4100, 7, 33, 2, "f32", "sorted"), (4095, 6, 64, 1, "f32", "random"),
+                                                (33000, 1, 40, 2, "bf16", "random"), (9001, 8, 290, 2, "bf16", "backwards")])
+def test_row_order_leaves_the_result_alone(N, R, d, p, dtype, rows, monkeypatch):
+    import paper_2307_12059_amd as kgc
+    import torch
+    E, Rv = _case(N + d, N, R, d, 9 if N < 1000 else 200, 0.1, dtype)
+    if rows != "random":
+        E = E[torch.argsort(E[:, 0].float(), descending=rows == "backwards")].contiguous()
+    delta = float(np.float32(0.1 * (np.sqrt(2.0 * d) * 0.95 if p == 2 else 1.08 * d)))
+    out = []
+    for order in ("0", "1"):
+        monkeypatch.setenv("KGC_ROW_ORDER", order)
+        j = kgc.Join(dtype=dtype, prune=PRUNE_OFF, factorised=p == 2 and d <= 282)
+        try:
+            got = j.join(E, Rv, p, delta, 1 << 23)
+        finally:
+            j.close()
+        assert got["code"] == 0 and got["stats"]["join_variant"] == 100
+        o = np.lexsort((got["t"], got["h"], got["r"]))
+        out.append(np.stack([got["r"][o], got["h"][o], got["t"][o], got["dist"][o].view(np.int32)], 1))
+    assert out[0].shape[0] > 100
+    np.testing.assert_array_equal(out[0], out[1])
