@@ -404,8 +404,9 @@ void launch_fact_products(hipStream_t st, const FactJob& j, const DevCounters* c
 // the kernel and the scores of the pairs it lists (cx counts its slots from the job's first)
 int launch_fact_join(kgc_handle* hd, hipStream_t st, const FactJob& j, DevCounters* cnt, const RecheckCtx& cx) {
   const int RBp = (int)fact_rows(j.RB), KS = (j.d + kNormCols + kSliceK - 1) / kSliceK;
-  const TileCfg tc = kL2Tiles[KS <= kDirectMaxKS ? kDirectL2Tile : kDirectHalfL2Tile];
-  const int nH = (int)(j.Nslots / tc.bm), nT = (int)(j.Nslots / tc.bn);
+  const bool wide = KS > kDirectMaxKS;                     // tiles of 128 x 512 instead of 256 x 256
+  const int bm = wide ? 128 : 256, bn = wide ? 512 : 256;
+  const int nH = (int)(j.Nslots / bm), nT = (int)((j.Nslots + bn - 1) / bn);
   JoinFactArgs fa{};
   fa.A = j.A; fa.B = j.B; fa.u = j.u; fa.limr = j.limr; fa.umin8 = j.umin;
   fa.umin64 = j.umin + (size_t)RBp * (j.Nslots / 64) * 8;
@@ -413,14 +414,19 @@ int launch_fact_join(kgc_handle* hd, hipStream_t st, const FactJob& j, DevCounte
   fa.Nslots = j.Nslots; fa.KS = KS; fa.k16 = (j.d + kNormCols + 15) / 16;
   fa.nT = nT; fa.r0 = j.r0; fa.RB = j.RB; fa.RBp = RBp;
   fa.list = j.list; fa.list_count = &cnt->n_fact; fa.list_cap = j.list_cap; fa.give_up = j.give_up;
-  void (*kern)(const JoinFactArgs) = tc.bm == 256 ? k_join_l2_fact<4, 2, 4> : k_join_l2_fact<2, 2, 4>;
-  const size_t dyn_lds = (size_t)KS * tc.bm * kSliceK * 2 + 8 * kFactWaveLds;
+  void (*kern)(const JoinFactArgs) = wide ? k_join_l2_fact<1, 8> : k_join_l2_fact<2, 4>;
+  const size_t dyn_lds = (size_t)KS * bm * kSliceK * 2 + 8 * kFactWaveLds;
   // A block takes a range of tail tiles of one head tile.  With few tile pairs the relations are cut too, down to one level-2
   // batch: a wave walks its relations one after the other, about 3 us each where its rows hold members of all clusters, and
   // a second contraction of the tile beside it costs an idle compute unit nothing.  (Cuts of 64: N = 1,000, R = 64, d = 32: 16
   // blocks, 198 us.)
   const int64_t pairs = (int64_t)nH * nT;
-  const int64_t nsplit = std::max<int64_t>(1, std::min<int64_t>({(4096 + nH - 1) / nH, (int64_t)nT, 65535}));
+  // Three tiles a block at least where that leaves every compute unit two blocks (a block's first microseconds, its head tile
+  // on the way to the LDS, are not hidden): N = 15,000, R = 1,345: 544 us with one, 491 with three; then eight blocks per
+  // compute unit, sixteen for the largest, whose tiles differ most in what their bounds leave open (N = 100,000, R = 200: 4,871
+  // and 4,474 us).
+  const int64_t blocks = pairs >= 65536 ? 4096 : std::min<int64_t>(2048, std::max<int64_t>(512, pairs / 3));
+  const int64_t nsplit = std::max<int64_t>(1, std::min<int64_t>({(blocks + nH - 1) / nH, (int64_t)nT, 65535}));
   const int64_t nz = std::max<int64_t>(1, std::min<int64_t>((512 + pairs - 1) / pairs, (j.RB + kFactBatch - 1) / kFactBatch));
   fa.zrel = (int)(((j.RB + nz - 1) / nz + kFactBatch - 1) / kFactBatch * kFactBatch);
   KGC_HIP(hd, hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn_lds));

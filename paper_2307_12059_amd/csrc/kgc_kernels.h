@@ -1541,9 +1541,13 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1) void k_join_l2_direct(const JoinS
 // On embeddings in clusters level 1 leaves a relation open where its source cluster has a member among the head rows or
 // its target cluster among the tail columns, level 2 where eight rows hold both a member of the source cluster and a
 // neighbour of the tail.  The candidates are those of the pair-wise filter.
-// Measured (dense joins, kernel alone): N = 15,000, R = 1,345, d = 100: 19 -> 4.7 ms; N = 100,000, R = 200, d = 200:
-// 86 -> 9.2 ms, of which the contraction takes about half.  With one level of 32 rows in place of levels 1 and 2 they
-// took 7.3 and 19.4 ms: on 500 clusters half of all (relation, wave) pairs then went to level 3.
+// Measured (dense joins, rows in order, kernel alone): N = 15,000, R = 1,345, d = 100: 245 us; N = 100,000, R = 200, d = 200: 3.7 ms,
+// 1.13 PFLOP/s over its contraction.  What bounds it there is issue: matrix pipes 50 % and vector pipes 39 % busy before the
+// accumulators were no longer cleared (a zero operand), minima lost their canonicalising v_max, exchanges between lanes left
+// the LDS, and level 1 kept what a block's tiles share in registers and the rest in flight under the contraction, as are
+// the next tile's first rows: 358 us and 4.24 ms before.  L1, 40,000, 18, 100: 611 -> 472 us; 20,011, 37, 512: 574 -> 379 us.
+// (With one level of 32 rows in place of levels 1 and 2, in the caller's order, half of all (relation, wave) pairs on 500 clusters
+// went to level 3.)
 // Candidates leave through a queue of 64 entries per wave (in LDS, no atomics) to a list in memory that
 // k_exact_pairs scores: a wave that scored its own would wait three memory round trips for one or two pairs.
 // A list that was too short is made longer by the host, which then runs the call again.
@@ -1566,9 +1570,10 @@ struct JoinFactArgs {
   unsigned long long give_up;      // with so many pairs listed the host takes another form: the waves end
 };
 constexpr int kFactQueue = 64;         // candidates a wave holds back
-constexpr int kFactIds = 128;          // relations a wave's level 1 has left open and level 2 has not taken yet
 constexpr int kFactBatch = 4;          // relations whose r.t and r.h a lane has in flight together
-constexpr size_t kFactWaveLds = 3 * kFactQueue * 4 + kFactIds * 2;
+constexpr int kFactChunks = 3;         // chunks of 64 relations whose level-1 loads are in flight together
+constexpr int kFactIds = 64 + 64 * kFactChunks;      // relations that level 1 has left open and level 2 has not taken yet
+constexpr size_t kFactWaveLds = 2 * kFactQueue * 4 + kFactIds * 2;      // (eight times this beside 19 slices of 128 rows fill the LDS)
 
 // Per-relation filter thresholds of the factorised join: limr[rl] = thr_r - ||r||^2.  A hit x = h + r - t, ||x|| <= delta,
 // has on the bf16-rounded rows x~ = h~ + r - t~ with ||x~|| <= delta + e_h + e_t (e = the distance that the rounding moves a
@@ -1711,9 +1716,41 @@ __global__ __launch_bounds__(256) void k_fact_dot(const void* __restrict__ Rv, c
 typedef const __attribute__((address_space(4))) float* scalar_f32_t;
 __device__ __forceinline__ scalar_f32_t scalar_f32(const float* p) { return (scalar_f32_t)(uintptr_t)p; }
 
-template <int TM, int WGM, int WGN>
+// The smaller of two floats in one instruction, as the median of them and -infinity: fminf puts a canonicalising v_max before
+// every operand the compiler has not seen computed, which doubles the minima over accumulators (and it turns a median with a
+// constant infinity back into fminf: the empty asm hides the value).  A NaN gives -infinity, and a set that holds one stays
+// open.
+__device__ __forceinline__ float vmin2(float a, float b) {
+  float lowest = -__builtin_inff();
+  asm("" : "+s"(lowest));
+  return __builtin_amdgcn_fmed3f(a, b, lowest);
+}
+// lane l < 32: the smaller of a in lanes l and l + 32; lane l >= 32: the smaller of b in lanes l - 32 and l
+__device__ __forceinline__ float min_halves(float a, float b) {
+  const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return vmin2(__uint_as_float(s[0]), __uint_as_float(s[1]));
+}
+template <int CTRL>
+__device__ __forceinline__ float dpp_min(float x) {
+  return vmin2(x, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true)));
+}
+// the minimum over the wave, in every lane: exchanges inside 16 lanes (quad permutes, mirrors), then between them
+__device__ __forceinline__ float wave_min(float x) {
+  x = dpp_min<0xB1>(x);                                    // quad_perm [1, 0, 3, 2]
+  x = dpp_min<0x4E>(x);                                    // quad_perm [2, 3, 0, 1]
+  x = dpp_min<0x141>(x);                                   // row_half_mirror
+  x = dpp_min<0x140>(x);                                   // row_mirror
+  const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  x = vmin2(__uint_as_float(s[0]), __uint_as_float(s[1]));
+  return min_halves(x, x);
+}
+
+// Two shapes, both with wave tiles of 128 x 64 (two LDS reads and one read through the vector cache per four MFMAs): 256 x 256
+// up to KS = 9, 128 x 512 beyond, where every tail row is read by one wave.  (128 x 256 with wave tiles of 64 x 64 asked the
+// vector cache for 64 bytes a cycle.)
+template <int WGM, int WGN>
 __global__ __launch_bounds__(WGM* WGN * 64, 1) void k_join_l2_fact(const JoinFactArgs a) {
-  constexpr int TN = 2;                                    // a wave holds 64 tail columns: one per lane in the bound
+  constexpr int TM = 4, TN = 2;                            // a wave holds 64 tail columns: one per lane in the bound
   constexpr int NT = WGM * WGN * 64;
   constexpr int WTM = TM * 32, WTN = TN * 32;
   constexpr int BM = WGM * WTM, BN = WGN * WTN;
@@ -1722,21 +1759,22 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1) void k_join_l2_fact(const JoinFac
   constexpr int ROWB = kSliceK * 2;
   static_assert(LA * NT == BM * 4, "tile rows must divide over the threads");
   constexpr int NG = TM * 4;                               // groups of eight head rows
-  static_assert(TM == 2 || TM == 4, "a wave's rows are whole groups of 64 slots");
+  static_assert(TM % 2 == 0, "a wave's rows are whole groups of 64 slots");
 
   extern __shared__ __attribute__((aligned(16))) uint16_t lds[];   // [KS][BM][32] head slices, then the waves' queues
   const int KS = a.KS;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WGN, wn = wave % WGN;
+  constexpr int NC = kFactChunks;
   char* wlds = (char*)(lds + (size_t)KS * ASZ) + wave * kFactWaveLds;
-  uint32_t* q = (uint32_t*)wlds;                           // candidates: relation, head slot, tail slot
-  uint16_t* ids = (uint16_t*)(wlds + 3 * kFactQueue * 4);  // relations of the batch (fewer than 65,536) that level 1 left open
+  uint32_t* q = (uint32_t*)wlds;                           // candidates: relation << 16 | head row of the wave, tail slot
+  uint16_t* ids = (uint16_t*)(wlds + 2 * kFactQueue * 4);  // relations of the batch (fewer than 65,536) that level 1 left open
   int qn = 0;                                              // entries in the queue (the same in all lanes)
 
   const int tH = (int)blockIdx.x;
   const int t_begin = (int)(((int64_t)a.nT * blockIdx.y) / gridDim.y);
-  const int t_end = (int)(((int64_t)a.nT * (blockIdx.y + 1)) / gridDim.y);
+  int t_end = (int)(((int64_t)a.nT * (blockIdx.y + 1)) / gridDim.y);
   const int rl_begin = (int)blockIdx.z * a.zrel;
   // The tables' padding rows are not walked: a NaN keeps a pair open whatever the threshold (rows whose norms leave
   // float32's range), and the exact stage would read past the last relation.
@@ -1759,6 +1797,8 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1) void k_join_l2_fact(const JoinFac
     }
   }
   __syncthreads();                                         // the only barrier: from here on the waves run on their own
+  if (((int64_t)(t_end - 1) * BN + wn * WTN) >= a.Nslots) --t_end;      // (BN = 512: half of the last tile may not be there)
+  if (t_end <= t_begin) return;
 
   const int rsw = lds_swizzle(lane & 31);
   const int rd_a = (wm * WTM + (lane & 31)) * kSliceK + (((lane >> 5) ^ rsw) * 8);
@@ -1782,7 +1822,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1) void k_join_l2_fact(const JoinFac
            (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)base);                         \
     if (fl < qn && base + (unsigned)fl < a.list_cap) {                                            \
       ExactEntry e;                                                                               \
-      e.r = (int32_t)q[fl]; e.hs0 = (int32_t)q[kFactQueue + fl]; e.ts0 = (int32_t)q[2 * kFactQueue + fl]; e.pad = 0; \
+      e.r = a.r0 + (int32_t)(q[fl] >> 16); e.hs0 = hrow0 + (int32_t)(q[fl] & 0xffffu); e.ts0 = (int32_t)q[kFactQueue + fl]; e.pad = 0; \
       a.list[base + (unsigned)fl] = e;                                                            \
     }                                                                                             \
     if (base > a.give_up) return;                                                                 \
@@ -1791,45 +1831,78 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1) void k_join_l2_fact(const JoinFac
     __builtin_amdgcn_wave_barrier();                                                              \
   } while (0)
 
+  const char* pB = (const char*)a.B + (int64_t)t_begin * BN * ROWB + boff;
+  bf16x8_t nb0[TN], nb1[TN];
+#pragma unroll
+  for (int j = 0; j < TN; ++j) {
+    nb0[j] = *(const bf16x8_t*)(pB + j * 32 * ROWB);
+    nb1[j] = *(const bf16x8_t*)(pB + j * 32 * ROWB + 32);
+  }
+  bf16x8_t fa[TM];
+#pragma unroll
+  for (int i = 0; i < TM; ++i) fa[i] = *(const bf16x8_t*)(lds + rd_a + i * 32 * kSliceK);
+  // level 1's first chunks: what does not change from tile to tile
+  float um_first[NC], lim_first[NC];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) {
+    const int rl = rl_begin + 64 * c + lane < rl_end ? rl_begin + 64 * c + lane : rl_end - 1;
+    um_first[c] = um64[rl];
+    lim_first[c] = a.limr[rl];
+#pragma unroll
+    for (int h = 1; h < TM / 2; ++h) um_first[c] = fminf(um_first[c], um64[(int64_t)h * a.RBp + rl]);
+  }
   for (int tT = t_begin; tT < t_end; ++tT) {
     // ---- G = ||h~ - t~||^2: tail fragments straight from the staged array, the next slice's in flight ----
     f32x16_t acc[TM][TN];
-    const char* pB = (const char*)a.B + (int64_t)tT * BN * ROWB + boff;
-    bf16x8_t nb0[TN], nb1[TN];
+    const int tcol = tT * BN + wn * WTN;                                  // this wave's first tail column
+    const float* ux64 = a.umax64 + (int64_t)(tcol >> 6) * a.RBp;
+    float ux_first[NC];                                    // ... and what does, in flight under the contraction
 #pragma unroll
-    for (int j = 0; j < TN; ++j) {
-      nb0[j] = *(const bf16x8_t*)(pB + j * 32 * ROWB);
-      nb1[j] = *(const bf16x8_t*)(pB + j * 32 * ROWB + 32);
-    }
-    const f32x16_t zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j) acc[i][j] = zero16;
+    for (int c = 0; c < NC; ++c) ux_first[c] = ux64[rl_begin + 64 * c + lane < rl_end ? rl_begin + 64 * c + lane : rl_end - 1];
+    // Order inside a slice, pinned by scheduling barriers: the next slice's loads first (left to itself the compiler issues
+    // them behind six MFMAs), then per block row its MFMAs followed by the LDS read of that row's fragment of the next step.
     for (int ks = 0; ks < KS; ++ks) {
-      const uint16_t* Ac = lds + ks * ASZ + rd_a;
-      bf16x8_t fb0[TN], fb1[TN], fa[TM];
+      const bool wrap = ks + 1 == KS, two = !wrap || last_two;
+      bf16x8_t fb0[TN], fb1[TN];
 #pragma unroll
       for (int j = 0; j < TN; ++j) { fb0[j] = nb0[j]; fb1[j] = nb1[j]; }
-      if (ks + 1 < KS) pB += slice_bytes;                  // (the last step asks for its own slice again)
+      // (the last slice asks for the next tile's first, which the bounds below then hide; the last tile's for its own)
+      if (!wrap) pB += slice_bytes;
+      else pB = (const char*)a.B + (int64_t)(tT + 1 < t_end ? tT + 1 : tT) * BN * ROWB + boff;
 #pragma unroll
       for (int j = 0; j < TN; ++j) {
         nb0[j] = *(const bf16x8_t*)(pB + j * 32 * ROWB);
         nb1[j] = *(const bf16x8_t*)(pB + j * 32 * ROWB + 32);
       }
+      __builtin_amdgcn_sched_barrier(0);
+      const uint16_t* An = lds + (wrap ? 0 : (ks + 1) * ASZ) + rd_a;      // the next slice's first step (the first of all behind the last)
+      const uint16_t* A1 = two ? lds + ks * ASZ + rd_a + rd_step : An;
+      if (ks == 0) {                                       // (a zero operand: no register is cleared)
+        const f32x16_t zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int i = 0; i < TM; ++i) fa[i] = *(const bf16x8_t*)(Ac + i * 32 * kSliceK);
+        for (int i = 0; i < TM; ++i) {
 #pragma unroll
-      for (int i = 0; i < TM; ++i)
+          for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], fb0[j], zero16, 0, 0, 0);
+          fa[i] = *(const bf16x8_t*)(A1 + i * 32 * kSliceK);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      } else {
 #pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], fb0[j], acc[i][j], 0, 0, 0);
-      if (ks < KS - 1 || last_two) {
+        for (int i = 0; i < TM; ++i) {
 #pragma unroll
-        for (int i = 0; i < TM; ++i) fa[i] = *(const bf16x8_t*)(Ac + i * 32 * kSliceK + rd_step);
+          for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], fb0[j], acc[i][j], 0, 0, 0);
+          fa[i] = *(const bf16x8_t*)(A1 + i * 32 * kSliceK);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+      if (two) {
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
+        for (int i = 0; i < TM; ++i) {
 #pragma unroll
           for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], fb1[j], acc[i][j], 0, 0, 0);
+          fa[i] = *(const bf16x8_t*)(An + i * 32 * kSliceK);
+          __builtin_amdgcn_sched_barrier(0);
+        }
       }
     }
 
@@ -1841,35 +1914,51 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1) void k_join_l2_fact(const JoinFac
       const int i = g >> 2, v = (g & 3) * 4;
       float m[TN];
 #pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        m[j] = fminf(fminf(acc[i][j][v], acc[i][j][v + 1]), fminf(acc[i][j][v + 2], acc[i][j][v + 3]));
-        m[j] = fminf(m[j], __shfl_xor(m[j], 32, 64));
-      }
-      gm[g] = lane < 32 ? m[0] : m[1];
+      for (int j = 0; j < TN; ++j) m[j] = vmin2(vmin2(acc[i][j][v], acc[i][j][v + 1]), vmin2(acc[i][j][v + 2], acc[i][j][v + 3]));
+      gm[g] = min_halves(m[0], m[1]);
     }
     float gt = gm[0];
 #pragma unroll
-    for (int g = 1; g < NG; ++g) gt = fminf(gt, gm[g]);
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) gt = fminf(gt, __shfl_xor(gt, off, 64));
+    for (int g = 1; g < NG; ++g) gt = vmin2(gt, gm[g]);
+    gt = wave_min(gt);
 
-    const int tcol = tT * BN + wn * WTN;                                  // this wave's first tail column
-    const float* ux64 = a.umax64 + (int64_t)(tcol >> 6) * a.RBp;
     const float* ut0 = a.u + tcol + lane;
     const float* uh0 = a.u + hrow0 + lane;
     int cnt = 0, rb = rl_begin;
     for (;;) {
-      // ---- level 1: one relation per lane ----
-      while (rb < rl_end && cnt <= kFactIds - 64) {
-        const int rl = rb + lane < rl_end ? rb + lane : rl_end - 1;
-        float um = um64[rl];
+      // ---- level 1: one relation per lane, NC chunks of 64 with their loads in flight together ----
+      while (rb < rl_end && cnt <= kFactIds - 64 * NC) {
+        float um[NC], lm[NC], ux[NC];
+        if (rb == rl_begin) {
 #pragma unroll
-        for (int h = 1; h < TM / 2; ++h) um = fminf(um, um64[(int64_t)h * a.RBp + rl]);
-        const bool open = rb + lane < rl_end && !(gt + um > a.limr[rl] + ux64[rl]);
-        const unsigned long long b = __builtin_amdgcn_ballot_w64(open);
-        if (open) ids[cnt + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u))] = (uint16_t)rl;
-        cnt += __builtin_popcountll(b);
-        rb += 64;
+          for (int c = 0; c < NC; ++c) { um[c] = um_first[c]; lm[c] = lim_first[c]; ux[c] = ux_first[c]; }
+        } else {
+          float uh[NC][TM / 2];
+#pragma unroll
+          for (int c = 0; c < NC; ++c) {
+            const int rl = rb + 64 * c + lane < rl_end ? rb + 64 * c + lane : rl_end - 1;
+            ux[c] = ux64[rl];
+            lm[c] = a.limr[rl];
+#pragma unroll
+            for (int h = 0; h < TM / 2; ++h) uh[c][h] = um64[(int64_t)h * a.RBp + rl];
+          }
+#pragma unroll
+          for (int c = 0; c < NC; ++c) {
+            um[c] = uh[c][0];
+#pragma unroll
+            for (int h = 1; h < TM / 2; ++h) um[c] = fminf(um[c], uh[c][h]);
+          }
+        }
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+          if (rb + 64 * c >= rl_end) break;                               // (the same for the whole wave)
+          const int rl = rb + 64 * c + lane;
+          const bool open = rl < rl_end && !(gt + um[c] > lm[c] + ux[c]);
+          const unsigned long long b = __builtin_amdgcn_ballot_w64(open);
+          if (open) ids[cnt + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u))] = (uint16_t)rl;
+          cnt += __builtin_popcountll(b);
+        }
+        rb += 64 * NC;
       }
       const bool last = rb >= rl_end;
       const int take = last ? cnt : cnt / kFactBatch * kFactBatch;        // (not the last: more than half full)
@@ -1948,9 +2037,8 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1) void k_join_l2_fact(const JoinFac
               if (cm != 0u) {
                 const int e = __builtin_ctz(cm);
                 const int pos = qn + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u));
-                q[pos] = (uint32_t)(a.r0 + rel);
-                q[kFactQueue + pos] = (uint32_t)(hrow0 + 8 * g + 4 * (lq >> 5) + (e & 3));
-                q[2 * kFactQueue + pos] = (uint32_t)(tcol + (e >> 2) * 32 + (lq & 31));
+                q[pos] = (uint32_t)rel << 16 | (uint32_t)(8 * g + 4 * (lq >> 5) + (e & 3));
+                q[kFactQueue + pos] = (uint32_t)(tcol + (e >> 2) * 32 + (lq & 31));
                 cm &= cm - 1u;
               }
               qn += n;
