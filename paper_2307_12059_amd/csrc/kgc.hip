@@ -304,15 +304,13 @@ inline int64_t fact_batch(int64_t bytes, int64_t slots, int64_t R) {
   const int64_t rows = std::max<int64_t>(1, std::max<int64_t>(bytes, 0) / fact_row_bytes(slots));
   return std::min<int64_t>({R, rows >= kFactChunk ? rows / kFactChunk * kFactChunk : rows, 65528});
 }
-// Dense L2 joins that the relation-factorised kernel takes by itself.  Its fixed part (products r.e, one contraction per
-// pair of entities, the list of pairs) is paid once, the other kernels contract every relation and score their candidates in
-// place.  Measured, whole calls in us, per-relation kernel / this one, float32, clusters of 60 rows in random order.  A few to
-// a thousand hits: N = 1,000, R = 16: 113 / 127 (d = 32), 129 / 127 (100), 151 / 165 (282), 223 / 197 (600); N = 2,000, R = 8:
-// 109 / 113 (32), 123 / 123 (100), 139 / 140 (200), 240 / 214 (600); N = 16,000, R = 8: 290 / 316 (32), 2,588 / 680 (600);
-// N = 1,000, R = 64, d = 32: 121 / 120; N = 1,000, R = 256, d = 100: 523 / 212; N = 3,000, R = 100, d = 64: 279 / 230.  With
-// 31,000 hits N = 1,000, R = 16, d = 32: 310 / 138, with 15,000 N = 16,000, R = 8, d = 32: 483 / 336.  The line lies where the
-// two are level without hits; below it (N = 1,000, R = 8; R = 4) the fixed part is not earned back.
-inline bool fact_pays(int64_t N, int64_t R) { return R >= 8 && N >= 1000 && N * R >= 16000; }
+// Dense L2 joins that the relation-factorised kernel takes by itself: its fixed part (products r.e, one contraction per pair of
+// entities, the list of pairs) is paid once, the other kernels contract every relation and score their candidates in place.
+// Measured, whole calls in us, per-relation kernel / this one, float32, clusters of 30 to 60 rows in random order: N = 300, R =
+// 100, d = 32: 170 / 93; 500, 16, 64: 92 / 89; 700, 200, 64: 160 / 107 (with 139,000 hits 1,173 / 174); 1,000, 4, 64: 85 / 84;
+// 2,000, 4, 64: 88 / 83; 4,000, 2, 100: 88 / 83; 4,000, 6, 400: 229 / 156; 15,000, 2, 64: 170 / 142; 15,000, 4, 512: 998 / 339;
+// 30,000, 2, 128: 502 / 349; 60,000, 4, 256: 5,952 / 1,792.  One relation has nothing to share: 60,000, 1, 128: 883 / 1,021.
+inline bool fact_pays(int64_t N, int64_t R) { return R >= 2 && N >= 256 && N * R >= 6000; }
 
 // Dense L1 joins that the relation-factorised kernel takes first: ||x||_2 <= ||x||_1, so every hit is among the pairs
 // within delta in L2, which its list then scores in L1.  Where the list grows past fact_list_max the L1 kernel does the

@@ -1626,14 +1626,52 @@ __device__ __forceinline__ void fact_params(const DevCounters* __restrict__ cnt,
   }
 }
 
+// The smaller of two floats in one instruction, as the median of them and -infinity: fminf puts a canonicalising v_max before
+// every operand the compiler has not seen computed, which doubles the minima over accumulators (and it turns a median with a
+// constant infinity back into fminf: the empty asm hides the value).  A NaN gives -infinity, and a set that holds one stays
+// open.
+__device__ __forceinline__ float vmin2(float a, float b) {
+  float lowest = -__builtin_inff();
+  asm("" : "+s"(lowest));
+  return __builtin_amdgcn_fmed3f(a, b, lowest);
+}
+__device__ __forceinline__ float vmax2(float a, float b) {
+  float highest = __builtin_inff();
+  asm("" : "+s"(highest));
+  return __builtin_amdgcn_fmed3f(a, b, highest);
+}
+// lane l < 32: the smaller of a in lanes l and l + 32; lane l >= 32: the smaller of b in lanes l - 32 and l
+__device__ __forceinline__ float min_halves(float a, float b) {
+  const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return vmin2(__uint_as_float(s[0]), __uint_as_float(s[1]));
+}
+template <int CTRL>
+__device__ __forceinline__ float dpp_min(float x) {
+  return vmin2(x, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true)));
+}
+template <int CTRL>
+__device__ __forceinline__ float dpp_max(float x) {
+  return vmax2(x, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true)));
+}
+// the minimum over the wave, in every lane: exchanges inside 16 lanes (quad permutes, mirrors), then between them
+__device__ __forceinline__ float wave_min(float x) {
+  x = dpp_min<0xB1>(x);                                    // quad_perm [1, 0, 3, 2]
+  x = dpp_min<0x4E>(x);                                    // quad_perm [2, 3, 0, 1]
+  x = dpp_min<0x141>(x);                                   // row_half_mirror
+  x = dpp_min<0x140>(x);                                   // row_mirror
+  const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  x = vmin2(__uint_as_float(s[0]), __uint_as_float(s[1]));
+  return min_halves(x, x);
+}
+
 // u[rl][slot] = r . e~ for the relations of a batch and the bf16-rounded row of every slot's entity (why rounded:
 // fact_params; 0 for padding slots and for rows from RB on), and the extremes of 2 r.e~ over 8 and over 64 consecutive
 // slots (padding does not count), on the float32 matrix pipes: a wave takes 32 relations x 64 slots, operands straight into
 // registers in the permuted order of dimensions that k_small_dot explains, every load of 64 dimensions issued before the
 // first is used.  The 128 x 128 vector tile kernel that did the products before left most of the chip idle on a thin product
 // (R = 2, d = 200: 60 us of latency) and needed a pass that cleared u and one that took the extremes: 204 us for the three,
-// now 87 us (N = 15,000, R = 1,345, d = 100, float32 rows; 4.0 GFLOP, 81 MB written), N = 100,000, R = 200, d = 200:
-// 284 -> 136 us.  One more workgroup per 32 relations makes their thresholds.
+// now 82 us (N = 15,000, R = 1,345, d = 100, float32 rows; 4.0 GFLOP, 81 MB written; 89 with the extremes taken through the
+// LDS), N = 100,000, R = 200, d = 200: 284 -> 136 us.  One more workgroup per 32 relations makes their thresholds.
 template <bool BF16, bool VEC>
 __global__ __launch_bounds__(256) void k_fact_dot(const void* __restrict__ Rv, const void* __restrict__ E,
                                                   const int32_t* __restrict__ slot_ent, int64_t Nslots, int r0, int RB, int RBp,
@@ -1695,18 +1733,16 @@ __global__ __launch_bounds__(256) void k_fact_dot(const void* __restrict__ Rv, c
       if (rl < RBp) u[(int64_t)rl * Nslots + g * 64 + 32 * j + row] = x;
       lo[j] = ent[j] >= 0 ? 2.f * x : 3e38f;
       hi[j] = ent[j] >= 0 ? 2.f * x : -3e38f;
-#pragma unroll
-      for (int off = 1; off < 8; off <<= 1) {
-        lo[j] = fminf(lo[j], __shfl_xor(lo[j], off, 64));
-        hi[j] = fmaxf(hi[j], __shfl_xor(hi[j], off, 64));
-      }
+      lo[j] = dpp_min<0x141>(dpp_min<0x4E>(dpp_min<0xB1>(lo[j])));         // eight slots: two exchanges in a quad, one of its neighbour
+      hi[j] = dpp_max<0x141>(dpp_max<0x4E>(dpp_max<0xB1>(hi[j])));
       if (rl < RBp && (lane & 7) == 0) umin8[(g * RBp + rl) * 8 + 4 * j + (row >> 3)] = lo[j];
     }
-    float l = fminf(lo[0], lo[1]), h = fmaxf(hi[0], hi[1]);
-#pragma unroll
-    for (int off = 8; off < 32; off <<= 1) {
-      l = fminf(l, __shfl_xor(l, off, 64));
-      h = fmaxf(h, __shfl_xor(h, off, 64));
+    float l = dpp_min<0x140>(vmin2(lo[0], lo[1])), h = dpp_max<0x140>(vmax2(hi[0], hi[1]));
+    {   // the two sixteens of a half wave
+      const auto sl = __builtin_amdgcn_permlane16_swap(__float_as_uint(l), __float_as_uint(l), false, false);
+      const auto sh = __builtin_amdgcn_permlane16_swap(__float_as_uint(h), __float_as_uint(h), false, false);
+      l = vmin2(__uint_as_float(sl[0]), __uint_as_float(sl[1]));
+      h = vmax2(__uint_as_float(sh[0]), __uint_as_float(sh[1]));
     }
     if (rl < RBp && row == 0) { umin64[g * RBp + rl] = l; umax64[g * RBp + rl] = h; }
   }
@@ -1715,35 +1751,6 @@ __global__ __launch_bounds__(256) void k_fact_dot(const void* __restrict__ Rv, c
 // A wave-uniform read-only array of an earlier launch, read through the scalar cache whatever else the kernel stores.
 typedef const __attribute__((address_space(4))) float* scalar_f32_t;
 __device__ __forceinline__ scalar_f32_t scalar_f32(const float* p) { return (scalar_f32_t)(uintptr_t)p; }
-
-// The smaller of two floats in one instruction, as the median of them and -infinity: fminf puts a canonicalising v_max before
-// every operand the compiler has not seen computed, which doubles the minima over accumulators (and it turns a median with a
-// constant infinity back into fminf: the empty asm hides the value).  A NaN gives -infinity, and a set that holds one stays
-// open.
-__device__ __forceinline__ float vmin2(float a, float b) {
-  float lowest = -__builtin_inff();
-  asm("" : "+s"(lowest));
-  return __builtin_amdgcn_fmed3f(a, b, lowest);
-}
-// lane l < 32: the smaller of a in lanes l and l + 32; lane l >= 32: the smaller of b in lanes l - 32 and l
-__device__ __forceinline__ float min_halves(float a, float b) {
-  const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
-  return vmin2(__uint_as_float(s[0]), __uint_as_float(s[1]));
-}
-template <int CTRL>
-__device__ __forceinline__ float dpp_min(float x) {
-  return vmin2(x, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true)));
-}
-// the minimum over the wave, in every lane: exchanges inside 16 lanes (quad permutes, mirrors), then between them
-__device__ __forceinline__ float wave_min(float x) {
-  x = dpp_min<0xB1>(x);                                    // quad_perm [1, 0, 3, 2]
-  x = dpp_min<0x4E>(x);                                    // quad_perm [2, 3, 0, 1]
-  x = dpp_min<0x141>(x);                                   // row_half_mirror
-  x = dpp_min<0x140>(x);                                   // row_mirror
-  const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  x = vmin2(__uint_as_float(s[0]), __uint_as_float(s[1]));
-  return min_halves(x, x);
-}
 
 // Two shapes, both with wave tiles of 128 x 64 (two LDS reads and one read through the vector cache per four MFMAs): 256 x 256
 // up to KS = 9, 128 x 512 beyond, where every tail row is read by one wave.  (128 x 256 with wave tiles of 64 x 64 asked the
