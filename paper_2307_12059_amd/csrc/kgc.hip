@@ -78,6 +78,7 @@ struct kgc_handle {
   DevBuf se_a, se_b;                           // connector rows of a relation batch (kgc_join_se)
   DevBuf xlist;                                // accumulator blocks listed for the exact stage (L2 joins)
   unsigned int xcap = kExactListCap;           // its length in entries: grows when a batch wanted to list more
+  DevBuf sample_counts;                        // close_share
   DevBuf flist, umin;                          // listed pairs; relation-factorised join: extremes of 2 r.e over 8 and 64 rows
   unsigned int fcap = 0;                       // entries of flist that an earlier call needed (see fact_list_start)
   unsigned int fcap_start = 0;                 // > 0: ... and to start with (tests)
@@ -87,7 +88,7 @@ struct kgc_handle {
   unsigned pairs_grid = 512;                   // workgroups of the tile-at-a-time kernel: two per compute unit (tests set fewer, so that a workgroup walks several batches of tiles)
   DevBuf zero_row, cent_a, rad_a;              // kgc_join_ab: the zero relation row; micro-tile summaries of A[r]
   DevBuf top1_a, top1_b, top1_pick, top_samples, topk_state;            // ... and the operands / entity samples of its sub-sampled dense pass
-  bool as_dense = false;                       // inside a pruned call whose rows form one group: the join without pruning
+  bool as_dense = false;                       // inside a pruned call that is run without pruning: the relation-factorised form
   bool no_fact = false;                        // inside a call that the relation-factorised form did not suit
   int no_self = 0;                             // set by kgc_top1 around its inner joins: drop h == t
   bool static_mode = false;                    // inside kgc_join_static: the DevBufs point into the static array, nothing may allocate
@@ -337,6 +338,34 @@ inline unsigned int fact_list_start(int64_t N, int64_t R) {
   return (unsigned int)std::min((double)(1u << 23), std::max((double)(1u << 18), (double)N * (double)N * (double)R / 64.0));
 }
 
+// A typical time of the factorised form in us without its hits (fit over 250 joins of N = 500 to 400,000, half of them within
+// 15 %): fixed part, contraction, row order, bounds, products, passes over the rows.
+inline double fact_us(int64_t N, int64_t R, int d) {
+  const double n = (double)N, r = (double)R, k = (double)((d + kNormCols + kSliceK - 1) / kSliceK * kSliceK);
+  const double piv = order_pays(N, R, d) ? std::min<double>(kOrderPivots, n / 8) : 0.0;
+  return 115.0 + 1.6e-9 * n * n * k + 2.8e-9 * n * piv * k + 1.25e-11 * n * n * r + 1.7e-5 * n * r + 1.7e-3 * n;
+}
+// ... and of its hits, as many as the caller makes room for (and no more than one pair in 200): listing and scoring a pair
+// costs what the pruned kernels, which score whole blocks, do not spend
+inline double hits_us(int64_t N, int64_t R, uint64_t cap) { return 2.5e-4 * std::min((double)cap, (double)N * (double)N * (double)R / 200.0); }
+// With KGC_PRUNE_AUTO a join goes to the factorised form where that is the shorter way.  Before grouping: grouping, bound test
+// and tile lists are a chain of 25 launches and two read-backs, 220 to 300 us up to N = 20,000 however well they prune.  Measured,
+// whole calls in us, pruned / factorised: 2,000, 8, 32: 220 / 90; 773, 21, 192: 255 / 120; 2,654, 180, 39: 273 / 158; 4,301, 9, 100:
+// 292 / 135; 13,334, 51, 200: 298 / 234; 15,000, 1,345, 100 (561 estimated): 330 / 485; with many hits 6,385, 46, 69 (342,000): 298 /
+// 368.
+constexpr double kAutoDenseUs = 270.0;
+// After grouping, where it went badly.  Rows without a group (clusters of fewer than kSmallGroup), or few units of which one
+// holds a quarter of the rows, so that bounds on them decide nothing: the pruned kernels take 3 to 2,500 times as long (12,242, 104, 100, Zipf sizes, a tenth of the rows
+// without a group: 5,290 / 214 us; 29,297, 639, 59, clusters of 12: 1.57 s / 635 us; 131,975, 9, 64, clusters of 14: 1.0 s / 2.9
+// ms; 38,077, 336, 100, four units: 161 / 2.0 ms; 245,439, 434, 64, Zipf sizes: 34 / 12.3 ms); from 20 ms of contraction on the
+// pruned kernels win again (1,000,000, 1,000, 128: 78 / 300 ms).  A large unit beside many small ones is no sign: 364,163, 20, 27:
+// 5,965 / 14,149; 17,272, 107, 254: 1,093 / 1,341.
+inline bool grouped_badly(int64_t N, int64_t tail_rows, int n_units, int max_unit, double us) {
+  return us < 20000.0 && (tail_rows * 128 > N || (n_units <= 64 && (int64_t)max_unit * kMicro * 4 > N));
+}
+// What a pair of the factorised form's list costs (L1, where a sample says how many there are)
+constexpr double kListedPairUs = 2e-4;
+
 // Units of the bound test (groups, micro-tiles without one) up to which a pruned L2 join is taken as a dense one: with
 // three units the bound could rule out at most eight of nine pairs, and the factorised kernel decides a pair and relation
 // in a sixteenth to a sixtieth of a contraction's time.
@@ -413,7 +442,9 @@ int launch_fact_join(kgc_handle* hd, hipStream_t st, const FactJob& j, DevCounte
   fa.nT = nT; fa.r0 = j.r0; fa.RB = j.RB; fa.RBp = RBp;
   fa.list = j.list; fa.list_count = &cnt->n_fact; fa.list_cap = j.list_cap; fa.give_up = j.give_up;
   void (*kern)(const JoinFactArgs) = wide ? k_join_l2_fact<1, 8> : k_join_l2_fact<2, 4>;
-  const size_t dyn_lds = (size_t)KS * bm * kSliceK * 2 + 8 * kFactWaveLds;
+  const size_t head_lds = (size_t)KS * bm * kSliceK * 2;
+  fa.queue = (int)std::min<size_t>(512, ((kMaxLds - head_lds) / 8 - fact_wave_lds(0)) / 8);      // (64 at least, with 19 slices of 128 rows)
+  const size_t dyn_lds = head_lds + 8 * fact_wave_lds(fa.queue);
   // A block takes a range of tail tiles of one head tile.  With few tile pairs the relations are cut too, down to one level-2
   // batch: a wave walks its relations one after the other, about 3 us each where its rows hold members of all clusters, and
   // a second contraction of the tile beside it costs an idle compute unit nothing.  (Cuts of 64: N = 1,000, R = 64, d = 32: 16
@@ -492,7 +523,7 @@ void kgc_destroy(kgc_handle* h) {
                     &h->gram, &h->relu, &h->reln, &h->asg_a, &h->asg_b, &h->limr, &h->top1_buf, &h->top1_state,
                     &h->unit_first, &h->unit_n, &h->cent_u, &h->rad_u, &h->cnorm_u, &h->gram_u, &h->relu_u, &h->pair_list,
                     &h->pair_count, &h->xlist, &h->tile_rows, &h->se_a, &h->se_b, &h->zero_row, &h->cent_a, &h->rad_a, &h->top1_a, &h->top1_b, &h->top1_pick, &h->top_samples, &h->topk_state,
-                    &h->flist, &h->umin})
+                    &h->flist, &h->umin, &h->sample_counts})
     release(*b);
   if (h->host_gstate) (void)hipHostFree(h->host_gstate);
   if (h->host_counters) (void)hipHostFree(h->host_counters);
@@ -975,6 +1006,26 @@ int group_rows(kgc_handle* hd, const void* E, int64_t N, int32_t d, int32_t p, f
   return KGC_OK;
 }
 
+// The share of random triples of relations r_begin .. r_begin + Rn - 1 that lie within delta in L2, at least one in
+// kSampleTriples (one small launch and a read-back, about 20 us)
+int close_share(kgc_handle* hd, const void* E, int64_t N, int32_t d, const void* Rvecs, int32_t r_begin, int64_t Rn, float delta, double* share) {
+  int rc;
+  if ((rc = ensure(hd, hd->sample_counts, kSampleBlocks * 4))) return rc;
+  RecheckCtx cx{};
+  cx.E = E; cx.Et = E; cx.Rv = Rvecs; cx.rstride = d; cx.dtype = hd->cfg.dtype; cx.d = d; cx.p = 2; cx.delta = (double)delta;
+  set_alignment(cx);
+  k_sample_close<<<kSampleBlocks, 256, 0, hd->stream>>>(cx, N, r_begin, (int)Rn, (unsigned int*)hd->sample_counts.p);
+  KGC_HIP(hd, hipGetLastError());
+  unsigned int* const got = hd->host_counters->max_a;      // (pinned, and of no meaning on the host otherwise)
+  KGC_HIP(hd, hipMemcpyAsync(got, hd->sample_counts.p, kSampleBlocks * 4, hipMemcpyDeviceToHost, hd->stream));
+  KGC_HIP(hd, hipEventRecord(hd->ev[2], hd->stream));
+  KGC_HIP(hd, wait_event(hd->ev[2]));
+  unsigned int n = 1;
+  for (int i = 0; i < kSampleBlocks; ++i) n += got[i];
+  *share = (double)n / (double)kSampleTriples;
+  return KGC_OK;
+}
+
 // Row order of a dense relation-factorised join (kgc_prune.h): the rows' and the pivots' operands lie where those of the
 // join are staged afterwards (`rows`, `pivots`: KS slices of Nslots and of at most kOrderPivots rows).
 int order_rows(kgc_handle* hd, const void* E, int64_t N, int32_t d, int KS, int k16, int64_t Nslots, uint16_t* rows, uint16_t* pivots) {
@@ -1437,10 +1488,21 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
 
   hipStream_t st = hd->stream;
   const int dtype = hd->cfg.dtype;
-  const bool prune = hd->cfg.prune != KGC_PRUNE_OFF && !hd->as_dense;
+  const bool free_choice = !win && !hd->static_mode && !hd->no_fact && hd->cfg.tile_cfg == 0;      // of the kernel
+  const int KS = (d + kNormCols + kSliceK - 1) / kSliceK;
+  // KGC_PRUNE_AUTO: pruned, or the factorised form (for L1 if a sample says that its list stays short)
+  const bool automatic = hd->cfg.prune == KGC_PRUNE_AUTO && free_choice && !hd->as_dense && hd->cfg.factorised == 0 && hd->cfg.group_radius == 0.f &&
+                         KS <= kDirectHalfMaxKS && delta >= 0.f && delta < 1e18f && fact_pays(N, Rn);
+  const double dense_us = automatic ? fact_us(N, Rn, d) + hits_us(N, Rn, cap) : 0.0;
+  KGC_HIP(hd, hipEventRecord(hd->ev[0], st));
+  double share = -1.0;                                     // close_share, once it is known
+  // (a share near what the list may hold is a try lost: fact_list_max)
+  auto listed_us = [&]() { return p == 2 ? 0.0 : share * 1024.0 > 1.0 ? 1e30 : kListedPairUs * share * (double)N * (double)N * (double)Rn; };
+  if (automatic && p == 1 && dense_us <= kAutoDenseUs && (rc = close_share(hd, E, N, d, Rvecs, r_begin, Rn, delta, &share)) != KGC_OK) return rc;
+  const bool straight = automatic && dense_us <= kAutoDenseUs && dense_us + listed_us() <= kAutoDenseUs;      // the factorised form without grouping
+  const bool prune = hd->cfg.prune != KGC_PRUNE_OFF && !hd->as_dense && !straight;
 
   // tile shape
-  const int KS = (d + kNormCols + kSliceK - 1) / kSliceK;
   const int k16 = (d + kNormCols + 15) / 16;
   // automatic choice.  Dense: the barrier-free head-resident kernel while the head tile fits in LDS with
   // some room to spare (256 rows for KS <= 9, d <= 282; 128 rows for KS <= 19, d <= 602).  Pruned: the head-resident list-walking kernels
@@ -1449,7 +1511,8 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
   const bool fact = !prune && !win && !hd->static_mode && !hd->no_fact &&
                     (p == 2 && hd->cfg.factorised != 0 ? KS <= kDirectMaxKS
                      : p == 2 ? hd->cfg.tile_cfg == 0 && fact_pays(N, Rn) && KS <= kDirectHalfMaxKS && delta < 1e18f
-                              : hd->cfg.tile_cfg == 0 && fact_pays_l1(N, Rn, d) && KS <= kDirectHalfMaxKS && delta >= 0.f && delta < 1e18f);
+                              : hd->cfg.tile_cfg == 0 && (straight || hd->as_dense || fact_pays_l1(N, Rn, d)) && KS <= kDirectHalfMaxKS &&
+                                    delta >= 0.f && delta < 1e18f);
   // ... and the part of a pruned L2 join that the bound test can do nothing for
   const bool part_ok = p == 2 && prune && !win && !hd->static_mode && !hd->no_fact && hd->cfg.tile_cfg == 0 && hd->cfg.factorised == 0 &&
                        KS <= kDirectHalfMaxKS && delta >= 0.f && delta < 1e18f;
@@ -1495,7 +1558,6 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
   const bool reuse = prep_mode != kPrepFresh && pr.valid && pr.E == E && pr.Rv == Rvecs && pr.N == N && pr.d == d && pr.p == p &&
                      pr.dtype == dtype && pr.prune == (int)prune && pr.tile_id == tile_id && pr.delta == delta &&
                      pr.group_radius == hd->cfg.group_radius && !fact;
-  KGC_HIP(hd, hipEventRecord(hd->ev[0], st));
   if (!reuse) {
     k_fill_u32<<<grid_for(sizeof(DevCounters) / 4, 256), 256, 0, st>>>((uint32_t*)cnt, sizeof(DevCounters) / 4, 0u);
   } else {    // (the running maxima of the staged tail rows stay)
@@ -1515,9 +1577,14 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
   } else if (prune) {
     if ((rc = group_rows(hd, E, N, d, p, delta, KS, k16, &Nslots, &n_groups, &ut)) != KGC_OK) return rc;
     const int64_t units = (int64_t)ut.n_big + (hd->host_gstate->tail_fill + kMicro - 1) / kMicro;      // (without those that are all padding)
-    if (part_ok && units <= kFewUnits && fact_pays(N, Rn)) {
-      // (almost) all rows in one group: there is nothing to prune by, and the factorised kernel takes the join as a
-      // dense one.  Broad embeddings, N = 20,000, R = 37, d = 512: 71 -> 1.4 ms.
+    // (Almost) all rows in one group: there is nothing to prune by, and the factorised kernel takes the join as a dense one
+    // (broad embeddings, N = 20,000, R = 37, d = 512: 71 -> 1.2 ms).  With KGC_PRUNE_AUTO also where the groups are poor.
+    bool dense = part_ok && units <= kFewUnits && fact_pays(N, Rn);
+    if (!dense && automatic && grouped_badly(N, hd->host_gstate->tail_fill, (int)std::min<int64_t>(units, 1 << 30), hd->host_gstate->max_unit, dense_us)) {
+      if (p == 1 && share < 0.0 && (rc = close_share(hd, E, N, d, Rvecs, r_begin, Rn, delta, &share)) != KGC_OK) return rc;
+      dense = grouped_badly(N, hd->host_gstate->tail_fill, (int)std::min<int64_t>(units, 1 << 30), hd->host_gstate->max_unit, dense_us + listed_us());
+    }
+    if (dense) {
       float ms = 0.f;
       (void)hipEventElapsedTime(&ms, hd->ev[0], hd->ev[3]);
       hd->as_dense = true;

@@ -97,7 +97,7 @@ struct RecheckCtx {
 // the group returns the norm.  When the rows are 16-byte aligned (d % 4 == 0 for float32, d % 8 == 0 for
 // bfloat16) each lane reads 16-byte chunks, so that a candidate costs a couple of memory round trips
 // rather than one per dimension.
-__device__ __forceinline__ double group16_exact_dist(const RecheckCtx& cx, int32_t h, int32_t r, int32_t t, int sub) {
+__device__ __forceinline__ double group16_exact_sum(const RecheckCtx& cx, int32_t h, int32_t r, int32_t t, int sub) {
   const int d = cx.d;
   const int64_t ho = (int64_t)r * cx.hstride + (int64_t)h * d, to = (int64_t)r * cx.tstride + (int64_t)t * d,
                 ro = (int64_t)r * cx.rstride;
@@ -148,7 +148,11 @@ __device__ __forceinline__ double group16_exact_dist(const RecheckCtx& cx, int32
   s += __shfl_xor(s, 4, 16);
   s += __shfl_xor(s, 2, 16);
   s += __shfl_xor(s, 1, 16);
-  return p2 ? sqrt(s) : s;
+  return s;
+}
+__device__ __forceinline__ double group16_exact_dist(const RecheckCtx& cx, int32_t h, int32_t r, int32_t t, int sub) {
+  const double s = group16_exact_sum(cx, h, r, t, sub);
+  return cx.p == 2 ? sqrt(s) : s;
 }
 
 // NC candidates of one relation at once (same arithmetic per candidate as group16_exact_dist): the loads of

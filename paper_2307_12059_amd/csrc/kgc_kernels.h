@@ -1548,7 +1548,8 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1) void k_join_l2_direct(const JoinS
 // the next tile's first rows: 358 us and 4.24 ms before.  L1, 40,000, 18, 100: 611 -> 472 us; 20,011, 37, 512: 574 -> 379 us.
 // (With one level of 32 rows in place of levels 1 and 2, in the caller's order, half of all (relation, wave) pairs on 500 clusters
 // went to level 3.)
-// Candidates leave through a queue of 64 entries per wave (in LDS, no atomics) to a list in memory that
+// Candidates leave through a queue per wave (in LDS, no atomics; one atomic a flush, and those on one word are served one after
+// the other, about 8 ns each: up to 512 entries where the LDS has room) to a list in memory that
 // k_exact_pairs scores: a wave that scored its own would wait three memory round trips for one or two pairs.
 // A list that was too short is made longer by the host, which then runs the call again.
 struct JoinFactArgs {
@@ -1568,12 +1569,13 @@ struct JoinFactArgs {
   unsigned long long* list_count;  // (may run past list_cap)
   unsigned int list_cap;
   unsigned long long give_up;      // with so many pairs listed the host takes another form: the waves end
+  int queue;                 // candidates a wave holds back, kFactQueue at least
 };
-constexpr int kFactQueue = 64;         // candidates a wave holds back
+constexpr int kFactQueue = 64;         // candidates a wave holds back, at least: as many as the LDS has room for (JoinFactArgs::queue)
 constexpr int kFactBatch = 4;          // relations whose r.t and r.h a lane has in flight together
 constexpr int kFactChunks = 3;         // chunks of 64 relations whose level-1 loads are in flight together
 constexpr int kFactIds = 64 + 64 * kFactChunks;      // relations that level 1 has left open and level 2 has not taken yet
-constexpr size_t kFactWaveLds = 2 * kFactQueue * 4 + kFactIds * 2;      // (eight times this beside 19 slices of 128 rows fill the LDS)
+inline __host__ __device__ size_t fact_wave_lds(int queue) { return (size_t)queue * 8 + kFactIds * 2; }      // (with kFactQueue, eight times this beside 19 slices of 128 rows fill the LDS)
 
 // Per-relation filter thresholds of the factorised join: limr[rl] = thr_r - ||r||^2.  A hit x = h + r - t, ||x|| <= delta,
 // has on the bf16-rounded rows x~ = h~ + r - t~ with ||x~|| <= delta + e_h + e_t (e = the distance that the rounding moves a
@@ -1774,9 +1776,9 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1) void k_join_l2_fact(const JoinFac
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WGN, wn = wave % WGN;
   constexpr int NC = kFactChunks;
-  char* wlds = (char*)(lds + (size_t)KS * ASZ) + wave * kFactWaveLds;
-  uint32_t* q = (uint32_t*)wlds;                           // candidates: relation << 16 | head row of the wave, tail slot
-  uint16_t* ids = (uint16_t*)(wlds + 2 * kFactQueue * 4);  // relations of the batch (fewer than 65,536) that level 1 left open
+  char* wlds = (char*)(lds + (size_t)KS * ASZ) + wave * fact_wave_lds(a.queue);
+  uint16_t* ids = (uint16_t*)wlds;  // relations of the batch (fewer than 65,536) that level 1 left open
+  uint2* q = (uint2*)(wlds + kFactIds * 2);                // candidates: relation << 16 | head row of the wave, tail slot
   int qn = 0;                                              // entries in the queue (the same in all lanes)
 
   const int tH = (int)blockIdx.x;
@@ -1827,10 +1829,10 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1) void k_join_l2_fact(const JoinFac
     if (fl == 0) base = atomicAdd(a.list_count, (unsigned long long)qn);                          \
     base = ((unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(base >> 32)) << 32) | \
            (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)base);                         \
-    if (fl < qn && base + (unsigned)fl < a.list_cap) {                                            \
+    for (int k = fl; k < qn && base + (unsigned)k < a.list_cap; k += 64) {                        \
       ExactEntry e;                                                                               \
-      e.r = a.r0 + (int32_t)(q[fl] >> 16); e.hs0 = hrow0 + (int32_t)(q[fl] & 0xffffu); e.ts0 = (int32_t)q[kFactQueue + fl]; e.pad = 0; \
-      a.list[base + (unsigned)fl] = e;                                                            \
+      e.r = a.r0 + (int32_t)(q[k].x >> 16); e.hs0 = hrow0 + (int32_t)(q[k].x & 0xffffu); e.ts0 = (int32_t)q[k].y; e.pad = 0; \
+      a.list[base + (unsigned)k] = e;                                                             \
     }                                                                                             \
     if (base > a.give_up) return;                                                                 \
     qn = 0;                                                                                       \
@@ -2040,12 +2042,11 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1) void k_join_l2_fact(const JoinFac
               const unsigned long long b = __builtin_amdgcn_ballot_w64(cm != 0u);
               if (b == 0ull) break;
               const int n = __builtin_popcountll(b);
-              if (qn + n > kFactQueue) KGC_FLUSH();
+              if (qn + n > a.queue) KGC_FLUSH();
               if (cm != 0u) {
                 const int e = __builtin_ctz(cm);
                 const int pos = qn + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u));
-                q[pos] = (uint32_t)rel << 16 | (uint32_t)(8 * g + 4 * (lq >> 5) + (e & 3));
-                q[kFactQueue + pos] = (uint32_t)(tcol + (e >> 2) * 32 + (lq & 31));
+                q[pos] = make_uint2((uint32_t)rel << 16 | (uint32_t)(8 * g + 4 * (lq >> 5) + (e & 3)), (uint32_t)(tcol + (e >> 2) * 32 + (lq & 31)));
                 cm &= cm - 1u;
               }
               qn += n;
@@ -2090,20 +2091,18 @@ __global__ __launch_bounds__(256) void k_exact_pairs(const ExactEntry* __restric
       r = en.r; h = cx.slot_ent[en.hs0]; t = cx.slot_ent_t[en.ts0];
       if (h < 0 || t < 0 || (cx.no_self && h == t)) h = -1;
     }
-    bool hit = false;
-    float distf = 0.f;
+    double sum = 0.0;                                      // of entry `lane` (one root for 64 entries, not one for four)
     for (int s = 0; s < (int)(per >> 2); ++s) {
       if (first + (unsigned)s * 4u >= n) break;            // the same for the whole wave
       const int src = 4 * s + grp;
       const int32_t hs = __shfl(h, src, 64), rs = __shfl(r, src, 64), ts = __shfl(t, src, 64);
-      const double dist = hs >= 0 ? group16_exact_dist(cx, hs, rs, ts, sub) : 0.0;
-      const int ok = (hs >= 0 && dist <= cx.delta) ? 1 : 0;
-      const float df = (float)dist;
-      const int from = 16 * (lane & 3);
-      const int okl = __shfl(ok, from, 64);
-      const float dl = __shfl(df, from, 64);
-      if ((lane >> 2) == s) { hit = okl != 0; distf = dl; }
+      const double g = hs >= 0 ? group16_exact_sum(cx, hs, rs, ts, sub) : 0.0;
+      const double gl = __shfl(g, 16 * (lane & 3), 64);
+      if ((lane >> 2) == s) sum = gl;
     }
+    const double dist = cx.p == 2 ? sqrt(sum) : sum;
+    const bool hit = h >= 0 && dist <= cx.delta;
+    const float distf = (float)dist;
     const unsigned long long m = __builtin_amdgcn_ballot_w64(hit);
     if (lane == 0) wave_hits[wave] = (unsigned int)__builtin_popcountll(m);
     __syncthreads();
@@ -2170,6 +2169,26 @@ __global__ __launch_bounds__(256) void k_top1_sample(RecheckCtx cx, int64_t N, i
     best = o < best ? o : best;
   }
   if ((threadIdx.x & 63) == 0 && best != ~0ull) atomicMin(&st->sample_min, best);
+}
+
+// How many of kSampleTriples random triples lie within cx.delta, counted by workgroup: one triple per 16-lane group and step.
+constexpr int kSampleBlocks = 256, kSampleSteps = 4, kSampleTriples = kSampleBlocks * 16 * kSampleSteps;      // (a step is two memory round trips)
+__global__ __launch_bounds__(256) void k_sample_close(RecheckCtx cx, int64_t N, int r_begin, int R, unsigned int* __restrict__ counts) {
+  __shared__ unsigned int n_s;
+  if (threadIdx.x == 0) n_s = 0;
+  __syncthreads();
+  const int sub = threadIdx.x & 15, grp = threadIdx.x >> 4;
+  unsigned int n = 0;
+  for (int i = 0; i < kSampleSteps; ++i) {
+    const uint32_t k = ((uint32_t)blockIdx.x * kSampleSteps + (uint32_t)i) * 16u + (uint32_t)grp;
+    const int32_t h = (int32_t)(((uint64_t)top1_hash(k * 3u + 1u) * (uint64_t)N) >> 32);
+    const int32_t t = (int32_t)(((uint64_t)top1_hash(k * 3u + 2u) * (uint64_t)N) >> 32);
+    const int32_t r = r_begin + (int32_t)(((uint64_t)top1_hash(k * 3u + 3u) * (uint64_t)R) >> 32);
+    if (group16_exact_dist(cx, h, r, t, sub) <= cx.delta) ++n;
+  }
+  if (sub == 0 && n) atomicAdd(&n_s, n);
+  __syncthreads();
+  if (threadIdx.x == 0) counts[blockIdx.x] = n_s;
 }
 
 __global__ __launch_bounds__(256) void k_top1_min(const kgc_triple* __restrict__ rec, const unsigned long long* __restrict__ count,
