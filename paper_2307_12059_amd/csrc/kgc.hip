@@ -1084,16 +1084,21 @@ int top_bounds(kgc_handle* hd, const void* E, int64_t N, int32_t d, const void* 
   const int n_sample = kTopSamples;
   k_fill_u32<<<1, 64, 0, st>>>((uint32_t*)ts, sizeof(Top1State) / 4, 0xffffffffu);
   k_top1_sample<<<1024, 256, 0, st>>>(cx, N, r_begin, R, n_sample, exclude_self ? 1 : 0, ts, dev_samples);
-  // 1b. (L2, head tile fits in LDS, enough entities)  A random triple is almost never a close one, so the
+  // 1b. (head tile fits in LDS, enough entities)  A random triple is almost never a close one, so the
   //     sampled bound is usually far above the answer, where a join prunes nothing.  A dense pass over a
   //     sub-sample -- up to 8,192 heads x 8,192 other tails x the first 32 relations, the barrier-free kernel
-  //     with an epilogue that keeps only the smallest squared distance -- costs about a millisecond and
-  //     usually lands within a few tens of percent of the answer.
+  //     with an epilogue that keeps only the smallest squared distance -- usually lands within a few tens of percent
+  //     of the answer.  2,048 or 4,096 rows a side do where they hold as many triples as half of one relation's
+  //     pairs (clusters of eight rows then have thirty aligned pairs among them): N = 15,000: 350 -> 22 us for the pass.
   const int KS = (d + kNormCols + kSliceK - 1) / kSliceK;
-  const bool sub_pass = KS <= kDirectMaxKS && N >= 1024;
+  // (with more than nine slices only where a join at the sampled bound would be long: 13,238, 52, 410: 850 us without, 1,110 with it;
+  // 67,262, 366, 499: seconds and 9.5 ms)
+  const bool sub_pass = N >= 1024 && (KS <= kDirectMaxKS || (KS <= kDirectHalfMaxKS && (double)N * (double)N * (double)R >= 1e10));
   if (sub_pass) {     // (the pass measures in L2; for an L1 search its bound is scaled below)
-    const int m = (int)std::min<int64_t>(8192, (N / 2) / 256 * 256);
     const int Rs = (int)std::min<int32_t>(R, 32);
+    int64_t rows = 2048;
+    while (rows < 8192 && 2.0 * Rs * (double)rows * (double)rows < (double)N * (double)N) rows *= 2;
+    const int m = (int)std::min<int64_t>(rows, (N / 2) / 256 * 256);
     const int k16 = (d + kNormCols + 15) / 16;
     const size_t op_rows = (size_t)KS * m * kSliceK * 2;
     if ((rc = ensure(hd, hd->top1_pick, (size_t)2 * m * 4)) || (rc = ensure(hd, hd->top1_b, op_rows)) ||
@@ -1113,13 +1118,13 @@ int top_bounds(kgc_handle* hd, const void* E, int64_t N, int32_t d, const void* 
         kStageRows);
     JoinStreamArgs sa{};
     sa.A = (const uint16_t*)hd->top1_a.p; sa.B = (const uint16_t*)hd->top1_b.p; sa.prm = nullptr; sa.Nslots = m;
-    sa.KS = KS; sa.k16 = k16; sa.nH = m / 256; sa.nT = m / 256; sa.r0 = 0; sa.RB = Rs; sa.thr_value = 0.f;
+    const int bm = KS <= kDirectMaxKS ? 256 : 128;
+    void (*kern)(const JoinStreamArgs) = bm == 256 ? k_join_l2_direct<256, 2, 4, kEpiMinDist> : k_join_l2_direct<128, 1, 8, kEpiMinDist>;
+    sa.KS = KS; sa.k16 = k16; sa.nH = m / bm; sa.nT = m / 256; sa.r0 = 0; sa.RB = Rs; sa.thr_value = 0.f;
     sa.best = &ts->sub_min;
-    const size_t dyn_lds = (size_t)KS * 256 * kSliceK * 2;
-    KGC_HIP(hd, hipFuncSetAttribute((const void*)k_join_l2_direct<256, 2, 4, kEpiMinDist>,
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn_lds));
-    hipLaunchKernelGGL((k_join_l2_direct<256, 2, 4, kEpiMinDist>), dim3((unsigned)(m / 256), (unsigned)Rs, 1), dim3(512), dyn_lds,
-                       st, sa);
+    const size_t dyn_lds = (size_t)KS * bm * kSliceK * 2;
+    KGC_HIP(hd, hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn_lds));
+    hipLaunchKernelGGL(kern, dim3((unsigned)sa.nH, (unsigned)Rs, 1), dim3(512), dyn_lds, st, sa);
     k_top1_bound<<<1, 64, 0, st>>>(cnt, hd->cfg.dtype, KS * kSliceK, ts);
   }
   // one read-back for both
