@@ -251,6 +251,23 @@ JoinL1Kernel l1_kernel_for(const RecheckCtx& cx) {
   return bf ? (vec ? k_join_l1<true, true> : k_join_l1<true, false>) : (vec ? k_join_l1<false, true> : k_join_l1<false, false>);
 }
 
+// a batch of a pruned L1 join by pairs of micro-tiles (k_l1_blocks): the blocks that the bound leaves of the listed tiles, their
+// pairs within the filter's threshold, the scores; both lists empty again afterwards
+void launch_l1_blocks(hipStream_t st, const L1MicroArgs& ma, JoinL1Args la, unsigned row_grid, ExactEntry* pairs, unsigned int pair_cap,
+                      DevCounters* cnt) {
+  const RecheckCtx& cx = la.cx;
+  const JoinParams* prm = la.prm;
+  k_l1_micro_pairs<<<512, 256, 0, st>>>(ma);
+  const bool bf = cx.dtype == KGC_BF16, vec = cx.vec_ok != 0;
+  auto kern = bf ? (vec ? k_l1_blocks<true, true> : k_l1_blocks<true, false>) : (vec ? k_l1_blocks<false, true> : k_l1_blocks<false, false>);
+  hipLaunchKernelGGL(kern, dim3(1024), dim3(256), 0, st, (const ExactEntry*)ma.list, (const unsigned int*)ma.count, ma.cap, &cnt->tile_cursor,
+                     &cnt->exact_need, prm, cx, pairs, &cnt->n_fact, pair_cap);
+  k_exact_pairs<<<2048, 256, 0, st>>>(pairs, &cnt->n_fact, pair_cap, &cnt->fact_need, cx);
+  la.block_count = ma.count; la.tile_total = &cnt->tile_cursor;      // (the batch whole tiles are better for)
+  hipLaunchKernelGGL(l1_kernel_for(cx), dim3(row_grid), dim3(256), 0, st, la);
+  k_fill_u32<<<1, 64, 0, st>>>(&cnt->n_exact, (sizeof(DevCounters) - offsetof(DevCounters, n_exact)) / 4, 0u);
+}
+
 // out[i][j] = x_i . y_j, one wave per 32 x 32 results on the float32 matrix pipes (k_small_dot): X rows of the storage
 // type, Y rows float32
 void launch_small_dot(hipStream_t st, const void* X, int dtype, int64_t n_rows, const float* Y, int64_t n_cols, int d, float* out) {
@@ -632,6 +649,13 @@ int kgc_join_ab(kgc_handle* hd, const void* A, const void* B, int64_t N, int32_t
                 (rc = ensure(hd, hd->active_rows, (size_t)RBmax * nH * 4))))
     return rc;
   const unsigned row_grid_max = 4096;
+  // pruned L1 joins go by pairs of micro-tiles, while their list of pairs is to be had and holds what a batch leaves
+  const unsigned long long pairs_most = fact_list_max(N, R, 2, ws);
+  const unsigned int pair_cap = (unsigned int)std::min<unsigned long long>(
+      std::max(hd->fcap, hd->fcap_start > 0 ? hd->fcap_start : fact_list_start(N, R)), pairs_most);
+  bool l1_blocks = prune && p == 1 && !hd->no_fact && 16.0 * (double)tiles_per_rel * (double)RBmax < 4e9;      // (the blocks are counted in 32 bits)
+  if (l1_blocks && (rc = ensure(hd, hd->xlist, (size_t)hd->xcap * sizeof(ExactEntry)))) return rc;
+  if (l1_blocks && !have_list(hd, pair_cap)) l1_blocks = false;
   int nbatch = 0;
   for (int64_t r0 = 0; r0 < R; r0 += RBmax, ++nbatch) {
     const int RB = (int)std::min<int64_t>(RBmax, R - r0);
@@ -754,7 +778,16 @@ int kgc_join_ab(kgc_handle* hd, const void* A, const void* B, int64_t N, int32_t
       k_join_params<<<1, 64, 0, st>>>(cnt, prm, delta, p, dtype, d, 0);
       JoinL1Args la{};
       la.prm = prm; la.Nslots = Nslots; la.nH = nH; la.nT = nT; la.r0 = (int)r0; la.RB = RB; la.cx = cx;
-      if (prune) {
+      if (l1_blocks) {
+        L1MicroArgs ma{};
+        ma.row_start = (const uint32_t*)hd->row_start.p; ma.row_count = (const uint32_t*)hd->row_count.p; ma.cols = (const uint32_t*)hd->cols.p;
+        ma.active_rows = active_rows; ma.n_active = n_active; ma.nH = nH; ma.r0 = (int)r0;
+        ma.cent_h = (const float*)hd->cent_a.p; ma.rad_h = (const float*)hd->rad_a.p; ma.cent_t = (const float*)hd->cent.p; ma.rad_t = (const float*)hd->rad.p;
+        ma.h_rel = n_micro; ma.t_rel = b_per_relation ? n_micro : 0; ma.dtype = dtype; ma.d = d; ma.delta = delta;
+        la.row_start = ma.row_start; la.row_count = ma.row_count; la.cols = ma.cols; la.active_rows = active_rows; la.n_active = n_active;
+        ma.list = (ExactEntry*)hd->xlist.p; ma.count = &cnt->n_exact; ma.cap = hd->xcap;
+        launch_l1_blocks(st, ma, la, row_grid, (ExactEntry*)hd->flist.p, pair_cap, cnt);
+      } else if (prune) {
         la.row_start = (const uint32_t*)hd->row_start.p; la.row_count = (const uint32_t*)hd->row_count.p;
         la.cols = (const uint32_t*)hd->cols.p; la.active_rows = active_rows; la.n_active = n_active;
         hipLaunchKernelGGL(l1_kernel_for(la.cx), dim3(row_grid, 1, 1), dim3(256), 0, st, la);
@@ -776,6 +809,15 @@ int kgc_join_ab(kgc_handle* hd, const void* A, const void* B, int64_t N, int32_t
     const unsigned long long need = hd->host_counters->exact_need;
     hd->xcap = (unsigned int)std::min<unsigned long long>(need + need / 4 + 1024, 0xffffffffull);
     return kgc_join_ab(hd, A, B, N, d, R, b_per_relation, p, delta, out_triples, cap, count);
+  }
+  if (l1_blocks && hd->host_counters->fact_need > pair_cap) {      // (the same of the list of pairs; longer than it may be: without it)
+    const unsigned long long need = hd->host_counters->fact_need;
+    const bool keep = hd->no_fact;
+    if (need > pairs_most) hd->no_fact = true;
+    else hd->fcap = (unsigned int)std::min<unsigned long long>(need + need / 4 + 1024, kFactListMax);
+    rc = kgc_join_ab(hd, A, B, N, d, R, b_per_relation, p, delta, out_triples, cap, count);
+    hd->no_fact = keep;
+    return rc;
   }
 
   kgc_stats& s = hd->stats;
@@ -1525,7 +1567,7 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
   const bool l2_ops = p == 2 || fact;          // staged operands of the matrix pipes
   const int64_t ws = hd->ws_override > 0 ? hd->ws_override
                                            : hd->cfg.workspace_bytes > 0 ? hd->cfg.workspace_bytes : kDefaultWorkspace;
-  const unsigned long long fact_most = fact_list_max(N, Rn, p, ws);
+  const unsigned long long fact_most = fact_list_max(N, Rn, prune ? 2 : p, ws);      // (pruned L1: what the blocks leave, no try to lose)
   const unsigned int fact_cap = (unsigned int)std::min<unsigned long long>(
       std::max(hd->fcap, hd->fcap_start > 0 ? hd->fcap_start : fact_list_start(N, Rn)), fact_most);
   // The same call again without the list of pairs (dense: the kernels that contract every relation or sum in L1; a pruned join
@@ -1619,7 +1661,11 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
   const int64_t part_n = Nslots - part0;
   // the barrier-free kernel over tile lists hands its candidates on (not in a call that does without the list)
   const bool lists_pairs = prune && p == 2 && tile_id == kDirectL2Tile && !hd->no_fact;
-  if ((fact || part_n || lists_pairs) && !have_list(hd, fact_cap)) {
+  // pruned L1 joins by pairs of micro-tiles need both lists
+  const bool l1_blocks = prune && p == 1 && !win && !hd->static_mode && !hd->no_fact &&
+                         16.0 * (double)tiles_per_rel * (double)Rn < 4e9;      // (the blocks are counted in 32 bits)
+  if (l1_blocks && (rc = ensure(hd, hd->xlist, (size_t)hd->xcap * sizeof(ExactEntry)))) return rc;
+  if ((fact || part_n || lists_pairs || l1_blocks) && !have_list(hd, fact_cap)) {
     pr.valid = reuse;                                      // (what the handle held is still there)
     return without_list();
   }
@@ -2013,8 +2059,17 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
       la.n_active = n_active; la.cx = cx;
       if (!prune) { la.nH = nHw; la.nT = nTw; la.cx = cxw; }
       if (timed) KGC_HIP(hd, hipEventRecord(hd->join_ev[2 * b], st));
-      hipLaunchKernelGGL(l1_kernel_for(la.cx), prune ? dim3(row_grid, 1, 1) : dim3((unsigned)nTw, (unsigned)nHw, (unsigned)RB), dim3(256), 0,
-                         st, la);
+      if (l1_blocks) {
+        L1MicroArgs ma{};
+        ma.row_start = row_start; ma.row_count = row_count; ma.cols = cols; ma.active_rows = active_rows; ma.n_active = n_active;
+        ma.nH = nH; ma.r0 = (int)r0; ma.cent_h = ma.cent_t = (const float*)hd->cent.p; ma.rad_h = ma.rad_t = (const float*)hd->rad.p;
+        ma.shift = Rvecs; ma.dtype = dtype; ma.d = d; ma.delta = delta;
+        ma.list = (ExactEntry*)hd->xlist.p; ma.count = &cnt->n_exact; ma.cap = hd->xcap;
+        launch_l1_blocks(st, ma, la, row_grid, (ExactEntry*)hd->flist.p, fact_cap, cnt);
+      } else {
+        hipLaunchKernelGGL(l1_kernel_for(la.cx), prune ? dim3(row_grid, 1, 1) : dim3((unsigned)nTw, (unsigned)nHw, (unsigned)RB), dim3(256), 0,
+                           st, la);
+      }
       if (timed) KGC_HIP(hd, hipEventRecord(hd->join_ev[2 * b + 1], st));
     }
     hd->stats.join_launches++;

@@ -2344,8 +2344,16 @@ struct JoinL1Args {
   const uint32_t* cols;
   const uint32_t* active_rows;
   const unsigned int* n_active;
+  const unsigned int* block_count; const unsigned long long* tile_total;      // not NULL: a batch that l1_by_blocks sends to k_l1_blocks is left alone
   RecheckCtx cx;
 };
+// A pruned batch goes by 32 x 32 blocks where the bound leaves at most six of a tile's sixteen (a block of its own costs twice
+// its share of a tile: four times the rows to load for a pair), or where there are so few that whole tiles would leave the chip
+// idle.
+constexpr unsigned int kL1FewBlocks = 16384;
+__device__ __forceinline__ bool l1_by_blocks(const unsigned int* blocks, const unsigned long long* tiles) {
+  return *blocks <= kL1FewBlocks || (unsigned long long)*blocks <= 6ull * *tiles;
+}
 
 // Kernel 3.  One block of 256 threads scores 128 x 128 tiles of (heads, tails) for one relation in
 // float32 vector arithmetic only: acc += |(h_k + r_k) - t_k| (Section 4.3's dist for p = 1).  A tile is
@@ -2371,6 +2379,7 @@ __global__ __launch_bounds__(256, 3) void k_join_l1(const JoinL1Args a) {
   __shared__ int32_t hent[BM], tent[BN];
   __shared__ BlockQueue queue;
   __shared__ uint32_t decided[2][4];      // per slice (alternating) and wave: the wave's candidates are known
+  if (a.block_count && l1_by_blocks(a.block_count, a.tile_total)) return;
 
   const int tid = threadIdx.x, wave = tid >> 6;
   if (tid == 0) { queue.count = 0u; queue.pending = 0u; queue.flag = 0u; queue.nhits = 0u; }   // published by the first barrier
@@ -2493,6 +2502,121 @@ __global__ __launch_bounds__(256, 3) void k_join_l1(const JoinL1Args a) {
   }
   if (!a.row_start) break;
   }   // rows
+}
+
+// ---------------------------------------------------------------------------------------------
+// Pruned L1 joins by pairs of micro-tiles.  A surviving 128 x 128 tile of small groups holds a few 32 x 32 blocks that the
+// bound lets through among sixteen, and k_join_l1 sums all of it, one workgroup per row of tiles: the structured-embedding
+// join of N = 15,000, R = 64 spent 1.9 ms there, N = 40,000, R = 18, whose 105 tiles are fewer than compute units, 200 us.
+// Here the bound is asked again for the sixteen pairs of every surviving tile (k_l1_micro_pairs), the blocks it leaves are
+// listed and dealt to waves (k_l1_blocks), and the pairs within the filter's threshold go to k_exact_pairs: 46 + 392 + 189 us and 8 + 27 + 13 us.
+// One wave per listed 32 x 32 block: rows staged 16 dimensions at a time into the wave's own LDS, 4 x 4 sums per lane; a block
+// ends when every sum has passed the threshold (terms are >= 0).  Bound by the vector units, two operations per pair and
+// dimension.  Candidates leave through a queue per wave.
+constexpr int kL1PairQueue = 256;
+constexpr int kL1BlockStride = 36;     // floats per dimension in LDS: 16-byte rows, and the two halves of a row's dimensions on different banks
+template <bool BF16, bool VEC>
+__global__ __launch_bounds__(256) void k_l1_blocks(const ExactEntry* __restrict__ list, const unsigned int* __restrict__ count, unsigned int cap,
+                                                   const unsigned long long* __restrict__ tiles, unsigned int* __restrict__ need, const JoinParams* __restrict__ prm, const RecheckCtx cx,
+                                                   ExactEntry* __restrict__ pairs, unsigned long long* __restrict__ pair_count,
+                                                   unsigned int pair_cap) {
+  __shared__ __attribute__((aligned(16))) float stage[4][2][kL1K * kL1BlockStride];
+  __shared__ int32_t queue[4][3][kL1PairQueue];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  float* const As = stage[wave][0];
+  float* const Bs = stage[wave][1];
+  int32_t (&q)[3][kL1PairQueue] = queue[wave];
+  int qn = 0;
+  auto flush = [&]() {
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+    unsigned long long base = 0ull;
+    if (lane == 0) base = atomicAdd(pair_count, (unsigned long long)qn);
+    base = ((unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(base >> 32)) << 32) |
+           (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)base);
+    for (int k = lane; k < qn && base + (unsigned)k < pair_cap; k += 64) pairs[base + (unsigned)k] = ExactEntry{q[0][k], q[1][k], q[2][k], 0};
+    qn = 0;
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+  };
+  if (!l1_by_blocks(count, tiles)) return;
+  const unsigned int n = *count <= cap ? *count : 0u;      // (a list that did not fit: the host makes it longer and runs the call again)
+  if (blockIdx.x == 0 && threadIdx.x == 0 && *count) atomicMax(need, *count);
+  const float thr = prm->thr;
+  const int d = cx.d;
+  const int row = lane >> 1, sk0 = (lane & 1) * 8, ly = lane >> 3, lx = lane & 7;
+  for (unsigned int e = blockIdx.x * 4u + (unsigned)wave; e < n; e += gridDim.x * 4u) {
+    const ExactEntry en = list[e];
+    const int r = __builtin_amdgcn_readfirstlane(en.r), hs0 = __builtin_amdgcn_readfirstlane(en.hs0), ts0 = __builtin_amdgcn_readfirstlane(en.ts0);
+    const int he = cx.slot_ent[hs0 + row], te = cx.slot_ent_t[ts0 + row];
+    const int64_t ho = (int64_t)r * cx.hstride + (int64_t)(he < 0 ? 0 : he) * d, to = (int64_t)r * cx.tstride + (int64_t)(te < 0 ? 0 : te) * d,
+                  ro = (int64_t)r * cx.rstride;
+    float acc[4][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[i][j] = 0.f;
+    f32x4_t xh[2], xr[2], xt[2];
+#define KGC_L1_LOAD(k0)                                                     \
+  _Pragma("unroll") for (int g = 0; g < 2; ++g) {                           \
+    const int k = (k0) + sk0 + 4 * g;                                       \
+    xh[g] = exact_ld4<BF16, VEC>(cx.E, ho, k, d);                           \
+    xr[g] = exact_ld4<BF16, VEC>(cx.Rv, ro, k, d);                          \
+    xt[g] = exact_ld4<BF16, VEC>(cx.Et, to, k, d);                          \
+  }
+    KGC_L1_LOAD(0);
+    bool open = true;                  // the same for the whole wave
+    for (int k0 = 0; k0 < d && open; k0 += kL1K) {
+      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");       // the previous slice is consumed (a wave's LDS operations complete in order)
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int g = 0; g < 8; ++g) {
+        As[(sk0 + g) * kL1BlockStride + row] = he < 0 ? 1e38f : xh[g >> 2][g & 3] + xr[g >> 2][g & 3];
+        Bs[(sk0 + g) * kL1BlockStride + row] = te < 0 ? -1e38f : xt[g >> 2][g & 3];
+      }
+      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+      __builtin_amdgcn_wave_barrier();
+      if (k0 + kL1K < d) { KGC_L1_LOAD(k0 + kL1K); }
+#pragma unroll
+      for (int k = 0; k < kL1K; ++k) {
+        const float4 av = *(const float4*)(As + k * kL1BlockStride + ly * 4);
+        const float4 bv = *(const float4*)(Bs + k * kL1BlockStride + lx * 4);
+        const float x[4] = {av.x, av.y, av.z, av.w}, y[4] = {bv.x, bv.y, bv.z, bv.w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) acc[i][j] += fabsf(x[i] - y[j]);
+      }
+      float m = acc[0][0];             // (passes over a NaN, whose pair is no candidate either)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) m = fminf(m, acc[i][j]);
+      open = __builtin_amdgcn_ballot_w64(m <= thr) != 0ull;
+    }
+#undef KGC_L1_LOAD
+    if (!open) continue;
+    uint32_t cm = 0u;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (acc[i][j] <= thr) cm |= 1u << (i * 4 + j);
+    for (;;) {                         // one pair per lane and round into the queue
+      const unsigned long long b = __builtin_amdgcn_ballot_w64(cm != 0u);
+      if (b == 0ull) break;
+      const int m = __builtin_popcountll(b);
+      if (qn + m > kL1PairQueue) flush();
+      if (cm != 0u) {
+        const int c = __builtin_ctz(cm);
+        const int pos = qn + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u));
+        q[0][pos] = r; q[1][pos] = hs0 + ly * 4 + (c >> 2); q[2][pos] = ts0 + lx * 4 + (c & 3);
+        cm &= cm - 1u;
+      }
+      qn += m;
+    }
+  }
+  if (qn > 0) flush();
 }
 
 }  // namespace kgc

@@ -1461,4 +1461,83 @@ __global__ __launch_bounds__(256) void k_rows_from_bitmap(const uint32_t* __rest
   }
 }
 
+// The bound once more for the sixteen micro-tile pairs of every surviving 128 x 128 tile of a pruned L1 join (k_l1_blocks): one wave
+// per row of tiles, a lane per dimension.
+struct L1MicroArgs {
+  const uint32_t* row_start; const uint32_t* row_count; const uint32_t* cols; const uint32_t* active_rows;      // see JoinStreamArgs
+  const unsigned int* n_active;
+  int nH, r0;
+  const float* cent_h; const float* rad_h; const float* cent_t; const float* rad_t;      // micro-tile summaries of heads and tails ...
+  int64_t h_rel, t_rel;                // ... and how many of them per relation (0: the same for all)
+  const void* shift; int dtype, d;     // added to the heads' centres: shift[(r0 + relation) * d ...] (NULL: nothing)
+  float delta;
+  ExactEntry* list; unsigned int* count; unsigned int cap;      // surviving blocks: relation, first head slot, first tail slot
+};
+constexpr int kL1MicroQueue = 64;      // blocks a wave holds back: one atomic a flush
+__global__ __launch_bounds__(256) void k_l1_micro_pairs(const L1MicroArgs a) {
+  static_assert(kL1Tile == 4 * 32, "four micro-tiles a side");
+  __shared__ int32_t queue[4][3][kL1MicroQueue];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  int32_t (&q)[3][kL1MicroQueue] = queue[wave];
+  int qn = 0;
+  auto flush = [&]() {
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+    unsigned int base = 0u;
+    if (lane == 0) base = atomicAdd(a.count, (unsigned int)qn);
+    base = (unsigned int)__builtin_amdgcn_readfirstlane((int)base);
+    if (lane < qn && base + (unsigned)lane < a.cap) a.list[base + (unsigned)lane] = ExactEntry{q[0][lane], q[1][lane], q[2][lane], 0};
+    qn = 0;
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+  };
+  const unsigned int n_rows = *a.n_active;
+  for (unsigned int i = blockIdx.x * 4u + (unsigned)wave; i < n_rows; i += gridDim.x * 4u) {
+    const int64_t row = (int64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)a.active_rows[i]);
+    const int rl = (int)(row / a.nH), tH = (int)(row - (int64_t)rl * a.nH);
+    const int64_t mh = rl * a.h_rel + tH * 4;
+    const int t0 = __builtin_amdgcn_readfirstlane((int)a.row_start[row]), nt = __builtin_amdgcn_readfirstlane((int)a.row_count[row]);
+    for (int t = 0; t < nt; ++t) {
+      const int tT = __builtin_amdgcn_readfirstlane((int)a.cols[t0 + t]);
+      const int64_t mt = rl * a.t_rel + (int64_t)tT * 4;
+      float s[16];                     // this lane's part of the distance of head micro-tile p / 4 and tail micro-tile p % 4
+#pragma unroll
+      for (int p = 0; p < 16; ++p) s[p] = 0.f;
+      for (int k = lane; k < a.d; k += 64) {
+        float h[4], c[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) { h[j] = a.cent_h[(mh + j) * a.d + k]; c[j] = a.cent_t[(mt + j) * a.d + k]; }
+        const float sh = a.shift ? ld_elem(a.shift, (int64_t)(a.r0 + rl) * a.d + k, a.dtype) : 0.f;
+#pragma unroll
+        for (int p = 0; p < 16; ++p) s[p] += fabsf(h[p >> 2] + sh - c[p & 3]);
+      }
+      // totals by halving exchanges: lane l ends up with pair 8 b5 + 4 b4 + 2 b3 + b2 (bits of l)
+      const bool b5 = lane & 32, b4 = lane & 16, b3 = lane & 8, b2 = lane & 4;
+      float s8[8], s4[4], s2[2], s1;
+#pragma unroll
+      for (int p = 0; p < 8; ++p) s8[p] = (b5 ? s[p + 8] : s[p]) + __shfl_xor(b5 ? s[p] : s[p + 8], 32, 64);
+#pragma unroll
+      for (int p = 0; p < 4; ++p) s4[p] = (b4 ? s8[p + 4] : s8[p]) + __shfl_xor(b4 ? s8[p] : s8[p + 4], 16, 64);
+#pragma unroll
+      for (int p = 0; p < 2; ++p) s2[p] = (b3 ? s4[p + 2] : s4[p]) + __shfl_xor(b3 ? s4[p] : s4[p + 2], 8, 64);
+      s1 = (b2 ? s2[1] : s2[0]) + __shfl_xor(b2 ? s2[0] : s2[1], 4, 64);
+      s1 += __shfl_xor(s1, 2, 64);
+      s1 += __shfl_xor(s1, 1, 64);
+      const int p = lane >> 2;
+      const float rh = a.rad_h[mh + (p >> 2)], rt = a.rad_t[mt + (p & 3)];
+      // (the bound of k_tile_dist's BOUND form; an empty micro-tile has radius -1)
+      const bool keep = (lane & 3) == 0 && rh >= 0.f && rt >= 0.f && !(s1 * (1.f - kBoundSlack) - rh - rt > a.delta * (1.f + kBoundSlack));
+      const unsigned long long b = __builtin_amdgcn_ballot_w64(keep);
+      const int n = __builtin_popcountll(b);
+      if (qn + n > kL1MicroQueue) flush();
+      if (keep) {
+        const int pos = qn + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u));
+        q[0][pos] = a.r0 + rl; q[1][pos] = tH * kL1Tile + (p >> 2) * 32; q[2][pos] = tT * kL1Tile + (p & 3) * 32;
+      }
+      qn += n;
+    }
+  }
+  if (qn > 0) flush();
+}
+
 }  // namespace kgc
