@@ -669,16 +669,16 @@ int kgc_join_ab(kgc_handle* hd, const void* A, const void* B, int64_t N, int32_t
               B, dtype, d, slot_ent, n_micro, (float*)hd->cent.p, (float*)hd->rad.p, (float*)hd->cnorm.p,
               b_per_relation ? (int)r0 : 0, b_per_relation ? (int64_t)N * d : 0);
         else
-          k_micro_summary<1><<<dim3((unsigned)n_micro, (unsigned)(b_per_relation ? RB : 1), 1), 64, 0, st>>>(
+          k_micro_summary<1, true><<<dim3((unsigned)n_micro, (unsigned)(b_per_relation ? RB : 1), 1), 64, 0, st>>>(
               B, dtype, d, slot_ent, n_micro, (float*)hd->cent.p, (float*)hd->rad.p, (float*)hd->cnorm.p,
-              b_per_relation ? (int)r0 : 0, b_per_relation ? (int64_t)N * d : 0);
+              b_per_relation ? (int)r0 : 0, b_per_relation ? (int64_t)N * d : 0, cnt->max_b);
       }
       if (p == 2)
         k_micro_summary<2><<<dim3((unsigned)n_micro, (unsigned)RB, 1), 64, 0, st>>>(
             A, dtype, d, slot_ent, n_micro, (float*)hd->cent_a.p, (float*)hd->rad_a.p, (float*)hd->cnorm.p, (int)r0, (int64_t)N * d);
       else
-        k_micro_summary<1><<<dim3((unsigned)n_micro, (unsigned)RB, 1), 64, 0, st>>>(
-            A, dtype, d, slot_ent, n_micro, (float*)hd->cent_a.p, (float*)hd->rad_a.p, (float*)hd->cnorm.p, (int)r0, (int64_t)N * d);
+        k_micro_summary<1, true><<<dim3((unsigned)n_micro, (unsigned)RB, 1), 64, 0, st>>>(
+            A, dtype, d, slot_ent, n_micro, (float*)hd->cent_a.p, (float*)hd->rad_a.p, (float*)hd->cnorm.p, (int)r0, (int64_t)N * d, cnt->max_a);
       const int64_t bm_words = (int64_t)RB * nH * words_per_row;
       k_fill_u32<<<grid_for(bm_words, 256), 256, 0, st>>>((uint32_t*)hd->bitmap.p, bm_words, 0u);
       TileDistArgs ta{};
@@ -769,9 +769,10 @@ int kgc_join_ab(kgc_handle* hd, const void* A, const void* B, int64_t N, int32_t
         k_fill_u32<<<1, 64, 0, st>>>(&cnt->n_exact, 1, 0u);
       }
     } else {
-      k_row_l1_max<<<grid_l1_max((int64_t)RB * N), 256, 0, st>>>((const char*)A + (size_t)r0 * N * d * esz, (int64_t)RB * N, d,
-                                                                    dtype, cnt->max_a);
-      if (b_per_relation || r0 == 0)
+      if (!prune)      // (the summaries of a pruned join take the largest norms on the way)
+        k_row_l1_max<<<grid_l1_max((int64_t)RB * N), 256, 0, st>>>((const char*)A + (size_t)r0 * N * d * esz, (int64_t)RB * N, d,
+                                                                      dtype, cnt->max_a);
+      if (!prune && (b_per_relation || r0 == 0))
         k_row_l1_max<<<grid_l1_max((int64_t)(b_per_relation ? RB : 1) * N), 256, 0, st>>>(
             (const char*)B + (b_per_relation ? (size_t)r0 * N * d * esz : 0), (int64_t)(b_per_relation ? RB : 1) * N, d, dtype,
             cnt->max_b);

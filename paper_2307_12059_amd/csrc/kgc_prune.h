@@ -300,11 +300,30 @@ __global__ __launch_bounds__(1024) void k_order_sort(const int32_t* __restrict__
 // are independent of each other (one memory round trip), the chunk's centre values come from their sum, and each
 // row's distance to the centre grows by its part of the chunk; the 32 row sums are then added across the lanes by a
 // halving exchange (32 shuffles).
-template <int P>
+// With MAXL1 the largest L1 norm of a row, which the L1 filter's error bound asks for, is taken on the way (max_l1; the float32 sums
+// run in another order than k_row_l1_max's: the bound they enter is widened by far more): two summaries and two passes of
+// k_row_l1_max over 384 MB of connector rows each took 201 + 147 us, now 240.
+__device__ __forceinline__ float micro_row_totals(const float (&rs)[kMicro], int lane) {
+  // after the five halving steps lane l holds the sum of row 16 b5 + 8 b4 + 4 b3 + 2 b2 + b1 (bits of l)
+  float a16[16], a8[8], a4[4], a2[2], a1;
+  const bool b5 = lane & 32, b4 = lane & 16, b3 = lane & 8, b2 = lane & 4, b1 = lane & 2;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) a16[i] = (b5 ? rs[i + 16] : rs[i]) + __shfl_xor(b5 ? rs[i] : rs[i + 16], 32, 64);
+#pragma unroll
+  for (int i = 0; i < 8; ++i) a8[i] = (b4 ? a16[i + 8] : a16[i]) + __shfl_xor(b4 ? a16[i] : a16[i + 8], 16, 64);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) a4[i] = (b3 ? a8[i + 4] : a8[i]) + __shfl_xor(b3 ? a8[i] : a8[i + 4], 8, 64);
+#pragma unroll
+  for (int i = 0; i < 2; ++i) a2[i] = (b2 ? a4[i + 2] : a4[i]) + __shfl_xor(b2 ? a4[i] : a4[i + 2], 4, 64);
+  a1 = (b1 ? a2[1] : a2[0]) + __shfl_xor(b1 ? a2[0] : a2[1], 2, 64);
+  return a1 + __shfl_xor(a1, 1, 64);
+}
+template <int P, bool MAXL1 = false>
 __global__ __launch_bounds__(64) void k_micro_summary(const void* __restrict__ E, int dtype, int d,
                                                       const int32_t* __restrict__ slot_ent, int64_t n_micro,
                                                       float* __restrict__ cent, float* __restrict__ rad,
-                                                      float* __restrict__ cnorm, int r0 = 0, int64_t rel_stride = 0) {
+                                                      float* __restrict__ cnorm, int r0 = 0, int64_t rel_stride = 0,
+                                                      unsigned int* __restrict__ max_l1 = nullptr) {
   // blockIdx.y: relation of a batch, for per-relation rows E[(r0 + y) * rel_stride + ...] (summaries then lie
   // relation after relation); one relation and rel_stride 0 for the TransE join
   static_assert(kMicro == 32, "the row sums below are laid out for 32 rows");
@@ -326,6 +345,9 @@ __global__ __launch_bounds__(64) void k_micro_summary(const void* __restrict__ E
   float rs[kMicro];                                   // this lane's part of every row's distance to the centre
 #pragma unroll
   for (int q = 0; q < kMicro; ++q) rs[q] = 0.f;
+  float l1[MAXL1 ? kMicro : 1];                       // ... and of its L1 norm
+#pragma unroll
+  for (int q = 0; q < (MAXL1 ? kMicro : 1); ++q) l1[q] = 0.f;
   for (int k0 = 0; k0 < d; k0 += 64) {
     const int k = k0 + lane;
     float v[kMicro];
@@ -336,6 +358,10 @@ __global__ __launch_bounds__(64) void k_micro_summary(const void* __restrict__ E
       for (int q = 0; q < kMicro; ++q) {
         const int32_t ent = __builtin_amdgcn_readlane(ent_l, q);
         if (ent >= 0) v[q] = ld_elem(E, (int64_t)ent * d + k, dtype);
+      }
+      if constexpr (MAXL1) {
+#pragma unroll
+        for (int q = 0; q < kMicro; ++q) l1[q] += fabsf(v[q]);
       }
       float sum = 0.f;
 #pragma unroll
@@ -352,24 +378,15 @@ __global__ __launch_bounds__(64) void k_micro_summary(const void* __restrict__ E
   }
   for (int off = 32; off > 0; off >>= 1) c2 += __shfl_xor(c2, off, 64);
   if (lane == 0) cnorm[m] = sqrtf(c2) * (1.f + kBoundSlack);
-  // row totals: after the five halving steps lane l holds the sum of row 16 b5 + 8 b4 + 4 b3 + 2 b2 + b1 (bits of l)
-  float a16[16], a8[8], a4[4], a2[2], a1;
-  {
-    const bool b5 = lane & 32, b4 = lane & 16, b3 = lane & 8, b2 = lane & 4, b1 = lane & 2;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) a16[i] = (b5 ? rs[i + 16] : rs[i]) + __shfl_xor(b5 ? rs[i] : rs[i + 16], 32, 64);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) a8[i] = (b4 ? a16[i + 8] : a16[i]) + __shfl_xor(b4 ? a16[i] : a16[i + 8], 16, 64);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) a4[i] = (b3 ? a8[i + 4] : a8[i]) + __shfl_xor(b3 ? a8[i] : a8[i + 4], 8, 64);
-#pragma unroll
-    for (int i = 0; i < 2; ++i) a2[i] = (b2 ? a4[i + 2] : a4[i]) + __shfl_xor(b2 ? a4[i] : a4[i + 2], 4, 64);
-    a1 = (b1 ? a2[1] : a2[0]) + __shfl_xor(b1 ? a2[0] : a2[1], 2, 64);
-    a1 += __shfl_xor(a1, 1, 64);
-  }
+  const float a1 = micro_row_totals(rs, lane);
   float rmax = (P == 2) ? sqrtf(a1) : a1;             // (a missing row has sum 0)
   for (int off = 32; off > 0; off >>= 1) rmax = fmaxf(rmax, __shfl_xor(rmax, off, 64));
   if (lane == 0) rad[m] = rmax * (1.f + kBoundSlack) + 1e-30f;
+  if constexpr (MAXL1) {
+    float n = micro_row_totals(l1, lane);             // (a missing row has sum 0)
+    for (int off = 32; off > 0; off >>= 1) n = fmaxf(n, __shfl_xor(n, off, 64));
+    if (lane == 0) atomicMax(&max_l1[(blockIdx.x + blockIdx.y * gridDim.x) % kMaxSlots], __float_as_uint(n));      // non-negative floats order like their bits
+  }
 }
 
 // ---------------------------------------------------------------------------------------------
