@@ -1541,11 +1541,12 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1) void k_join_l2_direct(const JoinS
 // On embeddings in clusters level 1 leaves a relation open where its source cluster has a member among the head rows or
 // its target cluster among the tail columns, level 2 where eight rows hold both a member of the source cluster and a
 // neighbour of the tail.  The candidates are those of the pair-wise filter.
-// Measured (dense joins, rows in order, kernel alone): N = 15,000, R = 1,345, d = 100: 245 us; N = 100,000, R = 200, d = 200: 3.7 ms,
-// 1.13 PFLOP/s over its contraction.  What bounds it there is issue: matrix pipes 50 % and vector pipes 39 % busy before the
-// accumulators were no longer cleared (a zero operand), minima lost their canonicalising v_max, exchanges between lanes left
-// the LDS, and level 1 kept what a block's tiles share in registers and the rest in flight under the contraction, as are
-// the next tile's first rows: 358 us and 4.24 ms before.  L1, 40,000, 18, 100: 611 -> 472 us; 20,011, 37, 512: 574 -> 379 us.
+// Measured (dense joins, rows in order, kernel alone): N = 15,000, R = 1,345, d = 100: 257 us; N = 100,000, R = 200, d = 200: 3.6 ms,
+// 1.15 PFLOP/s over its contraction.  What bounds it there is issue: matrix pipes 50 % and vector pipes 39 % busy (358 us and
+// 4.24 ms) before the accumulators were no longer cleared (a zero operand), minima lost their canonicalising v_max, exchanges
+// between lanes left the LDS, and level 1 kept what a block's tiles share in registers and the rest in flight under the
+// contraction, as are the next tile's first rows; 59 % and 32 % now.  L1, 40,000, 18, 100: 611 -> 414 us; 20,011, 37, 512: 574 ->
+// 374 us.
 // (With one level of 32 rows in place of levels 1 and 2, in the caller's order, half of all (relation, wave) pairs on 500 clusters
 // went to level 3.)
 // Candidates leave through a queue per wave (in LDS, no atomics; one atomic a flush, and those on one word are served one after
