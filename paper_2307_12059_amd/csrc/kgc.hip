@@ -1910,7 +1910,7 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
         TileDistArgs ta{};
         ta.X = hd->cent.p; ta.dtypeX = KGC_F32; ta.row_ids = nullptr; ta.n_rows_dev = nullptr; ta.n_rows = n_micro;
         ta.Y = hd->cent.p; ta.dtypeY = KGC_F32; ta.col_ids = nullptr; ta.n_cols_dev = nullptr; ta.n_cols = n_micro;
-        ta.shift = Rvecs; ta.dtype_shift = dtype; ta.r0 = (int)r0; ta.d = d;
+        ta.shift = Rvecs; ta.dtype_shift = dtype; ta.r0 = (int)r0; ta.d = d; ta.prm = prm;
         ta.rad = (const float*)hd->rad.p; ta.delta = delta; ta.bitmap = (uint32_t*)hd->bitmap.p;
         ta.nH = nH; ta.words_per_row = words_per_row; ta.micro_per_bm = BM / kMicro; ta.micro_per_bn = BN / kMicro;
         if (use_units) {
@@ -2064,7 +2064,7 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
         L1MicroArgs ma{};
         ma.row_start = row_start; ma.row_count = row_count; ma.cols = cols; ma.active_rows = active_rows; ma.n_active = n_active;
         ma.nH = nH; ma.r0 = (int)r0; ma.cent_h = ma.cent_t = (const float*)hd->cent.p; ma.rad_h = ma.rad_t = (const float*)hd->rad.p;
-        ma.shift = Rvecs; ma.dtype = dtype; ma.d = d; ma.delta = delta;
+        ma.shift = Rvecs; ma.prm = prm; ma.dtype = dtype; ma.d = d; ma.delta = delta;
         ma.list = (ExactEntry*)hd->xlist.p; ma.count = &cnt->n_exact; ma.cap = hd->xcap;
         launch_l1_blocks(st, ma, la, row_grid, (ExactEntry*)hd->flist.p, fact_cap, cnt);
       } else {

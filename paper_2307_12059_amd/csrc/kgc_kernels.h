@@ -29,7 +29,8 @@ constexpr int kMaxSlots = 1024;
 // device-side scalars of one join
 struct JoinParams {
   float thr;            // filter threshold: on the squared distance (L2) or on the float32 sum (L1)
-  float pad[3];
+  float base;           // L1: what the rounding of coordinates h + r can add to a sum (L2: 0, unused)
+  float pad[2];
 };
 
 struct DevCounters {
@@ -375,17 +376,18 @@ __global__ __launch_bounds__(64) void k_join_params(DevCounters* cnt, JoinParams
     mb = fmaxf(mb, __shfl_xor(mb, off, 64));
   }
   if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  float thr;
+  float thr, base = 0.f;
+  if (p == 1) base = 1.2e-7f * (ma + mb);
   if (delta < 0.f) {
     thr = -1.f;                                   // squared distances and sums are >= 0: nothing passes
   } else if (p == 2) {
     const float eacc = (float)(kp + 16) * 1.2e-7f * 2.f * (ma + mb);
     thr = (delta * delta + eacc) * (1.f + 1e-6f);
   } else {
-    const float base = 1.2e-7f * (ma + mb);
     thr = (delta + base + (float)(d + 2) * 1.2e-7f * (delta + base)) * (1.f + 1e-6f);
   }
   prm->thr = thr;
+  prm->base = base;
 }
 
 // ---------------------------------------------------------------------------------------------

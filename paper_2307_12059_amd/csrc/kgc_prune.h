@@ -440,7 +440,15 @@ struct TileDistArgs {
   // micro-tile summaries below (small pairs on the spot, the others through the list)
   UnitTable ut; BoundPairs bp;
   const float* fine_cent; const float* fine_rad; int64_t n_micro;
+  const JoinParams* prm;                           // L1 BOUND with a shift: see l1_reach
 };
+
+// What the float32 sum of |fl(c_H + r) - c_T| less the radii may come to for a pair that the exact bound keeps.  kBoundSlack pays
+// for roundings in proportion to the distance; that of the coordinates c_H + r goes with their size instead, 2^-24 (||c_H||_1 +
+// ||r||_1) at most, and JoinParams::base is twice that for the largest rows there are (the spare factor covers the roundings of
+// the centres' own means).  Rows at 12,288 under a relation of 5e-4 per dimension, half a unit in their last place: sum 0.0625
+// for a distance of 0.032.  Without a shift (connector rows, prm NULL) there is no such rounding.
+__device__ __forceinline__ float l1_reach(float delta, const JoinParams* prm) { return delta * (1.f + kBoundSlack) + (prm ? prm->base : 0.f); }
 
 // L1 bound of one unit pair on its micro-tile pairs: dist_1(c_H + r, c_T) - rho_H - rho_T <= delta, centre
 // distances summed over d by the calling lane; `lane_count` lanes starting at `lane0` share the pairs.
@@ -450,6 +458,7 @@ __device__ __forceinline__ void refine_unit_pair_l1(const TileDistArgs& a, int r
   unit_range(a.ut, uT, fT, nTm);
   const int64_t so = (int64_t)(a.r0 + rl) * a.d;
   const int64_t total = (int64_t)nHm * nTm;
+  const float reach = l1_reach(a.delta, a.prm);
   for (int64_t i = lane0; i < total; i += lane_count) {
     const int64_t mH = fH + i / nTm, mT = fT + i % nTm;
     const float rH = a.fine_rad[mH], rT = a.fine_rad[mT];
@@ -458,7 +467,7 @@ __device__ __forceinline__ void refine_unit_pair_l1(const TileDistArgs& a, int r
     const float* cT = a.fine_cent + mT * a.d;
     float s = 0.f;
     for (int k = 0; k < a.d; ++k) s += fabsf(cH[k] + ld_elem(a.shift, so + k, a.dtype_shift) - cT[k]);
-    if (s * (1.f - kBoundSlack) - rH - rT <= a.delta * (1.f + kBoundSlack)) {
+    if (s * (1.f - kBoundSlack) - rH - rT <= reach) {
       const int tH = (int)(mH / a.micro_per_bm), tT = (int)(mT / a.micro_per_bn);
       uint32_t* w = &a.bitmap[((int64_t)rl * a.nH + tH) * a.words_per_row + (tT >> 5)];
       if (!(*w & (1u << (tT & 31)))) atomicOr(w, 1u << (tT & 31));
@@ -500,6 +509,7 @@ __global__ __launch_bounds__(256) void k_tile_dist(const TileDistArgs a) {
   constexpr bool kEarly = P == 1 && (EPI == kEpiBound || EPI == kEpiBoundUnits);
   __shared__ uint32_t decided[2][4];                           // per slice (alternating) and wave
   float open_to = 0.f;
+  const float reach = P == 1 ? l1_reach(a.delta, a.prm) : a.delta * (1.f + kBoundSlack);      // (L2: without a shift only)
   int par = 0;
   if constexpr (kEarly) {
     const float* rad_r = (a.rad_rows ? a.rad_rows : a.rad) + (int64_t)blockIdx.z * a.x_rel_rows;
@@ -513,7 +523,7 @@ __global__ __launch_bounds__(256) void k_tile_dist(const TileDistArgs a) {
       mc = vc > mc || vc != vc ? vc : mc;
     }
     // (-1: all of the thread's rows, or columns, are empty; NaN: every pair stays open)
-    open_to = mr < 0.f || mc < 0.f ? -1.f : (a.delta * (1.f + kBoundSlack) + mr + mc) / (1.f - kBoundSlack) * (1.f + 1e-5f);
+    open_to = mr < 0.f || mc < 0.f ? -1.f : (reach + mr + mc) / (1.f - kBoundSlack) * (1.f + 1e-5f);
   }
   const int re = rid[srow], ce = cid[srow];
   const int64_t xo = ((int64_t)blockIdx.z * a.x_rel_rows + (re < 0 ? 0 : re)) * d,
@@ -631,7 +641,7 @@ __global__ __launch_bounds__(256) void k_tile_dist(const TileDistArgs a) {
         const float rc = a.rad[col0 + lc];
         if (rc < 0.f) continue;
         const float dist = (P == 2) ? sqrtf(acc[i][j]) : acc[i][j];
-        if (dist * (1.f - kBoundSlack) - rr - rc > a.delta * (1.f + kBoundSlack)) continue;
+        if (dist * (1.f - kBoundSlack) - rr - rc > reach) continue;
         const int uH = (int)(row0 + lr), uT = (int)(col0 + lc);
         int fH, nHm, fT, nTm;
         unit_range(a.ut, uH, fH, nHm);
@@ -663,7 +673,7 @@ __global__ __launch_bounds__(256) void k_tile_dist(const TileDistArgs a) {
         if (rc < 0.f) continue;
         const float dist = (P == 2) ? sqrtf(acc[i][j]) : acc[i][j];
         const float lb = dist * (1.f - kBoundSlack) - rr - rc;  // radii already carry their slack
-        if (lb <= a.delta * (1.f + kBoundSlack)) {
+        if (lb <= reach) {
           const int tH = (int)((row0 + lr) / a.micro_per_bm), tT = (int)((col0 + lc) / a.micro_per_bn);
           atomicOr(&a.bitmap[((int64_t)rl * a.nH + tH) * a.words_per_row + (tT >> 5)], 1u << (tT & 31));
         }
@@ -1222,6 +1232,7 @@ __device__ __forceinline__ void refine_unit_pair(const BoundL2Args& a, const Uni
     const float rH = a.rad[mH], rT = a.rad[mT];
     if (rH < 0.f || rT < 0.f) continue;
     if (!a.D) {           // small problems: no matrices, the distance of c_H + r and c_T summed over d
+      // (the coordinates c_H + r are rounded: 2^-24 (||c_H|| + ||r||) of distance, taken twice; see l1_reach)
       const float* cH = a.cent + mH * a.d;
       const float* cT = a.cent + mT * a.d;
       const int64_t so = (int64_t)(a.r0 + rl) * a.d;
@@ -1230,7 +1241,7 @@ __device__ __forceinline__ void refine_unit_pair(const BoundL2Args& a, const Uni
         const float x = cH[k] + ld_elem(a.Rv, so + k, a.dtype) - cT[k];
         sq += x * x;
       }
-      if (sqrtf(sq) * (1.f - kBoundSlack) - rH - rT <= dsl) keep_tile<LIST>(a, rl, (int)(mH / a.micro_per_bm), (int)(mT / a.micro_per_bn));
+      if (sqrtf(sq) * (1.f - kBoundSlack) - 1.2e-7f * (a.cnorm[mH] + srn) - rH - rT <= dsl) keep_tile<LIST>(a, rl, (int)(mH / a.micro_per_bm), (int)(mT / a.micro_per_bn));
       continue;
     }
     const float D = a.D[mH * a.n_micro + mT];
@@ -1487,7 +1498,7 @@ struct L1MicroArgs {
   const float* cent_h; const float* rad_h; const float* cent_t; const float* rad_t;      // micro-tile summaries of heads and tails ...
   int64_t h_rel, t_rel;                // ... and how many of them per relation (0: the same for all)
   const void* shift; int dtype, d;     // added to the heads' centres: shift[(r0 + relation) * d ...] (NULL: nothing)
-  float delta;
+  float delta; const JoinParams* prm;  // (see l1_reach)
   ExactEntry* list; unsigned int* count; unsigned int cap;      // surviving blocks: relation, first head slot, first tail slot
 };
 constexpr int kL1MicroQueue = 64;      // blocks a wave holds back: one atomic a flush
@@ -1509,6 +1520,7 @@ __global__ __launch_bounds__(256) void k_l1_micro_pairs(const L1MicroArgs a) {
     __builtin_amdgcn_wave_barrier();
   };
   const unsigned int n_rows = *a.n_active;
+  const float reach = l1_reach(a.delta, a.prm);
   for (unsigned int i = blockIdx.x * 4u + (unsigned)wave; i < n_rows; i += gridDim.x * 4u) {
     const int64_t row = (int64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)a.active_rows[i]);
     const int rl = (int)(row / a.nH), tH = (int)(row - (int64_t)rl * a.nH);
@@ -1543,7 +1555,7 @@ __global__ __launch_bounds__(256) void k_l1_micro_pairs(const L1MicroArgs a) {
       const int p = lane >> 2;
       const float rh = a.rad_h[mh + (p >> 2)], rt = a.rad_t[mt + (p & 3)];
       // (the bound of k_tile_dist's BOUND form; an empty micro-tile has radius -1)
-      const bool keep = (lane & 3) == 0 && rh >= 0.f && rt >= 0.f && !(s1 * (1.f - kBoundSlack) - rh - rt > a.delta * (1.f + kBoundSlack));
+      const bool keep = (lane & 3) == 0 && rh >= 0.f && rt >= 0.f && !(s1 * (1.f - kBoundSlack) - rh - rt > reach);
       const unsigned long long b = __builtin_amdgcn_ballot_w64(keep);
       const int n = __builtin_popcountll(b);
       if (qn + n > kL1MicroQueue) flush();

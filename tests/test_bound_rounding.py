@@ -68,3 +68,33 @@ def test_float32_bound_never_drops_a_pair_that_the_exact_bound_keeps():
     assert trials > 300
     # the check has teeth: with every widening term taken out the float32 test loses pairs
     assert dropped_without_slack > 0
+
+
+def _direct_keeps(p, cH, cT, r, reach, widen=True):
+    """The bounds that sum |fl(c_H + r) - c_T| over the dimensions themselves (all L1 bounds; refine_unit_pair for few
+    micro-tiles in L2), with the widening for the rounding of the coordinates c_H + r or without it."""
+    x = (cH + r).astype(np.float32) - cT
+    s = _sum32(np.abs(x)) if p == 1 else F(np.sqrt(_sum32(x * x)))
+    norm = (lambda v: _sum32(np.abs(v))) if p == 1 else (lambda v: F(np.sqrt(_sum32(v * v))))
+    base = F(1.2e-7) * (norm(cH) + norm(r)) if widen else F(0)
+    return bool(s * (F(1) - K_BOUND_SLACK) <= F(reach) * (F(1) + K_BOUND_SLACK) + base)
+
+
+def test_directly_summed_bounds_pay_for_the_rounding_of_the_coordinates():
+    """Centres far from the origin under relations of about a unit in their last place, the exact inequality held by a hair."""
+    g = np.random.default_rng(5)
+    for p in (1, 2):
+        trials = dropped_without = 0
+        for d in (7, 64, 960):
+            for size in (1.0, 300.0, 12288.0, 1e6):
+                for _ in range(40):
+                    cH = (size * (1.0 + 0.3 * g.standard_normal(d))).astype(np.float32)
+                    r = (size * 2.0 ** -24 * g.uniform(0.5, 1.5, d)).astype(np.float32)
+                    cT = cH
+                    x = cH.astype(np.float64) + r.astype(np.float64) - cT.astype(np.float64)
+                    exact = np.abs(x).sum() if p == 1 else np.sqrt((x * x).sum())
+                    reach = exact * (1.0 + 1e-6)
+                    trials += 1
+                    assert _direct_keeps(p, cH, cT, r, reach), (p, d, size)
+                    dropped_without += not _direct_keeps(p, cH, cT, r, reach, widen=False)
+        assert trials == 480 and dropped_without > 100
