@@ -69,8 +69,9 @@ typedef struct {
     int64_t workspace_bytes;  /* cap on the scratch that a batch of relations needs: staged operands (or, in the
                                  relation-factorised form, the tables of its products) of one relation at least;
                                  0 = 16 GiB.  Larger joins run in relation batches.  Beside it the handle holds what
-                                 does not grow with the relations, the tile lists, and the list of candidate pairs
-                                 (up to an eighth of this and 1 GiB, 16 MiB at least) */
+                                 does not grow with the relations, the tile lists, and the lists of candidate pairs and
+                                 of 32 x 32 blocks of pairs (each up to an eighth of this and 1 GiB, 16 MiB at least; a
+                                 pruned L2 join that lists more blocks makes that list longer) */
     void*   stream;           /* hipStream_t to enqueue on; NULL = the default stream */
     float   group_radius;     /* pruning only: radius of entity groups as a multiple of delta; 0 = 2.0 */
     int32_t range_kib;        /* dense L2 join, kernels 6-18: KiB of staged tail rows one block walks (L2 blocking);
@@ -106,7 +107,8 @@ typedef struct {
                                    100 = the relation-factorised kernel (dense joins of either norm, and pruned L2
                                    joins whose rows form one group) */
     int32_t  exact_blocks;      /* 32 x 32 blocks of pairs that the pruned L2 joins re-scored as whole blocks in double
-                                   precision (their candidates come in patches); 0 for the other paths */
+                                   precision (their candidates come in patches), or that the pruned L1 joins summed one
+                                   by one instead of whole 128 x 128 tiles; 0 for the other paths */
 } kgc_stats;
 
 /* Create a handle.  cfg may be NULL (defaults).  Returns KGC_OK and stores the handle in *out (host),

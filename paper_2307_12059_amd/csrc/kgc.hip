@@ -83,6 +83,8 @@ struct kgc_handle {
   unsigned int fcap = 0;                       // entries of flist that an earlier call needed (see fact_list_start)
   unsigned int fcap_start = 0;                 // > 0: ... and to start with (tests)
   size_t flist_limit = 0;                      // > 0: bytes past which flist counts as not to be had (tests)
+  size_t xlist_limit = 0;                      // > 0: the same of xlist in L1 joins (tests)
+  unsigned int block_most = 0;                 // > 0: most blocks that L1 joins list, in place of block_list_max (tests)
   int order_rows = 0;                          // > 0, < 0: dense factorised joins put their rows in order always, never (tests)
   int list_seg_cap = 0;                        // > 0: the pruned barrier-free kernel keeps at most this many entries of a row's tile list in the LDS (tests)
   unsigned pairs_grid = 512;                   // workgroups of the tile-at-a-time kernel: two per compute unit (tests set fewer, so that a workgroup walks several batches of tiles)
@@ -254,16 +256,16 @@ JoinL1Kernel l1_kernel_for(const RecheckCtx& cx) {
 // a batch of a pruned L1 join by pairs of micro-tiles (k_l1_blocks): the blocks that the bound leaves of the listed tiles, their
 // pairs within the filter's threshold, the scores; both lists empty again afterwards
 void launch_l1_blocks(hipStream_t st, const L1MicroArgs& ma, JoinL1Args la, unsigned row_grid, ExactEntry* pairs, unsigned int pair_cap,
-                      DevCounters* cnt) {
+                      unsigned int most, DevCounters* cnt) {
   const RecheckCtx& cx = la.cx;
   const JoinParams* prm = la.prm;
   k_l1_micro_pairs<<<512, 256, 0, st>>>(ma);
   const bool bf = cx.dtype == KGC_BF16, vec = cx.vec_ok != 0;
   auto kern = bf ? (vec ? k_l1_blocks<true, true> : k_l1_blocks<true, false>) : (vec ? k_l1_blocks<false, true> : k_l1_blocks<false, false>);
   hipLaunchKernelGGL(kern, dim3(1024), dim3(256), 0, st, (const ExactEntry*)ma.list, (const unsigned int*)ma.count, ma.cap, &cnt->tile_cursor,
-                     &cnt->exact_need, prm, cx, pairs, &cnt->n_fact, pair_cap);
+                     most, &cnt->exact_need, &cnt->exact_total, prm, cx, pairs, &cnt->n_fact, pair_cap);
   k_exact_pairs<<<2048, 256, 0, st>>>(pairs, &cnt->n_fact, pair_cap, &cnt->fact_need, cx);
-  la.block_count = ma.count; la.tile_total = &cnt->tile_cursor;      // (the batch whole tiles are better for)
+  la.block_count = ma.count; la.tile_total = &cnt->tile_cursor; la.block_most = most;      // (the batch whole tiles are better for)
   hipLaunchKernelGGL(l1_kernel_for(cx), dim3(row_grid), dim3(256), 0, st, la);
   k_fill_u32<<<1, 64, 0, st>>>(&cnt->n_exact, (sizeof(DevCounters) - offsetof(DevCounters, n_exact)) / 4, 0u);
 }
@@ -349,7 +351,12 @@ inline unsigned long long fact_list_max(int64_t N, int64_t R, int p, int64_t ws)
   const double n = (double)(N + kSlotAlign), worth = p == 2 ? n * n * (double)R : (double)N * (double)N * (double)R / 512.0;
   return std::max<unsigned long long>(1ull, (unsigned long long)std::min((double)std::min(kFactListMax, room), worth));
 }
-// ... and the length it starts with: one pair in 64 (4 MiB for the smallest joins, 128 MiB from 5 * 10^8 triples on).  A batch
+// Most 32 x 32 blocks that a pruned L1 join lists (a batch with more goes by whole tiles): the same room
+inline unsigned int block_list_max(const kgc_handle* hd, int64_t ws) {
+  if (hd->block_most > 0) return hd->block_most;
+  return (unsigned int)std::min<unsigned long long>(kFactListMax, std::max<unsigned long long>(kExactListCap, (unsigned long long)(ws / 8) / sizeof(ExactEntry)));
+}
+// ... and the length the list of pairs starts with: one pair in 64 (4 MiB for the smallest joins, 128 MiB from 5 * 10^8 triples on).  A batch
 // that wanted to list more makes it longer and runs again.
 inline unsigned int fact_list_start(int64_t N, int64_t R) {
   return (unsigned int)std::min((double)(1u << 23), std::max((double)(1u << 18), (double)N * (double)N * (double)R / 64.0));
@@ -414,6 +421,21 @@ bool have_list(kgc_handle* hd, unsigned int entries) {
     return false;
   }
   hd->flist.bytes = bytes;
+  return true;
+}
+
+// ... and the list of blocks of a pruned L1 join, which goes by whole tiles without it
+bool have_blocks(kgc_handle* hd) {
+  const size_t bytes = (size_t)hd->xcap * sizeof(ExactEntry);
+  if (hd->xlist.p && hd->xlist.bytes >= bytes) return true;
+  release(hd->xlist);
+  if ((hd->xlist_limit > 0 && bytes > hd->xlist_limit) || hipMalloc(&hd->xlist.p, bytes) != hipSuccess) {
+    (void)hipGetLastError();                               // (the failure is dealt with)
+    hd->xlist.p = nullptr;
+    hd->xcap = hd->fcap_start > 0 ? hd->fcap_start : kExactListCap;      // the next call asks for what it would start with
+    return false;
+  }
+  hd->xlist.bytes = bytes;
   return true;
 }
 
@@ -514,6 +536,8 @@ int kgc_create(const kgc_config* cfg, kgc_handle** out) {
   h->err.reserve(256);          // later error messages fit without a host allocation
   // the first length of the exact stage's block list (it grows by itself; tests set it small to see it grow)
   if (const char* e = std::getenv("KGC_EXACT_LIST_CAP")) h->xcap = h->fcap_start = (unsigned int)std::max(1L, std::atol(e));
+  if (const char* e = std::getenv("KGC_BLOCK_LIST_LIMIT")) h->xlist_limit = (size_t)std::max(1L, std::atol(e));
+  if (const char* e = std::getenv("KGC_BLOCK_LIST_MAX")) h->block_most = (unsigned int)std::max(1L, std::atol(e));
   if (const char* e = std::getenv("KGC_PAIR_LIST_LIMIT")) h->flist_limit = (size_t)std::max(1L, std::atol(e));
   if (const char* e = std::getenv("KGC_ROW_ORDER")) h->order_rows = std::atol(e) > 0 ? 1 : -1;
   if (const char* e = std::getenv("KGC_TILE_LIST_SEGMENT")) h->list_seg_cap = (int)std::max(1L, std::atol(e));
@@ -654,8 +678,8 @@ int kgc_join_ab(kgc_handle* hd, const void* A, const void* B, int64_t N, int32_t
   const unsigned int pair_cap = (unsigned int)std::min<unsigned long long>(
       std::max(hd->fcap, hd->fcap_start > 0 ? hd->fcap_start : fact_list_start(N, R)), pairs_most);
   bool l1_blocks = prune && p == 1 && !hd->no_fact && 16.0 * (double)tiles_per_rel * (double)RBmax < 4e9;      // (the blocks are counted in 32 bits)
-  if (l1_blocks && (rc = ensure(hd, hd->xlist, (size_t)hd->xcap * sizeof(ExactEntry)))) return rc;
-  if (l1_blocks && !have_list(hd, pair_cap)) l1_blocks = false;
+  const unsigned int block_most = block_list_max(hd, ws);
+  if (l1_blocks && (!have_blocks(hd) || !have_list(hd, pair_cap))) l1_blocks = false;
   int nbatch = 0;
   for (int64_t r0 = 0; r0 < R; r0 += RBmax, ++nbatch) {
     const int RB = (int)std::min<int64_t>(RBmax, R - r0);
@@ -787,7 +811,7 @@ int kgc_join_ab(kgc_handle* hd, const void* A, const void* B, int64_t N, int32_t
         ma.h_rel = n_micro; ma.t_rel = b_per_relation ? n_micro : 0; ma.dtype = dtype; ma.d = d; ma.delta = delta;
         la.row_start = ma.row_start; la.row_count = ma.row_count; la.cols = ma.cols; la.active_rows = active_rows; la.n_active = n_active;
         ma.list = (ExactEntry*)hd->xlist.p; ma.count = &cnt->n_exact; ma.cap = hd->xcap;
-        launch_l1_blocks(st, ma, la, row_grid, (ExactEntry*)hd->flist.p, pair_cap, cnt);
+        launch_l1_blocks(st, ma, la, row_grid, (ExactEntry*)hd->flist.p, pair_cap, block_most, cnt);
       } else if (prune) {
         la.row_start = (const uint32_t*)hd->row_start.p; la.row_count = (const uint32_t*)hd->row_count.p;
         la.cols = (const uint32_t*)hd->cols.p; la.active_rows = active_rows; la.n_active = n_active;
@@ -808,7 +832,7 @@ int kgc_join_ab(kgc_handle* hd, const void* A, const void* B, int64_t N, int32_t
   // them): the list grows to what was asked for and the join runs again from the start.
   if (hd->host_counters->exact_need > hd->xcap) {
     const unsigned long long need = hd->host_counters->exact_need;
-    hd->xcap = (unsigned int)std::min<unsigned long long>(need + need / 4 + 1024, 0xffffffffull);
+    hd->xcap = (unsigned int)std::min<unsigned long long>(need + need / 4 + 1024, l1_blocks ? std::max(block_most, hd->xcap) : 0xffffffffu);
     return kgc_join_ab(hd, A, B, N, d, R, b_per_relation, p, delta, out_triples, cap, count);
   }
   if (l1_blocks && hd->host_counters->fact_need > pair_cap) {      // (the same of the list of pairs; longer than it may be: without it)
@@ -1664,8 +1688,9 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
   const bool lists_pairs = prune && p == 2 && tile_id == kDirectL2Tile && !hd->no_fact;
   // pruned L1 joins by pairs of micro-tiles need both lists
   const bool l1_blocks = prune && p == 1 && !win && !hd->static_mode && !hd->no_fact &&
-                         16.0 * (double)tiles_per_rel * (double)Rn < 4e9;      // (the blocks are counted in 32 bits)
-  if (l1_blocks && (rc = ensure(hd, hd->xlist, (size_t)hd->xcap * sizeof(ExactEntry)))) return rc;
+                         16.0 * (double)tiles_per_rel * (double)Rn < 4e9 &&      // (the blocks are counted in 32 bits)
+                         have_blocks(hd);
+  const unsigned int block_most = block_list_max(hd, ws);
   if ((fact || part_n || lists_pairs || l1_blocks) && !have_list(hd, fact_cap)) {
     pr.valid = reuse;                                      // (what the handle held is still there)
     return without_list();
@@ -2066,7 +2091,7 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
         ma.nH = nH; ma.r0 = (int)r0; ma.cent_h = ma.cent_t = (const float*)hd->cent.p; ma.rad_h = ma.rad_t = (const float*)hd->rad.p;
         ma.shift = Rvecs; ma.prm = prm; ma.dtype = dtype; ma.d = d; ma.delta = delta;
         ma.list = (ExactEntry*)hd->xlist.p; ma.count = &cnt->n_exact; ma.cap = hd->xcap;
-        launch_l1_blocks(st, ma, la, row_grid, (ExactEntry*)hd->flist.p, fact_cap, cnt);
+        launch_l1_blocks(st, ma, la, row_grid, (ExactEntry*)hd->flist.p, fact_cap, block_most, cnt);
       } else {
         hipLaunchKernelGGL(l1_kernel_for(la.cx), prune ? dim3(row_grid, 1, 1) : dim3((unsigned)nTw, (unsigned)nHw, (unsigned)RB), dim3(256), 0,
                            st, la);
@@ -2093,7 +2118,7 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
   }
   if (hd->host_counters->exact_need > hd->xcap) {
     const unsigned long long need = hd->host_counters->exact_need;
-    hd->xcap = (unsigned int)std::min<unsigned long long>(need + need / 4 + 1024, 0xffffffffull);
+    hd->xcap = (unsigned int)std::min<unsigned long long>(need + need / 4 + 1024, l1_blocks ? std::max(block_most, hd->xcap) : 0xffffffffu);
     return join_range_impl(hd, E, N, d, Rvecs, R, p, delta, r_begin, r_end, out_triples, cap, count, win,
                            prep_mode == kPrepFresh ? kPrepReuse : prep_mode);      // (what was just prepared is still good)
   }

@@ -40,7 +40,7 @@ struct DevCounters {
   unsigned int n_active;          // rows (relation, head tile) of the batch that still have tail tiles
   unsigned int exact_need;        // most accumulator blocks any one batch wanted to list (see list_block)
   unsigned long long tiles;       // surviving tiles over all batches
-  unsigned long long exact_total; // accumulator blocks scored by the block form of the exact stage, over all batches
+  unsigned long long exact_total; // accumulator blocks scored by the block form of the exact stage (L1: blocks summed by k_l1_blocks), over all batches
   unsigned int fact_need, pad;    // most pairs any one batch of the relation-factorised kernel wanted to list
   unsigned int max_a[1024];       // running maxima of ||bf16(h + r)||^2 (L2) or ||e||_1 (L1), float bits, spread over slots
   unsigned int max_b[1024];       // running maxima of ||bf16(t)||^2 (L2) or ||r||_1 (L1)
@@ -2347,15 +2347,16 @@ struct JoinL1Args {
   const uint32_t* cols;
   const uint32_t* active_rows;
   const unsigned int* n_active;
-  const unsigned int* block_count; const unsigned long long* tile_total;      // not NULL: a batch that l1_by_blocks sends to k_l1_blocks is left alone
+  const unsigned int* block_count; const unsigned long long* tile_total; unsigned int block_most;      // not NULL: a batch that l1_by_blocks sends to k_l1_blocks is left alone
   RecheckCtx cx;
 };
 // A pruned batch goes by 32 x 32 blocks where the bound leaves at most six of a tile's sixteen (a block of its own costs twice
 // its share of a tile: four times the rows to load for a pair), or where there are so few that whole tiles would leave the chip
-// idle.
+// idle, and never where there are more than their list may hold (`most`).
 constexpr unsigned int kL1FewBlocks = 16384;
-__device__ __forceinline__ bool l1_by_blocks(const unsigned int* blocks, const unsigned long long* tiles) {
-  return *blocks <= kL1FewBlocks || (unsigned long long)*blocks <= 6ull * *tiles;
+__device__ __forceinline__ bool l1_by_blocks(const unsigned int* blocks, const unsigned long long* tiles, unsigned int most) {
+  const unsigned int n = *blocks;
+  return n <= most && (n <= kL1FewBlocks || (unsigned long long)n <= 6ull * *tiles);
 }
 
 // Kernel 3.  One block of 256 threads scores 128 x 128 tiles of (heads, tails) for one relation in
@@ -2382,7 +2383,7 @@ __global__ __launch_bounds__(256, 3) void k_join_l1(const JoinL1Args a) {
   __shared__ int32_t hent[BM], tent[BN];
   __shared__ BlockQueue queue;
   __shared__ uint32_t decided[2][4];      // per slice (alternating) and wave: the wave's candidates are known
-  if (a.block_count && l1_by_blocks(a.block_count, a.tile_total)) return;
+  if (a.block_count && l1_by_blocks(a.block_count, a.tile_total, a.block_most)) return;
 
   const int tid = threadIdx.x, wave = tid >> 6;
   if (tid == 0) { queue.count = 0u; queue.pending = 0u; queue.flag = 0u; queue.nhits = 0u; }   // published by the first barrier
@@ -2520,7 +2521,8 @@ constexpr int kL1PairQueue = 256;
 constexpr int kL1BlockStride = 36;     // floats per dimension in LDS: 16-byte rows, and the two halves of a row's dimensions on different banks
 template <bool BF16, bool VEC>
 __global__ __launch_bounds__(256) void k_l1_blocks(const ExactEntry* __restrict__ list, const unsigned int* __restrict__ count, unsigned int cap,
-                                                   const unsigned long long* __restrict__ tiles, unsigned int* __restrict__ need, const JoinParams* __restrict__ prm, const RecheckCtx cx,
+                                                   const unsigned long long* __restrict__ tiles, unsigned int most, unsigned int* __restrict__ need,
+                                                   unsigned long long* __restrict__ total, const JoinParams* __restrict__ prm, const RecheckCtx cx,
                                                    ExactEntry* __restrict__ pairs, unsigned long long* __restrict__ pair_count,
                                                    unsigned int pair_cap) {
   __shared__ __attribute__((aligned(16))) float stage[4][2][kL1K * kL1BlockStride];
@@ -2542,9 +2544,9 @@ __global__ __launch_bounds__(256) void k_l1_blocks(const ExactEntry* __restrict_
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
     __builtin_amdgcn_wave_barrier();
   };
-  if (!l1_by_blocks(count, tiles)) return;
+  if (!l1_by_blocks(count, tiles, most)) return;
   const unsigned int n = *count <= cap ? *count : 0u;      // (a list that did not fit: the host makes it longer and runs the call again)
-  if (blockIdx.x == 0 && threadIdx.x == 0 && *count) atomicMax(need, *count);
+  if (blockIdx.x == 0 && threadIdx.x == 0 && *count) { atomicMax(need, *count); *total += n; }
   const float thr = prm->thr;
   const int d = cx.d;
   const int row = lane >> 1, sk0 = (lane & 1) * 8, ly = lane >> 3, lx = lane & 7;
