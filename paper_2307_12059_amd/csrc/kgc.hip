@@ -255,10 +255,11 @@ JoinL1Kernel l1_kernel_for(const RecheckCtx& cx) {
 
 // a batch of a pruned L1 join by pairs of micro-tiles (k_l1_blocks): the blocks that the bound leaves of the listed tiles, their
 // pairs within the filter's threshold, the scores; both lists empty again afterwards
-void launch_l1_blocks(hipStream_t st, const L1MicroArgs& ma, JoinL1Args la, unsigned row_grid, ExactEntry* pairs, unsigned int pair_cap,
+void launch_l1_blocks(hipStream_t st, L1MicroArgs ma, JoinL1Args la, unsigned row_grid, ExactEntry* pairs, unsigned int pair_cap,
                       unsigned int most, DevCounters* cnt) {
   const RecheckCtx& cx = la.cx;
   const JoinParams* prm = la.prm;
+  ma.tiles = &cnt->tile_cursor; ma.most = most; ma.sample = &cnt->l1_sample;
   k_l1_micro_pairs<<<512, 256, 0, st>>>(ma);
   const bool bf = cx.dtype == KGC_BF16, vec = cx.vec_ok != 0;
   auto kern = bf ? (vec ? k_l1_blocks<true, true> : k_l1_blocks<true, false>) : (vec ? k_l1_blocks<false, true> : k_l1_blocks<false, false>);

@@ -47,6 +47,7 @@ struct DevCounters {
   unsigned int n_exact;           // accumulator blocks listed for the exact stage by the pruned L2 join kernels (per batch)
   unsigned int pair_mode;         // pruned L2 batch: 1 = its rows keep so few tiles that they are taken tile by tile
   unsigned long long n_fact;      // pairs listed by the relation-factorised kernel (per batch)
+  unsigned long long l1_sample;   // sampled tiles << 32 | their blocks (k_l1_micro_pairs, per batch)
 };
 
 __global__ void k_fill_u32(uint32_t* p, int64_t n, uint32_t v) {
@@ -2354,9 +2355,12 @@ struct JoinL1Args {
 // its share of a tile: four times the rows to load for a pair), or where there are so few that whole tiles would leave the chip
 // idle, and never where there are more than their list may hold (`most`).
 constexpr unsigned int kL1FewBlocks = 16384;
+__device__ __forceinline__ unsigned int l1_block_line(const unsigned long long* tiles, unsigned int most) {
+  const unsigned long long line = 6ull * *tiles > kL1FewBlocks ? 6ull * *tiles : kL1FewBlocks;
+  return line < most ? (unsigned int)line : most;
+}
 __device__ __forceinline__ bool l1_by_blocks(const unsigned int* blocks, const unsigned long long* tiles, unsigned int most) {
-  const unsigned int n = *blocks;
-  return n <= most && (n <= kL1FewBlocks || (unsigned long long)n <= 6ull * *tiles);
+  return *blocks <= l1_block_line(tiles, most);
 }
 
 // Kernel 3.  One block of 256 threads scores 128 x 128 tiles of (heads, tails) for one relation in

@@ -62,3 +62,30 @@ def test_lists_of_pruned_l1_joins(kind, env, by_blocks, monkeypatch):
     finally:
         ref.close()
         j.close()
+
+
+# Clusters of a dozen rows form no groups: micro-tiles of strangers, all of whose blocks are within reach.  Few rows of tiles (each dealt
+# to several waves) and many; a batch small enough for blocks whatever they are
+@pytest.mark.parametrize("N,R,d,by_blocks", [(6000, 6, 20, False), (3000, 120, 33, False), (700, 20, 16, True)])
+def test_batches_whose_blocks_are_mostly_within_reach(N, R, d, by_blocks):
+    import paper_2307_12059_amd as kgc
+    import torch
+    g = np.random.default_rng(N)
+    k = N // 12
+    cent = g.standard_normal((k, d))
+    src = g.integers(0, k, R)
+    E = torch.from_numpy((cent[g.integers(0, k, N)] + 0.1 * g.standard_normal((N, d))).astype(np.float32)).cuda()
+    Rv = torch.from_numpy((cent[(src + 1 + g.integers(0, k - 1, R)) % k] - cent[src]).astype(np.float32)).cuda()
+    delta = float(np.float32(0.1 * 1.128 * d))
+    out = []
+    for cfg in (dict(prune=OFF, tile_cfg=17), dict(prune=ON)):
+        j = kgc.Join(**cfg)
+        try:
+            got = j.join(E, Rv, 1, delta, 1 << 20)
+        finally:
+            j.close()
+        assert got["code"] == 0
+        o = np.lexsort((got["t"], got["h"], got["r"]))
+        out.append(np.stack([got["r"][o], got["h"][o], got["t"][o], got["dist"][o].view(np.int32)], 1))
+    assert out[0].shape[0] > 50 and (got["stats"]["exact_blocks"] > 0) == by_blocks, got["stats"]
+    np.testing.assert_array_equal(out[1], out[0])
