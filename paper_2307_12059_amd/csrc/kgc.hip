@@ -678,7 +678,7 @@ int kgc_join_ab(kgc_handle* hd, const void* A, const void* B, int64_t N, int32_t
   const unsigned long long pairs_most = fact_list_max(N, R, 2, ws);
   const unsigned int pair_cap = (unsigned int)std::min<unsigned long long>(
       std::max(hd->fcap, hd->fcap_start > 0 ? hd->fcap_start : fact_list_start(N, R)), pairs_most);
-  bool l1_blocks = prune && p == 1 && !hd->no_fact && 16.0 * (double)tiles_per_rel * (double)RBmax < 4e9;      // (the blocks are counted in 32 bits)
+  bool l1_blocks = prune && p == 1 && !hd->no_fact;      // (their count stops little past block_most: 32 bits do for any batch)
   const unsigned int block_most = block_list_max(hd, ws);
   if (l1_blocks && (!have_blocks(hd) || !have_list(hd, pair_cap))) l1_blocks = false;
   int nbatch = 0;
@@ -1688,9 +1688,8 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
   // the barrier-free kernel over tile lists hands its candidates on (not in a call that does without the list)
   const bool lists_pairs = prune && p == 2 && tile_id == kDirectL2Tile && !hd->no_fact;
   // pruned L1 joins by pairs of micro-tiles need both lists
-  const bool l1_blocks = prune && p == 1 && !win && !hd->static_mode && !hd->no_fact &&
-                         16.0 * (double)tiles_per_rel * (double)Rn < 4e9 &&      // (the blocks are counted in 32 bits)
-                         have_blocks(hd);
+  // (the count of blocks stops little past block_most: 32 bits do for any batch)
+  const bool l1_blocks = prune && p == 1 && !win && !hd->static_mode && !hd->no_fact && have_blocks(hd);
   const unsigned int block_most = block_list_max(hd, ws);
   if ((fact || part_n || lists_pairs || l1_blocks) && !have_list(hd, fact_cap)) {
     pr.valid = reuse;                                      // (what the handle held is still there)

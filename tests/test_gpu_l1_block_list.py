@@ -89,3 +89,35 @@ def test_batches_whose_blocks_are_mostly_within_reach(N, R, d, by_blocks):
         out.append(np.stack([got["r"][o], got["h"][o], got["t"][o], got["dist"][o].view(np.int32)], 1))
     assert out[0].shape[0] > 50 and (got["stats"]["exact_blocks"] > 0) == by_blocks, got["stats"]
     np.testing.assert_array_equal(out[1], out[0])
+
+
+def test_a_call_of_many_tiles_goes_by_blocks():
+    """16 blocks a tile times all its tiles is more than 32 bits count: the call goes by blocks all the same, batch by batch.  Its
+    first and last relations are compared with the dense kernel."""
+    import paper_2307_12059_amd as kgc
+    import torch
+    g = np.random.default_rng(3)
+    N, R, d, k = 60_000, 1_300, 8, 2_000
+    cent = 4.0 * g.standard_normal((k, d))
+    E = torch.from_numpy((cent[g.permutation(np.repeat(np.arange(k), N // k))] + 0.03 * g.standard_normal((N, d))).astype(np.float32)).cuda()
+    src = g.integers(0, k, R)
+    Rv = torch.from_numpy((cent[(src + 1 + g.integers(0, k - 1, R)) % k] - cent[src]).astype(np.float32)).cuda()
+    delta = float(np.float32(0.3))
+    recs = []
+    for cfg, ranges in ((dict(prune=ON), [None]), (dict(prune=OFF, tile_cfg=17), [(0, 3), (R - 3, R)])):
+        j = kgc.Join(**cfg)
+        try:
+            parts = []
+            for rr in ranges:
+                got = j.join(E, Rv, 1, delta, 1 << 22, r_range=rr)
+                assert got["code"] == 0
+                parts.append(np.stack([got["r"], got["h"], got["t"], got["dist"].view(np.int32)], 1))
+                if rr is None:
+                    assert got["stats"]["tiles_total"] * 16 > 4e9 and got["stats"]["exact_blocks"] > 0, str(got["stats"])
+        finally:
+            j.close()
+        x = np.concatenate(parts)
+        x = x[(x[:, 0] < 3) | (x[:, 0] >= R - 3)]
+        recs.append(x[np.lexsort((x[:, 2], x[:, 1], x[:, 0]))])
+    assert recs[1].shape[0] > 100
+    np.testing.assert_array_equal(recs[0], recs[1])
