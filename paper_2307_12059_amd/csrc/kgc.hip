@@ -297,6 +297,7 @@ inline bool order_pays(int64_t N, int64_t R, int d) { return N >= 1000 && N * R 
 struct FactJob {
   const void* E; const void* Rv; int dtype, d, r0, RB; float delta;
   const int32_t* slot_ent; int64_t Nslots;            // the run: a multiple of kSlotAlign slots
+  int32_t* rows;                                      // its entities without rows that hold non-finite elements (staging makes it)
   const uint16_t* A; const uint16_t* B;               // its staged operands (plain rows, norms less their slacks)
   float* u; float* umin; float* limr;                 // fact_rows(RB) x Nslots, x (Nslots / 64) x 10, x 1
   ExactEntry* list; unsigned int list_cap; unsigned long long give_up;
@@ -453,7 +454,7 @@ void launch_fact_stage(hipStream_t st, const FactJob& j, uint16_t* A, uint16_t* 
   const int KS = (j.d + kNormCols + kSliceK - 1) / kSliceK;
   const size_t stage_lds = (size_t)kStageRows * (KS * kSliceK + 8) * 2;
   k_stage_pair<<<dim3((unsigned)grid_for(j.Nslots / kStageRows, 1), 2, 1), 256, stage_lds, st>>>(j.E, j.dtype, j.d, j.slot_ent, j.Nslots, KS, A, B,
-                                                                                             cnt->max_a, cnt->max_b, j.delta);
+                                                                                             cnt->max_a, cnt->max_b, j.delta, j.rows);
 }
 
 // u[rl][slot] = r . e~ with its extremes over 8 and 64 slots, and the thresholds: rows read four elements at a time where
@@ -464,7 +465,7 @@ void launch_fact_products(hipStream_t st, const FactJob& j, const DevCounters* c
   const bool bf = j.dtype == KGC_BF16;
   const bool vec = j.d % 4 == 0 && (uintptr_t)j.E % (bf ? 8 : 16) == 0 && (uintptr_t)j.Rv % (bf ? 8 : 16) == 0;
   auto kern = bf ? (vec ? k_fact_dot<true, true> : k_fact_dot<true, false>) : (vec ? k_fact_dot<false, true> : k_fact_dot<false, false>);
-  hipLaunchKernelGGL(kern, dim3((unsigned)(j.Nslots / 256) + 1u, (unsigned)((RBp + 31) / 32), 1), dim3(256), 0, st, j.Rv, j.E, j.slot_ent, j.Nslots,
+  hipLaunchKernelGGL(kern, dim3((unsigned)(j.Nslots / 256) + 1u, (unsigned)((RBp + 31) / 32), 1), dim3(256), 0, st, j.Rv, j.E, j.rows, j.Nslots,
                      j.r0, j.RB, RBp, j.d, j.u, j.umin, umin64, umin64 + (size_t)RBp * (j.Nslots / 64), cnt, j.delta, KS * kSliceK, j.limr);
 }
 
@@ -1798,6 +1799,7 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
   }
   FactJob fj{};      // of the factorised form: the whole join, or its part
   fj.E = E; fj.Rv = Rvecs; fj.dtype = dtype; fj.d = d; fj.delta = delta; fj.slot_ent = slot_ent; fj.Nslots = Nslots;
+  fj.rows = (int32_t*)hd->normsA.p;      // (of Nslots words at least; the batches of a pruned join stage into it after its part is done)
   const size_t stage_lds = (size_t)kStageRows * (KS * kSliceK + 8) * 2;
   if (reuse) {
     // tail operands, summaries and (L1) the join parameters are in place
@@ -1824,7 +1826,7 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
     if (timed) KGC_HIP(hd, hipEventRecord(hd->join_ev[part_ev], st));
     launch_fact_stage(st, fj, (uint16_t*)at, (uint16_t*)(at + part_op), cnt);
     RecheckCtx cxf = cx;
-    cxf.slot_ent = cxf.slot_ent_t = fj.slot_ent;
+    cxf.slot_ent = cxf.slot_ent_t = fj.rows;
     for (int64_t r0 = r_begin; r0 < r_end; r0 += RBf) {
       fj.r0 = (int)r0; fj.RB = (int)std::min<int64_t>(RBf, r_end - r0);
       launch_fact_products(st, fj, cnt);
@@ -1978,7 +1980,9 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
       fj.list = (ExactEntry*)hd->flist.p; fj.list_cap = fact_cap; fj.give_up = fact_most;
       launch_fact_products(st, fj, cnt);
       if (timed) KGC_HIP(hd, hipEventRecord(hd->join_ev[2 * b], st));
-      if ((rc = launch_fact_join(hd, st, fj, cnt, cx)) != KGC_OK) return rc;
+      RecheckCtx cxf = cx;
+      cxf.slot_ent = cxf.slot_ent_t = fj.rows;
+      if ((rc = launch_fact_join(hd, st, fj, cnt, cxf)) != KGC_OK) return rc;
       if (r0 + RBmax < r_end) k_fill_u32<<<1, 64, 0, st>>>((uint32_t*)&cnt->n_fact, 2, 0u);      // an empty list for the next batch
       if (timed) KGC_HIP(hd, hipEventRecord(hd->join_ev[2 * b + 1], st));
     } else if (p == 2) {

@@ -225,11 +225,11 @@ __global__ __launch_bounds__(256, 4) void k_order_stage(const void* __restrict__
                                                         const int32_t* __restrict__ piv_ent, int P, uint16_t* __restrict__ rows,
                                                         uint16_t* __restrict__ pivots) {
   if (blockIdx.y == 0)
-    stage_operands<true>(E, nullptr, dtype, d, 0, 1, nullptr, Npad, KS, rows, nullptr, nullptr, nullptr, nullptr, 0, kStageRows, 0, nullptr,
-                         -1.f, N);
-  else
-    stage_operands<false>(E, nullptr, dtype, d, 0, 1, piv_ent, P, KS, pivots, nullptr, nullptr, nullptr, nullptr, 0, kStageRows, 0, nullptr,
-                          -1.f, 0);
+    stage_operands<true, true>(E, nullptr, dtype, d, 0, 1, nullptr, Npad, KS, rows, nullptr, nullptr, nullptr, nullptr, 0, kStageRows, 0, nullptr,
+                               -1.f, N);
+  else      // (a pivot that is no number would be the nearest of all rows, or of none)
+    stage_operands<false, true>(E, nullptr, dtype, d, 0, 1, piv_ent, P, KS, pivots, nullptr, nullptr, nullptr, nullptr, 0, kStageRows, 0, nullptr,
+                                -1.f, 0);
 }
 // Counting sort of the rows by pivot, one workgroup: sizes of the runs, offsets (the pivots of one of the first 256 side by
 // side), places.
