@@ -39,7 +39,8 @@ typedef struct { int32_t h, r, t; float dist; } kgc_triple;
 
 /* pruning */
 #define KGC_PRUNE_AUTO 0   /* KGC_PRUNE_ON, or every pair through the relation-factorised kernel where that is the shorter way
-                              (small joins, entities that group badly); the same result set */
+                              (small joins, entities that group badly); the same result set.  The choice takes cap for the
+                              number of hits, and a sample of the triples where cap is 0 or p is 1 */
 #define KGC_PRUNE_OFF  1   /* dense: every tile pair goes through the join kernel (Section 5.1's naive mode) */
 #define KGC_PRUNE_ON   2   /* tile pairs are skipped when the pivot bound of Lemma 1 (Section 4.4) exceeds delta */
 

@@ -92,6 +92,7 @@ struct kgc_handle {
   DevBuf top1_a, top1_b, top1_pick, top_samples, topk_state;            // ... and the operands / entity samples of its sub-sampled dense pass
   bool as_dense = false;                       // inside a pruned call that is run without pruning: the relation-factorised form
   bool no_fact = false;                        // inside a call that the relation-factorised form did not suit
+  bool no_straight = false;                    // inside a call that it did not suit without grouping
   int no_self = 0;                             // set by kgc_top1 around its inner joins: drop h == t
   bool static_mode = false;                    // inside kgc_join_static: the DevBufs point into the static array, nothing may allocate
   int64_t ws_override = 0;                     // ... and the staged operands of a relation batch get this many bytes
@@ -371,9 +372,14 @@ inline double fact_us(int64_t N, int64_t R, int d) {
   const double piv = order_pays(N, R, d) ? std::min<double>(kOrderPivots, n / 8) : 0.0;
   return 115.0 + 1.6e-9 * n * n * k + 2.8e-9 * n * piv * k + 1.25e-11 * n * n * r + 1.7e-5 * n * r + 1.7e-3 * n;
 }
-// ... and of its hits, as many as the caller makes room for (and no more than one pair in 200): listing and scoring a pair
-// costs what the pruned kernels, which score whole blocks, do not spend
-inline double hits_us(int64_t N, int64_t R, uint64_t cap) { return 2.5e-4 * std::min((double)cap, (double)N * (double)N * (double)R / 200.0); }
+// ... and of its hits: listing and scoring a pair costs what the pruned kernels, which score whole blocks, do not spend.  They are
+// taken for as many as the caller makes room for (and no more than one pair in 200); a call that only counts says nothing, and
+// has a sample taken.
+constexpr double kHitUs = 2.5e-4;
+inline double hits_us(int64_t N, int64_t R, uint64_t cap) { return kHitUs * std::min((double)cap, (double)N * (double)N * (double)R / 200.0); }
+// Pairs from which such a call is not what it was taken for, and goes the way over the groups after all: 4,301, 100, 64 with 28
+// million hits and room for 1,000: 2,585 us a call with a list of all of them, 782 with the try lost, 566 had it been pruned at once.
+inline double straight_most(uint64_t cap, double sampled) { return std::max({(double)(1u << 20), 8.0 * (double)cap, 2.0 * sampled}); }
 // With KGC_PRUNE_AUTO a join goes to the factorised form where that is the shorter way.  Before grouping: grouping, bound test
 // and tile lists are a chain of 25 launches and two read-backs, 220 to 300 us up to N = 20,000 however well they prune.  Measured,
 // whole calls in us, pruned / factorised: 2,000, 8, 32: 220 / 90; 773, 21, 192: 255 / 120; 2,654, 180, 39: 273 / 158; 4,301, 9, 100:
@@ -1567,13 +1573,17 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
   // KGC_PRUNE_AUTO: pruned, or the factorised form (for L1 if a sample says that its list stays short)
   const bool automatic = hd->cfg.prune == KGC_PRUNE_AUTO && free_choice && !hd->as_dense && hd->cfg.factorised == 0 && hd->cfg.group_radius == 0.f &&
                          KS <= kDirectHalfMaxKS && delta >= 0.f && delta < 1e18f && fact_pays(N, Rn);
-  const double dense_us = automatic ? fact_us(N, Rn, d) + hits_us(N, Rn, cap) : 0.0;
+  double dense_us = automatic ? fact_us(N, Rn, d) + hits_us(N, Rn, cap) : 0.0;
   KGC_HIP(hd, hipEventRecord(hd->ev[0], st));
   double share = -1.0;                                     // close_share, once it is known
   // (a share near what the list may hold is a try lost: fact_list_max)
   auto listed_us = [&]() { return p == 2 ? 0.0 : share * 1024.0 > 1.0 ? 1e30 : kListedPairUs * share * (double)N * (double)N * (double)Rn; };
-  if (automatic && p == 1 && dense_us <= kAutoDenseUs && (rc = close_share(hd, E, N, d, Rvecs, r_begin, Rn, delta, &share)) != KGC_OK) return rc;
-  const bool straight = automatic && dense_us <= kAutoDenseUs && dense_us + listed_us() <= kAutoDenseUs;      // the factorised form without grouping
+  const double triples = (double)N * (double)N * (double)Rn;
+  if (automatic && !hd->no_straight && (p == 1 || cap == 0) && dense_us <= kAutoDenseUs &&
+      (rc = close_share(hd, E, N, d, Rvecs, r_begin, Rn, delta, &share)) != KGC_OK)
+    return rc;
+  if (p == 2 && share > 0.0) dense_us += kHitUs * (share - 1.0 / kSampleTriples) * triples;      // (share counts one more than the sample held)
+  const bool straight = automatic && !hd->no_straight && dense_us <= kAutoDenseUs && dense_us + listed_us() <= kAutoDenseUs;      // the factorised form without grouping
   const bool prune = hd->cfg.prune != KGC_PRUNE_OFF && !hd->as_dense && !straight;
 
   // tile shape
@@ -1594,7 +1604,8 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
   const bool l2_ops = p == 2 || fact;          // staged operands of the matrix pipes
   const int64_t ws = hd->ws_override > 0 ? hd->ws_override
                                            : hd->cfg.workspace_bytes > 0 ? hd->cfg.workspace_bytes : kDefaultWorkspace;
-  const unsigned long long fact_most = fact_list_max(N, Rn, prune ? 2 : p, ws);      // (pruned L1: what the blocks leave, no try to lose)
+  unsigned long long fact_most = fact_list_max(N, Rn, prune ? 2 : p, ws);      // (pruned L1: what the blocks leave, no try to lose)
+  if (straight) fact_most = (unsigned long long)std::min((double)fact_most, straight_most(cap, std::max(share, 0.0) * triples));
   const unsigned int fact_cap = (unsigned int)std::min<unsigned long long>(
       std::max(hd->fcap, hd->fcap_start > 0 ? hd->fcap_start : fact_list_start(N, Rn)), fact_most);
   // The same call again without the list of pairs (dense: the kernels that contract every relation or sum in L1; a pruned join
@@ -1607,6 +1618,13 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
                                     prep_mode == kPrepFresh && hd->prep.valid ? kPrepReuse : prep_mode);
     hd->no_fact = false;
     hd->as_dense = as_dense;
+    return rc2;
+  };
+  // ... and again by way of the groups
+  auto not_straight = [&]() {
+    hd->no_straight = true;
+    const int rc2 = join_range_impl(hd, E, N, d, Rvecs, R, p, delta, r_begin, r_end, out_triples, cap, count, nullptr, kPrepFresh);
+    hd->no_straight = false;
     return rc2;
   };
   int tile_id = kDefaultL2Tile;
@@ -2115,6 +2133,7 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
   // them): the list grows to what was asked for and the join runs again from the start.
   if (hd->host_counters->fact_need > fact_cap) {      // (the same of the list of pairs)
     const unsigned long long need = hd->host_counters->fact_need;
+    if (need > fact_most && straight) return not_straight();
     if (need > fact_most) return without_list();      // a threshold that passes so much: pair by pair, scored in place
     hd->fcap = (unsigned int)std::min<unsigned long long>(need + need / 4 + 1024, kFactListMax);
     return join_range_impl(hd, E, N, d, Rvecs, R, p, delta, r_begin, r_end, out_triples, cap, count, win,

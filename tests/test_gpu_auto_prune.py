@@ -70,3 +70,35 @@ def test_default_mode_over_a_range_of_relations_and_with_a_list_that_grows(monke
     got, _, st = _records(AUTO, "f32", E, Rv, 2, delta, 1 << 18, r_range=(3, 15))
     assert st["join_variant"] == 14
     np.testing.assert_array_equal(got, want)
+
+
+# One cluster pair per relation with most of its pairs within delta: the list of pairs is the longer way.  A call that only counts (a
+# sample tells), one with room for a few of them (the list outgrows what the room announced), one with room for all
+@pytest.mark.parametrize("cap", [0, 1000, 1 << 23])
+def test_calls_with_many_hits_go_over_the_groups_whatever_their_room(cap):
+    import paper_2307_12059_amd as kgc
+    E, Rv = _case(9, 6400, 46, 64, 400, 0.1, "f32")
+    delta = float(np.float32(0.1 * np.sqrt(128.0) * 1.1))
+    res = []
+    for prune in (ON, AUTO):
+        j = kgc.Join(prune=prune)
+        try:
+            got = [j.join(E, Rv, 2, delta, cap, fetch=False) for _ in range(2)][1]
+        finally:
+            j.close()
+        res.append(got["count"])
+        assert got["code"] == (1 if cap < got["count"] else 0) and got["stats"]["join_variant"] == 14
+    assert res[0] == res[1] > 1 << 21
+
+
+def test_counting_calls_with_few_hits_stay_on_the_factorised_kernel():
+    import paper_2307_12059_amd as kgc
+    E, Rv = _case(2, 2000, 8, 32, 100, 0.1, "f32")
+    delta = float(np.float32(0.1 * np.sqrt(64.0) * 0.9))
+    want = _records(ON, "f32", E, Rv, 2, delta, 1 << 18)[0].shape[0]
+    j = kgc.Join(prune=AUTO)
+    try:
+        got = j.join(E, Rv, 2, delta, 0, fetch=False)
+    finally:
+        j.close()
+    assert got["code"] == 1 and got["count"] == want > 0 and got["stats"]["join_variant"] == 100
