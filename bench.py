@@ -89,6 +89,7 @@ def main():
     ap.add_argument("--also-dense", type=int, default=3, help="extra dense (prune off) steps reported beside a pruned run")
     ap.add_argument("--also-factorised", type=int, default=3,
                     help="extra dense steps through the relation-factorised kernel (L2, d <= 282), reported beside")
+    ap.add_argument("--also-default", type=int, default=3, help="extra steps of the default pruning mode, reported beside")
     ap.add_argument("--general-form", type=int, default=0, metavar="STEPS",
                     help="also time kgc_join_ab (connector outputs supplied by the caller, pruned and dense) on the TransE connectors "
                          "A[r][h] = E[h] + Rv[r], B = E of the workload; needs R * N * d elements of extra memory")
@@ -154,14 +155,14 @@ def main():
     N, R, d, p = spec.N, spec.R, spec.d, spec.p
     E, Rv, cap, out = resident(wl)
 
-    def run(prune, steps, warmup, factorised=False, wl=wl, E=E, Rv=Rv, cap=cap, out=out, matrix=False, by_number=0):
+    def run(prune, steps, warmup, factorised=False, wl=wl, E=E, Rv=Rv, cap=cap, out=out, matrix=False, by_number=0, default=False):
         spec = wl.spec
         N, R, d, p = spec.N, spec.R, spec.d, spec.p
         # matrix: the kernel that contracts every pair of every relation on the matrix pipes, by its tile number (left
         # alone, a dense L2 join of this size takes the relation-factorised kernel)
         tile = args.tile or by_number or (18 if matrix and p == 2 and d <= 282 else 0)
-        j = kgc.Join(dtype=spec.storage, prune=kgc.KGC_PRUNE_ON if prune else kgc.KGC_PRUNE_OFF, tile_cfg=tile,
-                     factorised=factorised)
+        mode = kgc.KGC_PRUNE_AUTO if default else kgc.KGC_PRUNE_ON if prune else kgc.KGC_PRUNE_OFF
+        j = kgc.Join(dtype=spec.storage, prune=mode, tile_cfg=tile, factorised=factorised)
         res = None
         for _ in range(warmup):
             res = j.join(E, Rv, p, wl.delta, cap, out=out, fetch=False)
@@ -180,23 +181,26 @@ def main():
         ms_join = acc["ms_join"] / steps
         work = 2.0 * d * st["pairs_evaluated"]                 # flop (L2) or lane-ops (L1) of the join kernel per step
         if st["join_variant"] == 100:
-            # relation-factorised kernel: the matrix work is 1/R of the per-relation form, and the vector arithmetic
-            # bounds 128 pairs of a column with about eight lane operations (four additions, two three-way minima, the
-            # threshold and the comparison)
-            work = 8.0 / 128.0 * st["pairs_evaluated"]
-            roof = {"bound": "alu", "achieved": work / (ms_join * 1e-3) / 1e12 if ms_join > 0 else 0.0,
-                    "peak": PEAK_VALU_TLANEOPS, "unit": "Tlane-op/s"}
+            # relation-factorised kernel: one contraction per pair of entities and relation batch is what no call can do
+            # without; how many bounds and pairs the vector units then look at depends on the data and is not counted
+            work = 2.0 * st["k_padded"] * N * N * st["relation_batches"]
+            roof = {"bound": "mfma", "achieved": work / (ms_join * 1e-3) / 1e12 if ms_join > 0 else 0.0,
+                    "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
+                    "note": "the contraction of the pairs of entities alone, over a time that holds the bounds of every relation "
+                            "and the exact scores of the listed pairs too"}
         elif p == 2:
             roof = {"bound": "mfma", "achieved": work / (ms_join * 1e-3) / 1e12 if ms_join > 0 else 0.0,
                     "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s"}
         else:
+            if st["exact_blocks"] > 0:                         # the blocks that the bound left, instead of whole tiles
+                work = 2.0 * d * 1024.0 * st["exact_blocks"]
             roof = {"bound": "alu", "achieved": work / (ms_join * 1e-3) / 1e12 if ms_join > 0 else 0.0,
                     "peak": PEAK_VALU_TLANEOPS, "unit": "Tlane-op/s",
                     "note": "counted as if every dimension of every pair were summed; tiles end earlier"}
         roof["frac"] = roof["achieved"] / roof["peak"]
         roof["traffic"] = None      # filled below for configurations with a committed counter measurement
         v = st["join_variant"]
-        roof["kernel"] = ("k_join_l2_fact" if v == 100 else "k_join_l1" if p == 1 else "k_join_l2_dense" if v == 18
+        roof["kernel"] = ("k_join_l2_fact" if v == 100 else "k_l1_blocks" if p == 1 and st["exact_blocks"] > 0 else "k_join_l1" if p == 1 else "k_join_l2_dense" if v == 18
                           else "k_join_l2_direct" if v >= 15 else "k_join_l2_ares" if v >= 11
                           else "k_join_l2_stream" if v >= 6 else "k_join_l2")
         if prune and p == 2 and 6 <= v <= 14:
@@ -237,6 +241,8 @@ def main():
             # every staged operand row once: R * N head rows and N tail rows, each in whole 32-wide K slices of bf16
             k_read = (stats["k_padded"] + 31) // 32 * 32
             r["algorithmic_bytes"] = 2.0 * k_read * n_rows * (n_rel + 1) if mode == "dense" else None
+            if r["tile_cfg"] == 100:      # ... of the factorised form: both sides once, and the products r.e
+                r["algorithmic_bytes"] = 2.0 * k_read * n_rows * 2 + 4.0 * n_rows * n_rel
             if calib is not None:
                 r["peak_calibrated"] = calib["mfma_only"]
                 r["frac_calibrated"] = r["achieved"] / calib["mfma_only"]
@@ -272,6 +278,12 @@ def main():
     }
     if calib is not None:
         line["calibration"] = calib
+    if args.also_default > 0 and args.tile == 0:
+        # what a caller gets who sets nothing: pruned, or the factorised kernel over every pair
+        dm = run(True, args.also_default, 1, default=True)
+        assert dm["count"] == main_run["count"], "the default mode and the main run disagree on the number of hits"
+        line["default_mode"] = {"ms_per_step": dm["ms_per_step"], "value": N * N * R / (dm["ms_per_step"] * 1e-3), "hits": dm["count"],
+                                "phase_ms": dm["phase_ms"], "kernel": dm["roofline"]["kernel"]}
     if args.prune == "on":
         # the pruned steps' join kernel: same accounting, on the pairs of the surviving tiles
         line["roofline_pruned"] = finish_roofline(rated["roofline"], spec.name, N, R, rated["stats"], "pruned")
