@@ -1650,8 +1650,10 @@ __device__ __forceinline__ void fact_params(const DevCounters* __restrict__ cnt,
 
 // The smaller of two floats in one instruction, as the median of them and -infinity: fminf puts a canonicalising v_max before
 // every operand the compiler has not seen computed, which doubles the minima over accumulators (and it turns a median with a
-// constant infinity back into fminf: the empty asm hides the value).  A NaN gives -infinity, and a set that holds one stays
-// open.
+// constant infinity back into fminf: the empty asm hides the value).  A median with a NaN is the smallest of its numbers: a NaN
+// gives -infinity here, and a set that holds one stays open; the maximum below passes over it.  That loses nothing: rows that hold
+// no numbers are left out (stage_operands), so that a product r.t is a NaN only where ||r||^2 or a row's ||t||^2 is beyond
+// float32 (|r.t| <= ||r|| ||t||), and then the relation's threshold, or every one, is infinite or a NaN and keeps the set open.
 __device__ __forceinline__ float vmin2(float a, float b) {
   float lowest = -__builtin_inff();
   asm("" : "+s"(lowest));
@@ -1990,7 +1992,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1) void k_join_l2_fact(const JoinFac
         rb += 64 * NC;
       }
       const bool last = rb >= rl_end;
-      const int take = last ? cnt : cnt / kFactBatch * kFactBatch;        // (not the last: more than half full)
+      const int take = last ? cnt : cnt / kFactBatch * kFactBatch;        // (not the last: more than a quarter full)
       __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
       __builtin_amdgcn_wave_barrier();
       // ---- level 2: the open relations, kFactBatch at a time, the next batch's r.t and r.h in flight ----

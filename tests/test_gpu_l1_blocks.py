@@ -30,20 +30,27 @@ def _records(E, Rv, delta, dtype, **cfg):
         j.close()
     assert got["code"] == 0
     o = np.lexsort((got["t"], got["h"], got["r"]))
-    return np.stack([got["r"][o], got["h"][o], got["t"][o], got["dist"][o].view(np.int32)], 1)
+    return np.stack([got["r"][o], got["h"][o], got["t"][o], got["dist"][o].view(np.int32)], 1), got["stats"]["exact_blocks"]
 
 
 # clusters of a micro-tile or less, of several (whole tiles survive), few and many blocks (either side of the line where a
 # batch goes back to whole tiles), d at the edges of the 16-dimension slices and odd, rows that start on no vector boundary
-@pytest.mark.parametrize("N,R,d,rows,dtype", [(700, 9, 16, 30, "f32"), (1500, 40, 17, 33, "bf16"), (3000, 20, 100, 200, "f32"),
-                                              (4000, 300, 12, 300, "f32"), (2600, 7, 33, 20, "f32"), (900, 5, 250, 60, "bf16")])
-def test_blocks_match_the_dense_kernel(N, R, d, rows, dtype, monkeypatch):
+@pytest.mark.parametrize("N,R,d,rows,dtype,by_blocks", [(700, 9, 16, 30, "f32", True), (1500, 40, 17, 33, "bf16", True),
+                                                        (3000, 20, 100, 200, "f32", True), (4000, 300, 12, 300, "f32", False),
+                                                        (2600, 7, 33, 20, "f32", True), (900, 5, 250, 60, "bf16", True)])
+def test_blocks_match_the_dense_kernel(N, R, d, rows, dtype, by_blocks, monkeypatch):
     E, Rv = _case(N + d, N, R, d, rows, dtype)
     delta = float(np.float32(0.1 * np.sqrt(2.0) * (0.798 * d - (1.3 if d == 12 else 0.5) * np.sqrt(d))))      # (fewer hits of 27 M aligned pairs)
-    want = _records(E, Rv, delta, dtype, prune=OFF, tile_cfg=17)
+    want = _records(E, Rv, delta, dtype, prune=OFF, tile_cfg=17)[0]
     assert want.shape[0] > 100
-    np.testing.assert_array_equal(_records(E, Rv, delta, dtype, prune=ON), want)
+    got, blocks = _records(E, Rv, delta, dtype, prune=ON)
+    np.testing.assert_array_equal(got, want)
+    assert (blocks > 0) == by_blocks
     monkeypatch.setenv("KGC_EXACT_LIST_CAP", "3")          # both lists grow
-    np.testing.assert_array_equal(_records(E, Rv, delta, dtype, prune=ON), want)
+    got, grown = _records(E, Rv, delta, dtype, prune=ON)
+    np.testing.assert_array_equal(got, want)
+    assert (grown > 3) == by_blocks
     monkeypatch.setenv("KGC_PAIR_LIST_LIMIT", "1")         # no list of pairs: whole tiles, scored in place
-    np.testing.assert_array_equal(_records(E, Rv, delta, dtype, prune=ON), want)
+    got, none = _records(E, Rv, delta, dtype, prune=ON)
+    np.testing.assert_array_equal(got, want)
+    assert none == 0
