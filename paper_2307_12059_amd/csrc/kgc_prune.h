@@ -1492,12 +1492,13 @@ __global__ __launch_bounds__(256) void k_rows_from_bitmap(const uint32_t* __rest
 // The bound once more for the sixteen micro-tile pairs of every surviving 128 x 128 tile of a pruned L1 join (k_l1_blocks): a wave
 // takes tiles of one row, a lane per dimension.  A tile is a few memory round trips, so a batch of few rows, whose tiles a wave each
 // would walk alone, deals every row's tiles to as many waves as there are for it.  The waves end once more blocks are listed than
-// l1_by_blocks accepts (*count only grows, and keeps within 64 a wave of that line): the batch then goes by whole tiles.  That is
+// l1_by_blocks accepts (*count only grows, and keeps within 256 a wave of that line): the batch then goes by whole tiles.  That is
 // mostly known far earlier: every eighth wave reports its first tile, one anywhere in its row, and the first report after which
 // those hold clearly more blocks than the line (eight a tile, six are allowed) puts *count past it: N = 16,000, R = 40, 625,000
-// tiles with all blocks within reach: 697 us with the line alone, 33 with the reports, beside 26.6 ms for the whole tiles.
-// (Atomics on one word are served one after the other, 8 ns each: more waves, or a look at the reports at every flush, cost more
-// than they saved.)
+// tiles with all blocks within reach: 697 us with the line alone, 16 with the reports, beside 26.6 ms for the whole tiles.
+// Atomics on one word are served one after the other, 8 ns each, so a workgroup asks for the last entries of its waves' queues
+// at once, and only its first wave flushes early, to see the count for all four (4,959, 7, 39: 28 us with 64 entries a wave, 17
+// so; N = 15,000, R = 64, by blocks: 44 and 30).  (More waves, or a look at the reports at every flush, cost more than they saved.)
 struct L1MicroArgs {
   const uint32_t* row_start; const uint32_t* row_count; const uint32_t* cols; const uint32_t* active_rows;      // see JoinStreamArgs
   const unsigned int* n_active;
@@ -1512,25 +1513,33 @@ struct L1MicroArgs {
 };
 constexpr unsigned int kL1SampleTiles = 64, kL1SampleBlocks = 8;      // tiles a decision takes at least, and blocks a tile it takes more than
 constexpr unsigned int kL1Whole = 0x80000000u;                  // *count of a batch that was sent to whole tiles early (more than may be listed)
-constexpr int kL1MicroQueue = 64;      // blocks a wave holds back: one atomic a flush
+constexpr int kL1MicroQueue = 256, kL1MicroEarly = 64;      // blocks a wave holds back, and the first of a workgroup
 __global__ __launch_bounds__(256) void k_l1_micro_pairs(const L1MicroArgs a) {
   static_assert(kL1Tile == 4 * 32, "four micro-tiles a side");
   __shared__ int32_t queue[4][3][kL1MicroQueue];
+  __shared__ int stop_s, qn_s[4];
+  __shared__ unsigned int base_s;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   int32_t (&q)[3][kL1MicroQueue] = queue[wave];
+  const int room = wave == 0 ? kL1MicroEarly : kL1MicroQueue;
   int qn = 0;
+  if (threadIdx.x == 0) stop_s = 0;
+  __syncthreads();
   const unsigned int line = l1_block_line(a.tiles, a.most);
   const bool early = *a.tiles * kL1SampleBlocks > line;
   bool report = ((blockIdx.x * 4u + (unsigned)wave) & 7u) == 0u && early;
-  bool over = false;                   // more blocks than the line, as of this wave's last flush (or *count put past it)
+  bool over = false;                   // more blocks than the line, as of a flush of this workgroup (or *count put past it)
   auto flush = [&]() {
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
     __builtin_amdgcn_wave_barrier();
     unsigned int base = 0u;
     if (lane == 0) base = atomicAdd(a.count, (unsigned int)qn);
     base = (unsigned int)__builtin_amdgcn_readfirstlane((int)base);
-    if (lane < qn && base + (unsigned)lane < a.cap) a.list[base + (unsigned)lane] = ExactEntry{q[0][lane], q[1][lane], q[2][lane], 0};
-    over = base + (unsigned)qn > line;
+    for (int k = lane; k < qn && base + (unsigned)k < a.cap; k += 64) a.list[base + (unsigned)k] = ExactEntry{q[0][k], q[1][k], q[2][k], 0};
+    if (base + (unsigned)qn > line) {
+      over = true;
+      __hip_atomic_store(&stop_s, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
     qn = 0;
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
     __builtin_amdgcn_wave_barrier();
@@ -1539,7 +1548,7 @@ __global__ __launch_bounds__(256) void k_l1_micro_pairs(const L1MicroArgs a) {
   const float reach = l1_reach(a.delta, a.prm);
   const unsigned int waves = gridDim.x * 4u, me = blockIdx.x * 4u + (unsigned)wave;
   const unsigned int parts = n_rows >= waves ? 1u : waves / (n_rows ? n_rows : 1u);      // of a row (a part past its tiles is empty)
-  for (unsigned int item = me; item < n_rows * parts; item += waves) {
+  for (unsigned int item = me; item < n_rows * parts && !over; item += waves) {
     const unsigned int i = item % n_rows, part = item / n_rows;
     const int64_t row = (int64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)a.active_rows[i]);
     const int rl = (int)(row / a.nH), tH = (int)(row - (int64_t)rl * a.nH);
@@ -1551,6 +1560,8 @@ __global__ __launch_bounds__(256) void k_l1_micro_pairs(const L1MicroArgs a) {
     const float rh = a.rad_h[mh + (p >> 2)];
     int tT_next = mine ? (int)a.cols[t0 + (int)(part + turn * parts)] : 0;
     for (unsigned int left = mine; left; --left) {
+      over = over || __builtin_amdgcn_readfirstlane(__hip_atomic_load(&stop_s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) != 0;
+      if (over) break;
       const int tT = __builtin_amdgcn_readfirstlane(tT_next);
       const int64_t mt = rl * a.t_rel + (int64_t)tT * 4;
       const float rt = a.rad_t[mt + (p & 3)];
@@ -1591,10 +1602,7 @@ __global__ __launch_bounds__(256) void k_l1_micro_pairs(const L1MicroArgs a) {
         }
         report = false;
       }
-      if (qn + n > kL1MicroQueue) {
-        flush();
-        if (over) return;
-      }
+      if (qn + n > room) flush();
       if (keep) {
         const int pos = qn + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0u));
         q[0][pos] = a.r0 + rl; q[1][pos] = tH * kL1Tile + (p >> 2) * 32; q[2][pos] = tT * kL1Tile + (p & 3) * 32;
@@ -1602,7 +1610,16 @@ __global__ __launch_bounds__(256) void k_l1_micro_pairs(const L1MicroArgs a) {
       qn += n;
     }
   }
-  if (qn > 0) flush();
+  // what the four waves still hold, by one atomic (where the batch goes by whole tiles nobody reads it)
+  if (lane == 0) qn_s[wave] = qn;
+  __syncthreads();
+  const int all = qn_s[0] + qn_s[1] + qn_s[2] + qn_s[3];
+  if (stop_s || all == 0) return;                                  // (the same for the workgroup)
+  if (threadIdx.x == 0) base_s = atomicAdd(a.count, (unsigned int)all);
+  __syncthreads();
+  unsigned int base = base_s;
+  for (int w = 0; w < wave; ++w) base += (unsigned)qn_s[w];
+  for (int k = lane; k < qn && base + (unsigned)k < a.cap; k += 64) a.list[base + (unsigned)k] = ExactEntry{q[0][k], q[1][k], q[2][k], 0};
 }
 
 }  // namespace kgc
