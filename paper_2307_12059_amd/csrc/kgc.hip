@@ -329,11 +329,16 @@ inline int64_t fact_batch(int64_t bytes, int64_t slots, int64_t R) {
 }
 // Dense L2 joins that the relation-factorised kernel takes by itself: its fixed part (products r.e, one contraction per pair of
 // entities, the list of pairs) is paid once, the other kernels contract every relation and score their candidates in place.
-// Measured, whole calls in us, per-relation kernel / this one, float32, clusters of 30 to 60 rows in random order: N = 300, R =
-// 100, d = 32: 170 / 93; 500, 16, 64: 92 / 89; 700, 200, 64: 160 / 107 (with 139,000 hits 1,173 / 174); 1,000, 4, 64: 85 / 84;
-// 2,000, 4, 64: 88 / 83; 4,000, 2, 100: 88 / 83; 4,000, 6, 400: 229 / 156; 15,000, 2, 64: 170 / 142; 15,000, 4, 512: 998 / 339;
-// 30,000, 2, 128: 502 / 349; 60,000, 4, 256: 5,952 / 1,792.  One relation has nothing to share: 60,000, 1, 128: 883 / 1,021.
-inline bool fact_pays(int64_t N, int64_t R) { return R >= 2 && N >= 256 && N * R >= 6000; }
+// Measured, whole calls, time of the per-relation kernel over that of this one, float32, clusters of 30 rows in random order, few
+// hits / many (a fiftieth, a third of the aligned pairs): d = 64: N = 256, R = 24: 0.86 / 1.30; 256, 64: 1.02 / 2.01; 1,000, 6:
+// 0.90 / 1.16; 1,000, 12: 0.96 / 1.42; 1,000, 16: 1.01 / 1.63; 2,000, 4: 0.94 / 1.14; 2,000, 8: 1.02 / 1.33; 5,000, 2: 0.98 /
+// 0.99; 5,000, 3: 1.05 / 1.09; 8,000, 2: 1.04 / 1.12; 12,000, 4: 1.42 / 1.48; d = 512: 1,000, 6: 0.85 / 0.97; 1,000, 16: 1.09 / 1.37;
+// 3,000, 2: 0.95 / 0.98; 5,000, 3: 1.32 / 1.39.  The line lies where the two are level with few hits, N R = 15,000.  With one K slice
+// (d <= 26) the contraction is nothing to share: 5,000, 3: 0.89 / 1.02; 12,000, 4: 0.69 / 0.75; 5,000, 12 (rows in order): 1.18 / 1.56.  One
+// relation has nothing to share either: 60,000, 1, 128: 883 / 1,021 us.
+inline bool fact_pays(int64_t N, int64_t R, int KS) { return R >= (KS > 1 ? 2 : 8) && N >= 256 && N * R >= 15000; }
+// ... and those that it may be asked to take in place of pruned ones, whose chain of launches is longer (see kAutoDenseUs)
+inline bool fact_may(int64_t N, int64_t R) { return R >= 2 && N >= 256 && N * R >= 6000; }
 
 // Dense L1 joins that the relation-factorised kernel takes first: ||x||_2 <= ||x||_1, so every hit is among the pairs
 // within delta in L2, which its list then scores in L1.  Where the list grows past fact_list_max the L1 kernel does the
@@ -1572,7 +1577,7 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
   const int KS = (d + kNormCols + kSliceK - 1) / kSliceK;
   // KGC_PRUNE_AUTO: pruned, or the factorised form (for L1 if a sample says that its list stays short)
   const bool automatic = hd->cfg.prune == KGC_PRUNE_AUTO && free_choice && !hd->as_dense && hd->cfg.factorised == 0 && hd->cfg.group_radius == 0.f &&
-                         KS <= kDirectHalfMaxKS && delta >= 0.f && delta < 1e18f && fact_pays(N, Rn);
+                         KS <= kDirectHalfMaxKS && delta >= 0.f && delta < 1e18f && fact_may(N, Rn);
   double dense_us = automatic ? fact_us(N, Rn, d) + hits_us(N, Rn, cap) : 0.0;
   KGC_HIP(hd, hipEventRecord(hd->ev[0], st));
   double share = -1.0;                                     // close_share, once it is known
@@ -1594,7 +1599,7 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
   // the relation-factorised form (dense, head tile in LDS) has one tile shape of its own; a tile_cfg asks for another kernel
   const bool fact = !prune && !win && !hd->static_mode && !hd->no_fact &&
                     (p == 2 && hd->cfg.factorised != 0 ? KS <= kDirectMaxKS
-                     : p == 2 ? hd->cfg.tile_cfg == 0 && fact_pays(N, Rn) && KS <= kDirectHalfMaxKS && delta < 1e18f
+                     : p == 2 ? hd->cfg.tile_cfg == 0 && (straight || hd->as_dense || fact_pays(N, Rn, KS)) && KS <= kDirectHalfMaxKS && delta < 1e18f
                               : hd->cfg.tile_cfg == 0 && (straight || hd->as_dense || fact_pays_l1(N, Rn, d)) && KS <= kDirectHalfMaxKS &&
                                     delta >= 0.f && delta < 1e18f);
   // ... and the part of a pruned L2 join that the bound test can do nothing for
@@ -1671,7 +1676,7 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
     const int64_t units = (int64_t)ut.n_big + (hd->host_gstate->tail_fill + kMicro - 1) / kMicro;      // (without those that are all padding)
     // (Almost) all rows in one group: there is nothing to prune by, and the factorised kernel takes the join as a dense one
     // (broad embeddings, N = 20,000, R = 37, d = 512: 71 -> 1.2 ms).  With KGC_PRUNE_AUTO also where the groups are poor.
-    bool dense = part_ok && units <= kFewUnits && fact_pays(N, Rn);
+    bool dense = part_ok && units <= kFewUnits && fact_may(N, Rn);
     if (!dense && automatic && grouped_badly(N, hd->host_gstate->tail_fill, (int)std::min<int64_t>(units, 1 << 30), hd->host_gstate->max_unit, dense_us)) {
       if (p == 1 && share < 0.0 && (rc = close_share(hd, E, N, d, Rvecs, r_begin, Rn, delta, &share)) != KGC_OK) return rc;
       dense = grouped_badly(N, hd->host_gstate->tail_fill, (int)std::min<int64_t>(units, 1 << 30), hd->host_gstate->max_unit, dense_us + listed_us());

@@ -174,3 +174,25 @@ def test_row_order_leaves_the_result_alone(N, R, d, p, dtype, rows, monkeypatch)
         out.append(np.stack([got["r"][o], got["h"][o], got["t"][o], got["dist"][o].view(np.int32)], 1))
     assert out[0].shape[0] > 100
     np.testing.assert_array_equal(out[0], out[1])
+
+
+# The line from which dense L2 joins take this kernel by themselves: N R = 15,000 with two K slices and more, eight relations with one
+# (d <= 26); calls on either side of it give the same records
+@pytest.mark.parametrize("N,R,d,taken", [(1000, 15, 64, True), (999, 15, 64, False), (7500, 2, 27, True), (7500, 2, 26, False),
+                                         (2200, 7, 26, False), (2200, 8, 26, True), (256, 60, 33, True), (255, 70, 33, False)])
+def test_line_of_the_dense_dispatch(N, R, d, taken):
+    import paper_2307_12059_amd as kgc
+    E, Rv = _case(N + d, N, R, d, max(3, N // 40), 0.1, "f32")
+    delta = float(np.float32(0.1 * np.sqrt(2.0 * d) * 0.95))
+    recs = []
+    for tile in (0, 18):
+        j = kgc.Join(prune=PRUNE_OFF, tile_cfg=tile)
+        try:
+            got = j.join(E, Rv, 2, delta, 1 << 20)
+        finally:
+            j.close()
+        assert got["code"] == 0 and got["stats"]["join_variant"] == (100 if taken and not tile else 18)
+        o = np.lexsort((got["t"], got["h"], got["r"]))
+        recs.append(np.stack([got["r"][o], got["h"][o], got["t"][o]], 1))
+    assert recs[0].shape[0] > 30
+    np.testing.assert_array_equal(recs[0], recs[1])
