@@ -285,14 +285,17 @@ void launch_small_dot(hipStream_t st, const void* X, int dtype, int64_t n_rows, 
 
 // Dense factorised joins whose rows are put in order first (order_rows): what the order saves is bounds that sets of
 // strangers leave open, which grow with N^2 R, and what it costs is four launches and a contraction with an eighth of the rows
-// (4,096 at most), about d N min(N, 32,768).  Measured, whole calls in us, caller's order (random) / put in order, float32
-// unless noted: N = 2,000, R = 8, d = 32: 97 / 100; 3,000, 16, 100: 113 / 118; 2,000, 30, 100: 113 / 116; 1,000, 64, 32: 106 /
-// 107; 6,000, 16, 100: 144 / 128; 3,000, 100, 64: 212 / 145; 8,000, 400, 256: 586 / 239; 15,000, 1,345, 100: 4,843 / 589; 50,000,
-// 200, 64: 2,854 / 961; 100,000, 200, 200 (bf16): 9,175 / 4,675; L1 40,000, 18, 100: 2,849 / 825.  Where d is long against the
-// relations the contraction decides: 20,000, 8, 512: 723 / 783; 50,000, 8, 512 (bf16): 3,058 / 3,333; 20,000, 32, 512: 796 /
-// 780; 10,000, 16, 512: 326 / 324; 10,000, 8, 256: 207 / 200.  With a quarter, an eighth and a sixteenth of
-// the rows as pivots 15,000, 1,345, 100 takes 688 / 589 / 658 us, L1 12,000, 100, 32 in groups of a dozen 321 / 310 / 386.
-inline bool order_pays(int64_t N, int64_t R, int d) { return N >= 1000 && N * R >= 60000 && R * 32 >= d; }
+// (4,096 at most), about N^2 k / 8 (k: staged length of a row).  Measured, whole calls, time in the caller's order (random) over that in
+// order, float32 clusters of 30 rows / broad ones in bfloat16: d = 100: N = 1,000, R = 64: 0.94 / 0.94; 1,000, 250: 1.08 / 1.06; 2,000, 32:
+// 0.92 / 0.95; 2,000, 64: 1.05 / 1.08; 5,000, 12: 0.93 / 0.94; 5,000, 16: 1.01 / 0.97; 12,000, 8: 0.91 / 0.92; 12,000, 16: 1.12 / 1.08; 20,000,
+// 12: 1.06 / 1.02; d = 602: 2,000, 32: 0.95 / 0.86; 5,000, 48: 1.12 / 1.01; 12,000, 16: 0.90 / 0.87; 12,000, 32: 0.99 / 0.93; d = 16: 8,000, 8:
+// 1.31 / 1.08.  Far from the line, in us: 15,000, 1,345, 100: 4,843 / 589; 50,000, 200, 64: 2,854 / 961; 100,000, 200, 200 (bf16): 9,175 / 4,675; L1
+// 40,000, 18, 100: 2,849 / 825.  With a quarter, an eighth and a sixteenth of the rows as pivots 15,000, 1,345, 100 takes 688 / 589 / 658 us, L1
+// 12,000, 100, 32 in groups of a dozen 321 / 310 / 386.
+inline bool order_pays(int64_t N, int64_t R, int d) {
+  const double k = (double)((d + kNormCols + kSliceK - 1) / kSliceK * kSliceK);
+  return N >= 1000 && (double)N * (double)N * (16.0 * (double)R - k) >= 3e9;
+}
 
 // One relation batch of the relation-factorised join over a run of slots.
 struct FactJob {
