@@ -399,9 +399,15 @@ constexpr double kAutoDenseUs = 270.0;
 // without a group: 5,290 / 214 us; 29,297, 639, 59, clusters of 12: 1.57 s / 635 us; 131,975, 9, 64, clusters of 14: 1.0 s / 2.9
 // ms; 38,077, 336, 100, four units: 161 / 2.0 ms; 245,439, 434, 64, Zipf sizes: 34 / 12.3 ms); from 20 ms of contraction on the
 // pruned kernels win again (1,000,000, 1,000, 128: 78 / 300 ms).  A large unit beside many small ones is no sign: 364,163, 20, 27:
-// 5,965 / 14,149; 17,272, 107, 254: 1,093 / 1,341.
-inline bool grouped_badly(int64_t N, int64_t tail_rows, int n_units, int max_unit, double us) {
-  return us < 20000.0 && (tail_rows * 128 > N || (n_units <= 64 && (int64_t)max_unit * kMicro * 4 > N));
+// 5,965 / 14,149; 17,272, 107, 254: 1,093 / 1,341.  In L2 what that costs the pruned kernels is weighed too: the rows without a group
+// against all rows and the largest unit against itself, contracted for every relation at 1 PFLOP/s, half of the pairs out of
+// reach.  Over 900 joins that group poorly (N = 1,000 to 400,000) 39 of 567 that took the factorised form without it were slower
+// for it, down to 0.20 times as fast (116,230, 5, 512, 1,502 rows without a group: 2,754 / 13,450); with it 17 of 522, 0.38 (97,372, 9, 200,
+// clusters of 18: 1,710 / 4,472); the geometric mean of all is 3.62 times the pruned kernels' speed, 1.05 times off the better of the two.
+inline bool grouped_badly(int64_t N, int64_t R, int KS, int p, int64_t tail_rows, int n_units, int max_unit, double us) {
+  const double unit_rows = (double)max_unit * kMicro;
+  const double pruned_us = 300.0 + 2e-9 * (double)KS * kSliceK * (double)R * ((double)tail_rows * (double)N + unit_rows * unit_rows);
+  return us < 20000.0 && (tail_rows * 128 > N || (n_units <= 64 && unit_rows * 4.0 > (double)N)) && (p == 1 || us < pruned_us);
 }
 // What a pair of the factorised form's list costs (L1, where a sample says how many there are)
 constexpr double kListedPairUs = 2e-4;
@@ -1680,9 +1686,12 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
     // (Almost) all rows in one group: there is nothing to prune by, and the factorised kernel takes the join as a dense one
     // (broad embeddings, N = 20,000, R = 37, d = 512: 71 -> 1.2 ms).  With KGC_PRUNE_AUTO also where the groups are poor.
     bool dense = part_ok && units <= kFewUnits && fact_may(N, Rn);
-    if (!dense && automatic && grouped_badly(N, hd->host_gstate->tail_fill, (int)std::min<int64_t>(units, 1 << 30), hd->host_gstate->max_unit, dense_us)) {
+    auto poor = [&](double us) {
+      return grouped_badly(N, Rn, KS, p, hd->host_gstate->tail_fill, (int)std::min<int64_t>(units, 1 << 30), hd->host_gstate->max_unit, us);
+    };
+    if (!dense && automatic && poor(dense_us)) {
       if (p == 1 && share < 0.0 && (rc = close_share(hd, E, N, d, Rvecs, r_begin, Rn, delta, &share)) != KGC_OK) return rc;
-      dense = grouped_badly(N, hd->host_gstate->tail_fill, (int)std::min<int64_t>(units, 1 << 30), hd->host_gstate->max_unit, dense_us + listed_us());
+      dense = poor(dense_us + listed_us());
     }
     if (dense) {
       float ms = 0.f;

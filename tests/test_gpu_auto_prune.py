@@ -102,3 +102,32 @@ def test_counting_calls_with_few_hits_stay_on_the_factorised_kernel():
     finally:
         j.close()
     assert got["code"] == 1 and got["count"] == want > 0 and got["stats"]["join_variant"] == 100
+
+
+def test_few_rows_without_a_group_do_not_send_a_large_join_to_the_factorised_kernel():
+    """Clusters of 25 rows, a hundredth of which form no group: contracting every pair of 60,000 rows at d = 300 takes far longer than the
+    pruned kernels spend on those few."""
+    import paper_2307_12059_amd as kgc
+    g = np.random.default_rng(8)
+    N, R, d, k = 60_000, 6, 300, 2_400
+    import torch
+    cent = g.standard_normal((k, d)).astype(np.float32)
+    lone = 800
+    E = np.concatenate([np.repeat(cent, 25, axis=0)[:N - lone] + 0.1 * g.standard_normal((N - lone, d)).astype(np.float32),
+                        g.standard_normal((lone, d)).astype(np.float32)])[g.permutation(N)].astype(np.float32)
+    src = g.integers(0, k, R)
+    Rv = (cent[(src + 1) % k] - cent[src]).astype(np.float32)
+    E, Rv = torch.from_numpy(E).cuda(), torch.from_numpy(Rv).cuda()
+    delta = float(np.float32(0.1 * np.sqrt(2.0 * d) * 0.98))
+    recs = []
+    for prune in (AUTO, ON):
+        j = kgc.Join(prune=prune)
+        try:
+            got = j.join(E, Rv, 2, delta, 1 << 18)
+        finally:
+            j.close()
+        assert got["code"] == 0 and got["stats"]["join_variant"] != 100 and got["stats"]["groups"] > 1000, got["stats"]
+        o = np.lexsort((got["t"], got["h"], got["r"]))
+        recs.append(np.stack([got["r"][o], got["h"][o], got["t"][o]], 1))
+    assert recs[0].shape[0] > 100
+    np.testing.assert_array_equal(recs[0], recs[1])
