@@ -78,7 +78,6 @@ struct kgc_handle {
   DevBuf se_a, se_b;                           // connector rows of a relation batch (kgc_join_se)
   DevBuf xlist;                                // accumulator blocks listed for the exact stage (L2 joins)
   unsigned int xcap = kExactListCap;           // its length in entries: grows when a batch wanted to list more
-  DevBuf sample_counts;                        // close_share
   DevBuf flist, umin;                          // listed pairs; relation-factorised join: extremes of 2 r.e over 8 and 64 rows
   unsigned int fcap = 0;                       // entries of flist that an earlier call needed (see fact_list_start)
   unsigned int fcap_start = 0;                 // > 0: ... and to start with (tests)
@@ -255,9 +254,9 @@ JoinL1Kernel l1_kernel_for(const RecheckCtx& cx) {
 }
 
 // a batch of a pruned L1 join by pairs of micro-tiles (k_l1_blocks): the blocks that the bound leaves of the listed tiles, their
-// pairs within the filter's threshold, the scores; both lists empty again afterwards
+// pairs within the filter's threshold, the scores; both lists empty again for the next batch, if there is one
 void launch_l1_blocks(hipStream_t st, L1MicroArgs ma, JoinL1Args la, unsigned row_grid, ExactEntry* pairs, unsigned int pair_cap,
-                      unsigned int most, DevCounters* cnt) {
+                      unsigned int most, DevCounters* cnt, bool last) {
   const RecheckCtx& cx = la.cx;
   const JoinParams* prm = la.prm;
   ma.tiles = &cnt->tile_cursor; ma.most = most; ma.sample = &cnt->l1_sample;
@@ -269,7 +268,7 @@ void launch_l1_blocks(hipStream_t st, L1MicroArgs ma, JoinL1Args la, unsigned ro
   k_exact_pairs<<<2048, 256, 0, st>>>(pairs, &cnt->n_fact, pair_cap, &cnt->fact_need, cx);
   la.block_count = ma.count; la.tile_total = &cnt->tile_cursor; la.block_most = most;      // (the batch whole tiles are better for)
   hipLaunchKernelGGL(l1_kernel_for(cx), dim3(row_grid), dim3(256), 0, st, la);
-  k_fill_u32<<<1, 64, 0, st>>>(&cnt->n_exact, (sizeof(DevCounters) - offsetof(DevCounters, n_exact)) / 4, 0u);
+  if (!last) k_fill_u32<<<1, 64, 0, st>>>(&cnt->n_exact, (sizeof(DevCounters) - offsetof(DevCounters, n_exact)) / 4, 0u);
 }
 
 // out[i][j] = x_i . y_j, one wave per 32 x 32 results on the float32 matrix pipes (k_small_dot): X rows of the storage
@@ -373,6 +372,14 @@ inline unsigned int fact_list_start(int64_t N, int64_t R) {
   return (unsigned int)std::min((double)(1u << 23), std::max((double)(1u << 18), (double)N * (double)N * (double)R / 64.0));
 }
 
+// Pruned L1 joins list what is within the float32 filter's threshold in the blocks the bound leaves, little more than the hits: as
+// many as the caller makes room for (a call that only counts says nothing).  Up to a MiB an allocation is a microsecond, beyond
+// it tens to hundreds the first time: first calls of 656, 77, 20 (bf16) and of structured embeddings of 1,340, 9, 18: 780 and 815 us with
+// the dense length, 700 and 745 so.
+inline unsigned int l1_list_start(int64_t N, int64_t R, uint64_t cap) {
+  return cap == 0 ? fact_list_start(N, R) : (unsigned int)std::min<uint64_t>(fact_list_start(N, R), std::max<uint64_t>(1u << 16, cap + cap / 8));
+}
+
 // A typical time of the factorised form in us without its hits (fit over 250 joins of N = 500 to 400,000, half of them within
 // 15 %): fixed part, contraction, row order, bounds, products, passes over the rows.
 inline double fact_us(int64_t N, int64_t R, int d) {
@@ -446,9 +453,13 @@ bool have_list(kgc_handle* hd, unsigned int entries) {
   return true;
 }
 
-// ... and the list of blocks of a pruned L1 join, which goes by whole tiles without it
-bool have_blocks(kgc_handle* hd) {
-  const size_t bytes = (size_t)hd->xcap * sizeof(ExactEntry);
+// entries of the list of blocks that a pruned L1 join of so many tiles a batch may fill (see l1_by_blocks)
+inline unsigned int l1_block_cap(const kgc_handle* hd, int64_t tiles) {
+  return (unsigned int)std::min<int64_t>(hd->xcap, std::max<int64_t>(kL1FewBlocks, 6 * tiles));
+}
+// ... and that list with room for `entries`: the join goes by whole tiles without it
+bool have_blocks(kgc_handle* hd, unsigned int entries) {
+  const size_t bytes = (size_t)entries * sizeof(ExactEntry);
   if (hd->xlist.p && hd->xlist.bytes >= bytes) return true;
   release(hd->xlist);
   if ((hd->xlist_limit > 0 && bytes > hd->xlist_limit) || hipMalloc(&hd->xlist.p, bytes) != hipSuccess) {
@@ -586,7 +597,7 @@ void kgc_destroy(kgc_handle* h) {
                     &h->gram, &h->relu, &h->reln, &h->asg_a, &h->asg_b, &h->limr, &h->top1_buf, &h->top1_state,
                     &h->unit_first, &h->unit_n, &h->cent_u, &h->rad_u, &h->cnorm_u, &h->gram_u, &h->relu_u, &h->pair_list,
                     &h->pair_count, &h->xlist, &h->tile_rows, &h->se_a, &h->se_b, &h->zero_row, &h->cent_a, &h->rad_a, &h->top1_a, &h->top1_b, &h->top1_pick, &h->top_samples, &h->topk_state,
-                    &h->flist, &h->umin, &h->sample_counts})
+                    &h->flist, &h->umin})
     release(*b);
   if (h->host_gstate) (void)hipHostFree(h->host_gstate);
   if (h->host_counters) (void)hipHostFree(h->host_counters);
@@ -698,10 +709,11 @@ int kgc_join_ab(kgc_handle* hd, const void* A, const void* B, int64_t N, int32_t
   // pruned L1 joins go by pairs of micro-tiles, while their list of pairs is to be had and holds what a batch leaves
   const unsigned long long pairs_most = fact_list_max(N, R, 2, ws);
   const unsigned int pair_cap = (unsigned int)std::min<unsigned long long>(
-      std::max(hd->fcap, hd->fcap_start > 0 ? hd->fcap_start : fact_list_start(N, R)), pairs_most);
+      std::max(hd->fcap, hd->fcap_start > 0 ? hd->fcap_start : l1_list_start(N, R, cap)), pairs_most);
   bool l1_blocks = prune && p == 1 && !hd->no_fact;      // (their count stops little past block_most: 32 bits do for any batch)
   const unsigned int block_most = block_list_max(hd, ws);
-  if (l1_blocks && (!have_blocks(hd) || !have_list(hd, pair_cap))) l1_blocks = false;
+  const unsigned int block_cap = l1_block_cap(hd, tiles_per_rel * RBmax);
+  if (l1_blocks && (!have_blocks(hd, block_cap) || !have_list(hd, pair_cap))) l1_blocks = false;
   int nbatch = 0;
   for (int64_t r0 = 0; r0 < R; r0 += RBmax, ++nbatch) {
     const int RB = (int)std::min<int64_t>(RBmax, R - r0);
@@ -832,8 +844,8 @@ int kgc_join_ab(kgc_handle* hd, const void* A, const void* B, int64_t N, int32_t
         ma.cent_h = (const float*)hd->cent_a.p; ma.rad_h = (const float*)hd->rad_a.p; ma.cent_t = (const float*)hd->cent.p; ma.rad_t = (const float*)hd->rad.p;
         ma.h_rel = n_micro; ma.t_rel = b_per_relation ? n_micro : 0; ma.dtype = dtype; ma.d = d; ma.delta = delta;
         la.row_start = ma.row_start; la.row_count = ma.row_count; la.cols = ma.cols; la.active_rows = active_rows; la.n_active = n_active;
-        ma.list = (ExactEntry*)hd->xlist.p; ma.count = &cnt->n_exact; ma.cap = hd->xcap;
-        launch_l1_blocks(st, ma, la, row_grid, (ExactEntry*)hd->flist.p, pair_cap, block_most, cnt);
+        ma.list = (ExactEntry*)hd->xlist.p; ma.count = &cnt->n_exact; ma.cap = block_cap;
+        launch_l1_blocks(st, ma, la, row_grid, (ExactEntry*)hd->flist.p, pair_cap, block_most, cnt, r0 + RBmax >= R);
       } else if (prune) {
         la.row_start = (const uint32_t*)hd->row_start.p; la.row_count = (const uint32_t*)hd->row_count.p;
         la.cols = (const uint32_t*)hd->cols.p; la.active_rows = active_rows; la.n_active = n_active;
@@ -1099,14 +1111,15 @@ int group_rows(kgc_handle* hd, const void* E, int64_t N, int32_t d, int32_t p, f
 // kSampleTriples (one small launch and a read-back, about 20 us)
 int close_share(kgc_handle* hd, const void* E, int64_t N, int32_t d, const void* Rvecs, int32_t r_begin, int64_t Rn, float delta, double* share) {
   int rc;
-  if ((rc = ensure(hd, hd->sample_counts, kSampleBlocks * 4))) return rc;
+  if ((rc = ensure(hd, hd->counters, sizeof(DevCounters)))) return rc;
+  unsigned int* const counts = ((DevCounters*)hd->counters.p)->sample;
   RecheckCtx cx{};
   cx.E = E; cx.Et = E; cx.Rv = Rvecs; cx.rstride = d; cx.dtype = hd->cfg.dtype; cx.d = d; cx.p = 2; cx.delta = (double)delta;
   set_alignment(cx);
-  k_sample_close<<<kSampleBlocks, 256, 0, hd->stream>>>(cx, N, r_begin, (int)Rn, (unsigned int*)hd->sample_counts.p);
+  k_sample_close<<<kSampleBlocks, 256, 0, hd->stream>>>(cx, N, r_begin, (int)Rn, counts);
   KGC_HIP(hd, hipGetLastError());
   unsigned int* const got = hd->host_counters->max_a;      // (pinned, and of no meaning on the host otherwise)
-  KGC_HIP(hd, hipMemcpyAsync(got, hd->sample_counts.p, kSampleBlocks * 4, hipMemcpyDeviceToHost, hd->stream));
+  KGC_HIP(hd, hipMemcpyAsync(got, counts, kSampleBlocks * 4, hipMemcpyDeviceToHost, hd->stream));
   KGC_HIP(hd, hipEventRecord(hd->ev[2], hd->stream));
   KGC_HIP(hd, wait_event(hd->ev[2]));
   unsigned int n = 1;
@@ -1621,7 +1634,7 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
   unsigned long long fact_most = fact_list_max(N, Rn, prune ? 2 : p, ws);      // (pruned L1: what the blocks leave, no try to lose)
   if (straight) fact_most = (unsigned long long)std::min((double)fact_most, straight_most(cap, std::max(share, 0.0) * triples));
   const unsigned int fact_cap = (unsigned int)std::min<unsigned long long>(
-      std::max(hd->fcap, hd->fcap_start > 0 ? hd->fcap_start : fact_list_start(N, Rn)), fact_most);
+      std::max(hd->fcap, hd->fcap_start > 0 ? hd->fcap_start : prune && p == 1 ? l1_list_start(N, Rn, cap) : fact_list_start(N, Rn)), fact_most);
   // The same call again without the list of pairs (dense: the kernels that contract every relation or sum in L1; a pruned join
   // whose rows form one group goes back to the pruned kernels, which score whole blocks of candidates).
   auto without_list = [&]() {
@@ -1725,7 +1738,8 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
   const bool lists_pairs = prune && p == 2 && tile_id == kDirectL2Tile && !hd->no_fact;
   // pruned L1 joins by pairs of micro-tiles need both lists
   // (the count of blocks stops little past block_most: 32 bits do for any batch)
-  const bool l1_blocks = prune && p == 1 && !win && !hd->static_mode && !hd->no_fact && have_blocks(hd);
+  const unsigned int block_cap = l1_block_cap(hd, tiles_per_rel * Rn);
+  const bool l1_blocks = prune && p == 1 && !win && !hd->static_mode && !hd->no_fact && have_blocks(hd, block_cap);
   const unsigned int block_most = block_list_max(hd, ws);
   if ((fact || part_n || lists_pairs || l1_blocks) && !have_list(hd, fact_cap)) {
     pr.valid = reuse;                                      // (what the handle held is still there)
@@ -2129,8 +2143,8 @@ static int join_range_impl(kgc_handle* hd, const void* E, int64_t N, int32_t d, 
         ma.row_start = row_start; ma.row_count = row_count; ma.cols = cols; ma.active_rows = active_rows; ma.n_active = n_active;
         ma.nH = nH; ma.r0 = (int)r0; ma.cent_h = ma.cent_t = (const float*)hd->cent.p; ma.rad_h = ma.rad_t = (const float*)hd->rad.p;
         ma.shift = Rvecs; ma.prm = prm; ma.dtype = dtype; ma.d = d; ma.delta = delta;
-        ma.list = (ExactEntry*)hd->xlist.p; ma.count = &cnt->n_exact; ma.cap = hd->xcap;
-        launch_l1_blocks(st, ma, la, row_grid, (ExactEntry*)hd->flist.p, fact_cap, block_most, cnt);
+        ma.list = (ExactEntry*)hd->xlist.p; ma.count = &cnt->n_exact; ma.cap = block_cap;
+        launch_l1_blocks(st, ma, la, row_grid, (ExactEntry*)hd->flist.p, fact_cap, block_most, cnt, r0 + RBmax >= r_end);
       } else {
         hipLaunchKernelGGL(l1_kernel_for(la.cx), prune ? dim3(row_grid, 1, 1) : dim3((unsigned)nTw, (unsigned)nHw, (unsigned)RB), dim3(256), 0,
                            st, la);

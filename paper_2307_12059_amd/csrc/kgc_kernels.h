@@ -44,6 +44,7 @@ struct DevCounters {
   unsigned int fact_need, pad;    // most pairs any one batch of the relation-factorised kernel wanted to list
   unsigned int max_a[1024];       // running maxima of ||bf16(h + r)||^2 (L2) or ||e||_1 (L1), float bits, spread over slots
   unsigned int max_b[1024];       // running maxima of ||bf16(t)||^2 (L2) or ||r||_1 (L1)
+  unsigned int sample[256];       // triples within delta by workgroup of k_sample_close
   unsigned int n_exact;           // accumulator blocks listed for the exact stage by the pruned L2 join kernels (per batch)
   unsigned int pair_mode;         // pruned L2 batch: 1 = its rows keep so few tiles that they are taken tile by tile
   unsigned long long n_fact;      // pairs listed by the relation-factorised kernel (per batch)
@@ -2194,6 +2195,7 @@ __global__ __launch_bounds__(256) void k_top1_sample(RecheckCtx cx, int64_t N, i
 }
 
 // How many of kSampleTriples random triples lie within cx.delta, counted by workgroup: one triple per 16-lane group and step.
+static_assert(sizeof(DevCounters::sample) == 256 * 4, "a word per workgroup");
 constexpr int kSampleBlocks = 256, kSampleSteps = 4, kSampleTriples = kSampleBlocks * 16 * kSampleSteps;      // (a step is two memory round trips)
 __global__ __launch_bounds__(256) void k_sample_close(RecheckCtx cx, int64_t N, int r_begin, int R, unsigned int* __restrict__ counts) {
   __shared__ unsigned int n_s;
